@@ -297,6 +297,8 @@ struct vf_index {
     size_t group_bytes() const { return (size_t)2 * ncp * 32 * 16; }
     // float32 seed proofs: |approximation - ordered distance| <= seed_err_bound() (|q|^2 + xn_max)
     float seed_err_bound() const { return (float)(tune.seed_slack * 3.0517578125e-05); }
+    // the same for the approximations of the join kernel (split bfloat16 products, see vf_join.hip)
+    float join_err_bound() const { return 4.0f * seed_err_bound(); }
 };
 
 namespace vf {

@@ -4,6 +4,7 @@
 #include <ctime>
 
 #include "vf_host.h"
+#include "vf_join.h"
 
 namespace vf {
 
@@ -113,7 +114,63 @@ void free_index(vf_index *ix)
     delete ix;
 }
 
-// Exact kNN rows of label l's list: interleave the list, contract it against itself, keep K candidates per
+// Exact kNN rows of the graph lists graph_labels[lo, hi), which lie one after the other in M_HS: pack them, contract every
+// list against itself in one launch (vf_join.hip; a list of a few thousand vectors alone would leave most of the chip
+// idle), keep K candidates per vertex and order `deg` of them into rows_out (per list [|C_l|][deg] local ids).
+// rows_out: row of the first vertex; norms: squared norms of all rows of X; global_ids as in build_graph_for_label.
+static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, int32_t deg, int32_t *rows_out, bool global_ids,
+                               const uint32_t *norms, DevBuf &cand_idx, DevBuf &cand_dist, DevBuf &d_items, hipStream_t s)
+{
+    const int64_t base0 = ix->O_HS[(size_t)ix->graph_labels[lo]];
+    std::vector<int64_t> grp_src;
+    std::vector<int32_t> grp_cnt;
+    std::vector<ScanItem> items;
+    for (size_t i = lo; i < hi; ++i) {
+        const int32_t l = ix->graph_labels[i], nl = ix->S[(size_t)l];
+        const int64_t base = ix->O_HS[(size_t)l], group0 = (int64_t)grp_src.size();
+        for (int32_t e = 0; e < nl; e += 32) { grp_src.push_back(base + e); grp_cnt.push_back(std::min(32, nl - e)); }
+        for (int32_t e = 0; e < nl; e += kJoinRows) {
+            ScanItem it{};
+            it.group0 = group0; it.n = nl;
+            it.q_begin = (int32_t)(base - base0 + e); it.q_count = std::min(kJoinRows, nl - e);
+            it.self_base = e; it.part_row = it.q_begin;
+            items.push_back(it);
+        }
+    }
+    // the tiles of the longest lists first: they take the longest
+    std::stable_sort(items.begin(), items.end(), [](const ScanItem &a, const ScanItem &b) { return a.n > b.n; });
+    int rc;
+    DevBuf d_src(&ix->alloc), d_cnt(&ix->alloc);
+    DevBufGuard rel{&d_src, &d_cnt};
+    if ((rc = upload(d_src, grp_src, s)) != VF_OK) return rc;
+    if ((rc = upload(d_cnt, grp_cnt, s)) != VF_OK) return rc;
+    if ((rc = upload(d_items, items, s)) != VF_OK) return rc;
+    const int32_t *map = ix->d_M_HS.as<int32_t>();
+    launch_join_pack(ix->dtype, ix->X, ix->dim, map, d_src.as<int64_t>(), d_cnt.as<int32_t>(), (int64_t)grp_src.size(), norms,
+                     ix->tmp_blk.as<uint4>(), ix->tmp_norm.p, s);
+    JoinParams p{};
+    p.xblk = ix->tmp_blk.as<uint4>(); p.xnorm = ix->tmp_norm.p;
+    p.qsrc = ix->X; p.qrow = map + base0; p.items = d_items.as<ScanItem>();
+    p.dim = ix->dim; p.K = K;
+    p.res_idx = cand_idx.as<int32_t>(); p.res_bits = cand_dist.as<uint32_t>();
+    p.meta = ix->meta();
+    launch_join(ix->dtype, p, (int)items.size(), s);
+    for (size_t i = lo; i < hi; ++i) {
+        const int32_t l = ix->graph_labels[i], nl = ix->S[(size_t)l];
+        const int64_t base = ix->O_HS[(size_t)l], at = base - base0;
+        // float32 rows are accepted only with a proof that the K candidates contain them
+        launch_graph_rows(ix->dtype, ix->X, ix->dim, map + base, nl, p.res_idx + at * K, p.res_bits + at * K, K, deg,
+                          rows_out + at * deg, ix->join_err_bound(), ix->xn_max, nullptr, s);
+        if (global_ids)
+            launch_graph_global_ids(rows_out + at * deg, map + base, (int64_t)nl * deg, ix->d_Gg.as<int32_t>() + base * ix->R, s);
+    }
+    VF_HIP(hipGetLastError());
+    VF_HIP(hipStreamSynchronize(s));   // the tables above are pageable host memory and temporaries
+    return VF_OK;
+}
+
+// The same for one list on the scan kernels: float32 tables whose norms the join's proofs do not cover (NaN, overflow,
+// norms outside [1e-24, 1e30]), and "build16" = 0.  Interleave the list, contract it against itself, keep K candidates per
 // vertex, order `deg` of them into rows_out ([|C_l|][deg] local ids); with global_ids the same rows also go
 // to the index's global-id table (deg == R).
 static int build_graph_for_label(vf_index *ix, int32_t l, int32_t K, int32_t deg, int32_t *rows_out, bool global_ids,
@@ -125,8 +182,7 @@ static int build_graph_for_label(vf_index *ix, int32_t l, int32_t K, int32_t deg
     const int32_t *map = ix->d_M_HS.as<int32_t>() + base;
     launch_interleave(ix->dtype, ix->X, ix->dim, map, nullptr, nullptr, nl, n_groups, ix->ncp, ix->tmp_blk.as<uint4>(),
                       ix->tmp_norm.p, s);
-    // float32: 16-row tiles on the 16x16x4 MFMA (their smaller LDS footprint more than doubles the resident
-    // waves); uint8: 32-row tiles
+    // dim 96 / 128: 16-row tiles on the 16x16x4 MFMA (their smaller LDS footprint more than doubles the resident waves)
     const int32_t TR = (ix->tune.build16 && scan16_supported(ix->dtype, ix->dim, 16)) ? 16 : 32;
     const int64_t n_tiles = (nl + TR - 1) / TR;
     std::vector<ScanItem> items((size_t)n_tiles);
@@ -397,14 +453,9 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
             if (pruned && (rc = d_knn.reserve((size_t)ix->n_HS * D * 4)) != VF_OK) return rc;
             DevBuf cand_idx(&ix->alloc), cand_dist(&ix->alloc), d_items(&ix->alloc);
             DevBufGuard r3{&cand_idx, &cand_dist, &d_items};
-            const int64_t max_groups = (max_list + 31) / 32;
-            if ((rc = ix->tmp_blk.reserve((size_t)max_groups * ix->group_bytes())) != VF_OK) return rc;
-            if ((rc = ix->tmp_norm.reserve((size_t)max_groups * 32 * 4)) != VF_OK) return rc;
-            if ((rc = cand_idx.reserve((size_t)max_groups * 32 * K * 4)) != VF_OK) return rc;
-            if ((rc = cand_dist.reserve((size_t)max_groups * 32 * K * 4)) != VF_OK) return rc;
-            // squared norm of every row of X and the largest of them: the matrix-core seed scoring reads the norms,
-            // its proofs and those of the float32 graph rows need the largest
-            if (ix->dtype == VF_F32 || seed_mfma_supported(ix->dtype, ix->dim)) {
+            // squared norm of every row of X and the largest of them: the joins and the matrix-core seed scoring read the
+            // norms, the proofs of both need the largest
+            {
                 if ((rc = ix->d_xnorm_all.reserve((size_t)n * 4)) != VF_OK) return rc;
                 launch_row_norms(ix->dtype, ix->X, ix->dim, n, ix->d_xnorm_all.as<uint32_t>(), s);
                 float mx = 0.f;
@@ -426,26 +477,57 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
                     ix->xn_max = mx;
                     ix->seed_mfma_ok = seed_mfma_supported(ix->dtype, ix->dim);
                 }
-                if (!finite || !ix->seed_mfma_ok) ix->d_xnorm_all.release();
+                if (!finite) ix->d_xnorm_all.release();
             }
+            const bool joined = ix->dtype == VF_U8 || (ix->xn_max > 0.f && ix->tune.build16);
+            // Lists are joined many to a launch: as many as fit, packed and with their candidates, into a GiB (or one list
+            // that is larger than that).  The scan kernels take one list at a time.
+            const size_t row_bytes_tmp = joined ? join_group_bytes(ix->dtype, ix->dim) / 32 + (size_t)K * 8 : 0;
+            const int64_t batch_rows = joined ? std::max<int64_t>((int64_t)(((size_t)1 << 30) / row_bytes_tmp), (int64_t)max_list) : max_list;
+            std::vector<size_t> batch_end;   // positions in graph_labels
+            int64_t tmp_groups = 0, tmp_rows = 0;
+            for (size_t i = 0; i < ix->graph_labels.size();) {
+                int64_t rows_in = 0, groups_in = 0;
+                size_t e = i;
+                while (e < ix->graph_labels.size() && (e == i || (joined && rows_in + ix->S[(size_t)ix->graph_labels[e]] <= batch_rows))) {
+                    rows_in += ix->S[(size_t)ix->graph_labels[e]];
+                    groups_in += (ix->S[(size_t)ix->graph_labels[e]] + 31) / 32;
+                    ++e;
+                }
+                tmp_groups = std::max(tmp_groups, groups_in);
+                tmp_rows = std::max(tmp_rows, rows_in);
+                batch_end.push_back(e);
+                i = e;
+            }
+            if ((rc = ix->tmp_blk.reserve((size_t)tmp_groups * (joined ? join_group_bytes(ix->dtype, ix->dim) : ix->group_bytes()))) != VF_OK) return rc;
+            if ((rc = ix->tmp_norm.reserve((size_t)tmp_groups * 32 * 4)) != VF_OK) return rc;
+            if ((rc = cand_idx.reserve((size_t)(tmp_rows + 31) / 32 * 32 * K * 4)) != VF_OK) return rc;
+            if ((rc = cand_dist.reserve((size_t)(tmp_rows + 31) / 32 * 32 * K * 4)) != VF_OK) return rc;
             // optionally a line on stderr every few seconds (index builds of 10^7 vectors take minutes)
             const bool progress = ix->tune.build_progress != 0;
             time_t last_print = time(nullptr);
             size_t done = 0;
-            for (int32_t l : ix->graph_labels) {
+            for (const size_t end : batch_end) {
                 if (progress && time(nullptr) - last_print >= 10) {
                     fprintf(stderr, "[vf_build_index] %zu of %zu label graphs built, next list holds %d vectors\n", done,
-                            ix->graph_labels.size(), ix->S[(size_t)l]);
+                            ix->graph_labels.size(), ix->S[(size_t)ix->graph_labels[done]]);
                     fflush(stderr);
                     last_print = time(nullptr);
                 }
-                ++done;
-                launch_bitset_fill(ix->d_M_HS.as<int32_t>() + ix->O_HS[(size_t)l], ix->S[(size_t)l],
-                                   ix->d_bitsets.as<uint32_t>() + (int64_t)ix->hs_slot[(size_t)l] * ix->bitset_words, s);
-                const int64_t base = ix->O_HS[(size_t)l];
+                for (size_t i = done; i < end; ++i) {
+                    const int32_t l = ix->graph_labels[i];
+                    launch_bitset_fill(ix->d_M_HS.as<int32_t>() + ix->O_HS[(size_t)l], ix->S[(size_t)l],
+                                       ix->d_bitsets.as<uint32_t>() + (int64_t)ix->hs_slot[(size_t)l] * ix->bitset_words, s);
+                }
+                const int32_t first = ix->graph_labels[done];
+                const int64_t base = ix->O_HS[(size_t)first];
                 int32_t *rows = pruned ? d_knn.as<int32_t>() + base * D : ix->d_G.as<int32_t>() + base * ix->R;
-                if ((rc = build_graph_for_label(ix, l, K, D, rows, !pruned, cand_idx, cand_dist, d_items, s)) != VF_OK)
-                    return rc;
+                if (joined)
+                    rc = build_graphs_joined(ix, done, end, K, D, rows, !pruned, ix->d_xnorm_all.as<uint32_t>(), cand_idx, cand_dist, d_items, s);
+                else
+                    rc = build_graph_for_label(ix, first, K, D, rows, !pruned, cand_idx, cand_dist, d_items, s);
+                if (rc != VF_OK) return rc;
+                done = end;
             }
             VF_HIP(hipStreamSynchronize(s));
             if (pruned) {

@@ -1,0 +1,462 @@
+// Contraction of many rows against whole lists with the exact top-K selection fused in: the kNN self-joins of the index
+// build (Alg. 1) and the scans of graph lists for the exact ground truth.  Where the scan kernels serve a handful of
+// queries per list and are bound by the list's bytes, a join has as many rows as it has and is bound by the matrix cores
+// and by the selection, so everything here is arranged around those two.
+//
+// Tile.  A workgroup of four waves takes 128 rows (32 per wave) and streams a segment of a list through LDS, one group
+// of 32 entries per step, shared by its waves: a group is fetched from L2 once per 128 rows instead of once per 16 (the
+// 16-row kernel's 16 KiB per group and 16 rows would need more L2 bandwidth than there is at this rate).  The rows'
+// operand stays in registers.  Lists come packed (join_pack_kernel): per group the 16-byte chunks chunk-major, which is
+// the B operand of the 32-column MFMAs, lane (n32, h) reading chunk 2 s + h of entry n32.
+//
+// float32 data: v_mfma_f32_32x32x16_bf16 on two-part splits of both operands, x = hi + lo with hi = bf16(x), lo =
+// bf16(x - hi): the products lo.hi and hi.lo first, then hi.hi, into one float32 accumulator (in this order the small
+// terms are summed while the partial sums are small).  Three products at 16 times the rate of the float32 MFMA.  What
+// they leave out, with u = 2^-24: |x - hi - lo| <= 2^-18 |x| twice and the product of the low parts 2^-18, together
+// 192 u |q||x| in q.x, 193 u (|q|^2 + |x|^2) in the distance; the sums of the high parts 2 u per term, <= 500 u
+// (|q|^2 + |x|^2) at 248 terms; norms, summed one after the other, 250 u; final additions, the thresholds' and the
+// ordered distance's own rounding < 100 u.  The bound used is 2048 u = join_err_bound(); callers re-rank what the join
+// keeps with the ordered distance and prove with that bound that nothing else belongs to the result.
+// uint8 data: v_mfma_i32_32x32x32_i8 on the bytes shifted by -128: exact.
+//
+// Selection.  With v = q.x - |x|^2 / 2 (uint8: 2 q.x - |x|^2) a distance is below a row's threshold where v is at least
+// a per-row constant, one subtraction and one compare per pair; the compares' lane masks are or-ed on the scalar unit,
+// and a group without a candidate (most, once the thresholds have tightened) is done.  Otherwise candidates go to the
+// rows' queues in LDS (32 slots; positions by population counts of the masks, no atomics), and full queues are merged
+// into the rows' sorted K best: two rows share a 64-lane sort network, then one merge network per row.  The K best live
+// in the partial result rows in global memory: a row is drained about 15 times, so LDS is better spent on a second
+// workgroup per CU.
+//
+// Measured, self-joins of 36 lists of 4,000 to 170,000 float32 vectors, dim 128 (4.7e10 pairs): 59 ms; the 16-row kernel
+// on the float32 MFMA, one launch per list and 4 MiB panel, 167 ms.  The matrix cores are busy for 15 ms of it; the
+// streaming alone (no candidates) takes 32 ms, whether the lists come from L2 or from memory: two waves per SIMD and a
+// barrier per group; the rest is the selection.
+#include "vf_join.h"
+#include "vf_select.h"
+
+namespace vf {
+
+typedef __bf16 v8bf_join __attribute__((ext_vector_type(8)));
+typedef float v16f_join __attribute__((ext_vector_type(16)));
+typedef int v16i_join __attribute__((ext_vector_type(16)));
+typedef int v4i_join __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u_join __attribute__((ext_vector_type(4)));
+
+constexpr int kJoinQueue = 32;   // pending keys per row: what one group can add
+
+template <int DT> struct JoinAcc { using type = v16f_join; using scalar = float; };
+template <> struct JoinAcc<0> { using type = v16i_join; using scalar = int; };
+
+template <int DT> __host__ __device__ constexpr int join_chunks(int nk) { return DT == 0 ? 2 * nk : 4 * nk; }
+
+// v of lane `lane` (a constant) := x (wave-uniform)
+__device__ __forceinline__ void set_lane(int &v, int x, int lane)
+{
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(lane));
+}
+
+// NK: contraction steps (16 components of float32, 32 of uint8), the vectors zero padded to them.
+template <int DT, int NK, bool AND>
+__global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
+{
+    extern __shared__ uint4 smem[];
+    using acc_t = typename JoinAcc<DT>::type;
+    using val_t = typename JoinAcc<DT>::scalar;
+    constexpr int NC = join_chunks<DT>(NK), STAGE = NC * 32, NL = (STAGE + 255) / 256;
+    constexpr int NBUF = join_buffers(NC);
+    const ScanItem it = p.items[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, n32 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int K = p.K, row_base = wave * 32;
+    const int rows = it.q_count - row_base < 32 ? it.q_count - row_base : 32;   // rows of this wave (<= 0: none)
+    uint64_t *pend = (uint64_t *)(smem + NBUF * STAGE) + row_base * kJoinQueue;   // [32 rows][32]
+
+    // ---- the rows' operand (lane (n32, h): chunk 2 s + h of row n32) and squared norms
+    const int qr = n32 < rows ? p.qrow[it.q_begin + row_base + n32] : -1;
+    uint4 a[NK], alo[DT == 0 ? 1 : NK];
+    val_t qnorm = 0;
+    {
+        const char *qp = (const char *)p.qsrc + (int64_t)(qr >= 0 ? qr : 0) * (p.dim * (DT == 0 ? 1 : 4));
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {
+            const int c = 2 * s + h;
+            if constexpr (DT == 0) {
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (qr >= 0 && c * 16 < p.dim) {
+                    v = *(const uint4 *)(qp + c * 16);
+                    v.x ^= 0x80808080u; v.y ^= 0x80808080u; v.z ^= 0x80808080u; v.w ^= 0x80808080u;
+                }
+                a[s] = v;
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) qnorm = __builtin_amdgcn_sdot4((int)w[i], (int)w[i], qnorm, false);
+            } else {
+                float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+                if (qr >= 0 && c * 8 < p.dim) x = *(const float4 *)(qp + c * 32);
+                if (qr >= 0 && c * 8 + 4 < p.dim) y = *(const float4 *)(qp + c * 32 + 16);
+                const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+                split_bf16x8(f, a[s], alo[s]);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) qnorm += f[i] * f[i];
+            }
+        }
+        qnorm += __shfl_xor(qnorm, 32);
+    }
+
+    // ---- state of row r, held by lane r < 32: keys waiting, K-th best key, threshold on v (rows that do not exist: never)
+    const val_t never = DT == 0 ? (val_t)0x7FFFFFFF : (val_t)__builtin_inff();
+    val_t tv = n32 < rows ? (DT == 0 ? (val_t)(-0x20000000) : (val_t)(-3.0e38f)) : never;
+    int pcv = 0;
+    uint64_t row_kth = KEY_MAX;
+    uint32_t touched = 0;            // rows whose partial result row has been written
+    const int64_t part0 = (int64_t)it.part_row + row_base;
+    // per accumulator element: row 8 (j / 4) + 4 h + j % 4
+    val_t t[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) t[j] = __shfl(tv, 8 * (j >> 2) + 4 * h + (j & 3));
+    uint32_t and_rows = 0;
+    int qr_of[AND ? 16 : 1];
+    if constexpr (AND) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int r = 8 * (j >> 2) + 4 * h + (j & 3);
+            qr_of[j] = __shfl(qr, r);
+            if (qr_of[j] >= 0 && p.others_off[qr_of[j] + 1] > p.others_off[qr_of[j]]) and_rows |= 1u << j;
+        }
+    }
+
+    auto qnorm_of = [&](int r) -> val_t {   // (wave-uniform r)
+        if constexpr (DT == 0) return __builtin_amdgcn_readlane(qnorm, r);
+        else return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(qnorm), r));
+    };
+    // Merge the queues of the rows in `todo` into their K best, four rows at a time, and empty them.
+    auto drain = [&](uint32_t todo) {
+        wave_lds_sync();
+        const uint32_t done = todo;
+        while (todo != 0) {
+            int r[4];
+            bool on[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                on[u] = todo != 0;
+                r[u] = on[u] ? __builtin_ctz(todo) : r[0];
+                todo &= todo - 1;
+            }
+            uint64_t best[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                best[u] = KEY_MAX;
+                if (((touched >> r[u]) & 1u) && lane < K) {
+                    const int64_t o = (part0 + r[u]) * K + lane;
+                    const int32_t idx = p.res_idx[o];
+                    if (idx >= 0) best[u] = ((uint64_t)p.res_bits[o] << 32) | (uint32_t)idx;
+                }
+            }
+            uint64_t x[2];   // rows r[2u] and r[2u + 1] in the wave's halves
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int c0 = __builtin_amdgcn_readlane(pcv, r[2 * u]), c1 = __builtin_amdgcn_readlane(pcv, r[2 * u + 1]);
+                const uint64_t k0 = readlane64(row_kth, r[2 * u]), k1 = readlane64(row_kth, r[2 * u + 1]);
+                uint64_t key = n32 < (h ? c1 : c0) ? pend[(h ? r[2 * u + 1] : r[2 * u]) * kJoinQueue + n32] : KEY_MAX;
+                if (key != KEY_MAX) {   // v -> distance of the row
+                    const val_t q0 = qnorm_of(r[2 * u]), q1 = qnorm_of(r[2 * u + 1]), q = h ? q1 : q0;
+                    const uint32_t vb = (uint32_t)(key >> 32);
+                    const uint32_t bits = DT == 0 ? (uint32_t)((int)q - (int)vb)
+                                                  : __float_as_uint(fmaxf((float)q - 2.0f * __uint_as_float(vb), 0.0f));
+                    key = ((uint64_t)bits << 32) | (uint32_t)key;
+                }
+                x[u] = key < (h ? k1 : k0) ? key : KEY_MAX;
+            }
+            lane_sort<32, true>(x);
+            uint64_t v[4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                // both halves' sorted keys in the upper lanes: descending behind KEY_MAX, against the ascending best
+                uint32_t l0, l1, h0, h1;
+                lane_pair<32>((uint32_t)x[u], l0, l1);
+                lane_pair<32>((uint32_t)(x[u] >> 32), h0, h1);
+                const uint64_t x0 = h ? ((uint64_t)h0 << 32) | l0 : KEY_MAX, x1 = h ? ((uint64_t)h1 << 32) | l1 : KEY_MAX;
+                v[2 * u] = best[2 * u] < x0 ? best[2 * u] : x0;
+                v[2 * u + 1] = best[2 * u + 1] < x1 ? best[2 * u + 1] : x1;
+            }
+            lane_merge<64>(v);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (on[u]) {   // wave-uniform
+                    if (lane < K) {
+                        const int64_t o = (part0 + r[u]) * K + lane;
+                        p.res_idx[o] = v[u] == KEY_MAX ? -1 : (int32_t)(uint32_t)v[u];
+                        p.res_bits[o] = (uint32_t)(v[u] >> 32);
+                    }
+                    const uint64_t nk = readlane64(v[u], K - 1);
+                    if (lane == r[u]) row_kth = nk;
+                }
+            }
+        }
+        touched |= done;
+        if ((done >> n32) & 1u) {
+            if (h == 0) pcv = 0;
+            if (row_kth != KEY_MAX) {
+                const uint32_t kd = (uint32_t)(row_kth >> 32);
+                if constexpr (DT == 0) tv = qnorm - (int)kd;
+                // (lowered by a few units in the last place: a pair that is left out has an approximation of at least
+                // the K-th best)
+                else tv = 0.5f * (qnorm - __uint_as_float(kd)) - 2.4e-7f * (qnorm + __uint_as_float(kd));
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t[j] = __shfl(tv, 8 * (j >> 2) + 4 * h + (j & 3));
+        wave_lds_sync();
+    };
+
+    // ---- stream the segment
+    const int n_groups = (it.n + kGroup - 1) / kGroup;
+    v4u_join pre[NL];   // (the native vector type: an array of uint4 ends up in scratch memory here)
+    auto fetch = [&](int g) {
+        const v4u_join *blk = (const v4u_join *)p.xblk + (it.group0 + g) * (int64_t)STAGE;
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            if (STAGE % 256 == 0 || tid + i * 256 < STAGE) pre[i] = blk[tid + i * 256];
+    };
+    auto put = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i)
+            if (STAGE % 256 == 0 || tid + i * 256 < STAGE) ((v4u_join *)smem)[buf * STAGE + tid + i * 256] = pre[i];
+    };
+    const val_t *xnorm = (const val_t *)p.xnorm;
+    fetch(0);
+    val_t xn_next = xnorm[it.group0 * kGroup + n32];
+    put(0);
+    __syncthreads();
+    for (int g = 0; g < n_groups; ++g) {
+        const bool more = g + 1 < n_groups;
+        const val_t xn = xn_next;
+        if (more) {
+            fetch(g + 1);
+            xn_next = xnorm[(it.group0 + g + 1) * kGroup + n32];
+        }
+        if (rows > 0) {   // wave-uniform
+            const uint4 *B = smem + (NBUF == 2 ? (g & 1) : 0) * STAGE;
+            acc_t acc;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[j] = 0;
+            // NPRE steps of the B operand at a time, requested before the first of them is used: left to itself the
+            // compiler requests each chunk right before its MFMA and waits for the LDS every time
+            constexpr int NPRE = NK < 8 ? NK : 8;
+            if constexpr (DT == 0) {
+#pragma unroll
+                for (int s0 = 0; s0 < NK; s0 += NPRE) {
+                    v4i_join b[NPRE];
+#pragma unroll
+                    for (int u = 0; u < NPRE; ++u) b[u] = ((const v4i_join *)B)[(2 * (s0 + u) + h) * 32 + n32];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < NPRE; ++u) {
+                        const v4i_join av = {(int)a[s0 + u].x, (int)a[s0 + u].y, (int)a[s0 + u].z, (int)a[s0 + u].w};
+                        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av, b[u], acc, 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll
+                for (int s0 = 0; s0 < NK; s0 += NPRE) {
+                    v8bf_join bh[NPRE], bl[NPRE];
+#pragma unroll
+                    for (int u = 0; u < NPRE; ++u) {
+                        bh[u] = ((const v8bf_join *)B)[(2 * (s0 + u) + h) * 32 + n32];
+                        bl[u] = ((const v8bf_join *)B)[(2 * NK + 2 * (s0 + u) + h) * 32 + n32];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < NPRE; ++u) {
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, alo[s0 + u]), bh[u], acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, a[s0 + u]), bl[u], acc, 0, 0, 0);
+                    }
+                    if (NK <= NPRE) {   // (all of it is still in registers)
+#pragma unroll
+                        for (int u = 0; u < NPRE; ++u)
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, a[s0 + u]), bh[u], acc, 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (NK > NPRE) {
+#pragma unroll
+                    for (int s0 = 0; s0 < NK; s0 += NPRE) {
+                        v8bf_join bh[NPRE];
+#pragma unroll
+                        for (int u = 0; u < NPRE; ++u) bh[u] = ((const v8bf_join *)B)[(2 * (s0 + u) + h) * 32 + n32];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = 0; u < NPRE; ++u)
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, a[s0 + u]), bh[u], acc, 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            uint64_t m[16], any = 0;
+            val_t v[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                v[j] = DT == 0 ? acc[j] * 2 - xn : acc[j] - xn;   // (float32: xn holds |x|^2 / 2)
+                m[j] = __builtin_amdgcn_ballot_w64(v[j] >= t[j]);
+                any |= m[j];
+            }
+            if (any != 0) {
+                const int entry = it.entry0 + g * kGroup + n32;   // list-relative
+                // graph build: the entry that is the row itself (self_base + row) is no candidate
+                const int self = it.self_base >= 0 ? it.self_base + row_base : -0x40000000;
+                if (self + 31 >= it.entry0 + g * kGroup && self <= it.entry0 + g * kGroup + 31) {
+                    const int rel = entry - self - 4 * h;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) m[j] &= __builtin_amdgcn_ballot_w64(rel != 8 * (j >> 2) + (j & 3));
+                }
+                if constexpr (AND) {
+                    const int gid = p.map[it.map_off + (g * kGroup + n32 < it.n ? entry : it.entry0)];
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) {
+                        if (m[j] == 0) continue;
+                        bool ok = (m[j] >> lane) & 1u;
+                        if (ok && ((and_rows >> j) & 1u)) {
+                            const int o_begin = p.others_off[qr_of[j]], o_end = p.others_off[qr_of[j] + 1];
+                            for (int o = o_begin; o < o_end && ok; ++o) ok = has_label(p.meta, p.others[o], gid);
+                        }
+                        m[j] = __builtin_amdgcn_ballot_w64(ok);
+                    }
+                }
+                int inc = 0;   // keys that row r receives from this group, in lane r
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const int row0 = 8 * (j >> 2) + (j & 3);
+                    set_lane(inc, __builtin_popcount((uint32_t)m[j]), row0);
+                    set_lane(inc, __builtin_popcount((uint32_t)(m[j] >> 32)), row0 + 4);
+                }
+                // (rows that are half full go along: their next drain would come soon)
+                if (__any(pcv + inc > kJoinQueue))
+                    drain((uint32_t)__ballot(lane < 32 && pcv > 0 && (pcv + inc > kJoinQueue || pcv >= kJoinQueue / 2)));
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    if (m[j] == 0) continue;
+                    const int row = 8 * (j >> 2) + (j & 3) + 4 * h;
+                    const uint32_t mine = h ? (uint32_t)(m[j] >> 32) : (uint32_t)m[j];
+                    const int at = __shfl(pcv, row);
+                    if ((mine >> n32) & 1u) {
+                        const int slot = at + __builtin_popcount(mine & ((1u << n32) - 1u));
+                        // (v for now: the drain makes a distance of it)
+                        pend[row * kJoinQueue + slot] = ((uint64_t)(DT == 0 ? (uint32_t)v[j] : __float_as_uint((float)v[j])) << 32) | (uint32_t)entry;
+                    }
+                }
+                pcv += inc;
+            }
+        }
+        if (more) {
+            if (NBUF == 1) __syncthreads();
+            put(NBUF == 2 ? (g + 1) & 1 : 0);
+            __syncthreads();
+        }
+    }
+    drain((uint32_t)__ballot(lane < 32 && pcv > 0));
+    for (int r = 0; r < rows; ++r)   // rows without a candidate
+        if (((touched >> r) & 1u) == 0 && lane < K) {
+            p.res_idx[(part0 + r) * K + lane] = -1;
+            p.res_bits[(part0 + r) * K + lane] = 0xFFFFFFFFu;
+        }
+}
+
+// One thread per (group, chunk, entry): the lists' vectors gathered through `map` in the layout the join reads (float32:
+// 2 NK chunks of high parts, then 2 NK of low parts), and per entry half its squared norm (uint8: the squared norm of
+// the shifted bytes); an entry past the end of its list never passes a threshold.
+template <int DT>
+__global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map, const int64_t *grp_src, const int32_t *grp_cnt,
+                                 int64_t n_groups, int32_t nk, const uint32_t *norm_all, uint4 *xblk, uint32_t *xnorm)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int nch = 2 * nk;
+    if (t >= n_groups * nch * 32) return;
+    const int v = (int)(t & 31);
+    const int64_t gc = t >> 5;
+    const int c = (int)(gc % nch);
+    const int64_t g = gc / nch;
+    const bool valid = v < grp_cnt[g];
+    const int64_t row = valid ? map[grp_src[g] + v] : 0;
+    if (DT == 0) {
+        uint4 w = make_uint4(0, 0, 0, 0);
+        if (valid && c * 16 < dim) {
+            w = *(const uint4 *)(X + row * dim + c * 16);
+            w.x ^= 0x80808080u; w.y ^= 0x80808080u; w.z ^= 0x80808080u; w.w ^= 0x80808080u;
+        }
+        xblk[(g * nch + c) * 32 + v] = w;
+        if (c == 0) xnorm[g * 32 + v] = valid ? norm_all[row] : 0x3FFFFFFFu;
+    } else {
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+        if (valid && c * 8 < dim) x = *(const float4 *)(X + row * dim * 4 + c * 32);
+        if (valid && c * 8 + 4 < dim) y = *(const float4 *)(X + row * dim * 4 + c * 32 + 16);
+        const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+        uint4 hi, lo;
+        split_bf16x8(f, hi, lo);
+        xblk[(g * 2 * nch + c) * 32 + v] = hi;
+        xblk[(g * 2 * nch + nch + c) * 32 + v] = lo;
+        if (c == 0) xnorm[g * 32 + v] = valid ? __float_as_uint(0.5f * __uint_as_float(norm_all[row])) : 0x7F800000u;
+    }
+}
+
+// Contraction steps the kernel is compiled for: the smallest that holds the vector.
+int32_t join_steps(int dtype, int32_t dim)
+{
+    const int32_t need = dtype == 0 ? (dim + 31) / 32 : (dim + 15) / 16;
+    for (const int32_t nk : {2, 4, 6, 8, 16}) if (need <= nk) return nk;
+    return dtype == 0 && need <= 32 ? 32 : 0;
+}
+
+size_t join_group_bytes(int dtype, int32_t dim)
+{
+    const int32_t nk = join_steps(dtype, dim);
+    return (size_t)(dtype == 0 ? join_chunks<0>(nk) : join_chunks<1>(nk)) * 512;
+}
+
+void launch_join_pack(int dtype, const void *X, int32_t dim, const int32_t *map, const int64_t *grp_src, const int32_t *grp_cnt,
+                      int64_t n_groups, const uint32_t *norm_all, uint4 *xblk, void *xnorm, hipStream_t s)
+{
+    if (n_groups <= 0) return;
+    const int32_t nk = join_steps(dtype, dim);
+    const unsigned blocks = (unsigned)((n_groups * 2 * nk * 32 + 255) / 256);
+    if (dtype == 0)
+        hipLaunchKernelGGL(join_pack_kernel<0>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, grp_src, grp_cnt,
+                           n_groups, nk, norm_all, xblk, (uint32_t *)xnorm);
+    else
+        hipLaunchKernelGGL(join_pack_kernel<1>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, grp_src, grp_cnt,
+                           n_groups, nk, norm_all, xblk, (uint32_t *)xnorm);
+}
+
+template <int DT, int NK> static void launch_join_nk(const JoinParams &p, int n_items, hipStream_t s)
+{
+    constexpr int NC = join_chunks<DT>(NK);
+    const size_t lds = (size_t)join_buffers(NC) * NC * 512 + kJoinRows * kJoinQueue * 8;
+    if (p.others_off != nullptr) hipLaunchKernelGGL((join_kernel<DT, NK, true>), dim3(n_items), dim3(256), lds, s, p);
+    else hipLaunchKernelGGL((join_kernel<DT, NK, false>), dim3(n_items), dim3(256), lds, s, p);
+}
+
+void launch_join(int dtype, const JoinParams &p, int n_items, hipStream_t s)
+{
+    if (n_items <= 0) return;
+    const int32_t nk = join_steps(dtype, p.dim);
+    if (dtype == 0) {
+        switch (nk) {
+        case 2: launch_join_nk<0, 2>(p, n_items, s); break;
+        case 4: launch_join_nk<0, 4>(p, n_items, s); break;
+        case 6: launch_join_nk<0, 6>(p, n_items, s); break;
+        case 8: launch_join_nk<0, 8>(p, n_items, s); break;
+        case 16: launch_join_nk<0, 16>(p, n_items, s); break;
+        default: launch_join_nk<0, 32>(p, n_items, s); break;
+        }
+    } else {
+        switch (nk) {
+        case 2: launch_join_nk<1, 2>(p, n_items, s); break;
+        case 4: launch_join_nk<1, 4>(p, n_items, s); break;
+        case 6: launch_join_nk<1, 6>(p, n_items, s); break;
+        case 8: launch_join_nk<1, 8>(p, n_items, s); break;
+        default: launch_join_nk<1, 16>(p, n_items, s); break;
+        }
+    }
+}
+
+}  // namespace vf

@@ -313,11 +313,13 @@ template <class T> int upload(DevBuf &b, const std::vector<T> &v, hipStream_t s)
 
 // vf_search.hip: the pieces of one search call
 struct BlobLayout {
-    size_t off_gq_query, off_gq_label, off_xq_query, off_xq_label, off_others_off, off_others, off_qrow, off_items, off_merges, off_tiles, off_empty, total;
+    size_t off_gq_query, off_gq_label, off_xq_query, off_xq_label, off_others_off, off_others, off_qrow, off_items, off_merges, off_tiles, off_empty, off_jlists, total;
 };
 
 // Everything the host decides about a call before anything is launched.
 struct HsRun { int32_t label; size_t item_lo, item_hi; };   // exact mode: the scan items of one graph list
+// exact mode on the join kernel: graph lists packed together, their positions in CallPlan::jlists and their items
+struct JoinBatch { size_t list_lo, list_hi, item_lo, item_hi; int64_t groups; };
 struct CallPlan {
     int64_t nq = 0;
     int32_t k = 0, itopk = 0, width = 0, iters = 0, n_seeds = 0;
@@ -328,6 +330,12 @@ struct CallPlan {
     size_t n_ls_items = 0, n_ls_merges = 0;
     std::vector<HsRun> hs_runs;
     int32_t max_hs_list = 0;
+    // ... the same on the join kernel (vf_join.hip): join_keep candidates per partial row, whose rows follow ls_part_words
+    std::vector<JoinList> jlists;
+    std::vector<JoinBatch> jbatches;
+    int64_t join_groups = 0;              // of the largest batch
+    int32_t join_keep = 0, join_max_nseg = 1;
+    size_t ls_part_words = 0;
     std::vector<SeedTile> tiles;          // dense seed scoring: tiles of <= 64 (32) graph queries of one label
     size_t n_gq = 0;
     size_t n_xq = 0;                      // AND queries answered by the exact predicate scan of a short graph list

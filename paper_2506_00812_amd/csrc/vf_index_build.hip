@@ -4,7 +4,6 @@
 #include <ctime>
 
 #include "vf_host.h"
-#include "vf_join.h"
 
 namespace vf {
 
@@ -122,13 +121,14 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
                                const uint32_t *norms, DevBuf &cand_idx, DevBuf &cand_dist, DevBuf &d_items, hipStream_t s)
 {
     const int64_t base0 = ix->O_HS[(size_t)ix->graph_labels[lo]];
-    std::vector<int64_t> grp_src;
-    std::vector<int32_t> grp_cnt;
+    std::vector<JoinList> lists;
     std::vector<ScanItem> items;
+    int64_t n_groups = 0;
     for (size_t i = lo; i < hi; ++i) {
         const int32_t l = ix->graph_labels[i], nl = ix->S[(size_t)l];
-        const int64_t base = ix->O_HS[(size_t)l], group0 = (int64_t)grp_src.size();
-        for (int32_t e = 0; e < nl; e += 32) { grp_src.push_back(base + e); grp_cnt.push_back(std::min(32, nl - e)); }
+        const int64_t base = ix->O_HS[(size_t)l], group0 = n_groups;
+        lists.push_back(JoinList{base, (int32_t)group0, nl});
+        n_groups += (nl + 31) / 32;
         for (int32_t e = 0; e < nl; e += kJoinRows) {
             ScanItem it{};
             it.group0 = group0; it.n = nl;
@@ -140,14 +140,12 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     // the tiles of the longest lists first: they take the longest
     std::stable_sort(items.begin(), items.end(), [](const ScanItem &a, const ScanItem &b) { return a.n > b.n; });
     int rc;
-    DevBuf d_src(&ix->alloc), d_cnt(&ix->alloc);
-    DevBufGuard rel{&d_src, &d_cnt};
-    if ((rc = upload(d_src, grp_src, s)) != VF_OK) return rc;
-    if ((rc = upload(d_cnt, grp_cnt, s)) != VF_OK) return rc;
+    DevBuf d_lists(&ix->alloc);
+    DevBufGuard rel{&d_lists};
+    if ((rc = upload(d_lists, lists, s)) != VF_OK) return rc;
     if ((rc = upload(d_items, items, s)) != VF_OK) return rc;
     const int32_t *map = ix->d_M_HS.as<int32_t>();
-    launch_join_pack(ix->dtype, ix->X, ix->dim, map, d_src.as<int64_t>(), d_cnt.as<int32_t>(), (int64_t)grp_src.size(), norms,
-                     ix->tmp_blk.as<uint4>(), ix->tmp_norm.p, s);
+    launch_join_pack(ix->dtype, ix->X, ix->dim, map, d_lists.as<JoinList>(), (int)lists.size(), n_groups, norms, ix->tmp_blk.as<uint4>(), ix->tmp_norm.p, s);
     JoinParams p{};
     p.xblk = ix->tmp_blk.as<uint4>(); p.xnorm = ix->tmp_norm.p;
     p.qsrc = ix->X; p.qrow = map + base0; p.items = d_items.as<ScanItem>();
@@ -376,6 +374,10 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
         if ((rc = upload(ix->d_M_LS, M_LS, s)) != VF_OK) return rc;
         VF_HIP(hipStreamSynchronize(s));
 
+        if (dtype == VF_F32) {   // failed proofs of the filtering scans
+            if ((rc = ix->d_scan_fb.reserve(4)) != VF_OK) return rc;
+            VF_HIP(hipMemsetAsync(ix->d_scan_fb.p, 0, 4, s));
+        }
         // ---- scan partition: StoreInterleaved over every scan list (Section 4.2.2)
         if (ix->n_groups_LS > 0) {
             std::vector<int64_t> grp_src((size_t)ix->n_groups_LS);
@@ -423,9 +425,6 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
                     mx_n = nr[i] > mx_n ? nr[i] : mx_n;
                 }
                 if (finite && mx_n >= 1e-24f && mx_n <= 1e30f) {
-                    if ((rc = ix->d_scan_fb.reserve(4)) != VF_OK) return rc;
-                    VF_HIP(hipMemsetAsync(ix->d_scan_fb.p, 0, 4, s));
-                    VF_HIP(hipStreamSynchronize(s));
                     ix->has_ls16 = true;
                     ix->ls_bf16_delta = (float)(std::sqrt(mx_e) * 1.001);
                     ix->ls_xn_max = mx_n;

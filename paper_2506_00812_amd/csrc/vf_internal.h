@@ -115,6 +115,37 @@ size_t scan_bf16_lds_bytes(int tile_rows, int keep);
 void launch_scan_bf16(const ScanParams &p, int n_items, int slots, hipStream_t s);
 void launch_scan_rerank(const RerankParams &p, int n_items, hipStream_t s);
 
+// ---------------------------------------------------------------- join kernel (vf_join.hip)
+
+// Many rows against whole lists with the top-K selection fused in.
+struct JoinParams {
+    const uint4 *xblk;      // packed lists (launch_join_pack)
+    const void *xnorm;      // per slot: half the squared norm (float32), the squared norm of the shifted bytes (uint8)
+    const int32_t *map;     // local -> global id (AND predicate)
+    const void *qsrc;       // row-major [*][dim]
+    const int32_t *qrow;    // row of qsrc for each tile row
+    const ScanItem *items;  // <= kJoinRows rows each; every item writes partial rows
+    int32_t dim, K;         // K <= 64
+    int32_t *res_idx;       // [*][K] list-relative entry index, ascending by (distance, index), -1 = none
+    uint32_t *res_bits;     //        distance bits: exact (uint8), approximations (float32)
+    const int32_t *others_off, *others;   // AND partner labels per query row value, may be null
+    LabelMeta meta;
+};
+
+constexpr int kJoinRows = 128;
+
+// One list to pack: its entries are map[src .. src + n), its first group in the packed buffer is group0 (ascending).
+struct JoinList {
+    int64_t src;
+    int32_t group0, n;
+};
+
+size_t join_group_bytes(int dtype, int32_t dim);   // packed bytes of a group of 32 vectors
+// n_groups: of all n_lists lists together
+void launch_join_pack(int dtype, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
+                      int64_t n_groups, const uint32_t *norm_all, uint4 *xblk, void *xnorm, hipStream_t s);
+void launch_join(int dtype, const JoinParams &p, int n_items, hipStream_t s);
+
 // ---------------------------------------------------------------- beam search kernel
 
 struct BeamParams {

@@ -31,7 +31,6 @@
 // on the float32 MFMA, one launch per list and 4 MiB panel, 167 ms.  The matrix cores are busy for 15 ms of it; the
 // streaming alone (no candidates) takes 32 ms, whether the lists come from L2 or from memory: two waves per SIMD and a
 // barrier per group; the rest is the selection.
-#include "vf_join.h"
 #include "vf_select.h"
 
 namespace vf {
@@ -41,6 +40,101 @@ typedef float v16f_join __attribute__((ext_vector_type(16)));
 typedef int v16i_join __attribute__((ext_vector_type(16)));
 typedef int v4i_join __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u_join __attribute__((ext_vector_type(4)));
+
+// LDS buffers of one group of nc chunks: two where both fit beside the queues in 64 KiB
+__host__ __device__ constexpr int join_buffers(int nc) { return nc <= 32 ? 2 : 1; }
+
+// bfloat16 high parts of eight floats, and the bfloat16 rounding of what they leave
+__device__ __forceinline__ void split_bf16x8(const float (&f)[8], uint4 &hi, uint4 &lo)
+{
+    uint32_t a[8], b[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        a[i] = bf16_rn_bits(f[i]);
+        b[i] = bf16_rn_bits(f[i] - __uint_as_float(a[i] << 16));
+    }
+    hi = make_uint4(a[0] | (a[1] << 16), a[2] | (a[3] << 16), a[4] | (a[5] << 16), a[6] | (a[7] << 16));
+    lo = make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16));
+}
+
+// ---------------------------------------------------------------- sorting networks over the lanes of a wave
+//
+// Bitonic networks over 64-bit keys held one per lane, every cross-lane move on the vector ALU: lane ^ 1, 2, 4, 8 are
+// DPP moves (xor 4 = the mirror of 8 lanes, then the mirror of 4), lane ^ 16 and ^ 32 the row swaps of gfx950, which
+// leave both partners' keys in both lanes.  Which lanes keep the smaller key of a stage is a constant, so a stage is two
+// moves, one compare, one scalar xor of its result with that constant, and two selects; through ds_bpermute (the usual
+// shuffle) it is two LDS accesses and twice the selects.  They pay where several sets run at a time, as here; a lone
+// chain waits for every stage's trip through the scalar unit (in the beam search: a lone query 92 -> 97 us), so the
+// search kernels keep the shuffles.
+
+// Lanes that keep the smaller key when keys at distance J are compared inside ascending (descending: DESC) blocks of K.
+template <int K, int J, bool LAST, bool DESC> __host__ __device__ constexpr uint64_t keep_min_lanes()
+{
+    uint64_t m = 0;
+    for (int l = 0; l < 64; ++l) {
+        const bool up = (LAST || (l & K) == 0) != DESC;
+        if (((l & J) == 0) == up) m |= 1ull << l;
+    }
+    return m;
+}
+
+// a, b: the keys of a lane and of its partner at lane ^ J (J = 1, 2, 4, 8: a is the lane's own key; J = 16, 32: a is
+// the key of the partner whose bit J is clear, in both lanes)
+template <int J> __device__ __forceinline__ void lane_pair(uint32_t v, uint32_t &a, uint32_t &b)
+{
+    static_assert(J == 1 || J == 2 || J == 4 || J == 8 || J == 16 || J == 32, "J is a power of two below 64");
+    if constexpr (J == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = r[0]; b = r[1];
+    } else if constexpr (J == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = r[0]; b = r[1];
+    } else {
+        a = v;
+        if constexpr (J == 1) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);        // quad_perm [1,0,3,2]
+        else if constexpr (J == 2) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+        else if constexpr (J == 8) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
+        else {
+            const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);                         // row_half_mirror
+            b = (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, true);                               // quad_perm [3,2,1,0]
+        }
+    }
+}
+
+// One compare-exchange stage: the lanes of MIN keep the smaller key of the pair (lane, lane ^ J), the others the larger.
+template <int J, uint64_t MIN> __device__ __forceinline__ uint64_t lane_exchange(uint64_t v)
+{
+    uint32_t al, bl, ah, bh;
+    lane_pair<J>((uint32_t)v, al, bl);
+    lane_pair<J>((uint32_t)(v >> 32), ah, bh);
+    const uint64_t a = ((uint64_t)ah << 32) | al, b = ((uint64_t)bh << 32) | bl;
+    return __builtin_amdgcn_inverse_ballot_w64(__builtin_amdgcn_ballot_w64(a < b) ^ ~MIN) ? a : b;
+}
+
+// The stages J, J / 2, .. 1 that make a bitonic sequence of each aligned block of K lanes ascending (DESC: descending);
+// LAST: every block, else blocks alternate.  NR independent sets: their dependent chains interleave.
+template <int K, int J, bool LAST, bool DESC, class T, int NR> __device__ __forceinline__ void lane_merge_stages(T (&v)[NR])
+{
+#pragma unroll
+    for (int u = 0; u < NR; ++u) v[u] = lane_exchange<J, keep_min_lanes<K, J, LAST, DESC>()>(v[u]);
+    if constexpr (J > 1) lane_merge_stages<K, J / 2, LAST, DESC>(v);
+}
+template <int K, int SEG, bool DESC, class T, int NR> __device__ __forceinline__ void lane_sort_stages(T (&v)[NR])
+{
+    lane_merge_stages<K, K / 2, K == SEG, DESC>(v);
+    if constexpr (K < SEG) lane_sort_stages<K * 2, SEG, DESC>(v);
+}
+
+// Sort of the values held one per lane, inside every aligned segment of SEG lanes.
+template <int SEG, bool DESC, class T, int NR> __device__ __forceinline__ void lane_sort(T (&v)[NR])
+{
+    lane_sort_stages<2, SEG, DESC>(v);
+}
+// Ascending sort of a sequence that is bitonic inside every aligned segment of SEG lanes.
+template <int SEG, class T, int NR> __device__ __forceinline__ void lane_merge(T (&v)[NR])
+{
+    lane_merge_stages<SEG, SEG / 2, true, false>(v);
+}
 
 constexpr int kJoinQueue = 32;   // pending keys per row: what one group can add
 
@@ -366,7 +460,7 @@ __global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
 // 2 NK chunks of high parts, then 2 NK of low parts), and per entry half its squared norm (uint8: the squared norm of
 // the shifted bytes); an entry past the end of its list never passes a threshold.
 template <int DT>
-__global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map, const int64_t *grp_src, const int32_t *grp_cnt,
+__global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map, const JoinList *lists, int32_t n_lists,
                                  int64_t n_groups, int32_t nk, const uint32_t *norm_all, uint4 *xblk, uint32_t *xnorm)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -376,8 +470,14 @@ __global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map,
     const int64_t gc = t >> 5;
     const int c = (int)(gc % nch);
     const int64_t g = gc / nch;
-    const bool valid = v < grp_cnt[g];
-    const int64_t row = valid ? map[grp_src[g] + v] : 0;
+    int lo = 0, hi = n_lists - 1;   // the list of group g
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (lists[mid].group0 <= g) lo = mid; else hi = mid - 1;
+    }
+    const int64_t e = (g - lists[lo].group0) * 32 + v;
+    const bool valid = e < lists[lo].n;
+    const int64_t row = valid ? map[lists[lo].src + e] : 0;
     if (DT == 0) {
         uint4 w = make_uint4(0, 0, 0, 0);
         if (valid && c * 16 < dim) {
@@ -413,17 +513,17 @@ size_t join_group_bytes(int dtype, int32_t dim)
     return (size_t)(dtype == 0 ? join_chunks<0>(nk) : join_chunks<1>(nk)) * 512;
 }
 
-void launch_join_pack(int dtype, const void *X, int32_t dim, const int32_t *map, const int64_t *grp_src, const int32_t *grp_cnt,
+void launch_join_pack(int dtype, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
                       int64_t n_groups, const uint32_t *norm_all, uint4 *xblk, void *xnorm, hipStream_t s)
 {
     if (n_groups <= 0) return;
     const int32_t nk = join_steps(dtype, dim);
     const unsigned blocks = (unsigned)((n_groups * 2 * nk * 32 + 255) / 256);
     if (dtype == 0)
-        hipLaunchKernelGGL(join_pack_kernel<0>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, grp_src, grp_cnt,
+        hipLaunchKernelGGL(join_pack_kernel<0>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, lists, n_lists,
                            n_groups, nk, norm_all, xblk, (uint32_t *)xnorm);
     else
-        hipLaunchKernelGGL(join_pack_kernel<1>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, grp_src, grp_cnt,
+        hipLaunchKernelGGL(join_pack_kernel<1>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, lists, n_lists,
                            n_groups, nk, norm_all, xblk, (uint32_t *)xnorm);
 }
 

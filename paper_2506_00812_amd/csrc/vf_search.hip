@@ -273,7 +273,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         const Tuning &tn = ix->tune;
         const int32_t keep = std::min(64, k + tn.scan_bf16_margin);
         const bool small_batch = tn.scan_valu == 2 || (tn.scan_valu == 1 && r.scan_pairs.size() <= 256);
-        if (!exact && ix->has_ls16 && tn.scan_bf16 && tn.scan16 && !small_batch && keep > k &&
+        if (ix->has_ls16 && tn.scan_bf16 && tn.scan16 && !small_batch && keep > k &&
             !r.scan_pairs.empty() && scan_bf16_supported(ix->dtype, ix->dim, ib.tile_rows, keep) &&
             scan_bf16_lds_bytes(std::max(ib.tile_rows, 16), keep) <= 64 * 1024) {
             P.scan_bf16 = true;
@@ -301,7 +301,57 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         i = e;
     }
     P.n_ls_items = ib.items.size(); P.n_ls_merges = ib.merges.size();
-    // exact mode: one temporary interleaved copy per graph label, used right after it is made
+    const size_t ls_qrows = ib.qrow.size();
+    VF_REQUIRE(ib.part_rows < ((int64_t)1 << 31), "too many partial result rows in one call");
+    P.ls_part_words = P.part_words = (size_t)ib.part_rows * (P.scan_bf16 ? P.scan_keep : k);
+    // Exact mode, graph lists: packed copies of all of them (as many as fit into a GiB, or one that is larger) and one join
+    // over their queries.  float32 keeps spare candidates and proves the re-ranked result, which needs the norms to be
+    // within the proofs' range and room for enough spare ones.
+    const int32_t join_keep = ix->dtype == VF_U8 ? k : std::min(64, k + 22);
+    const bool joined = exact && first_hs < r.scan_pairs.size() && ix->d_xnorm_all.p != nullptr &&
+                        (ix->dtype == VF_U8 || (ix->xn_max > 0.f && ix->tune.scan_bf16 && join_keep >= k + 16));
+    if (joined) {
+        P.join_keep = join_keep;
+        ItemBuilder jb(ix->tune);
+        jb.tile_rows = kJoinRows;
+        jb.all_partial = true;
+        int64_t tile_groups = 0;
+        for (size_t i = first_hs, e; i < r.scan_pairs.size(); i = e) {
+            const uint64_t l = r.scan_pairs[i] >> 32;
+            for (e = i; e < r.scan_pairs.size() && r.scan_pairs[e] >> 32 == l;) ++e;
+            tile_groups += (int64_t)((e - i + kJoinRows - 1) / kJoinRows) * ((ix->S[(size_t)l] + 31) / 32);
+        }
+        // segments: a row's thresholds start over in each, so no more of them than keep the chip busy (two workgroups per
+        // CU at a time; three rounds of them level out the last one)
+        jb.seg_groups = jb.seg_groups_heavy = (int)std::max<int64_t>(64, tile_groups / 1536);
+        const int64_t batch_groups = (int64_t)(((size_t)1 << 30) / join_group_bytes(ix->dtype, ix->dim));
+        int64_t groups = 0;
+        JoinBatch b{0, 0, 0, 0, 0};
+        auto close = [&]() {
+            b.list_hi = P.jlists.size(); b.item_hi = jb.items.size(); b.groups = groups;
+            P.jbatches.push_back(b);
+            P.join_groups = std::max(P.join_groups, groups);
+            b.list_lo = b.list_hi; b.item_lo = b.item_hi; groups = 0;
+        };
+        for (size_t i = first_hs, e; i < r.scan_pairs.size(); i = e) {
+            const int32_t l = (int32_t)(r.scan_pairs[i] >> 32), n = ix->S[(size_t)l];
+            for (e = i; e < r.scan_pairs.size() && (int32_t)(r.scan_pairs[e] >> 32) == l;) ++e;
+            const int64_t ng = (n + 31) / 32;
+            if (groups > 0 && groups + ng > batch_groups) close();
+            P.jlists.push_back(JoinList{ix->O_HS[(size_t)l], (int32_t)groups, n});
+            jb.add_label(r.scan_pairs, i, e, groups, ix->O_HS[(size_t)l], n);
+            groups += ng;
+        }
+        close();
+        for (ScanItem &it : jb.items) it.q_begin += (int32_t)ls_qrows;
+        VF_REQUIRE(jb.part_rows < ((int64_t)1 << 31), "too many partial result rows in one call");
+        P.part_words += (size_t)jb.part_rows * join_keep;
+        P.join_max_nseg = jb.max_nseg;
+        ib.qrow.insert(ib.qrow.end(), jb.qrow.begin(), jb.qrow.end());
+        ib.items.insert(ib.items.end(), jb.items.begin(), jb.items.end());
+        ib.merges.insert(ib.merges.end(), jb.merges.begin(), jb.merges.end());
+    } else
+    // ... or one temporary interleaved copy per graph label, used right after it is made
     for (size_t i = first_hs; i < r.scan_pairs.size();) {
         const int32_t l = (int32_t)(r.scan_pairs[i] >> 32);
         size_t e = i;
@@ -312,8 +362,10 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         P.max_hs_list = std::max(P.max_hs_list, ix->S[(size_t)l]);
         i = e;
     }
-    VF_REQUIRE(ib.part_rows < ((int64_t)1 << 31), "too many partial result rows in one call");
-    P.part_words = (size_t)ib.part_rows * (P.scan_bf16 ? P.scan_keep : k);
+    if (!joined) {
+        VF_REQUIRE(ib.part_rows < ((int64_t)1 << 31), "too many partial result rows in one call");
+        P.part_words = (size_t)ib.part_rows * (P.scan_bf16 ? P.scan_keep : k);
+    }
 
     // selectivity-aware routing: AND queries whose (smallest) graph list is short leave the graph path
     r.xq_query.clear(); r.xq_label.clear();
@@ -401,6 +453,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     L.off_merges = o; o = align_up(o + std::max<size_t>(ib.merges.size(), 1) * sizeof(MergeItem));
     L.off_tiles = o; o = align_up(o + std::max<size_t>(P.tiles.size(), 1) * sizeof(SeedTile));
     L.off_empty = o; o = align_up(o + std::max<size_t>(r.empty_q.size(), 1) * 4);
+    L.off_jlists = o; o = align_up(o + P.jlists.size() * sizeof(JoinList));
     L.total = o;
     return VF_OK;
 }
@@ -424,6 +477,7 @@ void fill_blob(const CallPlan &P, const Routed &r, char *hp)
     if (!ib.items.empty()) memcpy(hp + L.off_items, ib.items.data(), ib.items.size() * sizeof(ScanItem));
     if (!ib.merges.empty()) memcpy(hp + L.off_merges, ib.merges.data(), ib.merges.size() * sizeof(MergeItem));
     if (!P.tiles.empty()) memcpy(hp + L.off_tiles, P.tiles.data(), P.tiles.size() * sizeof(SeedTile));
+    if (!P.jlists.empty()) memcpy(hp + L.off_jlists, P.jlists.data(), P.jlists.size() * sizeof(JoinList));
     if (!r.empty_q.empty()) memcpy(hp + L.off_empty, r.empty_q.data(), r.empty_q.size() * 4);
 }
 
@@ -623,7 +677,8 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 ScanParams sb = sp;
                 sb.xblk = ix->d_X_LS16.as<uint4>(); sb.K = P.scan_keep;
                 launch_scan_bf16(sb, (int)P.n_ls_items, tune.scan_bf16_slots, ss);
-                if (prof) { ix->prof.scan_kernel = 3; VF_HIP(hipEventRecord(ix->prof_ev[1], ss)); }
+                if (prof) ix->prof.scan_kernel = 3;
+                if (prof && !exact) VF_HIP(hipEventRecord(ix->prof_ev[1], ss));
                 RerankParams rp{};
                 rp.items = d_merges; rp.res_idx = sp.res_idx; rp.res_bits = sp.res_bits; rp.map = sp.map;
                 rp.X = ix->X; rp.Q = queries; rp.dim = ix->dim; rp.Kc = P.scan_keep; rp.K = k;
@@ -634,10 +689,10 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 rp.others_off = sp.others_off; rp.others = sp.others; rp.meta = sp.meta;
                 rp.out_ids = out_ids; rp.out_dists = out_dists;
                 launch_scan_rerank(rp, (int)P.n_ls_merges, ss);
-            } else if (!exact && small_batch && scan_valu_supported(ix->dtype, ix->dim, sp.tile_rows)) {
+            } else if (small_batch && scan_valu_supported(ix->dtype, ix->dim, sp.tile_rows)) {
                 launch_scan_valu(sp, (int)P.n_ls_items, ss);
                 if (prof) ix->prof.scan_kernel = 2;
-            } else if (!exact && tune.scan16 && scan16_supported(ix->dtype, ix->dim, sp.tile_rows)) {
+            } else if (tune.scan16 && scan16_supported(ix->dtype, ix->dim, sp.tile_rows)) {
                 launch_scan16(sp, (int)P.n_ls_items, ss);
                 if (prof) ix->prof.scan_kernel = 1;
             } else {
@@ -645,9 +700,39 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
             }
             // a search times its scan kernel by itself (the merge of the segments' candidates follows it)
             if (!P.scan_bf16) {
-                if (prof && P.hs_runs.empty()) VF_HIP(hipEventRecord(ix->prof_ev[1], ss));
+                if (prof && !exact) VF_HIP(hipEventRecord(ix->prof_ev[1], ss));
                 launch_scan_merge(ix->dtype, d_merges, (int)P.n_ls_merges, sp.res_idx, sp.res_bits, k, ib.max_nseg * k,
                                   ix->d_M_LS.as<int32_t>(), out_ids, out_dists, ss);
+            }
+        }
+        if (!P.jbatches.empty()) {
+            if ((rc = ix->tmp_blk.reserve((size_t)P.join_groups * join_group_bytes(ix->dtype, ix->dim))) != VF_OK) return rc;
+            if ((rc = ix->tmp_norm.reserve((size_t)P.join_groups * 32 * 4)) != VF_OK) return rc;
+            JoinParams jp{};
+            jp.xblk = ix->tmp_blk.as<uint4>(); jp.xnorm = ix->tmp_norm.p; jp.map = ix->d_M_HS.as<int32_t>();
+            jp.qsrc = queries; jp.qrow = sp.qrow; jp.dim = ix->dim; jp.K = P.join_keep;
+            jp.res_idx = M.part_idx + P.ls_part_words; jp.res_bits = M.part_bits + P.ls_part_words;
+            jp.others_off = d_others_off; jp.others = d_others; jp.meta = sp.meta;
+            for (const JoinBatch &b : P.jbatches) {
+                launch_join_pack(ix->dtype, ix->X, ix->dim, jp.map, (const JoinList *)(dp + L.off_jlists) + b.list_lo,
+                                 (int)(b.list_hi - b.list_lo), b.groups, ix->d_xnorm_all.as<uint32_t>(), ix->tmp_blk.as<uint4>(),
+                                 ix->tmp_norm.p, s);
+                jp.items = (const ScanItem *)(dp + L.off_items) + P.n_ls_items + b.item_lo;
+                launch_join(ix->dtype, jp, (int)(b.item_hi - b.item_lo), s);
+            }
+            const int n_merges = (int)(ib.merges.size() - P.n_ls_merges);
+            if (ix->dtype == VF_U8) {
+                launch_scan_merge(ix->dtype, d_merges + P.n_ls_merges, n_merges, jp.res_idx, jp.res_bits, k, P.join_max_nseg * k,
+                                  jp.map, out_ids, out_dists, s);
+            } else {
+                RerankParams rp{};
+                rp.items = d_merges + P.n_ls_merges; rp.res_idx = jp.res_idx; rp.res_bits = jp.res_bits; rp.map = jp.map;
+                rp.X = ix->X; rp.Q = queries; rp.dim = ix->dim; rp.Kc = P.join_keep; rp.K = k;
+                rp.err_bound = ix->join_err_bound(); rp.xn_max = ix->xn_max; rp.err_q = 0.f;
+                rp.fail_count = ix->d_scan_fb.as<uint32_t>();
+                rp.others_off = sp.others_off; rp.others = sp.others; rp.meta = sp.meta;
+                rp.out_ids = out_ids; rp.out_dists = out_dists;
+                launch_scan_rerank(rp, n_merges, s);
             }
         }
         if (!P.hs_runs.empty()) {
@@ -665,7 +750,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
             launch_scan_merge(ix->dtype, d_merges + P.n_ls_merges, (int)(ib.merges.size() - P.n_ls_merges), sp.res_idx,
                               sp.res_bits, k, ib.max_nseg * k, ix->d_M_HS.as<int32_t>(), out_ids, out_dists, s);
         }
-        if (prof && !(P.hs_runs.empty() && P.n_ls_items)) VF_HIP(hipEventRecord(ix->prof_ev[1], ss));
+        if (prof && (exact || !P.n_ls_items)) VF_HIP(hipEventRecord(ix->prof_ev[1], ss));
         if (forked) VF_HIP(hipEventRecord(ev_join, ss));
         return VF_OK;
     };

@@ -32,3 +32,44 @@ def test_graph_rows_at_tile_edges(dtype, dim, R):
     got = ix.export("G_HS").reshape(-1, R)
     bad = np.flatnonzero((got != want).any(axis=1))
     assert len(bad) == 0, f"{len(bad)} of {len(got)} rows differ, first {bad[:3]}: {got[bad[0]]} {want[bad[0]]}"
+
+
+@pytest.mark.parametrize("dtype,dim,k", [("float32", 100, 10), ("float32", 128, 1), ("float32", 96, 48), ("float32", 40, 49),
+                                         ("float32", 244, 64), ("uint8", 128, 10), ("uint8", 48, 64), ("uint8", 400, 7)])
+def test_exact_search_at_tile_edges(dtype, dim, k):
+    """Ground truth over graph lists: one, 128, 129 and 300 queries of a label, lists of several segments, AND queries, k up
+    to the largest for which spare candidates are kept and beyond it."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_close_with_ties, assert_exact, to_np
+    rng = np.random.default_rng(dim + k)
+    n, n_labels = 9000, 8
+    centres = rng.normal(size=(16, dim)) * (30 if dtype == "uint8" else 2) + (128 if dtype == "uint8" else 0)
+
+    def points(count):
+        x = centres[rng.integers(0, 16, count)] + rng.normal(size=(count, dim)) * (12 if dtype == "uint8" else 1)
+        return np.rint(x).clip(0, 255).astype(np.uint8) if dtype == "uint8" else x.astype(np.float32)
+
+    x = points(n)
+    x[100:130] = x[7]                                   # equal distances are ordered by id
+    share = np.array([0.95, 0.5, 0.3, 0.1, 0.05, 0.012, 0.004, 0.0])
+    carry = rng.random((n, n_labels)) < share
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    ids = np.nonzero(carry)[1].astype(np.int32)
+    asked = [[0]] * 300 + [[1]] * 129 + [[2]] * 128 + [[3]] + [[4]] * 5 + [[5]] * 3 + [[6]] * 2 + [[7]] + [[0, 1]] * 40 + \
+            [[1, 2, 3]] * 20 + [[0, 5]] * 10 + [[0, 7]]
+    order = rng.permutation(len(asked))
+    asked = [asked[i] for i in order]
+    qoff = np.concatenate([[0], np.cumsum([len(a) for a in asked])]).astype(np.int64)
+    qids = np.array([l for a in asked for l in a], dtype=np.int32)
+    q = points(len(asked))
+    q[3], q[4] = x[7], x[8]
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, n_labels, 200, 16)
+    ixo = OracleIndex(x, off, ids, n_labels, 200, 16, lazy_graph=True)
+    for count in (len(asked), 1):
+        gi, gd = vf.search_exact(ix, torch.from_numpy(q[:count]).cuda(), qoff[:count + 1], qids[:qoff[count]], k)
+        oi, od = ixo.search(q[:count], qoff[:count + 1], qids[:qoff[count]], k, force_scan=True)
+        if dtype == "uint8":
+            assert_exact(to_np(gi), to_np(gd), oi, od, "exact")
+        else:
+            assert_close_with_ties(to_np(gi), to_np(gd), oi, od, 1e-4, "exact")

@@ -5,8 +5,8 @@
 // bumps a counter.  Workgroup 0 of the resident kernel is the DISPATCHER: it alone polls that counter across
 // PCIe, copies new jobs into a ring in device memory and publishes them by advancing a device-side tail.  The
 // other workgroups are WORKERS (one query at a time, as in the paper's one block per query; NW waves each: all of
-// them score a share of the query's seeds, then the first wave searches while the others wait at the workgroup's
-// barrier): a worker claims the next job with a compare-and-swap on the device-side head -- the atomic ring buffer of
+// them score a share of the query's seeds, or scan a share of its list, then the first wave searches or merges while
+// the others wait at the workgroup's barrier): a worker claims the next job with a compare-and-swap on the device-side head -- the atomic ring buffer of
 // the paper's figure; "which worker is free" needs no queue of its own, a free worker is one that is polling --
 // routes it (smallest list, graph or scan by T, Section 4.1.2 / 4.3.2), runs the same beam search or list
 // scan the batched kernels run (the device functions are shared), writes the k results straight into the
@@ -73,6 +73,7 @@ struct ServeParams {
     int64_t max_jobs, idle_polls;
     int32_t lds_kernels;        // bytes of LDS the search functions use; the worker's own words follow (lds_own bytes)
     int32_t lds_own;
+    int32_t lds_scan;           // bytes of LDS the scan of one wave uses
 };
 
 template <class T> __device__ __forceinline__ T load_sys(const T *p) { return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM); }
@@ -132,8 +133,8 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
 
     // ---------------- worker
     // Every wave of the workgroup passes the same four barriers per job.  LDS: the search functions' area (first
-    // wave), then [0..7] others, [8..9] others_off, [10] qrow, [11..12] job, [16..] the query (FMA scan only), then
-    // per wave a copy of the query and a run of 64 seed keys.
+    // wave; a scan: a part for each), then [0..7] others, [8..9] others_off, [10] qrow, [11..12] job, then per wave a
+    // copy of the query and a run of 64 seed keys (a scan: 64 entries and 64 distances).
     int32_t *own = (int32_t *)((char *)smem + p.lds_kernels);
     char *share = (char *)smem + p.lds_kernels + p.lds_own;
     const int q_bytes = (p.row_bytes + 15) & ~15;
@@ -219,6 +220,32 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
             const uint64_t key = part.cur[0];   // (distance bits << 32 | seed index << 1 | 1), ascending
             runs[wv * 64 + lane] = key == KEY_MAX ? KEY_MAX : (key & 0xFFFFFFFF00000000ull) | ((key >> 1) & 0x7FFFFFFFull);
         }
+        // a scan list is shared out the same way, in whole groups: each wave leaves the k best of its share (one wave
+        // scanning a list of a few thousand vectors was the longest job of a session)
+        int32_t *part_idx = (int32_t *)(runs + wv * 64);
+        uint32_t *part_bits = (uint32_t *)part_idx + 64;
+        if (!empty && !graph) {
+            const int n = p.bp.meta.S[best], per = ((n + kGroup * NW - 1) / (kGroup * NW)) * kGroup;
+            ScanParams sp = p.sp;
+            sp.qsrc = qvec; sp.qrow = own + 10;
+            sp.others_off = o_cnt > 0 ? own + 8 : nullptr; sp.others = own;
+            sp.res_idx = part_idx; sp.res_bits = part_bits;
+            ScanItem it;
+            it.group0 = p.GO_LS[best] + wv * (per / kGroup); it.map_off = p.bp.meta.O_LS[best]; it.entry0 = wv * per;
+            it.n = n - wv * per < per ? n - wv * per : per;
+            it.q_begin = 0; it.q_count = 1; it.self_base = -1; it.part_row = 0;
+            uint4 *scan_smem = (uint4 *)((char *)smem + (size_t)wv * p.lds_scan);
+            if (it.n <= 0) {
+                part_idx[lane] = -1;
+            } else if constexpr (DT == 1 && (NC == 24 || NC == 32)) {
+                // the FMA scan takes its query as a wave-uniform operand: from LDS here (see scan_valu_item)
+                for (int i = lane; i < NC; i += 64) hq[i] = ((const uint4 *)qvec)[i];
+                wave_sync<true>();
+                scan_valu_item<NC, true>(sp, it, scan_smem, (const float *)hq);
+            } else {
+                scan_topk_item<DT, NC, true>(sp, it, scan_smem);
+            }
+        }
         __syncthreads();
 
         if (wv == 0) {
@@ -236,21 +263,18 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
                 }
                 beam_search_wave<DT, 1, true>(bp, bq, smem);
             } else {
-                ScanParams sp = p.sp;
-                sp.qsrc = qvec; sp.qrow = own + 10;
-                sp.others_off = o_cnt > 0 ? own + 8 : nullptr; sp.others = own;
-                sp.out_ids = res->ids; sp.out_dists = res->dists;
-                ScanItem it;
-                it.group0 = p.GO_LS[best]; it.map_off = p.bp.meta.O_LS[best]; it.entry0 = 0; it.n = p.bp.meta.S[best];
-                it.q_begin = 0; it.q_count = 1; it.self_base = -1; it.part_row = -1;
-                if constexpr (DT == 1 && (NC == 24 || NC == 32)) {
-                    // the FMA scan takes its query as a wave-uniform operand: from LDS here (see scan_valu_item)
-                    float *q_lds = (float *)(own + 16);
-                    for (int i = lane; i < NC; i += 64) ((uint4 *)q_lds)[i] = ((const uint4 *)qvec)[i];
-                    wave_sync<true>();
-                    scan_valu_item<NC, true>(sp, it, smem, q_lds);
-                } else {
-                    scan_topk_item<DT, NC, true>(sp, it, smem);
+                TopM<1> list;   // the waves' runs, ascending by (distance, entry)
+                list.init(k);
+                for (int w = 0; w < NW; ++w) {
+                    const int32_t *ri = (const int32_t *)(runs + w * 64);
+                    const int32_t idx = lane < k ? ri[lane] : -1;
+                    merge_sorted_run(list, idx >= 0 ? ((uint64_t)(uint32_t)ri[64 + lane] << 32) | (uint32_t)idx : KEY_MAX, lane);
+                }
+                if (lane < k) {
+                    const uint64_t key = list.cur[0];
+                    const uint32_t hi = (uint32_t)(key >> 32);
+                    res->ids[lane] = key == KEY_MAX ? -1 : (int64_t)p.sp.map[p.bp.meta.O_LS[best] + (uint32_t)key];
+                    res->dists[lane] = key == KEY_MAX ? __builtin_inff() : DT == 0 ? (float)(int)hi : __uint_as_float(hi);
                 }
             }
             wave_sync<true>();
@@ -366,11 +390,11 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     const size_t beam_lds = beam_lds_bytes(p.bp, ix->dtype);
     // scan: one query against a whole list
     p.sp.xblk = ix->d_X_LS.as<uint4>(); p.sp.xnorm = ix->d_xnorm_LS.p; p.sp.map = ix->d_M_LS.as<int32_t>();
-    p.sp.dim = ix->dim; p.sp.ncp = ix->ncp; p.sp.K = k; p.sp.tile_rows = 16; p.sp.meta = ix->meta();
+    p.sp.dim = ix->dim; p.sp.ncp = ix->ncp; p.sp.K = k; p.sp.tile_rows = 1; p.sp.meta = ix->meta();
     const bool valu = scan_valu_supported(ix->dtype, ix->dim, 16);
-    const size_t scan_lds = valu ? (size_t)16 * (96 + (k | 1)) * 8 + 2 * 32 * 4 : scan_lds_bytes(ix->ncp, 16, k);
-    const size_t lds_kernels = (std::max(beam_lds, scan_lds) + 63) & ~(size_t)63;
-    const size_t lds_own = (64 + (valu ? (size_t)sv->row_bytes : 0) + 63) & ~(size_t)63;
+    const size_t scan_lds = ((valu ? (size_t)(96 + (k | 1)) * 8 + 2 * 32 * 4 : scan_lds_bytes(ix->ncp, 1, k)) + 63) & ~(size_t)63;   // of one wave
+    const size_t lds_kernels = (std::max(beam_lds, waves * scan_lds) + 63) & ~(size_t)63;
+    const size_t lds_own = 64;
     // per wave a copy of the query and a run of 64 seed keys
     const size_t lds_share = (size_t)waves * ((((size_t)sv->row_bytes + 15) & ~(size_t)15) + 64 * 8);
     VF_REQUIRE(lds_kernels + lds_own + lds_share <= 64 * 1024, "search parameters need more than 64 KiB of LDS");
@@ -381,7 +405,7 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     VF_HIP(hipHostGetDevicePointer(&dv, sv->h_results, 0)); p.results = (ServeResult *)dv;
     VF_HIP(hipHostGetDevicePointer(&dv, sv->h_ctrl, 0)); p.hctrl = (ServeHostCtrl *)dv;
     p.dev_ring = sv->d_ring.as<char>(); p.dctrl = sv->d_ctrl.as<ServeDevCtrl>();
-    p.max_jobs = max_jobs; p.idle_polls = idle_polls; p.lds_kernels = (int32_t)lds_kernels; p.lds_own = (int32_t)lds_own;
+    p.max_jobs = max_jobs; p.idle_polls = idle_polls; p.lds_kernels = (int32_t)lds_kernels; p.lds_own = (int32_t)lds_own; p.lds_scan = (int32_t)scan_lds;
     const size_t lds = lds_kernels + lds_own + lds_share;
     if (ix->dtype == VF_U8) {
         if (ix->dim == 128) launch_serve<0, 4>(p, n_workers, waves, lds, sv->stream);
@@ -471,7 +495,7 @@ static int serve_end_impl(vf_server *sv, int64_t *jobs_done, int32_t *exit_reaso
     return VF_OK;
 }
 
-// A host batch through the session: submit in order with at most in_flight jobs outstanding, collect in order.
+// A host batch through the session: submit in order with at most in_flight jobs outstanding, collect as they finish.
 static int serve_run_impl(vf_server *sv, const void *queries, int64_t nq, const int64_t *qoff, const int32_t *qids,
                           int32_t in_flight, int64_t *out_ids, float *out_dists, float *latency_us)
 {
@@ -480,35 +504,41 @@ static int serve_run_impl(vf_server *sv, const void *queries, int64_t nq, const 
     using clock = std::chrono::steady_clock;
     std::vector<clock::time_point> t_sub((size_t)nq);
     std::vector<int64_t> job_of((size_t)nq);
-    int64_t next = 0, head = 0;   // next query to submit, oldest query not collected yet
+    // Jobs finish out of order (a scan of a short list long before a graph search): each is collected when it is done and
+    // its place in flight goes to the next query at once.  Waiting for the oldest first left most of the places idle.
+    std::vector<int64_t> open;    // submitted, not collected; ascending
+    open.reserve((size_t)in_flight);
+    int64_t next = 0;
     const auto deadline = clock::now() + std::chrono::seconds(120);
-    while (head < nq) {
+    while (next < nq || !open.empty()) {
         bool moved = false;
-        if (next < nq && next - head < in_flight) {
+        // (a result must be read before ring_slots further jobs are submitted)
+        while (next < nq && (int64_t)open.size() < in_flight && (open.empty() || next - open[0] < sv->ring_slots)) {
             const int64_t b = qoff[next], e = qoff[next + 1];
             VF_REQUIRE(e > b && e - b <= kMaxOthers + 1, "a query needs 1 to 8 labels");
             int64_t job = -1;
             const int rc = serve_submit_impl(sv, (const char *)queries + (size_t)next * sv->row_bytes, qids + b, (int32_t)(e - b), &job);
-            if (rc == VF_OK) {
-                t_sub[(size_t)next] = clock::now();
-                job_of[(size_t)next] = job;
-                ++next;
-                moved = true;
-            } else if (rc != VF_EBUSY) {
-                return rc;
-            }
+            if (rc == VF_EBUSY) break;
+            if (rc != VF_OK) return rc;
+            t_sub[(size_t)next] = clock::now();
+            job_of[(size_t)next] = job;
+            open.push_back(next);
+            ++next;
+            moved = true;
         }
-        if (head < next) {
+        size_t left = 0;
+        for (const int64_t q : open) {
             int32_t done = 0;
-            const int rc = serve_poll_impl(sv, job_of[(size_t)head], out_ids + head * sv->k, out_dists + head * sv->k, &done);
+            const int rc = serve_poll_impl(sv, job_of[(size_t)q], out_ids + q * sv->k, out_dists + q * sv->k, &done);
             if (rc != VF_OK) return rc;
             if (done) {
-                if (latency_us)
-                    latency_us[head] = std::chrono::duration<float, std::micro>(clock::now() - t_sub[(size_t)head]).count();
-                ++head;
+                if (latency_us) latency_us[q] = std::chrono::duration<float, std::micro>(clock::now() - t_sub[(size_t)q]).count();
                 moved = true;
+            } else {
+                open[left++] = q;
             }
         }
+        open.resize(left);
         if (!moved && clock::now() > deadline) {
             set_error("vf_serve_run: no progress for two minutes");
             return VF_EHIP;

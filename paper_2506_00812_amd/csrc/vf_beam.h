@@ -492,12 +492,23 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     auto select_seeds = [&](TopM<1> &list, const uint32_t *drow, bool as_index) -> int {
         constexpr int NBLK = VF_SEED_BLOCKS;
         int done_to = 0;
+        // LAT: the next chunk is requested before this one is dealt with (nothing else hides its latency)
+        uint32_t ahead[LAT ? NBLK : 1];
+        if constexpr (LAT) {
+#pragma unroll
+            for (int i = 0; i < NBLK; ++i) ahead[i] = i * 64 + lane < ns ? drow[i * 64 + lane] : 0xFFFFFFFFu;
+        }
         for (int jc = 0; jc < ns; jc += 64 * NBLK) {
             uint32_t v[NBLK];
 #pragma unroll
             for (int i = 0; i < NBLK; ++i) {
                 const int j = jc + i * 64 + lane;
-                v[i] = j < ns ? drow[j] : 0xFFFFFFFFu;
+                if constexpr (LAT) {
+                    v[i] = ahead[i];
+                    ahead[i] = j + 64 * NBLK < ns ? drow[j + 64 * NBLK] : 0xFFFFFFFFu;
+                } else {
+                    v[i] = j < ns ? drow[j] : 0xFFFFFFFFu;
+                }
             }
             const int chunk_n = ns - jc < 64 * NBLK ? ns - jc : 64 * NBLK;
             int chunk_scored = chunk_n, chunk_tested = o_cnt > 0 ? chunk_n : 0;   // every seed counts as tested

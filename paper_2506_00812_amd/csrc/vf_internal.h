@@ -216,7 +216,7 @@ struct SeedParams {
     int32_t seed_bf16;          // float32 data: seed_blk holds the seeds rounded to bfloat16 (chunks of 8 components)
     const uint32_t *seed_norm;  // [group * 32 + v] squared norms as in xnorm_all
     const int64_t *seed_goff;   // [n_graph_labels] first group of each graph list, by rank among graph labels
-    int32_t chunk_seeds;        // seeds per wave: kSeedMfmaChunk, or four times that (interleaved copy only); max_chunks matches it
+    int32_t chunk_seeds;        // seeds per wave: kSeedMfmaChunk, or 32 or four times kSeedMfmaChunk (interleaved copy only); max_chunks matches it
     int64_t dump_off;           // seed_mfma_kernel: dseed[dump_off .. dump_off + 64 * (dump_mask + 1)) takes the stores of
     int32_t dump_mask;          // lanes without a pair, 64 entries per workgroup index & dump_mask (2^k - 1)
 };

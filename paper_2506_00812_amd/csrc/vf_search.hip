@@ -621,6 +621,9 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                     sd.chunk_seeds = 4 * kSeedMfmaChunk;
                     if ((int64_t)P.tiles.size() * ((P.ns_stride + sd.chunk_seeds - 1) / sd.chunk_seeds) < 512)
                         sd.chunk_seeds = kSeedMfmaChunk;
+                    // a launch that leaves most SIMDs without a wave even so (a handful of queries): a wave per group of
+                    // 32 seeds, its four groups' serial chain of MFMAs cut to one
+                    if ((int64_t)P.tiles.size() * ((P.ns_stride + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 256) sd.chunk_seeds = 32;
                     sd.max_chunks = (P.ns_stride + sd.chunk_seeds - 1) / sd.chunk_seeds;
                 }
                 launch_seed_mfma(ix->dtype, sd, (int)P.tiles.size(), s);

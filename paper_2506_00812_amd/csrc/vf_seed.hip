@@ -28,7 +28,9 @@
 
 namespace vf {
 
-template <int DT, int NCH>
+// NCH: 16-byte chunks per vector; FIT = false: an upper bound of them (dimensions without an instantiation of their own),
+// the chunks that do not exist are zero on both sides, which leaves every partial sum as it is.
+template <int DT, int NCH, bool FIT>
 __global__ __launch_bounds__(64) void seed_dist_kernel(SeedParams p)
 {
     constexpr int SC = kSeedChunk;
@@ -42,7 +44,8 @@ __global__ __launch_bounds__(64) void seed_dist_kernel(SeedParams p)
     const int j0 = chunk * SC;
     if (j0 >= ns) return;
     const int cnt = ns - j0 < SC ? ns - j0 : SC;
-    constexpr int row_bytes = NCH * kChunkBytes;
+    const int nch = FIT ? NCH : p.dim * (DT == 0 ? 1 : 4) / kChunkBytes;
+    const int row_bytes = nch * kChunkBytes;
 
     // seeds of this chunk -> global ids (lane i holds seed j0 + i)
     int g = 0;
@@ -55,7 +58,8 @@ __global__ __launch_bounds__(64) void seed_dist_kernel(SeedParams p)
         const uint4 *qrow = (const uint4 *)((const char *)p.Q + (int64_t)qi * row_bytes);
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
-            const uint4 v = qrow[ch];
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (FIT || ch < nch) v = qrow[ch];
             q[ch * 4] = v.x; q[ch * 4 + 1] = v.y; q[ch * 4 + 2] = v.z; q[ch * 4 + 3] = v.w;
         }
     }
@@ -70,14 +74,26 @@ __global__ __launch_bounds__(64) void seed_dist_kernel(SeedParams p)
         // as a scalar operand -- no LDS staging, no cross-lane traffic
         const int gi = __builtin_amdgcn_readlane(g, i);
         const uint32_t *__restrict__ xp = (const uint32_t *)((const char *)p.X + (int64_t)gi * row_bytes);
+        // chunk ch of the seed (every load is a whole chunk, unconditional and in bounds, so that all of a vector's can be
+        // in flight)
+        auto chunk_of = [&](int ch, uint32_t (&x)[4]) {
+            const uint32_t *c = xp + 4 * (FIT || ch < nch ? ch : nch - 1);
+#pragma unroll
+            for (int w = 0; w < 4; ++w) x[w] = c[w];
+            if (!FIT && ch >= nch) x[0] = x[1] = x[2] = x[3] = 0u;
+        };
         uint32_t bits;
         if (DT == 0) {
             uint32_t xx = 0, qx = 0;
 #pragma unroll
-            for (int w = 0; w < NCH * 4; ++w) {
-                const uint32_t x = xp[w];
-                xx = __builtin_amdgcn_udot4(x, x, xx, false);
-                qx = __builtin_amdgcn_udot4(q[w], x, qx, false);
+            for (int ch = 0; ch < NCH; ++ch) {
+                uint32_t x[4];
+                chunk_of(ch, x);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    xx = __builtin_amdgcn_udot4(x[w], x[w], xx, false);
+                    qx = __builtin_amdgcn_udot4(q[ch * 4 + w], x[w], qx, false);
+                }
             }
             bits = (uint32_t)((int)qq + (int)xx - 2 * (int)qx);
         } else {
@@ -86,9 +102,11 @@ __global__ __launch_bounds__(64) void seed_dist_kernel(SeedParams p)
             for (int u = 0; u < 8; ++u) a[u] = 0.0f;
 #pragma unroll
             for (int ch = 0; ch < NCH; ++ch) {
+                uint32_t x[4];
+                chunk_of(ch, x);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const float d = __uint_as_float(q[ch * 4 + c]) - __uint_as_float(xp[ch * 4 + c]);
+                    const float d = __uint_as_float(q[ch * 4 + c]) - __uint_as_float(x[c]);
                     a[ch & 7] = __builtin_fmaf(d, d, a[ch & 7]);
                 }
             }
@@ -674,21 +692,25 @@ void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s
     const dim3 grid((unsigned)n_tiles * (unsigned)p.max_chunks), block(64);
     // separate instantiations for the two operand sources (one kernel holding both paths needs so many
     // registers that a SIMD takes a single wave of it) and for the seeds per wave (p.chunk_seeds: 128,
-    // or 512 with the interleaved copy)
+    // or 32 or 512 with the interleaved copy)
     const bool cached = p.seed_blk != nullptr;
     const bool wide = cached && p.chunk_seeds == 4 * kSeedMfmaChunk;
+    const bool narrow = cached && p.chunk_seeds == 32;
 #define VF_LAUNCH_SEED(DT_, NCP_) \
     do { \
         if (wide) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 16>), grid, block, 0, s, p); \
+        else if (narrow) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 1>), grid, block, 0, s, p); \
         else if (cached) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 4>), grid, block, 0, s, p); \
         else hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, false, 4>), grid, block, 0, s, p); \
     } while (0)
     if (dtype == 1 && p.seed_bf16 && cached) {
         if (p.dim == 128) {
             if (wide) hipLaunchKernelGGL((seed_mfma_kernel<2, 8, true, 16>), grid, block, 0, s, p);
+            else if (narrow) hipLaunchKernelGGL((seed_mfma_kernel<2, 8, true, 1>), grid, block, 0, s, p);
             else hipLaunchKernelGGL((seed_mfma_kernel<2, 8, true, 4>), grid, block, 0, s, p);
         } else if (p.dim == 96) {
             if (wide) hipLaunchKernelGGL((seed_mfma_kernel<2, 6, true, 16>), grid, block, 0, s, p);
+            else if (narrow) hipLaunchKernelGGL((seed_mfma_kernel<2, 6, true, 1>), grid, block, 0, s, p);
             else hipLaunchKernelGGL((seed_mfma_kernel<2, 6, true, 4>), grid, block, 0, s, p);
         }
     } else if (dtype == 1 && p.dim == 128) VF_LAUNCH_SEED(1, 16);
@@ -791,22 +813,31 @@ void launch_row_norms(int dtype, const void *X, int32_t dim, int64_t n, uint32_t
     else hipLaunchKernelGGL(row_norm_kernel<0>, grid, block, 0, s, X, dim, n, out);
 }
 
+// every dimension an index may have (at most 62 chunks)
 bool seed_dist_supported(int dtype, int dim)
 {
     const int nch = dim * (dtype == 0 ? 1 : 4) / kChunkBytes;
-    return nch == 8 || nch == 12 || nch == 16 || nch == 24 || nch == 32;
+    return nch >= 1 && nch <= 64;
 }
 
+// Dimensions without an instantiation of their own take the next larger one with the missing chunks zeroed: a few
+// scalar selects per seed (1,200 graph queries x 777 seeds, dim 100: the beam kernel gathering its seeds instead
+// took 214 us, both together 176 us).
 template <int DT> static void launch_seed_dt(const SeedParams &p, int nch, unsigned grid, hipStream_t s)
 {
-    switch (nch) {
-    case 8: hipLaunchKernelGGL((seed_dist_kernel<DT, 8>), dim3(grid), dim3(64), 0, s, p); break;
-    case 12: hipLaunchKernelGGL((seed_dist_kernel<DT, 12>), dim3(grid), dim3(64), 0, s, p); break;
-    case 16: hipLaunchKernelGGL((seed_dist_kernel<DT, 16>), dim3(grid), dim3(64), 0, s, p); break;
-    case 24: hipLaunchKernelGGL((seed_dist_kernel<DT, 24>), dim3(grid), dim3(64), 0, s, p); break;
-    case 32: hipLaunchKernelGGL((seed_dist_kernel<DT, 32>), dim3(grid), dim3(64), 0, s, p); break;
-    default: break;
-    }
+#define VF_SEED_DIST(NCH_, FIT_) hipLaunchKernelGGL((seed_dist_kernel<DT, NCH_, FIT_>), dim3(grid), dim3(64), 0, s, p)
+    if (nch == 8) VF_SEED_DIST(8, true);
+    else if (nch == 12) VF_SEED_DIST(12, true);
+    else if (nch == 16) VF_SEED_DIST(16, true);
+    else if (nch == 24) VF_SEED_DIST(24, true);
+    else if (nch == 32) VF_SEED_DIST(32, true);
+    else if (nch < 8) VF_SEED_DIST(8, false);
+    else if (nch < 16) VF_SEED_DIST(16, false);
+    else if (nch < 24) VF_SEED_DIST(24, false);
+    else if (nch < 32) VF_SEED_DIST(32, false);
+    else if (nch <= 48) VF_SEED_DIST(48, false);
+    else VF_SEED_DIST(64, false);
+#undef VF_SEED_DIST
 }
 
 void launch_seed_dist(int dtype, const SeedParams &p, int n_tiles, hipStream_t s)

@@ -377,6 +377,9 @@ class Server:
                             int(waves_per_worker), int(max_jobs), int(idle_polls))
         h = C.c_void_p()
         index._enter()
+        if index.allocator is not None:   # its blocks follow the current stream's order; the session uses them on a stream of its own
+            import torch
+            torch.cuda.current_stream().synchronize()
         _check(load_library().vf_serve_begin(index._h, C.byref(prm), C.byref(h)))
         self._h = h
         self._np_dtype = np.uint8 if _dtype_code(index.vectors) == VF_U8 else np.float32

@@ -859,7 +859,8 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     // follows the previous call's scan, not the previous call's beam search, so the upload is off the
     // critical path.  The buffer was last read two calls ago, by kernels on the side stream (which precede the
     // upload there) and on the caller's stream: those precede the fork event of the previous call, which the
-    // side stream has waited for -- if that call forked; if not, the upload first waits for the caller's stream.
+    // side stream has waited for -- if that call forked; if not, and where the buffer is new, the upload first waits for
+    // the caller's stream.
     // A small blob (small batches) is not copied at all: the kernels read the few hundred bytes they need
     // straight from the pinned staging buffer, which saves the copy's submission and its latency; the
     // staging buffer then stays untouched until the call's last kernel has ended.
@@ -873,10 +874,13 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
         M.blob = (char *)dev_view;
     } else {
         W->blob_next ^= 1;
+        // (a buffer that is allocated now may, with an allocator that works in stream order, still be in use by work that
+        // the caller has queued on its stream: another index's outputs, say)
+        const bool fresh = L.total > blob.cap;
         if ((rc = blob.reserve(L.total)) != VF_OK) return rc;
         M.blob = blob.as<char>();
         hipStream_t cs = forked ? W->side : s;
-        if (forked && !W->prev_forked) {
+        if (forked && (!W->prev_forked || fresh)) {
             VF_HIP(hipEventRecord(W->ev_fork, s));
             VF_HIP(hipStreamWaitEvent(cs, W->ev_fork, 0));
         }

@@ -89,7 +89,9 @@ struct Tuning {
     int seg_groups_heavy = 16;    // the same for tiles of >= heavy_rows queries
     int heavy_rows = 9;
     int tile_rows = 16;           // queries per scan tile
-    int zero_copy_bytes = 8192;   // a per-call routing blob up to this size is read in place from pinned host memory
+    // a per-call routing blob up to this size is read in place from pinned host memory: a call of 1,000 queries saves the
+    // copy, its event and a wait, 105 -> 80 us; at 10,000 queries the reads cost more than that (216 -> 222 us)
+    int zero_copy_bytes = 32768;
     int scan_valu = 1;            // float32 FMA scan kernel: 0 never, 1 for batches of <= 256 scan queries, 2 always
     int scan16 = 1;               // 0: float32 search tiles keep the 32-row matrix-core kernel
     int scan_bf16 = 1;            // float32 lists of large batches: filter from the bfloat16 copy, re-rank exactly (0: off)

@@ -292,6 +292,7 @@ struct BeamQuery {
     int32_t *counters;         // optional [4]: distances computed, rows expanded, predicate tests, mode word
     int32_t *gathered;         // optional [1]
     const uint32_t *dseed_row; // optional: the query's row of the seed distance matrix
+    const uint32_t *dmin_row = nullptr; // optional, with it: smallest value of every block of 32 seeds
     const uint64_t *runs;      // optional: the query's runs from the selecting seed kernel
     int32_t seed_pass;         // seeds that pass the predicate (profiling, AND), -1: not counted
 };
@@ -489,9 +490,89 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     // instead of the local id floor(j * n / ns).  Returns the number of seeds dealt with (a chunk
     // whose bound lets more than 128 seeds through ends the selection early).
     bool lazy_used = false, lazy_ok = true;
+    // The same selection through the blocks' minima, for queries without a predicate: with tau the M-th smallest minimum
+    // at least M seeds are at or below tau, and all of those lie in the M blocks (more with ties) whose minimum is at or
+    // below it: those blocks are read and nothing else of the row.  Returns false, with nothing offered, where it does not
+    // apply: few blocks per list entry (most would be read), rows of more minima than a lane's registers take, more ties
+    // than there is room for; or with something offered where a chunk holds more candidates than there is room for.
+    auto select_by_blocks = [&](TopM<1> &list, const uint32_t *drow, bool as_index) -> bool {
+        constexpr int NBLK = VF_SEED_BLOCKS;
+        const int nb = (ns + 31) >> 5;
+        if (nb < 3 * list.itopk || nb > 64 * NBLK) return false;
+        uint32_t v[NBLK];
+        uint32_t m1 = 0xFFFFFFFFu, m2 = 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < NBLK; ++i) {
+            v[i] = 0xFFFFFFFFu;
+            if (i * 64 < nb && i * 64 + lane < nb) v[i] = bq.dmin_row[i * 64 + lane];
+        }
+#pragma unroll
+        for (int i = 0; i < NBLK; ++i) {
+            const uint32_t hi = v[i] > m1 ? v[i] : m1;
+            m2 = hi < m2 ? hi : m2;
+            m1 = v[i] < m1 ? v[i] : m1;
+        }
+        const uint32_t s1 = wave_sort_u32(m1, lane), s2 = wave_sort_u32(m2, lane);
+        const uint32_t s2r = (uint32_t)__shfl((int)s2, 63 - lane);
+        const uint32_t tau = (uint32_t)__builtin_amdgcn_readlane((int)wave_merge_u32(s1 < s2r ? s1 : s2r, lane), list.itopk - 1);
+        if (tau == 0xFFFFFFFFu) return false;
+        int n_blocks = 0;
+        wave_sync<STREAM_SEEDS>();
+#pragma unroll
+        for (int i = 0; i < NBLK; ++i) {
+            const uint64_t m = __ballot(v[i] <= tau);
+            if (m == 0) continue;
+            const int at = n_blocks + __popcll(m & ((1ull << lane) - 1ull));
+            if (v[i] <= tau && at < 128) cand_g[at] = i * 64 + lane;
+            n_blocks += __popcll(m);
+        }
+        wave_sync<STREAM_SEEDS>();
+        if (n_blocks > 128) return false;
+        for (int b0 = 0; b0 < n_blocks; b0 += 2 * NBLK) {
+            int jv[NBLK];
+#pragma unroll
+            for (int i = 0; i < NBLK; ++i) {
+                const int b = b0 + 2 * i + (lane >> 5);
+                jv[i] = b < n_blocks ? cand_g[b] * 32 + (lane & 31) : ns;
+                v[i] = jv[i] < ns ? drow[jv[i]] : 0xFFFFFFFFu;
+            }
+            const uint32_t bound = (uint32_t)(list.worst >> 32) < tau ? (uint32_t)(list.worst >> 32) : tau;
+            int cnt = 0;
+#pragma unroll
+            for (int i = 0; i < NBLK; ++i) {
+                const bool pass = v[i] <= bound && jv[i] < ns;
+                const uint64_t m = __ballot(pass);
+                if (m == 0) continue;
+                const int at = cnt + __popcll(m & ((1ull << lane) - 1ull));
+                if (pass && at < 128) {
+                    cand_d[at] = v[i];
+                    cand_c[at] = jv[i];
+                }
+                cnt += __popcll(m);
+            }
+            wave_sync<STREAM_SEEDS>();
+            if (cnt > 128) return false;
+            for (int i0 = 0; i0 < cnt; i0 += 64) {
+                const int i = i0 + lane;
+                const bool valid = i < cnt;
+                int c = valid ? cand_c[i] : 0;
+                if (!as_index) c = (int)(((uint64_t)c * (uint64_t)n) / (uint64_t)ns);
+                offer_seeds_to(list, valid, valid ? cand_d[i] : 0u, c);
+            }
+            wave_sync<STREAM_SEEDS>();
+        }
+        n_scored += ns;
+        return true;
+    };
     auto select_seeds = [&](TopM<1> &list, const uint32_t *drow, bool as_index) -> int {
         constexpr int NBLK = VF_SEED_BLOCKS;
         int done_to = 0;
+        if constexpr (!LAT && !STREAM_SEEDS && (DT == 0 || !AND)) {   // (few queries have no minima; float32 with a predicate: no registers)
+            if (bq.dmin_row != nullptr && o_cnt == 0) {
+                if (select_by_blocks(list, drow, as_index)) return ns;
+                list.init(list.itopk);   // (whatever it has offered is offered again)
+            }
+        }
         // LAT: the next chunk is requested before this one is dealt with (nothing else hides its latency)
         uint32_t ahead[LAT ? NBLK : 1];
         if constexpr (LAT) {

@@ -31,6 +31,7 @@ __global__ __launch_bounds__(64, LAT ? 2 : (DT == 1 && E == 1) ? (AND ? 6 : 7) :
     bq.counters = p.counters != nullptr ? p.counters + (int64_t)qi * 4 : nullptr;
     bq.gathered = p.gathered != nullptr ? p.gathered + qi : nullptr;
     bq.dseed_row = p.dseed != nullptr ? p.dseed + (int64_t)gq * p.ns_stride : nullptr;
+    bq.dmin_row = p.dmin != nullptr ? p.dmin + (int64_t)gq * p.nb_stride : nullptr;
     bq.runs = p.seed_runs != nullptr ? p.seed_runs + (int64_t)gq * p.run_segs * p.run_K : nullptr;
     bq.seed_pass = p.seed_pass != nullptr ? p.seed_pass[gq] : -1;
     beam_search_wave<DT, E, false, AND, LAT>(p, bq, smem);

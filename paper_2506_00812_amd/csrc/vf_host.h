@@ -328,6 +328,7 @@ struct CallPlan {
     bool exact = false;
     int32_t beam_LP = 128, beam_hb = 9;   // beam kernel geometry: list slots and visited-table size
     int32_t ns_stride = 0;                // row length of the seed distance matrix
+    int32_t nb_stride = 0;                // > 0: the seed kernel leaves the minima of its 32-seed blocks too, rows of this length
     ItemBuilder ib;
     size_t n_ls_items = 0, n_ls_merges = 0;
     std::vector<HsRun> hs_runs;

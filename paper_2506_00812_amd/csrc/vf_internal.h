@@ -167,6 +167,10 @@ struct BeamParams {
     int32_t *gathered; // optional [nq]: distances whose vector the kernel fetched itself
     const uint32_t *dseed; // optional [n_gq][ns_stride]: seed distance bits from seed_dist_kernel / seed_mfma_kernel
     int32_t ns_stride;
+    // optional, with dseed: [n_gq][nb_stride] smallest value of every block of 32 consecutive seeds (whole blocks of the
+    // query's seeds; the rest of a row is undefined)
+    const uint32_t *dmin;
+    int32_t nb_stride;
     // dseed holds MFMA approximations (float32 only): the kernel re-scores the best of them with the
     // ordered distance and proves, with B = err_bound * (|q|^2 + xn_max) + err_q * |q|, that no other seed can matter
     int32_t seed_approx;
@@ -217,6 +221,8 @@ struct SeedParams {
     const uint32_t *seed_norm;  // [group * 32 + v] squared norms as in xnorm_all
     const int64_t *seed_goff;   // [n_graph_labels] first group of each graph list, by rank among graph labels
     int32_t chunk_seeds;        // seeds per wave: kSeedMfmaChunk, or 32 or four times kSeedMfmaChunk (interleaved copy only); max_chunks matches it
+    uint32_t *dmin;             // optional (chunk_seeds = 4 * kSeedMfmaChunk): see BeamParams::dmin; rows of nb_stride words, a multiple of 16
+    int32_t nb_stride;
     int64_t dump_off;           // seed_mfma_kernel: dseed[dump_off .. dump_off + 64 * (dump_mask + 1)) takes the stores of
     int32_t dump_mask;          // lanes without a pair, 64 entries per workgroup index & dump_mask (2^k - 1)
 };

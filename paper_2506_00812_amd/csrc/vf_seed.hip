@@ -154,6 +154,41 @@ typedef __bf16 v8bf_seed __attribute__((ext_vector_type(8)));
 // v_mfma_f32_32x32x16_bf16 into one float32 accumulator: half the operand bytes and a quarter of the
 // matrix-core time of the float32 form (two products per component at sixteen times the rate).  The norms stay those of the unrounded vectors, so the only new
 // error is 2 q.(x - bf16(x)), which the beam kernel's bound carries as err_q * |q|.
+// The smallest of a group's 32 values for each of the accumulator's rows: lane n32 of a half holds element jj of the 16
+// (row 8 (jj / 4) + 4 h + jj % 4) for column n32; each step halves the elements a lane keeps and doubles the columns they
+// cover, so 16 rows cost about as many instructions as two reductions of one value.  Returns element n32 & 15 over all
+// columns.  valid: the lane's column exists.
+__device__ __forceinline__ uint32_t group_min(const uint32_t (&bits)[16], bool valid, int n32)
+{
+    uint32_t a[8], b[4], c[2];
+    const bool b0 = n32 & 1, b1 = n32 & 2, b2 = n32 & 4, b3 = n32 & 8;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t x = valid ? bits[2 * i] : 0xFFFFFFFFu, y = valid ? bits[2 * i + 1] : 0xFFFFFFFFu;
+        const uint32_t keep = b0 ? y : x, give = b0 ? x : y;
+        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0xB1, 0xF, 0xF, true);    // lane ^ 1
+        a[i] = keep < got ? keep : got;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t keep = b1 ? a[2 * i + 1] : a[2 * i], give = b1 ? a[2 * i] : a[2 * i + 1];
+        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0x4E, 0xF, 0xF, true);    // lane ^ 2
+        b[i] = keep < got ? keep : got;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t keep = b2 ? b[2 * i + 1] : b[2 * i], give = b2 ? b[2 * i] : b[2 * i + 1];
+        const int m = __builtin_amdgcn_update_dpp(0, (int)give, 0x141, 0xF, 0xF, true);                    // lane ^ 7
+        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, true);            // ... ^ 3: lane ^ 4
+        c[i] = keep < got ? keep : got;
+    }
+    const uint32_t keep = b3 ? c[1] : c[0], give = b3 ? c[0] : c[1];
+    const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0x128, 0xF, 0xF, true);       // lane ^ 8
+    const uint32_t d = keep < got ? keep : got;
+    const auto r = __builtin_amdgcn_permlane16_swap(d, d, false, false);                                  // columns below and from 16
+    return r[0] < r[1] ? r[0] : r[1];
+}
+
 template <int DT, int NCP, bool CACHED, int NG>
 __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
 {
@@ -254,6 +289,7 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
 #pragma unroll
     for (int jj = 0; jj < 16; ++jj) qn[jj] = qnorm_s[8 * (jj >> 2) + 4 * h + (jj & 3)];
 
+    uint32_t gmin[NG >= 16 ? NG : 1];   // per group: smallest value of row row_of(n32 & 15, h), see group_min
     uint4 bnext[NCP];
     auto fetch_group = [&](int g) {   // group g of this wave's seeds (exists)
         if (cached) {
@@ -324,6 +360,7 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
                 bits[jj] = __float_as_uint(fmaxf(d, 0.0f));
             }
         }
+        if constexpr (NG >= 16) gmin[g] = p.dmin != nullptr ? group_min(bits, j0 + g * 32 + n32 < ns, n32) : 0u;
         // Every lane stores every value, those without a (query, seed) pair into a dump area behind the
         // matrix: with the stores under conditions the compiler cannot count them, and its wait for the next
         // group's operand loads becomes a wait for these stores to be acknowledged as well.  The dump area has
@@ -337,6 +374,16 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
             const bool ok = j < ns && row < t.q_count;
             uint32_t *dst = ok ? p.dseed + (int64_t)(t.gq_begin + row) * p.ns_stride + j : dump;
             *dst = bits[jj];
+        }
+    }
+    if constexpr (NG >= 16) {
+        // lane (n32 < 16, h) has row 8 (n32 / 4) + 4 h + n32 % 4: its groups' minima are consecutive words
+        const int row = 8 * ((n32 & 15) >> 2) + 4 * h + (n32 & 3);
+        if (p.dmin != nullptr && n32 < 16 && row < t.q_count) {
+            uint32_t *dst = p.dmin + (int64_t)(t.gq_begin + row) * p.nb_stride + j0 / 32;
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                if (j0 + g * 32 < ns) dst[g] = gmin[g];
         }
     }
 }

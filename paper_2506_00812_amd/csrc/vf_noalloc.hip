@@ -67,6 +67,7 @@ int search_noalloc_impl(vf_index *ix, const void *queries, int64_t nq, const int
     size_t off_idx = 0, off_bits = 0, off_dseed = 0, total = 0;
     for (int attempt = 0; attempt < 2; ++attempt) {
         P = CallPlan(ix->tune);
+        P.tight = true;
         const uint64_t budget_words = attempt == 0 ? kScratchBytes / 4 : 0;
         if ((rc = plan_call(ix, r, nq, qoff, qids, false, false, k, itopk, width, iters, n_seeds, 0, budget_words, sc, P)) != VF_OK)
             return rc;

@@ -296,8 +296,9 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     // A launch with fewer work items than SIMDs lasts as long as its longest item, and an item is one wave's serial chain:
     // short lists are then cut into up to eight segments (1,000 queries on lists of up to 500 uint8 vectors, 60 items of
     // 16 groups: 63 us, in segments of two groups 28 us and 7 us for the merge).
+    const bool cut_short = !P.scan_bf16 && !P.tight;
     int64_t tile_groups = 0;
-    if (!P.scan_bf16)
+    if (cut_short)
         for (size_t i = 0; i < first_hs;) {
             const uint64_t l = r.scan_pairs[i] >> 32;
             size_t e = i;
@@ -310,7 +311,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         const int32_t l = (int32_t)(r.scan_pairs[i] >> 32);
         size_t e = i;
         while (e < first_hs && (int32_t)(r.scan_pairs[e] >> 32) == l) ++e;
-        if (!P.scan_bf16) {
+        if (cut_short) {
             const int least = (int)std::max<int64_t>(2, std::max<int64_t>(tile_groups / 1024, (ix->S[(size_t)l] + 255) / 256));
             ib.seg_groups = std::min(seg_default, least);
             ib.seg_groups_heavy = std::min(seg_heavy, least);
@@ -462,7 +463,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     // row) and enough queries can use them: no predicate, and three blocks per kept seed or more (fewer: most blocks would
     // be read anyway).  50,000 uint8 queries with 16,384 seeds: seed kernel 805 -> 825 us, beam kernel 1,561 -> 1,260; 10,000
     // float32 queries with 6,144 seeds: 107 -> 115 and 269 -> 221 us.
-    if (P.seeds_mfma && !P.seed_select && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || !r.any_and) &&
+    if (P.seeds_mfma && !P.seed_select && !P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || !r.any_and) &&
         (int64_t)P.tiles.size() * ((P.ns_stride + 4 * kSeedMfmaChunk - 1) / (4 * kSeedMfmaChunk)) >= 512) {
         const int32_t keep = ix->dtype == VF_U8 ? itopk : std::min(64, itopk + std::max(tune.seed_margin_bf16, tune.seed_margin));
         const int32_t stride = (P.ns_stride / 32 + 15) & ~15;

@@ -110,8 +110,8 @@ struct Tuning {
     int seed_fb_window = 131072;  // graph queries between two looks at the failed-proof counter
     int seed_select = 0;          // 1: the seed kernel also selects (runs of keys instead of every distance; itopk <= 64)
     int seed_seg_seeds = 0;       // seeds per wave of the selecting seed kernel; 0: chosen per call (512 .. 16384)
-    int build16 = 1;              // float32 kNN self-joins on 16-row tiles
-    int build_panel_kb = 4096;    // self-joins of long lists go panel by panel, this much of the list per launch
+    int build16 = 1;              // 0: float32 kNN self-joins on the 32-row scan kernel, list by list, not on the join kernel
+    int build_panel_kb = 4096;    // 16-row self-joins of long lists (tables the join's proofs do not cover) go panel by panel, this much of the list per launch
     int build_progress = 0;       // 1: a line on stderr every ten seconds while graphs are built
     // returns false for an unknown name or a value out of range
     bool set(const char *name, double value);

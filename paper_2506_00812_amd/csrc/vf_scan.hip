@@ -41,12 +41,12 @@ constexpr int kScan16Waves = 2;   // and the 16-row kernel
 // the MFMAs of the current group run, which is what keeps HBM busy at the skinny
 // shapes of the search (a handful of queries per list).  NCP == 0: any p.ncp, no
 // prefetch.
-template <int DT, int NCP>
+template <int DT, int NCP, bool MASKS>
 __global__ __launch_bounds__(64, kScanWaves) void scan_topk_kernel(ScanParams p)
 {
     extern __shared__ uint4 smem[];
     const ScanItem it = p.items[blockIdx.x];
-    scan_topk_item<DT, NCP>(p, it, smem);
+    scan_topk_item<DT, NCP, false, MASKS>(p, it, smem);
 }
 
 // float32 search tiles of <= 16 queries: the same selection around v_mfma_f32_16x16x4_f32, which
@@ -351,21 +351,27 @@ size_t scan_lds_bytes(int32_t ncp, int32_t tile_rows, int32_t K)
 
 template <int DT> static void launch_scan_dt(const ScanParams &p, int n_items, hipStream_t s)
 {
-    const size_t lds = scan_lds_bytes(p.ncp, p.tile_rows, p.K);
+    size_t lds = scan_lds_bytes(p.ncp, p.tile_rows, p.K);
+    // AND batches: masks per window of groups, where they fit (only tiles of the longest vectors and results do not leave
+    // room for them: those test the predicate where a candidate turns up).  50,000 uint8 queries, 30 % of them pairs: the
+    // kernel alone 633 -> 135 us, the call 2.13 -> 2.09 ms.
+    const size_t mask_lds = (size_t)p.tile_rows * kMaskGroups * 4;
+    // (float32 dim 96 / 128: batches that matter run on other kernels, and the registers do not suffice for both)
+    const bool fixed_f32 = DT == 1 && (p.ncp == 12 || p.ncp == 16);
+    const bool masks = p.others_off != nullptr && !fixed_f32 && lds + mask_lds <= 64 * 1024;
+    if (masks) lds += mask_lds;
     const dim3 grid(n_items), block(64);
-    if (DT == 0) {
-        switch (p.ncp) {
-        case 4: hipLaunchKernelGGL((scan_topk_kernel<DT, 4>), grid, block, lds, s, p); break;   // uint8 dim 128
-        case 6: hipLaunchKernelGGL((scan_topk_kernel<DT, 6>), grid, block, lds, s, p); break;   // uint8 dim 192
-        default: hipLaunchKernelGGL((scan_topk_kernel<DT, 0>), grid, block, lds, s, p); break;
-        }
-    } else {
-        switch (p.ncp) {
-        case 12: hipLaunchKernelGGL((scan_topk_kernel<DT, 12>), grid, block, lds, s, p); break; // float dim 96
-        case 16: hipLaunchKernelGGL((scan_topk_kernel<DT, 16>), grid, block, lds, s, p); break; // float dim 128
-        default: hipLaunchKernelGGL((scan_topk_kernel<DT, 0>), grid, block, lds, s, p); break;
-        }
-    }
+#define VF_SCAN(NCP_) \
+    do { \
+        if (masks) hipLaunchKernelGGL((scan_topk_kernel<DT, NCP_, true>), grid, block, lds, s, p); \
+        else hipLaunchKernelGGL((scan_topk_kernel<DT, NCP_, false>), grid, block, lds, s, p); \
+    } while (0)
+    if (DT == 0 && p.ncp == 4) VF_SCAN((DT == 0 ? 4 : 0));         // uint8 dim 128
+    else if (DT == 0 && p.ncp == 6) VF_SCAN((DT == 0 ? 6 : 0));    // uint8 dim 192
+    else if (!fixed_f32) VF_SCAN(0);
+    else if (p.ncp == 12) hipLaunchKernelGGL((scan_topk_kernel<DT, (DT == 1 ? 12 : 0), false>), grid, block, lds, s, p);
+    else hipLaunchKernelGGL((scan_topk_kernel<DT, (DT == 1 ? 16 : 0), false>), grid, block, lds, s, p);
+#undef VF_SCAN
 }
 
 bool scan16_supported(int dtype, int dim, int tile_rows)

@@ -20,7 +20,7 @@
 // is the exact one.  Otherwise (rare: counted, and reported by the profile) the wave scans the query's whole list
 // itself with the ordered distance, 64 entries a step: predicate, gather, score, merge into the k best.
 #include "vf_beam.h"
-#include "vf_select.h"
+#include "vf_scan_item.h"
 
 namespace vf {
 
@@ -28,7 +28,6 @@ typedef __bf16 v8bf_scan __attribute__((ext_vector_type(8)));
 typedef float v4f_scan __attribute__((ext_vector_type(4)));
 
 constexpr int kScanBf16Waves = 2;   // waves per SIMD the kernel is compiled for
-constexpr int kMaskGroups = 24;     // list groups per window of AND masks (768 entries: a segment at the default size)
 
 template <int NCH16, bool AND, int SLOTS>
 __global__ __launch_bounds__(64, kScanBf16Waves) void scan_bf16_kernel(ScanParams p)
@@ -51,84 +50,8 @@ __global__ __launch_bounds__(64, kScanBf16Waves) void scan_bf16_kernel(ScanParam
     for (int i = lane; i < TR * KS; i += 64) best[i] = KEY_MAX;
     __syncthreads();
 
-    // AND: where row r's partner labels are, and what it takes to test the first of them, in lane r
-    int o_begin = 0, o_cnt = 0, o_slot = -1, o_size = 0;
-    int64_t o_off = -1;
-    if (AND) {
-        const int qr = lane < it.q_count && lane < 32 ? qrow_s[lane] : -1;
-        if (qr >= 0) {
-            o_begin = p.others_off[qr];
-            o_cnt = p.others_off[qr + 1] - o_begin;
-            if (o_cnt > 0) {
-                const int l = p.others[o_begin];
-                o_slot = p.meta.hs_slot[l]; o_off = p.meta.O_LS[l]; o_size = p.meta.S[l];
-            }
-        }
-    }
-    // The predicate of every row for a window of kMaskGroups groups from group g0 on, as bit masks.  A test is a chain of
-    // dependent loads (the entry's id, then a word of the partner's bitset or a binary search of its list), and until a
-    // row's list is full every entry needs one: done where a candidate turns up, the wave waits for the chain of one row
-    // after the other in every group.  Here a lane has the twelve chains of its entries of the window in flight at a time
-    // (12,000 two-label scan queries on 500,000 x 96: the kernel 1016 -> 206 us, the call 1.09 -> 0.79 ms).
-    auto window_masks = [&](int g0) {
-        constexpr int NE = kMaskGroups / 2;
-        int gid[NE];
-        uint32_t exist = 0;
-#pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            const int e = g0 * kGroup + i * 64 + lane;
-            exist |= (e < it.n ? 1u : 0u) << i;
-            gid[i] = p.map[it.map_off + it.entry0 + (e < it.n ? e : 0)];
-        }
-        wave_lds_sync();
-        for (int r = 0; r < it.q_count; ++r) {
-            const int cnt = __builtin_amdgcn_readlane(o_cnt, r);
-            if (cnt == 0) continue;   // (a row without partners takes no mask)
-            uint32_t ok = exist;
-            for (int o = 0; o < cnt; ++o) {
-                int slot = __builtin_amdgcn_readlane(o_slot, r), size = __builtin_amdgcn_readlane(o_size, r);
-                int64_t off = (int64_t)readlane64((uint64_t)o_off, r);
-                if (o > 0) {
-                    const int l = p.others[__builtin_amdgcn_readlane(o_begin, r) + o];
-                    slot = p.meta.hs_slot[l]; off = p.meta.O_LS[l]; size = p.meta.S[l];
-                }
-                if (slot >= 0) {
-                    const uint32_t *bits = p.meta.bitsets + (int64_t)slot * p.meta.bitset_words;
-                    uint32_t w[NE];
-#pragma unroll
-                    for (int i = 0; i < NE; ++i) w[i] = bits[gid[i] >> 5];
-#pragma unroll
-                    for (int i = 0; i < NE; ++i) ok &= ~((~(w[i] >> (gid[i] & 31)) & 1u) << i);
-                } else if (off < 0) {
-                    ok = 0;
-                } else {   // entries of the partner's ascending list that are <= gid, all twelve searches step by step
-                    const int32_t *list = p.meta.M_LS + off;
-                    int pos[NE];
-#pragma unroll
-                    for (int i = 0; i < NE; ++i) pos[i] = 0;
-                    for (int step = 1 << (31 - __builtin_clz(size)); step > 0; step >>= 1) {
-                        int v[NE];
-#pragma unroll
-                        for (int i = 0; i < NE; ++i) v[i] = list[(pos[i] + step <= size ? pos[i] + step : size) - 1];
-#pragma unroll
-                        for (int i = 0; i < NE; ++i)
-                            if (pos[i] + step <= size && v[i] <= gid[i]) pos[i] += step;
-                    }
-                    int v[NE];
-#pragma unroll
-                    for (int i = 0; i < NE; ++i) v[i] = list[pos[i] > 0 ? pos[i] - 1 : 0];
-#pragma unroll
-                    for (int i = 0; i < NE; ++i) ok &= ~((v[i] == gid[i] ? 0u : 1u) << i);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < NE; ++i) {
-                const uint64_t m = __ballot((ok >> i) & 1u);
-                if (lane < 2) amask[r * kMaskGroups + 2 * i + lane] = (uint32_t)(lane == 0 ? m : m >> 32);
-            }
-        }
-        wave_lds_sync();
-    };
+    AndRow partners;
+    if (AND) partners = and_row_of_lane(p, it, qrow_s, lane);
 
     // A operand, resident in registers: the chunks 4 sq + kq of query row c16, split into two bfloat16 parts;
     // the row's squared norm (of the float32 values) is summed over the four lanes that share it
@@ -220,7 +143,7 @@ __global__ __launch_bounds__(64, kScanBf16Waves) void scan_bf16_kernel(ScanParam
 #pragma unroll
       for (int slot = 0; slot < SLOTS; ++slot) {
         if (AND && mask_at == kMaskGroups) {
-            window_masks(grp0 + slot);
+            and_window_masks(p, it, partners, grp0 + slot, amask, lane);
             mask_at = 0;
         }
         // (a group count that is no multiple of SLOTS ends with phantom steps on the re-fetched last group,

@@ -41,3 +41,42 @@ def test_and_masks_at_window_edges(dim, seg_groups, slots):
     assert ix.profile_read()["scan_kernel"] == 3 and (info["method"] == 1).sum() > 256
     s = info["method"] != 2
     assert_close_with_ties(to_np(gi)[s], to_np(gd)[s], oi[s], od[s], 1e-4, "AND scan")
+
+
+@pytest.mark.parametrize("dtype,dim,seg_groups", [("uint8", 128, 16), ("uint8", 192, 64), ("uint8", 80, 25), ("uint8", 992, 48),
+                                                  ("float32", 100, 24), ("float32", 40, 60)])
+def test_and_masks_of_the_plain_scan(dtype, dim, seg_groups):
+    """The same on the 32-row kernel (uint8, and float32 of other dimensions)."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_exact
+    rng = np.random.default_rng(dim + seg_groups)
+    n, T = 5000, 2500
+    k = 64 if dim == 992 else 10
+    x = rng.normal(size=(20, dim))[rng.integers(0, 20, n)] * (30 if dtype == "uint8" else 2) + rng.normal(size=(n, dim)) * (12 if dtype == "uint8" else 1)
+    x = np.rint(x + 128).clip(0, 255).astype(np.uint8) if dtype == "uint8" else x.astype(np.float32)
+    sizes = [4000, 2400, 1537, 1536, 769, 768, 767, 33, 32, 1]
+    carry = np.zeros((n, len(sizes)), dtype=bool)
+    for l, size in enumerate(sizes):
+        carry[rng.permutation(n)[:size], l] = True
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    ids = np.nonzero(carry)[1].astype(np.int32)
+    asked = [sorted(set(rng.integers(0 if j % 2 else 1, len(sizes), [1, 2, 2, 3][j % 4]).tolist())) for j in range(400)]
+    qoff = np.concatenate([[0], np.cumsum([len(a) for a in asked])]).astype(np.int64)
+    qids = np.array([l for a in asked for l in a], dtype=np.int32)
+    q = np.ascontiguousarray(x[rng.integers(0, n, 400)])
+    if dtype == "float32":
+        q += 0.5 * rng.normal(size=q.shape).astype(np.float32)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, len(sizes), T, 8)
+    ix.tune("seg_groups", seg_groups)
+    ix.tune("seg_groups_heavy", seg_groups)
+    ixo = OracleIndex(x, off, ids, len(sizes), T, 8, lazy_graph=True)
+    params = dict(itopk=64, width=1, iters=4, n_seeds=128)
+    for count in (400, 3):
+        gi, gd = vf.search(ix, torch.from_numpy(q[:count]).cuda(), qoff[:count + 1], qids[:qoff[count]], k, **params)
+        oi, od, info = ixo.search(q[:count], qoff[:count + 1], qids[:qoff[count]], k, with_info=True, **params)
+        if dtype == "uint8":
+            assert_exact(to_np(gi), to_np(gd), oi, od, "AND scan")
+        else:
+            s = info["method"] != 2
+            assert_close_with_ties(to_np(gi)[s], to_np(gd)[s], oi[s], od[s], 1e-4, "AND scan")

@@ -173,7 +173,8 @@ struct ItemBuilder {
 // stream that calls it, so that calls on different streams can overlap on the GPU (small batches leave most
 // of the chip idle); calls on one stream share one workspace and run in order.
 struct Workspace {
-    DevBuf ws_blob, ws_blob_b, part_idx, part_bits, dseed;
+    DevBuf ws_blob, ws_blob_b;
+    DevBuf dseed;   // seed distances, then partial result rows
     // vf_search_multi: gathered query rows, results of the sub-searches, their parents
     DevBuf multi_q, multi_ids, multi_dists, multi_meta;
     std::vector<int32_t> multi_host;      // [n_sub parents | nq + 1 first sub-search of each query], alive until the next call
@@ -192,7 +193,7 @@ struct Workspace {
     hipStream_t owner = nullptr; // the stream whose calls use this workspace
     std::vector<DevBuf *> bufs()
     {
-        return {&ws_blob, &ws_blob_b, &part_idx, &part_bits, &dseed, &multi_q, &multi_ids, &multi_dists, &multi_meta};
+        return {&ws_blob, &ws_blob_b, &dseed, &multi_q, &multi_ids, &multi_dists, &multi_meta};
     }
 };
 

@@ -888,11 +888,10 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     char *hp = (char *)st->p;
     fill_blob(P, r, hp);
     const auto t_blob = std::chrono::steady_clock::now();
-    if (P.dense_seeds && (rc = W->dseed.reserve(P.dseed_words * 4)) != VF_OK) return rc;
-    if (P.part_words > 0) {
-        if ((rc = W->part_idx.reserve(P.part_words * 4)) != VF_OK) return rc;
-        if ((rc = W->part_bits.reserve(P.part_words * 4)) != VF_OK) return rc;
-    }
+    // seed distances and partial rows in one buffer: one allocation where a workspace meets its first call
+    auto words_up = [](size_t v) { return (v + 63) & ~(size_t)63; };
+    const size_t dseed_words = P.dense_seeds ? words_up(P.dseed_words) : 0, part_words = words_up(P.part_words);
+    if (dseed_words + part_words > 0 && (rc = W->dseed.reserve((dseed_words + 2 * part_words) * 4)) != VF_OK) return rc;
     // The scan path runs on the side stream beside the graph path on the caller's stream.
     const bool forked = tune.overlap && !ix->prof_serial && !exact && P.n_gq > 0 && !P.ib.items.empty();
     // Two device blobs alternate.  When the call forks, its blob is uploaded on the side stream: there it
@@ -931,8 +930,8 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     }
     W->prev_forked = forked;
     M.dseed = W->dseed.as<uint32_t>();
-    M.part_idx = W->part_idx.as<int32_t>();
-    M.part_bits = W->part_bits.as<uint32_t>();
+    M.part_idx = W->dseed.as<int32_t>() + dseed_words;
+    M.part_bits = W->dseed.as<uint32_t>() + dseed_words + part_words;
     if ((rc = launch_call(ix, P, r, M, sc, queries, out_ids, out_dists, s, forked ? W->side : nullptr, W->ev_fork,
                           W->ev_join, true)) != VF_OK)
         return rc;

@@ -259,7 +259,7 @@ void launch_seed_map(const int32_t *M_HS, const int64_t *slot_base, const int32_
 
 constexpr int kSeedMfmaChunk = 128;  // seeds per wave of the MFMA seed kernel when it gathers rows (four 32-seed groups)
 
-bool seed_dist_supported(int dtype, int dim);
+bool seed_dist_pays(int dtype, int dim, int n_seeds, int64_t n_gq);
 void launch_seed_dist(int dtype, const SeedParams &p, int n_tiles, hipStream_t s);
 // |q|^2 + |x|^2 - 2 q.x through the matrix cores: approximate for float32, exact for uint8
 bool seed_mfma_supported(int dtype, int dim);

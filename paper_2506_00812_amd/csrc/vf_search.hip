@@ -445,7 +445,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     if (!P.seed_select) {
         // every distance goes through the seed distance matrix, which must fit
         const uint64_t need = (uint64_t)P.n_gq * (uint64_t)P.ns_stride + 64 * 1024;
-        P.dense_seeds = !exact && P.n_gq > 0 && seed_dist_supported(ix->dtype, ix->dim) && need <= dseed_budget_words;
+        P.dense_seeds = !exact && P.n_gq > 0 && seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq) && need <= dseed_budget_words;
         P.seeds_mfma = P.dense_seeds && mfma_ok;
         if (P.dense_seeds) P.dseed_words = (size_t)need;
     }

@@ -860,11 +860,27 @@ void launch_row_norms(int dtype, const void *X, int32_t dim, int64_t n, uint32_t
     else hipLaunchKernelGGL(row_norm_kernel<0>, grid, block, 0, s, X, dim, n, out);
 }
 
-// every dimension an index may have (at most 62 chunks)
-bool seed_dist_supported(int dtype, int dim)
+// Whether a launch of the dense kernel pays.  Dimensions with an instantiation of their own: always.  Others (an index has
+// vectors of at most 62 chunks) score n_gq queries with the chunks of the next larger one, and leave the distances where
+// the beam kernel, which would gather its seeds itself in the same launch, has to read them: that needs enough seeds per
+// query, and beyond 32 chunks, where a query no longer fits into registers beside the sums, few enough queries.  Whole
+// calls among others, gathering -> dense (at the lines for up to 32 chunks a call that is waited for is 10 us faster):
+//   float32 dim 36     512 queries x   128 seeds   53 ->  59 us, x   192  57 ->  58, x   512  76 ->  59
+//   float32 dim 100     64 queries x   256 seeds   62 ->  72 us, x   384  70 ->  73, x 1,024 109 ->  72
+//   float32 dim 200      1 query   x   512 seeds  102 -> 100 us, x 1,024 158 ->  99
+//                      512 queries x 1,024 seeds  217 -> 239 us, x 4,096 685 -> 536
+//                    3,000 queries x 1,024 seeds  248 -> 433 us, x 4,096 721 -> 1,105
+//   uint8 dim 528       64 queries x   256 seeds   80 -> 110 us, x   512 113 -> 109
+//   uint8 dim 992    3,000 queries x 1,024 seeds  491 -> 519 us, x 4,096 1,578 -> 1,266
+bool seed_dist_pays(int dtype, int dim, int n_seeds, int64_t n_gq)
 {
     const int nch = dim * (dtype == 0 ? 1 : 4) / kChunkBytes;
-    return nch >= 1 && nch <= 64;
+    if (nch == 8 || nch == 12 || nch == 16 || nch == 24 || nch == 32) return true;
+    if (nch < 1 || nch > 64) return false;
+    if (nch <= 16) return n_seeds >= 192;
+    if (nch <= 32) return n_seeds >= 384;
+    if (dtype == 1) return n_gq <= 512 && n_seeds >= std::max<int64_t>(1024, 8 * n_gq);
+    return n_seeds >= 512 && (nch <= 48 || n_gq <= 1024 || n_seeds >= 2048);
 }
 
 // Dimensions without an instantiation of their own take the next larger one with the missing chunks zeroed: a few

@@ -319,6 +319,8 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         ib.add_label(r.scan_pairs, i, e, ix->GO_LS[(size_t)l], ix->O_LS[(size_t)l], ix->S[(size_t)l]);
         i = e;
     }
+    // (graph lists of exact mode: what the scan lists' kernels and sizes have asked for is not theirs)
+    ib.seg_groups = ix->tune.seg_groups; ib.seg_groups_heavy = ix->tune.seg_groups_heavy;
     P.n_ls_items = ib.items.size(); P.n_ls_merges = ib.merges.size();
     const size_t ls_qrows = ib.qrow.size();
     VF_REQUIRE(ib.part_rows < ((int64_t)1 << 31), "too many partial result rows in one call");

@@ -391,8 +391,9 @@ typedef struct vf_profile {
                                           3 = filter from the bfloat16 copy of the lists + exact re-ranking (float32 data)         */
     int64_t seed_selected;             /* 1: the seed kernel also selected (a few keys per query and seed segment instead of every distance) */
     int64_t seed_run_keys;             /* 8-byte keys that kernel left for the beam kernel (sum over graph queries of segments x keys per run) */
-    int64_t scan_fallbacks;            /* scan queries since profiling was enabled whose filtered result (scan_kernel 3) could not
-                                          be proven complete and that the exact kernels scanned again                         */
+    int64_t scan_fallbacks;            /* scan queries since profiling was enabled whose filtered result (scan_kernel 3; in
+                                          vf_search_exact also that of float32 graph lists) could not be proven complete and
+                                          that the exact kernels scanned again                                                */
     double host_plan_ms_sum, host_blob_ms_sum, host_launch_ms_sum; /* host time inside the calls since profiling was enabled:
                                           routing and work lists; assembling the routing blob; everything else (HIP calls)   */
     double host_wait_ms_sum;           /* ... and time the host waited for a staging buffer (two calls ahead of the device) */

@@ -168,7 +168,7 @@ static int profile_enable_impl(vf_index *ix, int on)
     ix->prof_scan_sum = ix->prof_seed_sum = ix->prof_beam_sum = 0;
     ix->prof_host_plan = ix->prof_host_blob = ix->prof_host_launch = ix->prof_host_wait = 0;
     ix->prof_calls = 0;
-    if (on && ix->has_ls16) {   // failed scan proofs are counted from here on
+    if (on && ix->d_scan_fb.p != nullptr) {   // failed scan proofs are counted from here on
         VF_HIP(hipDeviceSynchronize());
         VF_HIP(hipMemcpy(&ix->scan_fb_seen, ix->d_scan_fb.p, 4, hipMemcpyDeviceToHost));
     }
@@ -201,7 +201,7 @@ static int profile_read_impl(vf_index *ix, vf_profile *out, int32_t *per_query)
             if (per_query) memcpy(per_query + (size_t)j * 4, row, 16);
         }
     }
-    if (ix->has_ls16) {
+    if (ix->d_scan_fb.p != nullptr) {
         uint32_t now = 0;
         VF_HIP(hipMemcpy(&now, ix->d_scan_fb.p, 4, hipMemcpyDeviceToHost));
         pf.scan_fallbacks = (int64_t)(uint32_t)(now - ix->scan_fb_seen);

@@ -113,7 +113,7 @@ __global__ void graph_rows_copy_kernel(const int32_t *cand_idx, int64_t n, int32
 __global__ __launch_bounds__(64) void graph_rows_rerank_kernel(const char *X, int32_t row_bytes, const int32_t *map,
                                                                int64_t n, const int32_t *cand_idx, const uint32_t *cand_bits,
                                                                int32_t K, int32_t R, int32_t *G_rows, float err_bound,
-                                                               float xn_max, uint32_t *rescanned)
+                                                               float xn_max, const float *centre, uint32_t *rescanned)
 {
     extern __shared__ uint4 smem[];
     const int lane = threadIdx.x, team = lane >> 3, tl = lane & 7;
@@ -139,7 +139,9 @@ __global__ __launch_bounds__(64) void graph_rows_rerank_kernel(const char *X, in
         float vn = 0.f;
         for (int i = lane; i < nchunks; i += 64) {
             const uint4 v = qv[i];
-            const float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+            float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+            if (centre != nullptr)
+                for (int u = 0; u < 4; ++u) f[u] -= centre[i * 4 + u];
             vn += f[0] * f[0] + f[1] * f[1] + f[2] * f[2] + f[3] * f[3];
         }
 #pragma unroll
@@ -173,7 +175,7 @@ __global__ __launch_bounds__(64) void graph_rows_rerank_kernel(const char *X, in
 
 void launch_graph_rows(int dtype, const void *X, int32_t dim, const int32_t *map, int64_t n, const int32_t *cand_idx,
                        const uint32_t *cand_bits, int32_t K, int32_t R, int32_t *G_rows, float err_bound, float xn_max,
-                       uint32_t *rescanned, hipStream_t s)
+                       const float *centre, uint32_t *rescanned, hipStream_t s)
 {
     if (n <= 0) return;
     if (dtype == 0) {
@@ -183,7 +185,7 @@ void launch_graph_rows(int dtype, const void *X, int32_t dim, const int32_t *map
         const int32_t row_bytes = dim * 4;
         hipLaunchKernelGGL(graph_rows_rerank_kernel, dim3((unsigned)n), dim3(64), (size_t)row_bytes + 64 * 8, s,
                            (const char *)X, row_bytes, map, n, cand_idx, cand_bits, K, R, G_rows, err_bound, xn_max,
-                           rescanned);
+                           centre, rescanned);
     }
 }
 

@@ -242,6 +242,10 @@ struct vf_index {
     // seed scoring (its error bound needs the largest norm)
     vf::DevBuf d_xnorm_all;
     float xn_max = 0.f;
+    // float32: the join kernel's origin (a vector near the mean of X), the squared norms of all rows measured from it and the
+    // largest of them (0: the table's norms are outside the proofs' range, nothing is joined)
+    vf::DevBuf d_centre, d_xnorm_c;
+    float xc_max = 0.f;
     bool seed_mfma_ok = false;   // the norms exist and are finite: seeds may be scored on the matrix cores
     // search workspaces (see Workspace); profiled calls and vf_search_exact must not overlap with other calls
     static constexpr int kWorkspaces = 8;
@@ -285,7 +289,7 @@ struct vf_index {
     std::vector<vf::DevBuf *> bufs()
     {
         return {&d_S, &d_O_HS, &d_O_LS, &d_hs_slot, &d_M_HS, &d_M_LS, &d_G, &d_Gg, &d_X_LS, &d_xnorm_LS, &d_bitsets,
-                &d_xnorm_all, &tmp_blk, &tmp_norm, &counters, &d_fb_count, &d_X_LS16, &d_scan_fb};
+                &d_xnorm_all, &d_centre, &d_xnorm_c, &tmp_blk, &tmp_norm, &counters, &d_fb_count, &d_X_LS16, &d_scan_fb};
     }
     vf::LabelMeta meta() const
     {
@@ -300,8 +304,11 @@ struct vf_index {
     size_t group_bytes() const { return (size_t)2 * ncp * 32 * 16; }
     // float32 seed proofs: |approximation - ordered distance| <= seed_err_bound() (|q|^2 + xn_max)
     float seed_err_bound() const { return (float)(tune.seed_slack * 3.0517578125e-05); }
-    // the same for the approximations of the join kernel (split bfloat16 products, see vf_join.hip)
-    float join_err_bound() const { return 4.0f * seed_err_bound(); }
+    // squared norms the join kernel takes for its lists
+    const uint32_t *join_norms() const { return dtype == VF_U8 ? d_xnorm_all.as<uint32_t>() : d_xnorm_c.as<uint32_t>(); }
+    // the same for the approximations of the join kernel (split bfloat16 products, norms from its origin, see vf_join.hip);
+    // what it decides is stored or is the ground truth: "seed_slack" below 1 does not make its proofs weaker
+    float join_err_bound() const { return (float)(std::max(1.0, tune.seed_slack) * (512 + 4 * dim) * 5.9604644775390625e-08); }
 };
 
 namespace vf {

@@ -116,9 +116,9 @@ void free_index(vf_index *ix)
 // Exact kNN rows of the graph lists graph_labels[lo, hi), which lie one after the other in M_HS: pack them, contract every
 // list against itself in one launch (vf_join.hip; a list of a few thousand vectors alone would leave most of the chip
 // idle), keep K candidates per vertex and order `deg` of them into rows_out (per list [|C_l|][deg] local ids).
-// rows_out: row of the first vertex; norms: squared norms of all rows of X; global_ids as in build_graph_for_label.
+// rows_out: row of the first vertex; global_ids as in build_graph_for_label.
 static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, int32_t deg, int32_t *rows_out, bool global_ids,
-                               const uint32_t *norms, DevBuf &cand_idx, DevBuf &cand_dist, DevBuf &d_items, hipStream_t s)
+                               DevBuf &cand_idx, DevBuf &cand_dist, DevBuf &d_items, hipStream_t s)
 {
     const int64_t base0 = ix->O_HS[(size_t)ix->graph_labels[lo]];
     std::vector<JoinList> lists;
@@ -145,11 +145,12 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     if ((rc = upload(d_lists, lists, s)) != VF_OK) return rc;
     if ((rc = upload(d_items, items, s)) != VF_OK) return rc;
     const int32_t *map = ix->d_M_HS.as<int32_t>();
-    launch_join_pack(ix->dtype, ix->X, ix->dim, map, d_lists.as<JoinList>(), (int)lists.size(), n_groups, norms, ix->tmp_blk.as<uint4>(), ix->tmp_norm.p, s);
+    launch_join_pack(ix->dtype, ix->X, ix->dim, map, d_lists.as<JoinList>(), (int)lists.size(), n_groups, ix->join_norms(),
+                     ix->d_centre.as<float>(), ix->tmp_blk.as<uint4>(), ix->tmp_norm.p, s);
     JoinParams p{};
     p.xblk = ix->tmp_blk.as<uint4>(); p.xnorm = ix->tmp_norm.p;
     p.qsrc = ix->X; p.qrow = map + base0; p.items = d_items.as<ScanItem>();
-    p.dim = ix->dim; p.K = K;
+    p.dim = ix->dim; p.K = K; p.centre = ix->d_centre.as<float>();
     p.res_idx = cand_idx.as<int32_t>(); p.res_bits = cand_dist.as<uint32_t>();
     p.meta = ix->meta();
     launch_join(ix->dtype, p, (int)items.size(), s);
@@ -158,7 +159,7 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         const int64_t base = ix->O_HS[(size_t)l], at = base - base0;
         // float32 rows are accepted only with a proof that the K candidates contain them
         launch_graph_rows(ix->dtype, ix->X, ix->dim, map + base, nl, p.res_idx + at * K, p.res_bits + at * K, K, deg,
-                          rows_out + at * deg, ix->join_err_bound(), ix->xn_max, nullptr, s);
+                          rows_out + at * deg, ix->join_err_bound(), ix->xc_max, p.centre, nullptr, s);
         if (global_ids)
             launch_graph_global_ids(rows_out + at * deg, map + base, (int64_t)nl * deg, ix->d_Gg.as<int32_t>() + base * ix->R, s);
     }
@@ -222,7 +223,7 @@ static int build_graph_for_label(vf_index *ix, int32_t l, int32_t K, int32_t deg
     // float32 matrix-core approximations, relative to the largest squared norm of the table)
     const bool checked = ix->dtype == VF_F32 && ix->xn_max > 0.f;
     launch_graph_rows(ix->dtype, ix->X, ix->dim, map, nl, cand_idx.as<int32_t>(), cand_dist.as<uint32_t>(), K, deg, rows_out,
-                      checked ? ix->seed_err_bound() : -1.f, ix->xn_max, nullptr, s);
+                      checked ? ix->seed_err_bound() : -1.f, ix->xn_max, nullptr, nullptr, s);
     if (global_ids)
         launch_graph_global_ids(rows_out, map, (int64_t)nl * deg, ix->d_Gg.as<int32_t>() + base * ix->R, s);
     VF_HIP(hipGetLastError());
@@ -453,32 +454,43 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
             DevBuf cand_idx(&ix->alloc), cand_dist(&ix->alloc), d_items(&ix->alloc);
             DevBufGuard r3{&cand_idx, &cand_dist, &d_items};
             // squared norm of every row of X and the largest of them: the joins and the matrix-core seed scoring read the
-            // norms, the proofs of both need the largest
-            {
-                if ((rc = ix->d_xnorm_all.reserve((size_t)n * 4)) != VF_OK) return rc;
-                launch_row_norms(ix->dtype, ix->X, ix->dim, n, ix->d_xnorm_all.as<uint32_t>(), s);
-                float mx = 0.f;
-                bool finite = true;
-                if (ix->dtype == VF_F32) {
-                    std::vector<float> hn((size_t)n);
-                    VF_HIP(hipMemcpyAsync(hn.data(), ix->d_xnorm_all.p, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-                    VF_HIP(hipStreamSynchronize(s));
-                    for (float v : hn) { finite = finite && v == v && v <= 3.0e38f; mx = v > mx ? v : mx; }
-                }
+            // norms, the proofs of both need the largest (float32 joins: those of the centred rows)
+            if ((rc = ix->d_xnorm_all.reserve((size_t)n * 4)) != VF_OK) return rc;
+            if (ix->dtype == VF_F32) {
+                DevBuf parts(&ix->alloc);
+                DevBufGuard rp{&parts};
+                if ((rc = parts.reserve(((size_t)kCentreParts * dim + 2) * 4)) != VF_OK) return rc;
+                if ((rc = ix->d_centre.reserve((size_t)dim * 4)) != VF_OK) return rc;
+                if ((rc = ix->d_xnorm_c.reserve((size_t)n * 4)) != VF_OK) return rc;
+                uint32_t *max_bits = parts.as<uint32_t>() + (size_t)kCentreParts * dim;
+                launch_centre(ix->X, dim, n, parts.as<float>(), ix->d_centre.as<float>(), s);
+                VF_HIP(hipMemsetAsync(max_bits, 0, 8, s));
+                launch_row_norms_f32(ix->X, dim, n, ix->d_centre.as<float>(), ix->d_xnorm_all.as<uint32_t>(), ix->d_xnorm_c.as<uint32_t>(),
+                                     max_bits, s);
+                VF_HIP(hipGetLastError());
+                float mx[2] = {0.f, 0.f};
+                VF_HIP(hipMemcpyAsync(mx, max_bits, 8, hipMemcpyDeviceToHost, s));
+                VF_HIP(hipStreamSynchronize(s));
                 // a table with NaN or overflowing norms keeps the exact kernel, and so does one whose largest
                 // squared norm is outside [1e-24, 1e30]: the proofs' bound is relative to that norm and assumes
                 // that what the matrix cores flush (products under 1.2e-38) is negligible beside it.
                 // The bound itself: |approximation - ordered distance| <= 300 u (|q|^2 + |x|^2), u = 2^-24 (dot
                 // product of <= 512 terms in any order, two norms, the final additions, the ordered sum's own
                 // error); 512 u = 2^-15 is used (vf_index::seed_err_bound).
-                if (ix->dtype == VF_F32 && !(mx >= 1e-24f && mx <= 1e30f)) finite = false;
-                if (finite) {
-                    ix->xn_max = mx;
+                auto in_range = [](float m) { return m >= 1e-24f && m <= 1e30f; };
+                if (in_range(mx[0])) {
+                    ix->xn_max = mx[0];
                     ix->seed_mfma_ok = seed_mfma_supported(ix->dtype, ix->dim);
+                } else {
+                    ix->d_xnorm_all.release();
                 }
-                if (!finite) ix->d_xnorm_all.release();
+                if (in_range(mx[0]) && in_range(mx[1])) ix->xc_max = mx[1];
+                else ix->d_xnorm_c.release();
+            } else {
+                launch_row_norms_u8(ix->X, ix->dim, n, ix->d_xnorm_all.as<uint32_t>(), s);
+                ix->seed_mfma_ok = seed_mfma_supported(ix->dtype, ix->dim);
             }
-            const bool joined = ix->dtype == VF_U8 || (ix->xn_max > 0.f && ix->tune.build16);
+            const bool joined = ix->dtype == VF_U8 || (ix->xc_max > 0.f && ix->tune.build16);
             // Lists are joined many to a launch: as many as fit, packed and with their candidates, into a GiB (or one list
             // that is larger than that).  The scan kernels take one list at a time.
             const size_t row_bytes_tmp = joined ? join_group_bytes(ix->dtype, ix->dim) / 32 + (size_t)K * 8 : 0;
@@ -522,7 +534,7 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
                 const int64_t base = ix->O_HS[(size_t)first];
                 int32_t *rows = pruned ? d_knn.as<int32_t>() + base * D : ix->d_G.as<int32_t>() + base * ix->R;
                 if (joined)
-                    rc = build_graphs_joined(ix, done, end, K, D, rows, !pruned, ix->d_xnorm_all.as<uint32_t>(), cand_idx, cand_dist, d_items, s);
+                    rc = build_graphs_joined(ix, done, end, K, D, rows, !pruned, cand_idx, cand_dist, d_items, s);
                 else
                     rc = build_graph_for_label(ix, first, K, D, rows, !pruned, cand_idx, cand_dist, d_items, s);
                 if (rc != VF_OK) return rc;

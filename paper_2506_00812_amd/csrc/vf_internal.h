@@ -103,6 +103,7 @@ struct RerankParams {
     const void *Q;
     int32_t dim, Kc, K;
     float err_bound, xn_max, err_q;   // |approximation - ordered distance| <= err_bound (|q|^2 + xn_max) + err_q |q|
+    const float *centre;        // the approximations' origin, which |q| is measured from; null: zero
     uint32_t *fail_count;       // incremented once per query whose proof failed
     const int32_t *others_off;  // AND partner labels per query; null when the batch has none
     const int32_t *others;
@@ -121,6 +122,7 @@ void launch_scan_rerank(const RerankParams &p, int n_items, hipStream_t s);
 struct JoinParams {
     const uint4 *xblk;      // packed lists (launch_join_pack)
     const void *xnorm;      // per slot: half the squared norm (float32), the squared norm of the shifted bytes (uint8)
+    const float *centre;    // float32: subtracted from the rows, as it is from the packed lists
     const int32_t *map;     // local -> global id (AND predicate)
     const void *qsrc;       // row-major [*][dim]
     const int32_t *qrow;    // row of qsrc for each tile row
@@ -143,7 +145,14 @@ struct JoinList {
 size_t join_group_bytes(int dtype, int32_t dim);   // packed bytes of a group of 32 vectors
 // n_groups: of all n_lists lists together
 void launch_join_pack(int dtype, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
-                      int64_t n_groups, const uint32_t *norm_all, uint4 *xblk, void *xnorm, hipStream_t s);
+                      int64_t n_groups, const uint32_t *norm_all, const float *centre, uint4 *xblk, void *xnorm, hipStream_t s);
+// float32: a vector near the mean of the table's rows; tmp: kCentreParts * dim floats
+constexpr int kCentreParts = 64;
+void launch_centre(const void *X, int32_t dim, int64_t n, float *tmp, float *centre, hipStream_t s);
+// squared norms of all rows of a table (float bits), from zero and from the centre, and the largest of each as bits in
+// max_bits[2] (zero before; NaN and infinity are above all others)
+void launch_row_norms_f32(const void *X, int32_t dim, int64_t n, const float *centre, uint32_t *out, uint32_t *out_c, uint32_t *max_bits,
+                          hipStream_t s);
 void launch_join(int dtype, const JoinParams &p, int n_items, hipStream_t s);
 
 // ---------------------------------------------------------------- beam search kernel
@@ -264,8 +273,8 @@ void launch_seed_dist(int dtype, const SeedParams &p, int n_tiles, hipStream_t s
 // |q|^2 + |x|^2 - 2 q.x through the matrix cores: approximate for float32, exact for uint8
 bool seed_mfma_supported(int dtype, int dim);
 void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s);
-// squared norms of all rows of a table (float bits, or int32 of the -128 shifted bytes)
-void launch_row_norms(int dtype, const void *X, int32_t dim, int64_t n, uint32_t *out, hipStream_t s);
+// uint8: squared norms of all rows of a table, of the -128 shifted bytes (float32: launch_row_norms_f32)
+void launch_row_norms_u8(const void *X, int32_t dim, int64_t n, uint32_t *out, hipStream_t s);
 
 size_t beam_lds_bytes(const BeamParams &p, int dtype);
 void launch_beam(int dtype, const BeamParams &p, int n_gq, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
@@ -285,11 +294,11 @@ void launch_bitset_fill(const int32_t *map, int64_t n, uint32_t *bits, hipStream
 // Graph rows from candidate lists: u8 copies the first R candidates (already exact);
 // f32 re-scores K candidates with the ordered fp32 distance and keeps the best R, provided that no member the
 // self-join dropped can belong to the row (cand_bits: the candidates' approximate distances; err_bound, xn_max:
-// |approximation - ordered distance| <= err_bound (|x_v|^2 + xn_max); err_bound < 0: unchecked); a row without
-// that proof is computed from every member of the list and counted in *rescanned (optional).
+// |approximation - ordered distance| <= err_bound (|x_v|^2 + xn_max), norms measured from `centre`, null: from zero;
+// err_bound < 0: unchecked); a row without that proof is computed from every member of the list and counted in *rescanned (optional).
 void launch_graph_rows(int dtype, const void *X, int32_t dim, const int32_t *map, int64_t n, const int32_t *cand_idx,
                        const uint32_t *cand_bits, int32_t K, int32_t R, int32_t *G_rows, float err_bound, float xn_max,
-                       uint32_t *rescanned, hipStream_t s);
+                       const float *centre, uint32_t *rescanned, hipStream_t s);
 
 // out[i] = map[rows[i]] (rows[i] >= 0), -1 otherwise: graph rows as global ids
 void launch_graph_global_ids(const int32_t *rows, const int32_t *map, int64_t count, int32_t *out, hipStream_t s);

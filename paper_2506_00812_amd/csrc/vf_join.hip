@@ -10,13 +10,17 @@
 // the B operand of the 32-column MFMAs, lane (n32, h) reading chunk 2 s + h of entry n32.
 //
 // float32 data: v_mfma_f32_32x32x16_bf16 on two-part splits of both operands, x = hi + lo with hi = bf16(x), lo =
-// bf16(x - hi): the products lo.hi and hi.lo first, then hi.hi, into one float32 accumulator (in this order the small
+// bf16(x - hi), after subtraction of a vector near the table's mean: distances stay what they are, and what the norms
+// and products lose is relative to the spread of the data instead of to its distance from the origin (100,000 x 128,
+// unit noise, shifted by 20 per coordinate: without it most rows are refused a proof, build 77 ms, 3,000 queries' ground
+// truth 5.5 ms; with it 12.5 ms and 1.25 ms, as without the shift).  The products lo.hi and hi.lo first, then hi.hi, into one float32 accumulator (in this order the small
 // terms are summed while the partial sums are small).  Three products at 16 times the rate of the float32 MFMA.  What
 // they leave out, with u = 2^-24: |x - hi - lo| <= 2^-18 |x| twice and the product of the low parts 2^-18, together
-// 192 u |q||x| in q.x, 193 u (|q|^2 + |x|^2) in the distance; the sums of the high parts 2 u per term, <= 500 u
-// (|q|^2 + |x|^2) at 248 terms; norms, summed one after the other, 250 u; final additions, the thresholds' and the
-// ordered distance's own rounding < 100 u.  The bound used is 2048 u = join_err_bound(); callers re-rank what the join
-// keeps with the ordered distance and prove with that bound that nothing else belongs to the result.
+// 192 u |q||x| in q.x, 193 u (|q|^2 + |x|^2) in the distance; the sums of the high parts 2 u per term; norms, summed one
+// after the other, u per term; the subtraction of the centre, u per component, 4 u (|q|^2 + |x|^2) in the distance; final
+// additions, the thresholds' and the ordered distance's own rounding < 100 u: 300 u + 3 u per component in all.  The
+// bound used is 512 u + 4 u per component = join_err_bound(); callers re-rank what the join keeps with the ordered
+// distance and prove with that bound that nothing else belongs to the result.
 // uint8 data: v_mfma_i32_32x32x32_i8 on the bytes shifted by -128: exact.
 //
 // Selection.  With v = q.x - |x|^2 / 2 (uint8: 2 q.x - |x|^2) a distance is below a row's threshold where v is at least
@@ -43,6 +47,13 @@ typedef uint32_t v4u_join __attribute__((ext_vector_type(4)));
 
 // LDS buffers of one group of nc chunks: two where both fit beside the queues in 64 KiB
 __host__ __device__ constexpr int join_buffers(int nc) { return nc <= 32 ? 2 : 1; }
+
+// four components of a row (chunk c) less those of the centre
+__device__ __forceinline__ float4 centred(float4 v, const float *centre, int c)
+{
+    const float4 m = ((const float4 *)centre)[c];
+    return make_float4(v.x - m.x, v.y - m.y, v.z - m.z, v.w - m.w);
+}
 
 // bfloat16 high parts of eight floats, and the bfloat16 rounding of what they leave
 __device__ __forceinline__ void split_bf16x8(const float (&f)[8], uint4 &hi, uint4 &lo)
@@ -186,8 +197,8 @@ __global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
                 for (int i = 0; i < 4; ++i) qnorm = __builtin_amdgcn_sdot4((int)w[i], (int)w[i], qnorm, false);
             } else {
                 float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
-                if (qr >= 0 && c * 8 < p.dim) x = *(const float4 *)(qp + c * 32);
-                if (qr >= 0 && c * 8 + 4 < p.dim) y = *(const float4 *)(qp + c * 32 + 16);
+                if (qr >= 0 && c * 8 < p.dim) x = centred(*(const float4 *)(qp + c * 32), p.centre, 2 * c);
+                if (qr >= 0 && c * 8 + 4 < p.dim) y = centred(*(const float4 *)(qp + c * 32 + 16), p.centre, 2 * c + 1);
                 const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
                 split_bf16x8(f, a[s], alo[s]);
 #pragma unroll
@@ -457,11 +468,11 @@ __global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
 }
 
 // One thread per (group, chunk, entry): the lists' vectors gathered through `map` in the layout the join reads (float32:
-// 2 NK chunks of high parts, then 2 NK of low parts), and per entry half its squared norm (uint8: the squared norm of
-// the shifted bytes); an entry past the end of its list never passes a threshold.
+// 2 NK chunks of high parts, then 2 NK of low parts, of the centred vector), and per entry half its squared norm (uint8:
+// the squared norm of the shifted bytes); an entry past the end of its list never passes a threshold.
 template <int DT>
 __global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map, const JoinList *lists, int32_t n_lists,
-                                 int64_t n_groups, int32_t nk, const uint32_t *norm_all, uint4 *xblk, uint32_t *xnorm)
+                                 int64_t n_groups, int32_t nk, const uint32_t *norm_all, const float *centre, uint4 *xblk, uint32_t *xnorm)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int nch = 2 * nk;
@@ -488,8 +499,8 @@ __global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map,
         if (c == 0) xnorm[g * 32 + v] = valid ? norm_all[row] : 0x3FFFFFFFu;
     } else {
         float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
-        if (valid && c * 8 < dim) x = *(const float4 *)(X + row * dim * 4 + c * 32);
-        if (valid && c * 8 + 4 < dim) y = *(const float4 *)(X + row * dim * 4 + c * 32 + 16);
+        if (valid && c * 8 < dim) x = centred(*(const float4 *)(X + row * dim * 4 + c * 32), centre, 2 * c);
+        if (valid && c * 8 + 4 < dim) y = centred(*(const float4 *)(X + row * dim * 4 + c * 32 + 16), centre, 2 * c + 1);
         const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
         uint4 hi, lo;
         split_bf16x8(f, hi, lo);
@@ -497,6 +508,85 @@ __global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map,
         xblk[(g * 2 * nch + nch + c) * 32 + v] = lo;
         if (c == 0) xnorm[g * 32 + v] = valid ? __float_as_uint(0.5f * __uint_as_float(norm_all[row])) : 0x7F800000u;
     }
+}
+
+// The centre: the mean of up to 16,384 rows spread over the table.  Any fixed vector would do, so a sample is enough; one
+// pass over 8 MiB at dim 128.  Block b takes every kCentreParts-th row of the sample, a thread four components of every
+// rows_at_a_time-th of them.
+__global__ __launch_bounds__(256) void centre_part_kernel(const float *X, int32_t dim, int64_t n, float *parts)
+{
+    __shared__ float4 sum[256];
+    const int nch = dim / 4, rows_at_a_time = 256 / nch;   // (at most 62 chunks)
+    const int c = threadIdx.x % nch, r = threadIdx.x / nch;
+    const int64_t sample = n < 16384 ? n : 16384;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (r < rows_at_a_time)
+        for (int64_t i = blockIdx.x + (int64_t)r * kCentreParts; i < sample; i += (int64_t)rows_at_a_time * kCentreParts) {
+            const float4 v = ((const float4 *)(X + i * n / sample * dim))[c];
+            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+        }
+    sum[threadIdx.x] = a;
+    __syncthreads();
+    if (r == 0) {
+        for (int o = 1; o < rows_at_a_time; ++o) {
+            const float4 v = sum[o * nch + c];
+            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+        }
+        ((float4 *)(parts + (int64_t)blockIdx.x * dim))[c] = a;
+    }
+}
+
+__global__ __launch_bounds__(256) void centre_mean_kernel(const float *parts, int32_t dim, int64_t n, float *centre)
+{
+    const int e = threadIdx.x;
+    if (e >= dim) return;
+    float a = 0.f;
+    for (int b = 0; b < kCentreParts; ++b) a += parts[b * dim + e];
+    centre[e] = a / (float)(n < 16384 ? n : 16384);
+}
+
+// One thread per row, elements in ascending order (400,000 x 128: 0.32 ms).
+__global__ __launch_bounds__(256) void row_norm_f32_kernel(const float *X, int32_t dim, int64_t n, const float *centre, uint32_t *out,
+                                                           uint32_t *out_c, uint32_t *max_bits)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    float acc = 0.f, acc_c = 0.f;
+    if (i < n) {
+        const float4 *x = (const float4 *)(X + i * dim);
+        for (int c = 0; c < dim / 4; ++c) {
+            const float4 v = x[c], w = centred(v, centre, c);
+            acc += v.x * v.x; acc += v.y * v.y; acc += v.z * v.z; acc += v.w * v.w;
+            acc_c += w.x * w.x; acc_c += w.y * w.y; acc_c += w.z * w.z; acc_c += w.w * w.w;
+        }
+        out[i] = __float_as_uint(acc);
+        out_c[i] = __float_as_uint(acc_c);
+    }
+    // (no norm is negative: their bits are ordered as they are, with NaN of either sign above infinity)
+    uint32_t m = __float_as_uint(acc), m_c = __float_as_uint(acc_c);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t v = (uint32_t)__shfl_xor((int)m, o), w = (uint32_t)__shfl_xor((int)m_c, o);
+        m = v > m ? v : m;
+        m_c = w > m_c ? w : m_c;
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(max_bits, m);
+        atomicMax(max_bits + 1, m_c);
+    }
+}
+
+void launch_centre(const void *X, int32_t dim, int64_t n, float *tmp, float *centre, hipStream_t s)
+{
+    hipLaunchKernelGGL(centre_part_kernel, dim3(kCentreParts), dim3(256), 0, s, (const float *)X, dim, n, tmp);
+    hipLaunchKernelGGL(centre_mean_kernel, dim3(1), dim3(256), 0, s, (const float *)tmp, dim, n, centre);
+}
+
+void launch_row_norms_f32(const void *X, int32_t dim, int64_t n, const float *centre, uint32_t *out, uint32_t *out_c, uint32_t *max_bits,
+                          hipStream_t s)
+{
+    if (n <= 0) return;
+    hipLaunchKernelGGL(row_norm_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const float *)X, dim, n, centre, out,
+                       out_c, max_bits);
 }
 
 // Contraction steps the kernel is compiled for: the smallest that holds the vector.
@@ -514,17 +604,17 @@ size_t join_group_bytes(int dtype, int32_t dim)
 }
 
 void launch_join_pack(int dtype, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
-                      int64_t n_groups, const uint32_t *norm_all, uint4 *xblk, void *xnorm, hipStream_t s)
+                      int64_t n_groups, const uint32_t *norm_all, const float *centre, uint4 *xblk, void *xnorm, hipStream_t s)
 {
     if (n_groups <= 0) return;
     const int32_t nk = join_steps(dtype, dim);
     const unsigned blocks = (unsigned)((n_groups * 2 * nk * 32 + 255) / 256);
     if (dtype == 0)
         hipLaunchKernelGGL(join_pack_kernel<0>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, lists, n_lists,
-                           n_groups, nk, norm_all, xblk, (uint32_t *)xnorm);
+                           n_groups, nk, norm_all, centre, xblk, (uint32_t *)xnorm);
     else
         hipLaunchKernelGGL(join_pack_kernel<1>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, lists, n_lists,
-                           n_groups, nk, norm_all, xblk, (uint32_t *)xnorm);
+                           n_groups, nk, norm_all, centre, xblk, (uint32_t *)xnorm);
 }
 
 template <int DT, int NK> static void launch_join_nk(const JoinParams &p, int n_items, hipStream_t s)

@@ -270,7 +270,9 @@ __global__ __launch_bounds__(64) void scan_rerank_kernel(RerankParams p)
     float qn = 0.f;
     for (int i = lane; i < nchunks; i += 64) {
         const uint4 v = qv[i];
-        const float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+        float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+        if (p.centre != nullptr)
+            for (int u = 0; u < 4; ++u) f[u] -= p.centre[i * 4 + u];
         qn += f[0] * f[0] + f[1] * f[1] + f[2] * f[2] + f[3] * f[3];
     }
 #pragma unroll

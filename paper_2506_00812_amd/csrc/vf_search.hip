@@ -329,8 +329,8 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     // over their queries.  float32 keeps spare candidates and proves the re-ranked result, which needs the norms to be
     // within the proofs' range and room for enough spare ones.
     const int32_t join_keep = ix->dtype == VF_U8 ? k : std::min(64, k + 22);
-    const bool joined = exact && first_hs < r.scan_pairs.size() && ix->d_xnorm_all.p != nullptr &&
-                        (ix->dtype == VF_U8 || (ix->xn_max > 0.f && ix->tune.scan_bf16 && join_keep >= k + 16));
+    const bool joined = exact && first_hs < r.scan_pairs.size() && ix->join_norms() != nullptr &&
+                        (ix->dtype == VF_U8 || (ix->xc_max > 0.f && ix->tune.scan_bf16 && join_keep >= k + 16));
     if (joined) {
         P.join_keep = join_keep;
         ItemBuilder jb(ix->tune);
@@ -755,12 +755,12 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
             if ((rc = ix->tmp_norm.reserve((size_t)P.join_groups * 32 * 4)) != VF_OK) return rc;
             JoinParams jp{};
             jp.xblk = ix->tmp_blk.as<uint4>(); jp.xnorm = ix->tmp_norm.p; jp.map = ix->d_M_HS.as<int32_t>();
-            jp.qsrc = queries; jp.qrow = sp.qrow; jp.dim = ix->dim; jp.K = P.join_keep;
+            jp.qsrc = queries; jp.qrow = sp.qrow; jp.dim = ix->dim; jp.K = P.join_keep; jp.centre = ix->d_centre.as<float>();
             jp.res_idx = M.part_idx + P.ls_part_words; jp.res_bits = M.part_bits + P.ls_part_words;
             jp.others_off = d_others_off; jp.others = d_others; jp.meta = sp.meta;
             for (const JoinBatch &b : P.jbatches) {
                 launch_join_pack(ix->dtype, ix->X, ix->dim, jp.map, (const JoinList *)(dp + L.off_jlists) + b.list_lo,
-                                 (int)(b.list_hi - b.list_lo), b.groups, ix->d_xnorm_all.as<uint32_t>(), ix->tmp_blk.as<uint4>(),
+                                 (int)(b.list_hi - b.list_lo), b.groups, ix->join_norms(), ix->d_centre.as<float>(), ix->tmp_blk.as<uint4>(),
                                  ix->tmp_norm.p, s);
                 jp.items = (const ScanItem *)(dp + L.off_items) + P.n_ls_items + b.item_lo;
                 launch_join(ix->dtype, jp, (int)(b.item_hi - b.item_lo), s);
@@ -773,7 +773,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 RerankParams rp{};
                 rp.items = d_merges + P.n_ls_merges; rp.res_idx = jp.res_idx; rp.res_bits = jp.res_bits; rp.map = jp.map;
                 rp.X = ix->X; rp.Q = queries; rp.dim = ix->dim; rp.Kc = P.join_keep; rp.K = k;
-                rp.err_bound = ix->join_err_bound(); rp.xn_max = ix->xn_max; rp.err_q = 0.f;
+                rp.err_bound = ix->join_err_bound(); rp.xn_max = ix->xc_max; rp.err_q = 0.f; rp.centre = jp.centre;
                 rp.fail_count = ix->d_scan_fb.as<uint32_t>();
                 rp.others_off = sp.others_off; rp.others = sp.others; rp.meta = sp.meta;
                 rp.out_ids = out_ids; rp.out_dists = out_dists;

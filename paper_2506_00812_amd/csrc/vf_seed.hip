@@ -820,44 +820,31 @@ void launch_seed_map(const int32_t *M_HS, const int64_t *slot_base, const int32_
                        slot_n, n_seeds, grp_slot, grp_j0, n_groups, seed_map);
 }
 
-// One thread per row, elements in ascending order.  float32: sum of squares (float bits);
-// uint8: sum of (x - 128)^2 (int32).
-template <int DT> __global__ void row_norm_kernel(const void *X, int32_t dim, int64_t n, uint32_t *out)
+// One thread per row: sum of (x - 128)^2 over the bytes.
+__global__ void row_norm_u8_kernel(const uint8_t *X, int32_t dim, int64_t n, uint32_t *out)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    if (DT == 1) {
-        const float4 *x = (const float4 *)((const float *)X + i * dim);
-        float acc = 0.f;
-        for (int e = 0; e < dim / 4; ++e) {
-            const float4 v = x[e];
-            acc += v.x * v.x; acc += v.y * v.y; acc += v.z * v.z; acc += v.w * v.w;
-        }
-        out[i] = __float_as_uint(acc);
-    } else {
-        const uint4 *x = (const uint4 *)((const uint8_t *)X + i * dim);
-        int acc = 0;
-        for (int e = 0; e < dim / 16; ++e) {
-            const uint4 v = x[e];
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    const uint4 *x = (const uint4 *)(X + i * dim);
+    int acc = 0;
+    for (int e = 0; e < dim / 16; ++e) {
+        const uint4 v = x[e];
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int d = (int)((w[a] >> (8 * b)) & 0xFFu) - 128;
-                    acc += d * d;
-                }
-        }
-        out[i] = (uint32_t)acc;
+            for (int b = 0; b < 4; ++b) {
+                const int d = (int)((w[a] >> (8 * b)) & 0xFFu) - 128;
+                acc += d * d;
+            }
     }
+    out[i] = (uint32_t)acc;
 }
 
-void launch_row_norms(int dtype, const void *X, int32_t dim, int64_t n, uint32_t *out, hipStream_t s)
+void launch_row_norms_u8(const void *X, int32_t dim, int64_t n, uint32_t *out, hipStream_t s)
 {
     if (n <= 0) return;
-    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    if (dtype == 1) hipLaunchKernelGGL(row_norm_kernel<1>, grid, block, 0, s, X, dim, n, out);
-    else hipLaunchKernelGGL(row_norm_kernel<0>, grid, block, 0, s, X, dim, n, out);
+    hipLaunchKernelGGL(row_norm_u8_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const uint8_t *)X, dim, n, out);
 }
 
 // Whether a launch of the dense kernel pays.  Dimensions with an instantiation of their own: always.  Others (an index has

@@ -73,3 +73,64 @@ def test_exact_search_at_tile_edges(dtype, dim, k):
             assert_exact(to_np(gi), to_np(gd), oi, od, "exact")
         else:
             assert_close_with_ties(to_np(gi), to_np(gd), oi, od, 1e-4, "exact")
+
+
+def _shifted(dim, shift, spread, n=6000, nq=200):
+    rng = np.random.default_rng(dim)
+    centres = rng.normal(size=(12, dim)) * spread + shift
+    x = (centres[rng.integers(0, 12, n)] + rng.normal(size=(n, dim))).astype(np.float32)
+    q = (centres[rng.integers(0, 12, nq)] + rng.normal(size=(nq, dim))).astype(np.float32)
+    carry = rng.random((n, 2)) < [0.99, 0.5]
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    return x, q, off, np.nonzero(carry)[1].astype(np.int32), carry
+
+
+def _truth(x, q, member, k):
+    """The k nearest members of every query in 64 bits."""
+    at = np.flatnonzero(member)
+    v, q = x[at].astype(np.float64), q.astype(np.float64)
+    d = ((q[:, None, :] - v[None, :, :]) ** 2).sum(2) if len(at) * q.size < 1 << 28 else \
+        np.stack([((q[j] - v) ** 2).sum(1) for j in range(len(q))])
+    order = np.argsort(d, axis=1, kind="stable")[:, :k]
+    return at[order], np.take_along_axis(d, order, 1)
+
+
+@pytest.mark.parametrize("dim", [40, 100, 128, 132, 248])
+def test_tables_far_from_the_origin(dim):
+    """A table and its queries shifted by 30 (noise 1, clusters of 500): every row and result has its proof, and is right."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_close_with_ties, to_np
+    x, q, off, ids, carry = _shifted(dim, 30.0, 2.0)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, 2, 100, 16)
+    rows = ix.export("G_HS").reshape(-1, 16)
+    member = np.flatnonzero(carry[:, 0])
+    local, _ = _truth(x, x[member[:40]], carry[:, 0], 17)
+    for j in range(40):   # (the row's own vertex is the nearest of its list)
+        assert set(member[rows[j]]) == set(local[j, 1:])
+    ix.profile_enable(True)
+    for label in (0, 1):
+        qoff, qids = np.arange(len(q) + 1, dtype=np.int64), np.full(len(q), label, dtype=np.int32)
+        gi, gd = vf.search_exact(ix, torch.from_numpy(q).cuda(), qoff, qids, 10)
+        wi, wd = _truth(x, q, carry[:, label], 10)
+        assert_close_with_ties(to_np(gi), to_np(gd), wi, wd.astype(np.float32), 1e-5, "exact")
+    assert ix.profile_read()["scan_fallbacks"] == 0
+
+
+def test_proofs_of_the_ground_truth_are_not_weakened():
+    """Clusters so far apart that some proofs fail: as many of them with "seed_slack" below 1 as at 1, the same results."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_close_with_ties, to_np
+    x, q, off, ids, carry = _shifted(128, 0.0, 150.0)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, 2, 100, 16)
+    qoff, qids = np.arange(len(q) + 1, dtype=np.int64), np.zeros(len(q), dtype=np.int32)
+    failed = []
+    for slack in (1.0, 0.001):
+        ix.tune("seed_slack", slack)
+        ix.profile_enable(True)
+        gi, gd = vf.search_exact(ix, torch.from_numpy(q).cuda(), qoff, qids, 10)
+        wi, wd = _truth(x, q, carry[:, 0], 10)
+        assert_close_with_ties(to_np(gi), to_np(gd), wi, wd.astype(np.float32), 1e-5, "exact")
+        failed.append(ix.profile_read()["scan_fallbacks"])
+    assert failed[0] == failed[1] > 0

@@ -233,7 +233,8 @@ struct vf_index {
     vf::DevBuf d_S, d_O_HS, d_O_LS, d_hs_slot, d_M_HS, d_M_LS, d_G, d_X_LS, d_xnorm_LS, d_bitsets;
     // float32 data: the scan lists once more in bfloat16 (16-byte chunks of 8 components, half the bytes), which the
     // filtering scan kernel streams; ls_bf16_delta = max |x - bf16(x)| over the lists' vectors (its error bound)
-    vf::DevBuf d_X_LS16, d_scan_fb;
+    vf::DevBuf d_X_LS16, d_scan_fb;    // d_scan_fb: [0] failed proofs, [1] refused queries of the ground-truth call that runs
+    bool refused_unread = false;       // [1] may not be zero (a call failed between)
     bool has_ls16 = false;
     float ls_bf16_delta = 0.f, ls_xn_max = 0.f;   // ... and the largest squared norm of a list vector
     uint32_t scan_fb_seen = 0;   // failed proofs already reported (d_scan_fb counts them on the device)
@@ -371,6 +372,8 @@ struct CallMem {
     uint32_t *dseed = nullptr;
     int32_t *part_idx = nullptr;
     uint32_t *part_bits = nullptr;
+    int32_t *refused = nullptr;    // ground truth: see RerankParams::refused
+    uint32_t *refused_any = nullptr;
 };
 
 int check_search_args(const vf_index *ix, const void *queries, int64_t nq, int32_t k, const int64_t *out_ids,

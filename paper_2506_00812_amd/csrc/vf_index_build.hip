@@ -376,8 +376,8 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
         VF_HIP(hipStreamSynchronize(s));
 
         if (dtype == VF_F32) {   // failed proofs of the filtering scans
-            if ((rc = ix->d_scan_fb.reserve(4)) != VF_OK) return rc;
-            VF_HIP(hipMemsetAsync(ix->d_scan_fb.p, 0, 4, s));
+            if ((rc = ix->d_scan_fb.reserve(8)) != VF_OK) return rc;
+            VF_HIP(hipMemsetAsync(ix->d_scan_fb.p, 0, 8, s));
         }
         // ---- scan partition: StoreInterleaved over every scan list (Section 4.2.2)
         if (ix->n_groups_LS > 0) {

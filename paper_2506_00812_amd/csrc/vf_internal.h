@@ -105,6 +105,13 @@ struct RerankParams {
     float err_bound, xn_max, err_q;   // |approximation - ordered distance| <= err_bound (|q|^2 + xn_max) + err_q |q|
     const float *centre;        // the approximations' origin, which |q| is measured from; null: zero
     uint32_t *fail_count;       // incremented once per query whose proof failed
+    // where the caller answers such queries itself (launch_ordered_scan): their merge items' indices, this launch's counted
+    // from refused_first, their number, and a word of host memory that is set if there are any (so that a batch without
+    // them, nearly every one, has nothing to clear or to fetch); null: the re-ranking wave scans the list at once
+    int32_t *refused;
+    int32_t *refused_count;
+    uint32_t *refused_any;
+    int32_t refused_first;
     const int32_t *others_off;  // AND partner labels per query; null when the batch has none
     const int32_t *others;
     LabelMeta meta;
@@ -115,6 +122,22 @@ bool scan_bf16_supported(int dtype, int dim, int tile_rows, int keep);
 size_t scan_bf16_lds_bytes(int tile_rows, int keep);
 void launch_scan_bf16(const ScanParams &p, int n_items, int slots, hipStream_t s);
 void launch_scan_rerank(const RerankParams &p, int n_items, hipStream_t s);
+
+// Exact top K of a few queries by the ordered distance itself, float32 rows gathered from the table: the queries whose
+// proof failed.  Every item writes partial rows.
+struct OrderedScanParams {
+    const void *X, *Q;          // row-major [*][dim]
+    const int32_t *map;         // local -> global id
+    const ScanItem *items;      // <= kOrderedRows queries each (group0, self_base unused)
+    const int32_t *qrow;
+    int32_t dim, K;             // K <= 64
+    int32_t *res_idx;           // [*][K] list-relative entry index, ascending by (distance, index), -1 = none
+    uint32_t *res_bits;
+    const int32_t *others_off, *others;   // AND partner labels per query, may be null
+    LabelMeta meta;
+};
+constexpr int kOrderedRows = 8;
+void launch_ordered_scan(const OrderedScanParams &p, int n_items, hipStream_t s);
 
 // ---------------------------------------------------------------- join kernel (vf_join.hip)
 

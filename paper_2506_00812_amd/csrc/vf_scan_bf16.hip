@@ -305,6 +305,13 @@ __global__ __launch_bounds__(64) void scan_rerank_kernel(RerankParams p)
     }
     if (!proven) {   // (wave-uniform) the definition itself: every entry of the list that passes the predicate
         if (lane == 0) atomicAdd(p.fail_count, 1u);
+        if (p.refused != nullptr) {
+            if (lane == 0) {
+                p.refused[atomicAdd(p.refused_count, 1)] = p.refused_first + (int32_t)blockIdx.x;
+                __hip_atomic_store(p.refused_any, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+            return;
+        }
         int o_begin = 0, o_end = 0;
         if (p.others_off != nullptr) { o_begin = p.others_off[it.qrow]; o_end = p.others_off[it.qrow + 1]; }
         TopM<1> ex;
@@ -338,6 +345,101 @@ __global__ __launch_bounds__(64) void scan_rerank_kernel(RerankParams p)
         p.out_ids[o] = none ? -1 : (int64_t)p.map[it.map_off + (uint32_t)key];
         p.out_dists[o] = none ? __builtin_inff() : __uint_as_float((uint32_t)(key >> 32));
     }
+}
+
+// Queries without a proof, where the host can wait to learn which they are (ground truth): up to eight of a list share the
+// loads of a segment, one entry per lane, and a list is cut into segments for as many waves as the chip takes.  Bound by
+// the vector ALU (two instructions per component and pair) from a few queries on; a lone query by the latency of its
+// gathers, eight 16-byte loads per lane in flight.  The sums are the eight interleaved ones of an 8-lane team
+// (team_dist_bits_f32), so distances have the same bits.
+__global__ __launch_bounds__(64) void ordered_scan_kernel(OrderedScanParams p)
+{
+    extern __shared__ uint4 smem[];
+    constexpr int NR = kOrderedRows, PC = 128;                  // (a step adds <= 64 keys to a row that holds <= 64)
+    const ScanItem it = p.items[blockIdx.x];
+    const int lane = threadIdx.x, K = p.K, KS = K | 1;
+    const int nch = p.dim * 4 / kChunkBytes;
+    uint4 *qv = smem;                                           // [NR][nch]
+    uint64_t *pend = (uint64_t *)(smem + NR * nch);             // [NR][PC]
+    uint64_t *best = pend + NR * PC;                            // [NR][KS]
+    const int qr_lane = lane < it.q_count ? p.qrow[it.q_begin + lane] : -1;
+    for (int r = 0; r < it.q_count; ++r) {
+        const char *q = (const char *)p.Q + (int64_t)__builtin_amdgcn_readlane(qr_lane, r) * (p.dim * 4);
+        for (int c = lane; c < nch; c += 64) qv[r * nch + c] = *(const uint4 *)(q + c * kChunkBytes);
+    }
+    for (int i = lane; i < NR * KS; i += 64) best[i] = KEY_MAX;
+    int o_begin = 0, o_end = 0;   // partner labels of row r, in lane r
+    if (p.others_off != nullptr && qr_lane >= 0) { o_begin = p.others_off[qr_lane]; o_end = p.others_off[qr_lane + 1]; }
+    int pcv = 0;
+    uint64_t row_kth = KEY_MAX;
+    __syncthreads();
+    for (int e0 = 0; e0 < it.n; e0 += 64) {
+        const int e = e0 + lane;
+        const bool exist = e < it.n;
+        const int32_t g = p.map[it.map_off + it.entry0 + (exist ? e : 0)];
+        const char *x = (const char *)p.X + (int64_t)g * (p.dim * 4);
+        float a[NR][8];
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a[r][u] = 0.f;
+        for (int c0 = 0; c0 < nch; c0 += 8) {
+            uint4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = *(const uint4 *)(x + (c0 + u < nch ? c0 + u : c0) * kChunkBytes);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                if (r >= it.q_count) break;   // (wave-uniform, as the next one)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (c0 + u >= nch) break;
+                    const uint4 q = qv[r * nch + c0 + u];
+                    float d;
+                    d = __uint_as_float(q.x) - __uint_as_float(v[u].x); a[r][u] = __builtin_fmaf(d, d, a[r][u]);
+                    d = __uint_as_float(q.y) - __uint_as_float(v[u].y); a[r][u] = __builtin_fmaf(d, d, a[r][u]);
+                    d = __uint_as_float(q.z) - __uint_as_float(v[u].z); a[r][u] = __builtin_fmaf(d, d, a[r][u]);
+                    d = __uint_as_float(q.w) - __uint_as_float(v[u].w); a[r][u] = __builtin_fmaf(d, d, a[r][u]);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            if (r >= it.q_count) break;
+            const float d = ((a[r][0] + a[r][1]) + (a[r][2] + a[r][3])) + ((a[r][4] + a[r][5]) + (a[r][6] + a[r][7]));
+            const uint64_t key = ((uint64_t)__float_as_uint(d) << 32) | (uint32_t)(it.entry0 + e);
+            bool ok = exist && key < readlane64(row_kth, r);
+            const int ob = __builtin_amdgcn_readlane(o_begin, r), oe = __builtin_amdgcn_readlane(o_end, r);
+            for (int o = ob; o < oe; ++o)
+                if (ok) ok = has_label(p.meta, p.others[o], g);
+            const uint64_t m = __ballot(ok);
+            if (m == 0) continue;
+            const int at = __builtin_amdgcn_readlane(pcv, r) + __popcll(m & ((1ull << lane) - 1ull));
+            if (ok) pend[r * PC + at] = key;
+            if (lane == r) pcv += __popcll(m);
+        }
+        if (__any(pcv > PC - 64)) {
+            wave_lds_sync();
+            wave_drain_rows<4>(pend, PC, best, KS, K, pcv, row_kth, lane);
+            wave_lds_sync();
+        }
+    }
+    wave_lds_sync();
+    wave_drain_rows<4>(pend, PC, best, KS, K, pcv, row_kth, lane);
+    wave_lds_sync();
+    for (int r = 0; r < it.q_count; ++r) {
+        if (lane >= K) continue;
+        const uint64_t key = best[r * KS + lane];
+        const int64_t o = (int64_t)(it.part_row + r) * K + lane;
+        p.res_idx[o] = key == KEY_MAX ? -1 : (int32_t)(uint32_t)key;
+        p.res_bits[o] = (uint32_t)(key >> 32);
+    }
+}
+
+void launch_ordered_scan(const OrderedScanParams &p, int n_items, hipStream_t s)
+{
+    if (n_items <= 0) return;
+    const size_t lds = (size_t)kOrderedRows * (p.dim * 4 + 128 * 8 + (p.K | 1) * 8);
+    hipLaunchKernelGGL(ordered_scan_kernel, dim3(n_items), dim3(64), lds, s, p);
 }
 
 bool scan_bf16_supported(int dtype, int dim, int tile_rows, int keep)

@@ -732,6 +732,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 rp.err_bound = ix->seed_err_bound() * 8.0f; rp.xn_max = ix->ls_xn_max; rp.err_q = 2.0f * ix->ls_bf16_delta;
                 rp.fail_count = ix->d_scan_fb.as<uint32_t>();
                 rp.others_off = sp.others_off; rp.others = sp.others; rp.meta = sp.meta;
+                rp.refused = M.refused; rp.refused_any = M.refused_any; rp.refused_count = ix->d_scan_fb.as<int32_t>() + 1;
                 rp.out_ids = out_ids; rp.out_dists = out_dists;
                 launch_scan_rerank(rp, (int)P.n_ls_merges, ss);
             } else if (small_batch && scan_valu_supported(ix->dtype, ix->dim, sp.tile_rows)) {
@@ -776,6 +777,8 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 rp.err_bound = ix->join_err_bound(); rp.xn_max = ix->xc_max; rp.err_q = 0.f; rp.centre = jp.centre;
                 rp.fail_count = ix->d_scan_fb.as<uint32_t>();
                 rp.others_off = sp.others_off; rp.others = sp.others; rp.meta = sp.meta;
+                rp.refused = M.refused; rp.refused_any = M.refused_any; rp.refused_count = ix->d_scan_fb.as<int32_t>() + 1;
+                rp.refused_first = (int32_t)P.n_ls_merges;
                 rp.out_ids = out_ids; rp.out_dists = out_dists;
                 launch_scan_rerank(rp, n_merges, s);
             }
@@ -836,6 +839,74 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
     return VF_OK;
 }
 
+// Ground truth of the queries whose filtered result was refused a proof (RerankParams::refused): by the ordered distance,
+// kOrderedRows of a list at a time, every list cut into as many segments as keep the chip busy.  (One wave per query, in
+// the re-ranking kernel, takes as long as the longest list: 400,000 x 128 float32, one query with a NaN made a batch of
+// 4,000 take 21.6 instead of 2.2 ms, now 2.5; a table whose clusters lie so far apart that 2,245 of them are refused 21.0,
+// now 6.5.)  The stream is idle; waits for the results.
+static int answer_refused(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem &M, const void *queries, int64_t *out_ids,
+                          float *out_dists, hipStream_t s)
+{
+    int32_t n_refused = 0;
+    VF_HIP(hipMemcpy(&n_refused, ix->d_scan_fb.as<int32_t>() + 1, 4, hipMemcpyDeviceToHost));
+    std::vector<int32_t> which((size_t)n_refused);
+    VF_HIP(hipMemcpy(which.data(), M.refused, which.size() * 4, hipMemcpyDeviceToHost));
+    std::sort(which.begin(), which.end());   // queries of a list become neighbours, scan lists come first
+    const std::vector<MergeItem> &merges = P.ib.merges;
+    constexpr size_t kBatch = 4096;          // bounds the partial rows: 64 segments of 64 results each
+    DevBuf d_items(&ix->alloc), d_merges(&ix->alloc), d_qrow(&ix->alloc), parts(&ix->alloc);
+    DevBufGuard guard{&d_items, &d_merges, &d_qrow, &parts};
+    int rc;
+    for (size_t lo = 0; lo < which.size();) {
+        const bool ls = (size_t)which[lo] < P.n_ls_merges;
+        size_t hi = lo;
+        while (hi < which.size() && hi - lo < kBatch && ((size_t)which[hi] < P.n_ls_merges) == ls) ++hi;
+        ItemBuilder ib(ix->tune);
+        ib.tile_rows = kOrderedRows;
+        ib.all_partial = true;
+        std::vector<uint64_t> rows;          // (queries of one list)
+        auto list_end = [&](size_t i) {
+            size_t e = i;
+            while (e < hi && merges[(size_t)which[e]].map_off == merges[(size_t)which[i]].map_off) ++e;
+            return e;
+        };
+        int64_t tile_groups = 0;
+        for (size_t i = lo, e; i < hi; i = e) {
+            e = list_end(i);
+            tile_groups += (int64_t)((e - i + kOrderedRows - 1) / kOrderedRows) * ((merges[(size_t)which[i]].n + 31) / 32);
+        }
+        ib.seg_groups = ib.seg_groups_heavy = (int)std::max<int64_t>(8, tile_groups / 4096);
+        for (size_t i = lo, e; i < hi; i = e) {
+            e = list_end(i);
+            rows.clear();
+            for (size_t u = i; u < e; ++u) rows.push_back((uint64_t)(uint32_t)merges[(size_t)which[u]].qrow);
+            ib.add_label(rows, 0, rows.size(), 0, merges[(size_t)which[i]].map_off, merges[(size_t)which[i]].n);
+        }
+        const size_t words = (size_t)ib.part_rows * P.k;
+        if ((rc = parts.reserve(words * 8)) != VF_OK) return rc;
+        if ((rc = upload(d_items, ib.items, s)) != VF_OK || (rc = upload(d_merges, ib.merges, s)) != VF_OK ||
+            (rc = upload(d_qrow, ib.qrow, s)) != VF_OK)
+            return rc;
+        OrderedScanParams p{};
+        p.X = ix->X; p.Q = queries; p.map = ls ? ix->d_M_LS.as<int32_t>() : ix->d_M_HS.as<int32_t>();
+        p.items = d_items.as<ScanItem>(); p.qrow = d_qrow.as<int32_t>();
+        p.dim = ix->dim; p.K = P.k;
+        p.res_idx = parts.as<int32_t>(); p.res_bits = parts.as<uint32_t>() + words;
+        if (r.any_and) {
+            p.others_off = (const int32_t *)(M.blob + P.L.off_others_off);
+            p.others = (const int32_t *)(M.blob + P.L.off_others);
+        }
+        p.meta = ix->meta();
+        launch_ordered_scan(p, (int)ib.items.size(), s);
+        launch_scan_merge(ix->dtype, d_merges.as<MergeItem>(), (int)ib.merges.size(), p.res_idx, p.res_bits, P.k, ib.max_nseg * P.k,
+                          p.map, out_ids, out_dists, s);
+        VF_HIP(hipGetLastError());
+        VF_HIP(hipStreamSynchronize(s));     // the tables are pageable host memory, the next batch takes the same buffers
+        lo = hi;
+    }
+    return VF_OK;
+}
+
 // first_is_searched: every query searches the list of its first label (the others are the
 // predicate) instead of its smallest list -- the sub-searches of vf_search_multi.
 int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qoff, const int32_t *qids, int32_t k,
@@ -885,7 +956,9 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     const BlobLayout &L = P.L;
     const auto t_planned = std::chrono::steady_clock::now();
     Staging *st = nullptr;
-    if ((rc = get_staging(W, L.total, &st)) != VF_OK) return rc;
+    // (ground truth: behind the blob is the word that says whether there are refused queries)
+    const size_t flag_at = (L.total + 63) & ~(size_t)63;
+    if ((rc = get_staging(W, flag_at + 64, &st)) != VF_OK) return rc;
     const auto t_staged = std::chrono::steady_clock::now();   // (waiting for the staging buffer is the GPU's time, not the host's)
     char *hp = (char *)st->p;
     fill_blob(P, r, hp);
@@ -893,7 +966,8 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     // seed distances and partial rows in one buffer: one allocation where a workspace meets its first call
     auto words_up = [](size_t v) { return (v + 63) & ~(size_t)63; };
     const size_t dseed_words = P.dense_seeds ? words_up(P.dseed_words) : 0, part_words = words_up(P.part_words);
-    if (dseed_words + part_words > 0 && (rc = W->dseed.reserve((dseed_words + 2 * part_words) * 4)) != VF_OK) return rc;
+    const size_t refused_words = exact && (P.scan_bf16 || (!P.jbatches.empty() && ix->dtype == VF_F32)) ? words_up(P.ib.merges.size()) : 0;
+    if (dseed_words + part_words > 0 && (rc = W->dseed.reserve((dseed_words + 2 * part_words + refused_words) * 4)) != VF_OK) return rc;
     // The scan path runs on the side stream beside the graph path on the caller's stream.
     const bool forked = tune.overlap && !ix->prof_serial && !exact && P.n_gq > 0 && !P.ib.items.empty();
     // Two device blobs alternate.  When the call forks, its blob is uploaded on the side stream: there it
@@ -934,6 +1008,15 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     M.dseed = W->dseed.as<uint32_t>();
     M.part_idx = W->dseed.as<int32_t>() + dseed_words;
     M.part_bits = W->dseed.as<uint32_t>() + dseed_words + part_words;
+    if (refused_words > 0) {
+        M.refused = W->dseed.as<int32_t>() + dseed_words + 2 * part_words;
+        void *dev_view = nullptr;
+        VF_HIP(hipHostGetDevicePointer(&dev_view, st->p, 0));
+        M.refused_any = (uint32_t *)((char *)dev_view + flag_at);
+        memset(hp + flag_at, 0, 4);
+        if (ix->refused_unread) VF_HIP(hipMemsetAsync(ix->d_scan_fb.as<uint32_t>() + 1, 0, 4, s));
+        ix->refused_unread = true;
+    }
     if ((rc = launch_call(ix, P, r, M, sc, queries, out_ids, out_dists, s, forked ? W->side : nullptr, W->ev_fork,
                           W->ev_join, true)) != VF_OK)
         return rc;
@@ -954,6 +1037,10 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
         VF_HIP(hipStreamSynchronize(s));
         ix->tmp_blk.release();
         ix->tmp_norm.release();
+        uint32_t any = 0;
+        if (M.refused != nullptr) memcpy(&any, hp + flag_at, 4);
+        if (any != 0 && (rc = answer_refused(ix, P, r, M, queries, out_ids, out_dists, s)) != VF_OK) return rc;
+        if (any == 0) ix->refused_unread = false;
     }
     return VF_OK;
 }

@@ -134,3 +134,57 @@ def test_proofs_of_the_ground_truth_are_not_weakened():
         assert_close_with_ties(to_np(gi), to_np(gd), wi, wd.astype(np.float32), 1e-5, "exact")
         failed.append(ix.profile_read()["scan_fallbacks"])
     assert failed[0] == failed[1] > 0
+
+
+@pytest.mark.parametrize("dim,k,sizes,nq", [(128, 10, [9000, 4000, 700, 130], 300), (100, 48, [9000, 2500, 400], 60), (4, 1, [3000, 129], 5000),
+                                            (96, 25, [6000, 65, 64, 33], 400), (248, 7, [1030, 200], 41)])
+def test_ground_truth_without_proofs(dim, k, sizes, nq):
+    """A bound that no result meets sends every query of a float32 graph list (and of a scan list, in batches that filter) to
+    the ordered scan: one query or many of a list, AND queries, several segments; the results keep their bits.  Queries with
+    NaN, infinities and overflowing norms go there by themselves."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    rng = np.random.default_rng(dim + k)
+    n, T = max(sizes) + 50, 300
+    x = ((rng.normal(size=(16, dim)) * 2)[rng.integers(0, 16, n)] + rng.normal(size=(n, dim))).astype(np.float32)
+    carry = np.zeros((n, len(sizes)), dtype=bool)
+    for l, size in enumerate(sizes):
+        carry[rng.permutation(n)[:size], l] = True
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    ids = np.nonzero(carry)[1].astype(np.int32)
+    asked = [[l] for l in range(len(sizes))] + [[0, 1], [0, len(sizes) - 1]]
+    asked += [sorted(set(rng.integers(0, len(sizes), rng.integers(1, 3)).tolist())) for _ in range(nq - len(asked))]
+    qoff = np.concatenate([[0], np.cumsum([len(a) for a in asked])]).astype(np.int64)
+    qids = np.array([l for a in asked for l in a], dtype=np.int32)
+    q = x[rng.integers(0, n, nq)] + 0.5 * rng.normal(size=(nq, dim)).astype(np.float32)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, len(sizes), T, 8)
+    ix.profile_enable(True)
+
+    def search(q):
+        out = vf.search_exact(ix, torch.from_numpy(np.ascontiguousarray(q)).cuda(), qoff, qids, k)
+        return [t.cpu().numpy() for t in out], ix.profile_read()["scan_fallbacks"]
+
+    (ids0, d0), _ = search(q)
+    graph = np.array([min(int(carry[:, l].sum()) for l in a) >= T for a in asked])
+    ix.tune("seed_slack", 1e6)
+    ix.profile_enable(True)
+    (ids1, d1), failed = search(q)
+    # (a query with fewer members than are kept needs no proof)
+    enough = np.array([int(carry[:, a].all(1).sum()) >= min(64, k + 22) for a in asked])
+    assert failed >= (graph & enough).sum() > 0
+    assert np.array_equal(ids0[graph], ids1[graph]) and np.array_equal(d0[graph].view(np.uint32), d1[graph].view(np.uint32))
+    assert np.array_equal(ids0, ids1) and np.allclose(d0, d1, rtol=1e-5)
+    ix.tune("seed_slack", 1.0)
+    odd = {0: np.nan, 1: np.inf, 4: -np.inf, 5: 3e19}
+    q2 = q.copy()
+    for j, v in odd.items():
+        if j < nq:
+            q2[j, dim // 2] = v
+    (ids2, d2), failed = search(q2)
+    rest = [j for j in range(nq) if j not in odd]
+    assert np.array_equal(ids2[rest], ids0[rest])
+    for j, v in odd.items():
+        if graph[j]:   # all distances are the same: the lowest ids
+            want = np.flatnonzero(carry[:, asked[j]].all(1))[:k]
+            assert np.array_equal(ids2[j][:len(want)], want) and (ids2[j][len(want):] == -1).all()
+            assert np.isnan(d2[j][:len(want)]).all() if np.isnan(v) else np.isinf(d2[j]).all()

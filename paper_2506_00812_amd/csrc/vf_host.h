@@ -380,9 +380,26 @@ int check_search_args(const vf_index *ix, const void *queries, int64_t nq, int32
                       const float *out_dists);
 int check_search_params(const vf_index *ix, bool exact, int32_t k, int32_t &itopk, int32_t width, int32_t iters,
                         int32_t &n_seeds);
+// How many words a call's seed distances may take.  words: what is allocated or fixed; beyond that, where the buffer may
+// grow (cap: its bytes), into at most half of the free memory -- the driver is only asked by a call that needs it, the
+// query is slow.
+struct SeedBudget {
+    uint64_t words = 0;
+    bool grows = false;
+    size_t cap = 0;
+    bool fits(uint64_t need)
+    {
+        if (need <= words || !grows) return need <= words;
+        grows = false;
+        size_t free_b = 0, total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) { (void)hipGetLastError(); return false; }
+        words = std::max<uint64_t>(words, (uint64_t)((free_b + cap) / 2) / 5);   // / 4 bytes, / 1.25 growth
+        return need <= words;
+    }
+};
 int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, const int32_t *qids, bool exact,
               bool first_is_searched, int32_t k, int32_t itopk, int32_t width, int32_t iters, int32_t n_seeds,
-              int32_t and_scan_limit, uint64_t dseed_budget_words, const SeedCopy *sc, CallPlan &P);
+              int32_t and_scan_limit, SeedBudget budget, const SeedCopy *sc, CallPlan &P);
 // May this call's seeds be scored on the matrix cores (so that an interleaved seed copy is worth having)?
 bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_seeds);
 // The resident copy for n_seeds, or (build = true) a new one; *out stays null when there is none.

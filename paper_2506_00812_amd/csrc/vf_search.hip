@@ -244,11 +244,11 @@ int check_search_params(const vf_index *ix, bool exact, int32_t k, int32_t &itop
     return VF_OK;
 }
 
-// Routing, work lists, blob layout.  dseed_budget_words: how large a seed distance matrix may be (beyond it the
+// Routing, work lists, blob layout.  budget: how large a seed distance matrix may be (beyond it the
 // beam kernel gathers the seeds itself).
 int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, const int32_t *qids, bool exact,
                      bool first_is_searched, int32_t k, int32_t itopk, int32_t width, int32_t iters, int32_t n_seeds,
-                     int32_t and_scan_limit, uint64_t dseed_budget_words, const SeedCopy *sc, CallPlan &P)
+                     int32_t and_scan_limit, SeedBudget budget, const SeedCopy *sc, CallPlan &P)
 {
     int rc;
     P.nq = nq; P.k = k; P.itopk = itopk; P.width = width; P.iters = iters; P.n_seeds = n_seeds; P.exact = exact;
@@ -438,7 +438,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         P.seg_seeds = seg;
         P.max_segs = (longest + seg - 1) / seg;
         const uint64_t need = (uint64_t)P.n_gq * (uint64_t)P.max_segs * (uint64_t)P.sel_K * 2;   // 8-byte keys
-        if (need <= dseed_budget_words) {
+        if (budget.fits(need)) {
             P.seed_select = true;
             P.dense_seeds = P.seeds_mfma = true;
             P.dseed_words = (size_t)need;
@@ -447,7 +447,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     if (!P.seed_select) {
         // every distance goes through the seed distance matrix, which must fit
         const uint64_t need = (uint64_t)P.n_gq * (uint64_t)P.ns_stride + 64 * 1024;
-        P.dense_seeds = !exact && P.n_gq > 0 && seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq) && need <= dseed_budget_words;
+        P.dense_seeds = !exact && P.n_gq > 0 && seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq) && budget.fits(need);
         P.seeds_mfma = P.dense_seeds && mfma_ok;
         if (P.dense_seeds) P.dseed_words = (size_t)need;
     }
@@ -472,7 +472,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         size_t plain = P.n_gq;
         if (r.any_and)
             for (size_t i = 0; i < P.n_gq; ++i) plain -= r.others_off[(size_t)r.gq_query[i] + 1] > r.others_off[(size_t)r.gq_query[i]] ? 1 : 0;
-        if (P.ns_stride / 32 >= 3 * keep && 2 * plain >= P.n_gq && (uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride <= dseed_budget_words) {
+        if (P.ns_stride / 32 >= 3 * keep && 2 * plain >= P.n_gq && budget.fits((uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride)) {
             P.nb_stride = stride;
             P.dseed_words += P.n_gq * (size_t)stride;
         }
@@ -923,13 +923,10 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     if (nq == 0) return VF_OK;
     const Tuning &tune = ix->tune;
     // the seed distance matrix reuses what is allocated, or grows into at most half of the free memory
-    uint64_t dseed_budget = W->dseed.cap / 4;
-    // (the driver is only asked when the buffer at hand may be too small for this call: the query is slow)
-    if ((uint64_t)nq * (uint64_t)((std::max(n_seeds, itopk) + 31) & ~31) + 64 * 1024 > dseed_budget) {
-        size_t free_b = 0, total_b = 0;
-        VF_HIP(hipMemGetInfo(&free_b, &total_b));
-        dseed_budget = std::max<uint64_t>(dseed_budget, (uint64_t)((free_b + W->dseed.cap) / 2) / 5);   // / 4 bytes, / 1.25 growth
-    }
+    SeedBudget budget;
+    budget.words = W->dseed.cap / 4;
+    budget.grows = true;
+    budget.cap = W->dseed.cap;
     // the interleaved copy of the seeds for this seed count (built on first use), after a look at the watch
     // on failed float32 proofs
     SeedCopy *sc = nullptr;
@@ -951,7 +948,7 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     Routed &r = W->routed;
     VF_REQUIRE(and_scan_limit >= 0, "and_scan_limit must be >= 0");
     if ((rc = plan_call(ix, r, nq, qoff, qids, exact, first_is_searched, k, itopk, width, iters, n_seeds, and_scan_limit,
-                        dseed_budget, sc, P)) != VF_OK)
+                        budget, sc, P)) != VF_OK)
         return rc;
     const BlobLayout &L = P.L;
     const auto t_planned = std::chrono::steady_clock::now();

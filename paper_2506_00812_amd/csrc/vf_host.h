@@ -175,9 +175,9 @@ struct ItemBuilder {
 struct Workspace {
     DevBuf ws_blob, ws_blob_b;
     DevBuf dseed;   // seed distances, then partial result rows
-    // vf_search_multi: gathered query rows, results of the sub-searches, their parents
-    DevBuf multi_q, multi_ids, multi_dists, multi_meta;
-    std::vector<int32_t> multi_host;      // [n_sub parents | nq + 1 first sub-search of each query], alive until the next call
+    // vf_search_multi: gathered query rows, results of the sub-searches
+    DevBuf multi_q, multi_ids, multi_dists;
+    std::vector<int32_t> multi_host;      // [n_sub parents | nq + 1 first sub-search of each query]
     std::vector<int64_t> multi_qoff;
     std::vector<int32_t> multi_qids;
     // the scan path runs beside the graph path on a second stream of the same (default) priority
@@ -193,7 +193,7 @@ struct Workspace {
     hipStream_t owner = nullptr; // the stream whose calls use this workspace
     std::vector<DevBuf *> bufs()
     {
-        return {&ws_blob, &ws_blob_b, &dseed, &multi_q, &multi_ids, &multi_dists, &multi_meta};
+        return {&ws_blob, &ws_blob_b, &dseed, &multi_q, &multi_ids, &multi_dists};
     }
 };
 
@@ -324,7 +324,7 @@ template <class T> int upload(DevBuf &b, const std::vector<T> &v, hipStream_t s)
 
 // vf_search.hip: the pieces of one search call
 struct BlobLayout {
-    size_t off_gq_query, off_gq_label, off_xq_query, off_xq_label, off_others_off, off_others, off_qrow, off_items, off_merges, off_tiles, off_empty, off_jlists, total;
+    size_t off_gq_query, off_gq_label, off_xq_query, off_xq_label, off_others_off, off_others, off_qrow, off_items, off_merges, off_tiles, off_empty, off_jlists, off_multi, total;
 };
 
 // Everything the host decides about a call before anything is launched.
@@ -417,9 +417,19 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
 void free_index(vf_index *ix);
 
 // vf_search.hip
+// What vf_search_multi adds to the batch of its sub-searches: their queries are gathered from `rows` before it, their
+// results merged into out_* after it.
+struct MultiCall {
+    const std::vector<int32_t> *host;   // [n_sub parents | nq + 1 first sub-search of each query]
+    const void *rows;
+    int64_t nq;
+    int64_t *out_ids;
+    float *out_dists;
+};
 int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qoff, const int32_t *qids, int32_t k,
                 int32_t itopk, int32_t width, int32_t iters, int32_t n_seeds, bool exact, int64_t *out_ids,
-                float *out_dists, hipStream_t s, bool first_is_searched = false, int32_t and_scan_limit = 0);
+                float *out_dists, hipStream_t s, bool first_is_searched = false, int32_t and_scan_limit = 0,
+                const MultiCall *multi = nullptr);
 int search_multi_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qoff, const int32_t *qids,
                       int32_t mode, int32_t k, int32_t itopk, int32_t width, int32_t iters, int32_t n_seeds,
                       int64_t *out_ids, float *out_dists, hipStream_t s);

@@ -911,7 +911,7 @@ static int answer_refused(vf_index *ix, const CallPlan &P, const Routed &r, cons
 // predicate) instead of its smallest list -- the sub-searches of vf_search_multi.
 int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qoff, const int32_t *qids, int32_t k,
                 int32_t itopk, int32_t width, int32_t iters, int32_t n_seeds, bool exact, int64_t *out_ids,
-                float *out_dists, hipStream_t s, bool first_is_searched, int32_t and_scan_limit)
+                float *out_dists, hipStream_t s, bool first_is_searched, int32_t and_scan_limit, const MultiCall *multi)
 {
     int rc = check_search_args(ix, queries, nq, k, out_ids, out_dists);
     if (rc != VF_OK) return rc;
@@ -950,6 +950,10 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     if ((rc = plan_call(ix, r, nq, qoff, qids, exact, first_is_searched, k, itopk, width, iters, n_seeds, and_scan_limit,
                         budget, sc, P)) != VF_OK)
         return rc;
+    if (multi != nullptr) {   // (a copy of its own would wait for the caller's stream: the vectors are pageable memory)
+        P.L.off_multi = P.L.total;
+        P.L.total = align_up(P.L.total + multi->host->size() * 4);
+    }
     const BlobLayout &L = P.L;
     const auto t_planned = std::chrono::steady_clock::now();
     Staging *st = nullptr;
@@ -959,6 +963,7 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     const auto t_staged = std::chrono::steady_clock::now();   // (waiting for the staging buffer is the GPU's time, not the host's)
     char *hp = (char *)st->p;
     fill_blob(P, r, hp);
+    if (multi != nullptr) memcpy(hp + L.off_multi, multi->host->data(), multi->host->size() * 4);
     const auto t_blob = std::chrono::steady_clock::now();
     // seed distances and partial rows in one buffer: one allocation where a workspace meets its first call
     auto words_up = [](size_t v) { return (v + 63) & ~(size_t)63; };
@@ -1014,10 +1019,17 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
         if (ix->refused_unread) VF_HIP(hipMemsetAsync(ix->d_scan_fb.as<uint32_t>() + 1, 0, 4, s));
         ix->refused_unread = true;
     }
+    if (multi != nullptr)
+        launch_gather_rows(multi->rows, (int32_t)((size_t)ix->dim * ix->elem()), (const int32_t *)(M.blob + L.off_multi), nq, W->multi_q.p, s);
     if ((rc = launch_call(ix, P, r, M, sc, queries, out_ids, out_dists, s, forked ? W->side : nullptr, W->ev_fork,
                           W->ev_join, true)) != VF_OK)
         return rc;
-    if (zero_copy) {
+    auto merge_multi = [&] {
+        launch_multi_merge((const int32_t *)(M.blob + L.off_multi) + nq, multi->nq, out_ids, out_dists, k, multi->out_ids, multi->out_dists, s);
+    };
+    if (multi != nullptr && !exact) merge_multi();
+    // (nothing reads the blob after this; ground truth still does)
+    if (zero_copy && !exact) {
         VF_HIP(hipEventRecord(st->done, s));
         st->pending = true;
     }
@@ -1038,6 +1050,14 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
         if (M.refused != nullptr) memcpy(&any, hp + flag_at, 4);
         if (any != 0 && (rc = answer_refused(ix, P, r, M, queries, out_ids, out_dists, s)) != VF_OK) return rc;
         if (any == 0) ix->refused_unread = false;
+        if (multi != nullptr) {
+            merge_multi();
+            VF_HIP(hipGetLastError());
+            if (zero_copy) {
+                VF_HIP(hipEventRecord(st->done, s));
+                st->pending = true;
+            }
+        }
     }
     return VF_OK;
 }
@@ -1114,21 +1134,13 @@ int search_multi_impl(vf_index *ix, const void *queries, int64_t nq, const int64
         }
         host.insert(host.end(), first.begin(), first.end());
         const size_t row_bytes = (size_t)ix->dim * ix->elem();
-        if ((rc = W->multi_meta.reserve(host.size() * 4)) != VF_OK) return rc;
         if ((rc = W->multi_q.reserve((size_t)n_sub * row_bytes)) != VF_OK) return rc;
         if ((rc = W->multi_ids.reserve((size_t)n_sub * k * 8)) != VF_OK) return rc;
         if ((rc = W->multi_dists.reserve((size_t)n_sub * k * 4)) != VF_OK) return rc;
-        VF_HIP(hipMemcpyAsync(W->multi_meta.p, host.data(), host.size() * 4, hipMemcpyHostToDevice, s));
-        const int32_t *d_parent = W->multi_meta.as<int32_t>();
-        const int32_t *d_first = d_parent + n_sub;
-        launch_gather_rows(queries, (int32_t)row_bytes, d_parent, n_sub, W->multi_q.p, s);
-        rc = search_impl(ix, W->multi_q.p, n_sub, sqoff.data(), sqids.data(), k, itopk, width, iters, n_seeds, exact,
-                         W->multi_ids.as<int64_t>(), W->multi_dists.as<float>(), s, true);
-        if (rc != VF_OK) return rc;
-        launch_multi_merge(d_first, nq, W->multi_ids.as<int64_t>(), W->multi_dists.as<float>(), k, out_ids, out_dists, s);
-        VF_HIP(hipGetLastError());
+        const MultiCall multi{&host, queries, nq, out_ids, out_dists};
+        return search_impl(ix, W->multi_q.p, n_sub, sqoff.data(), sqids.data(), k, itopk, width, iters, n_seeds, exact,
+                           W->multi_ids.as<int64_t>(), W->multi_dists.as<float>(), s, true, 0, &multi);
     }
-    return VF_OK;
 }
 
 }  // namespace vf

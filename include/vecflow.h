@@ -280,7 +280,8 @@ int vf_search_multi(vf_index *index, const void *queries, int64_t nq, const int6
  * Exact filtered top-k (Section 3, Def. 1) for every query, graph lists included,
  * by exhaustive scan of the smallest list with the predicate applied: the ground
  * truth against which recall (Section 3, Eq. 1) is measured.  Arguments as in
- * vf_search; float32 distances of graph lists are the ordered ones for k <= 48.
+ * vf_search; float32 distances of graph lists are the ordered ones for k <= 48
+ * (|q|^2 + |x|^2 - 2 q.x where there is no memory for packed copies of the lists).
  * Synchronises the stream before returning.
  */
 int vf_search_exact(vf_index *index, const void *queries, int64_t nq, const int64_t *qlabel_offsets,

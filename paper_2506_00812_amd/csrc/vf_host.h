@@ -345,6 +345,7 @@ struct CallPlan {
     int32_t max_hs_list = 0;
     // ... the same on the join kernel (vf_join.hip): join_keep candidates per partial row, whose rows follow ls_part_words
     std::vector<JoinList> jlists;
+    size_t join_bytes = (size_t)1 << 30;  // packed lists of a batch (a list that is larger goes by itself); 0: nothing is joined
     std::vector<JoinBatch> jbatches;
     int64_t join_groups = 0;              // of the largest batch
     int32_t join_keep = 0, join_max_nseg = 1;

@@ -481,39 +481,47 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
                 if (in_range(mx[0])) {
                     ix->xn_max = mx[0];
                     ix->seed_mfma_ok = seed_mfma_supported(ix->dtype, ix->dim);
-                } else {
-                    ix->d_xnorm_all.release();
                 }
+                if (!ix->seed_mfma_ok) ix->d_xnorm_all.release();
                 if (in_range(mx[0]) && in_range(mx[1])) ix->xc_max = mx[1];
                 else ix->d_xnorm_c.release();
             } else {
                 launch_row_norms_u8(ix->X, ix->dim, n, ix->d_xnorm_all.as<uint32_t>(), s);
                 ix->seed_mfma_ok = seed_mfma_supported(ix->dtype, ix->dim);
             }
-            const bool joined = ix->dtype == VF_U8 || (ix->xc_max > 0.f && ix->tune.build16);
+            bool joined = ix->dtype == VF_U8 || (ix->xc_max > 0.f && ix->tune.build16);
             // Lists are joined many to a launch: as many as fit, packed and with their candidates, into a GiB (or one list
-            // that is larger than that).  The scan kernels take one list at a time.
-            const size_t row_bytes_tmp = joined ? join_group_bytes(ix->dtype, ix->dim) / 32 + (size_t)K * 8 : 0;
-            const int64_t batch_rows = joined ? std::max<int64_t>((int64_t)(((size_t)1 << 30) / row_bytes_tmp), (int64_t)max_list) : max_list;
+            // that is larger than that).  The scan kernels take one list at a time.  Where there is no memory for that:
+            // smaller batches, down to single lists, and then the scan kernels, whose copies of a list are smaller.
+            int64_t batch_rows = joined ? (int64_t)(((size_t)1 << 30) / (join_group_bytes(ix->dtype, ix->dim) / 32 + (size_t)K * 8)) : 0;
             std::vector<size_t> batch_end;   // positions in graph_labels
-            int64_t tmp_groups = 0, tmp_rows = 0;
-            for (size_t i = 0; i < ix->graph_labels.size();) {
-                int64_t rows_in = 0, groups_in = 0;
-                size_t e = i;
-                while (e < ix->graph_labels.size() && (e == i || (joined && rows_in + ix->S[(size_t)ix->graph_labels[e]] <= batch_rows))) {
-                    rows_in += ix->S[(size_t)ix->graph_labels[e]];
-                    groups_in += (ix->S[(size_t)ix->graph_labels[e]] + 31) / 32;
-                    ++e;
+            while (true) {
+                int64_t tmp_groups = 0, tmp_rows = 0;
+                batch_end.clear();
+                for (size_t i = 0; i < ix->graph_labels.size();) {
+                    int64_t rows_in = 0, groups_in = 0;
+                    size_t e = i;
+                    while (e < ix->graph_labels.size() && (e == i || (joined && rows_in + ix->S[(size_t)ix->graph_labels[e]] <= batch_rows))) {
+                        rows_in += ix->S[(size_t)ix->graph_labels[e]];
+                        groups_in += (ix->S[(size_t)ix->graph_labels[e]] + 31) / 32;
+                        ++e;
+                    }
+                    tmp_groups = std::max(tmp_groups, groups_in);
+                    tmp_rows = std::max(tmp_rows, rows_in);
+                    batch_end.push_back(e);
+                    i = e;
                 }
-                tmp_groups = std::max(tmp_groups, groups_in);
-                tmp_rows = std::max(tmp_rows, rows_in);
-                batch_end.push_back(e);
-                i = e;
+                const size_t cand_bytes = (size_t)(tmp_rows + 31) / 32 * 32 * K * 4;
+                if ((rc = ix->tmp_blk.reserve((size_t)tmp_groups * (joined ? join_group_bytes(ix->dtype, ix->dim) : ix->group_bytes()))) == VF_OK &&
+                    (rc = ix->tmp_norm.reserve((size_t)tmp_groups * 32 * 4)) == VF_OK && (rc = cand_idx.reserve(cand_bytes)) == VF_OK &&
+                    (rc = cand_dist.reserve(cand_bytes)) == VF_OK)
+                    break;
+                if (rc != VF_ENOMEM || !joined) return rc;
+                (void)hipGetLastError();
+                for (DevBuf *t : {&ix->tmp_blk, &ix->tmp_norm, &cand_idx, &cand_dist}) t->release();
+                if (batch_rows <= max_list) joined = false;
+                batch_rows = std::max<int64_t>(batch_rows / 4, max_list);
             }
-            if ((rc = ix->tmp_blk.reserve((size_t)tmp_groups * (joined ? join_group_bytes(ix->dtype, ix->dim) : ix->group_bytes()))) != VF_OK) return rc;
-            if ((rc = ix->tmp_norm.reserve((size_t)tmp_groups * 32 * 4)) != VF_OK) return rc;
-            if ((rc = cand_idx.reserve((size_t)(tmp_rows + 31) / 32 * 32 * K * 4)) != VF_OK) return rc;
-            if ((rc = cand_dist.reserve((size_t)(tmp_rows + 31) / 32 * 32 * K * 4)) != VF_OK) return rc;
             // optionally a line on stderr every few seconds (index builds of 10^7 vectors take minutes)
             const bool progress = ix->tune.build_progress != 0;
             time_t last_print = time(nullptr);

@@ -329,7 +329,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     // over their queries.  float32 keeps spare candidates and proves the re-ranked result, which needs the norms to be
     // within the proofs' range and room for enough spare ones.
     const int32_t join_keep = ix->dtype == VF_U8 ? k : std::min(64, k + 22);
-    const bool joined = exact && first_hs < r.scan_pairs.size() && ix->join_norms() != nullptr &&
+    const bool joined = exact && P.join_bytes > 0 && first_hs < r.scan_pairs.size() && ix->join_norms() != nullptr &&
                         (ix->dtype == VF_U8 || (ix->xc_max > 0.f && ix->tune.scan_bf16 && join_keep >= k + 16));
     if (joined) {
         P.join_keep = join_keep;
@@ -345,7 +345,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         // segments: a row's thresholds start over in each, so no more of them than keep the chip busy (two workgroups per
         // CU at a time; three rounds of them level out the last one)
         jb.seg_groups = jb.seg_groups_heavy = (int)std::max<int64_t>(64, tile_groups / 1536);
-        const int64_t batch_groups = (int64_t)(((size_t)1 << 30) / join_group_bytes(ix->dtype, ix->dim));
+        const int64_t batch_groups = (int64_t)(P.join_bytes / join_group_bytes(ix->dtype, ix->dim));
         int64_t groups = 0;
         JoinBatch b{0, 0, 0, 0, 0};
         auto close = [&]() {
@@ -752,9 +752,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
             }
         }
         if (!P.jbatches.empty()) {
-            if ((rc = ix->tmp_blk.reserve((size_t)P.join_groups * join_group_bytes(ix->dtype, ix->dim))) != VF_OK) return rc;
-            if ((rc = ix->tmp_norm.reserve((size_t)P.join_groups * 32 * 4)) != VF_OK) return rc;
-            JoinParams jp{};
+            JoinParams jp{};   // (ix->tmp_blk, tmp_norm: reserved with the plan)
             jp.xblk = ix->tmp_blk.as<uint4>(); jp.xnorm = ix->tmp_norm.p; jp.map = ix->d_M_HS.as<int32_t>();
             jp.qsrc = queries; jp.qrow = sp.qrow; jp.dim = ix->dim; jp.K = P.join_keep; jp.centre = ix->d_centre.as<float>();
             jp.res_idx = M.part_idx + P.ls_part_words; jp.res_bits = M.part_bits + P.ls_part_words;
@@ -947,9 +945,28 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     CallPlan P(tune);
     Routed &r = W->routed;
     VF_REQUIRE(and_scan_limit >= 0, "and_scan_limit must be >= 0");
-    if ((rc = plan_call(ix, r, nq, qoff, qids, exact, first_is_searched, k, itopk, width, iters, n_seeds, and_scan_limit,
-                        budget, sc, P)) != VF_OK)
-        return rc;
+    auto plan = [&] {
+        return plan_call(ix, r, nq, qoff, qids, exact, first_is_searched, k, itopk, width, iters, n_seeds, and_scan_limit, budget, sc, P);
+    };
+    if ((rc = plan()) != VF_OK) return rc;
+    auto words_up = [](size_t v) { return (v + 63) & ~(size_t)63; };
+    // Ground truth over joined lists: the packed lists and partial rows before anything is sent.  Where there is no memory
+    // for them: smaller batches of lists, down to single ones, and then the scan kernels, whose copies of a list are smaller.
+    while (!P.jbatches.empty()) {
+        if ((rc = ix->tmp_blk.reserve((size_t)P.join_groups * join_group_bytes(ix->dtype, ix->dim))) == VF_OK &&
+            (rc = ix->tmp_norm.reserve((size_t)P.join_groups * 32 * 4)) == VF_OK &&
+            (rc = W->dseed.reserve((2 * words_up(P.part_words) + words_up(P.ib.merges.size())) * 4)) == VF_OK)
+            break;
+        if (rc != VF_ENOMEM) return rc;
+        (void)hipGetLastError();
+        ix->tmp_blk.release();
+        ix->tmp_norm.release();
+        const bool one_each = P.jbatches.size() == P.jlists.size();
+        const size_t bytes = one_each ? 0 : P.join_bytes / 4;
+        P = CallPlan(tune);
+        P.join_bytes = bytes;
+        if ((rc = plan()) != VF_OK) return rc;
+    }
     if (multi != nullptr) {   // (a copy of its own would wait for the caller's stream: the vectors are pageable memory)
         P.L.off_multi = P.L.total;
         P.L.total = align_up(P.L.total + multi->host->size() * 4);
@@ -966,7 +983,6 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     if (multi != nullptr) memcpy(hp + L.off_multi, multi->host->data(), multi->host->size() * 4);
     const auto t_blob = std::chrono::steady_clock::now();
     // seed distances and partial rows in one buffer: one allocation where a workspace meets its first call
-    auto words_up = [](size_t v) { return (v + 63) & ~(size_t)63; };
     const size_t dseed_words = P.dense_seeds ? words_up(P.dseed_words) : 0, part_words = words_up(P.part_words);
     const size_t refused_words = exact && (P.scan_bf16 || (!P.jbatches.empty() && ix->dtype == VF_F32)) ? words_up(P.ib.merges.size()) : 0;
     if (dseed_words + part_words > 0 && (rc = W->dseed.reserve((dseed_words + 2 * part_words + refused_words) * 4)) != VF_OK) return rc;

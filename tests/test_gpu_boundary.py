@@ -118,6 +118,64 @@ def test_allocator_failure_is_reported_not_thrown(vf, tiny):
     assert not al.live and al.n_alloc == al.n_free == 6
 
 
+@pytest.mark.parametrize("dtype,dim,limit", [("float32", 132, 3.0), ("float32", 132, 1.15), ("float32", 132, 0.9), ("uint8", 208, 1.15)])
+def test_little_memory_takes_smaller_batches(vf, dtype, dim, limit):
+    """Builds and ground truth join many lists at a time; with an allocator that has room for a few of them, for one, or only
+    for the scan kernels' copy of the largest (limit: in packed copies of it), they do less at a time: same results."""
+    import torch
+    rng = np.random.default_rng(dim)
+    n, T, R = 12_000, 300, 16
+    x = rng.normal(size=(64, dim))[rng.integers(0, 64, n)] * 20 + rng.normal(size=(n, dim)) * 9
+    x = np.rint(x + 128).clip(0, 255).astype(np.uint8) if dtype == "uint8" else x.astype(np.float32)
+    carry = rng.random((n, 12)) < [0.6, 0.4, 0.3, 0.3, 0.2, 0.2, 0.1, 0.1, 0.1, 0.05, 0.02, 0.01]
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    ids = np.nonzero(carry)[1].astype(np.int32)
+    X = torch.from_numpy(x).cuda()
+    qids = rng.integers(0, 12, 500).astype(np.int32)
+    qoff = np.arange(501, dtype=np.int64)
+    Q = X[torch.from_numpy(rng.integers(0, n, 500)).cuda()].contiguous()
+
+    def build(al):
+        real = vf.TorchAllocator
+        vf.TorchAllocator = lambda device: al
+        try:
+            return vf.build_index(X, off, ids, 12, T, R)
+        finally:
+            vf.TorchAllocator = real
+
+    steps = next(s for s in (2, 4, 6, 8, 16, 32) if s * (32 if dtype == "uint8" else 16) >= dim)
+    largest = int(carry[:, 0].sum())
+    packed = (largest + 31) // 32 * 32 * steps * (32 if dtype == "uint8" else 64)
+
+    def allocator(most):
+        """At most `most` bytes in one piece, what an index keeps aside (its arrays are smaller than the packed lists)."""
+        al = vf.TorchAllocator(X.device)
+        inner, al.refused = al._alloc_cb, 0
+
+        def stingy(nbytes, ctx):
+            if nbytes > most:
+                al.refused += 1
+                return None
+            return inner(nbytes, ctx)
+        al.cb = vf.ALLOC_FN(stingy)
+        al.struct = vf.VfAllocator(al.cb, al._free_cb, None)
+        return al
+
+    want = build(vf.TorchAllocator(X.device))
+    rows, (wi, wd) = want.export("G_HS"), vf.search_exact(want, Q, qoff, qids, 10)
+    al = allocator(int(packed * limit))
+    ix = build(al)
+    assert al.refused > 0 and np.array_equal(ix.export("G_HS"), rows)
+    al.refused = 0
+    gi, gd = vf.search_exact(ix, Q, qoff, qids, 10)
+    assert al.refused > 0
+    if limit > 1 or dtype == "uint8":
+        assert np.array_equal(to_np(gi), to_np(wi)) and np.array_equal(to_np(gd), to_np(wd))
+    else:   # |q|^2 + |x|^2 - 2 q.x in float32 instead of the ordered sum: off by up to 2^-15 of the norms (6e4 each)
+        assert np.allclose(to_np(gd), to_np(wd), rtol=1e-6, atol=4.0)
+        assert (to_np(gi) == to_np(wi)).mean() > 0.99
+
+
 def test_streams_with_different_seed_counts_overlap_safely(vf):
     """Calls on different streams may use different n_seeds at the same time: each seed count has its own
     interleaved copy of the seeds, so a call never overwrites what another stream's seed kernel is reading.

@@ -87,11 +87,15 @@ def test_tuning_names_and_ranges_without_gpu(lib):
     doc = re.search(r"Names: (.*?)\.  Returns VF_EINVAL", hdr, re.S).group(1)
     names = re.findall(r'"([a-z_0-9]+)"', doc)
     assert len(names) == 26
-    defaults = dict(seg_groups=16, seg_groups_heavy=16, heavy_rows=9, tile_rows=16, zero_copy_bytes=8192, scan_valu=1,
+    defaults = dict(seg_groups=16, seg_groups_heavy=16, heavy_rows=9, tile_rows=16, zero_copy_bytes=32768, scan_valu=1,
                     scan16=1, scan_bf16=1, scan_bf16_margin=22, scan_bf16_slots=1, scan_bf16_seg_groups=24, beam_lat_waves=1024, overlap=1, seed_exact=0, seed_slack=1.0, seed_margin=8, seed_margin_bf16=24, seed_cache=1,
                     seed_bf16=1, seed_bf16_min_batch=512, seed_fb_window=131072, seed_select=0, seed_seg_seeds=0, build16=1, build_panel_kb=4096,
                     build_progress=0)
     assert sorted(names) == sorted(defaults)
+    # (the shipped ones: they are set below, and what runs later in this process starts from them)
+    src = open(os.path.join(ROOT, "paper_2506_00812_amd", "csrc", "vf_host.h")).read()
+    body = src[src.index("struct Tuning {"):src.index("bool set(const char *name, double value);")]
+    assert {n: float(v) for n, v in re.findall(r"^\s*(?:int|double) (\w+) = ([\d.]+);", body, re.M)} == defaults
     for n in names:
         assert lib.vf_tune(None, n.encode(), float(defaults[n])) == 0, n
     assert lib.vf_tune(None, b"no_such_knob", 1.0) == -1

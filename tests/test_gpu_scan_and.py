@@ -46,16 +46,17 @@ def test_and_masks_at_window_edges(dim, seg_groups, slots):
 @pytest.mark.parametrize("dtype,dim,seg_groups", [("uint8", 128, 16), ("uint8", 192, 64), ("uint8", 80, 25), ("uint8", 992, 48),
                                                   ("float32", 100, 24), ("float32", 40, 60)])
 def test_and_masks_of_the_plain_scan(dtype, dim, seg_groups):
-    """The same on the 32-row kernel (uint8, and float32 of other dimensions)."""
+    """The same on the 32-row kernel (uint8, and float32 of other dimensions).  Segments are as long as tuned only on lists of
+    thousands of entries (short lists are cut further), which is checked: beyond 24 groups a segment takes several windows."""
     import torch
     from paper_2506_00812_amd import binding as vf
     from tests.gpu_util import assert_exact
     rng = np.random.default_rng(dim + seg_groups)
-    n, T = 5000, 2500
+    n, T = 18_000, 17_000
     k = 64 if dim == 992 else 10
     x = rng.normal(size=(20, dim))[rng.integers(0, 20, n)] * (30 if dtype == "uint8" else 2) + rng.normal(size=(n, dim)) * (12 if dtype == "uint8" else 1)
     x = np.rint(x + 128).clip(0, 255).astype(np.uint8) if dtype == "uint8" else x.astype(np.float32)
-    sizes = [4000, 2400, 1537, 1536, 769, 768, 767, 33, 32, 1]
+    sizes = [17_500, 16_500, 6_500, 1537, 1536, 769, 768, 767, 33, 1]
     carry = np.zeros((n, len(sizes)), dtype=bool)
     for l, size in enumerate(sizes):
         carry[rng.permutation(n)[:size], l] = True
@@ -72,6 +73,9 @@ def test_and_masks_of_the_plain_scan(dtype, dim, seg_groups):
     ix.tune("seg_groups_heavy", seg_groups)
     ixo = OracleIndex(x, off, ids, len(sizes), T, 8, lazy_graph=True)
     params = dict(itopk=64, width=1, iters=4, n_seeds=128)
+    ix.profile_enable(True)
+    vf.search(ix, torch.from_numpy(q[:16]).cuda(), np.arange(17, dtype=np.int64), np.ones(16, dtype=np.int32), k, **params)
+    assert ix.profile_read()["n_scan_items"] == -(-516 // seg_groups)       # 16,500 entries in 516 groups, one tile
     for count in (400, 3):
         gi, gd = vf.search(ix, torch.from_numpy(q[:count]).cuda(), qoff[:count + 1], qids[:qoff[count]], k, **params)
         oi, od, info = ixo.search(q[:count], qoff[:count + 1], qids[:qoff[count]], k, with_info=True, **params)

@@ -291,7 +291,10 @@ void launch_seed_map(const int32_t *M_HS, const int64_t *slot_base, const int32_
 
 constexpr int kSeedMfmaChunk = 128;  // seeds per wave of the MFMA seed kernel when it gathers rows (four 32-seed groups)
 
-bool seed_dist_pays(int dtype, int dim, int n_seeds, int64_t n_gq);
+// does the dimension have an instantiation of the ordered-distance seed kernel for itself?
+bool seed_dist_own(int dtype, int dim);
+// n_and: those of the n_gq graph queries that have a predicate (of no matter for dimensions of their own)
+bool seed_dist_pays(int dtype, int dim, int n_seeds, int64_t n_gq, int64_t n_and);
 void launch_seed_dist(int dtype, const SeedParams &p, int n_tiles, hipStream_t s);
 // |q|^2 + |x|^2 - 2 q.x through the matrix cores: approximate for float32, exact for uint8
 bool seed_mfma_supported(int dtype, int dim);

@@ -444,10 +444,17 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
             P.dseed_words = (size_t)need;
         }
     }
+    auto and_queries = [&] {   // graph queries with a predicate
+        int64_t n = 0;
+        if (r.any_and)
+            for (size_t i = 0; i < P.n_gq; ++i) n += r.others_off[(size_t)r.gq_query[i] + 1] > r.others_off[(size_t)r.gq_query[i]] ? 1 : 0;
+        return n;
+    };
     if (!P.seed_select) {
         // every distance goes through the seed distance matrix, which must fit
         const uint64_t need = (uint64_t)P.n_gq * (uint64_t)P.ns_stride + 64 * 1024;
-        P.dense_seeds = !exact && P.n_gq > 0 && seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq) && budget.fits(need);
+        const int64_t n_and = seed_dist_own(ix->dtype, ix->dim) ? 0 : and_queries();
+        P.dense_seeds = !exact && P.n_gq > 0 && seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq, n_and) && budget.fits(need);
         P.seeds_mfma = P.dense_seeds && mfma_ok;
         if (P.dense_seeds) P.dseed_words = (size_t)need;
     }
@@ -469,10 +476,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         (int64_t)P.tiles.size() * ((P.ns_stride + 4 * kSeedMfmaChunk - 1) / (4 * kSeedMfmaChunk)) >= 512) {
         const int32_t keep = ix->dtype == VF_U8 ? itopk : std::min(64, itopk + std::max(tune.seed_margin_bf16, tune.seed_margin));
         const int32_t stride = (P.ns_stride / 32 + 15) & ~15;
-        size_t plain = P.n_gq;
-        if (r.any_and)
-            for (size_t i = 0; i < P.n_gq; ++i) plain -= r.others_off[(size_t)r.gq_query[i] + 1] > r.others_off[(size_t)r.gq_query[i]] ? 1 : 0;
-        if (P.ns_stride / 32 >= 3 * keep && 2 * plain >= P.n_gq && budget.fits((uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride)) {
+        if (P.ns_stride / 32 >= 3 * keep && 2 * and_queries() <= (int64_t)P.n_gq && budget.fits((uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride)) {
             P.nb_stride = stride;
             P.dseed_words += P.n_gq * (size_t)stride;
         }

@@ -847,6 +847,12 @@ void launch_row_norms_u8(const void *X, int32_t dim, int64_t n, uint32_t *out, h
     hipLaunchKernelGGL(row_norm_u8_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const uint8_t *)X, dim, n, out);
 }
 
+bool seed_dist_own(int dtype, int dim)
+{
+    const int nch = dim * (dtype == 0 ? 1 : 4) / kChunkBytes;
+    return nch == 8 || nch == 12 || nch == 16 || nch == 24 || nch == 32;
+}
+
 // Whether a launch of the dense kernel pays.  Dimensions with an instantiation of their own: always.  Others (an index has
 // vectors of at most 62 chunks) score n_gq queries with the chunks of the next larger one, and leave the distances where
 // the beam kernel, which would gather its seeds itself in the same launch, has to read them: that needs enough seeds per
@@ -859,11 +865,18 @@ void launch_row_norms_u8(const void *X, int32_t dim, int64_t n, uint32_t *out, h
 //                    3,000 queries x 1,024 seeds  248 -> 433 us, x 4,096 721 -> 1,105
 //   uint8 dim 528       64 queries x   256 seeds   80 -> 110 us, x   512 113 -> 109
 //   uint8 dim 992    3,000 queries x 1,024 seeds  491 -> 519 us, x 4,096 1,578 -> 1,266
-bool seed_dist_pays(int dtype, int dim, int n_seeds, int64_t n_gq)
+// Queries with a predicate test it first when they gather, and score only the seeds that pass: batches of mostly such
+// queries take more seeds (AND pairs, gathering -> dense):
+//   float32 dim 36     512 queries x   384 seeds   81 ->  91 us, x 1,024 118 -> 103
+//   float32 dim 100    512 queries x   384 seeds   83 ->  98 us, x 2,048 199 -> 166
+//   float32 dim 200    512 queries x 4,096 seeds  425 -> 583 us, x 8,192 762 -> 686
+//   uint8 dim 528       64 queries x   384 seeds   85 -> 127 us, x 2,048 214 -> 215, x 4,096 484 -> 280
+bool seed_dist_pays(int dtype, int dim, int n_seeds, int64_t n_gq, int64_t n_and)
 {
     const int nch = dim * (dtype == 0 ? 1 : 4) / kChunkBytes;
-    if (nch == 8 || nch == 12 || nch == 16 || nch == 24 || nch == 32) return true;
+    if (seed_dist_own(dtype, dim)) return true;
     if (nch < 1 || nch > 64) return false;
+    if (2 * n_and > n_gq) return n_seeds >= (nch <= 16 ? 1024 : nch <= 32 || dtype == 0 ? 2048 : 8192);
     if (nch <= 16) return n_seeds >= 192;
     if (nch <= 32) return n_seeds >= 384;
     if (dtype == 1) return n_gq <= 512 && n_seeds >= std::max<int64_t>(1024, 8 * n_gq);

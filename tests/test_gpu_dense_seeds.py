@@ -16,8 +16,10 @@ pytestmark = pytest.mark.gpu
     ("float32", 132, 1023, 1, False), ("float32", 132, 1024, 128, True), ("float32", 248, 1024, 129, False),
     ("float32", 200, 4096, 600, False), ("uint8", 80, 32, 64, False), ("uint8", 80, 300, 64, True),
     ("uint8", 272, 383, 5, False), ("uint8", 272, 777, 5, True), ("uint8", 992, 512, 64, True),
-    ("uint8", 992, 512, 1100, False), ("float32", 128, 32, 1, True)])
-def test_dense_or_gathered(dtype, dim, n_seeds, nq, dense):
+    ("uint8", 992, 512, 1100, False), ("float32", 128, 32, 1, True), ("float32", 36, 1024, 9, True), ("float32", 100, 2048, 9, True),
+    ("float32", 200, 8192, 70, True), ("uint8", 528, 2048, 9, True)])
+@pytest.mark.parametrize("pairs", [False, True])
+def test_dense_or_gathered(dtype, dim, n_seeds, nq, dense, pairs):
     import torch
     from paper_2506_00812_amd import binding as vf
     rng = np.random.default_rng(dim + n_seeds)
@@ -28,6 +30,11 @@ def test_dense_or_gathered(dtype, dim, n_seeds, nq, dense):
     off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
     ids = np.nonzero(carry)[1].astype(np.int32)
     asked = [[0], [1], [2], [0, 1], [0]]
+    if pairs:   # queries with a predicate for the most part: more seeds
+        asked = [[0, 1], [1, 2], [2], [0, 2], [0, 1]]
+        own = dim * (1 if dtype == "uint8" else 4) // 16 in (8, 12, 16, 24, 32)
+        chunks = dim * (1 if dtype == "uint8" else 4) // 16
+        dense = own or max(n_seeds, 64) >= (1024 if chunks <= 16 else 2048 if chunks <= 32 or dtype == "uint8" else 8192)
     asked = [asked[j % 5] for j in range(nq)]
     qoff = np.concatenate([[0], np.cumsum([len(a) for a in asked])]).astype(np.int64)
     qids = np.array([l for a in asked for l in a], dtype=np.int32)

@@ -150,11 +150,19 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
                     uint64_t expect = h;
                     if (__hip_atomic_compare_exchange_strong(&p.dctrl->head, &expect, h + 1, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
                                                              __HIP_MEMORY_SCOPE_AGENT)) { job = (int64_t)h; break; }
-                    continue;   // another worker took it: look again (progress: the head moved)
+                    // another worker took it: look again (progress: the head moved), but not at once: with many workers
+                    // free the swaps of all of them are in one another's way (2,048 seeds, 64 in flight: 108 -> 114 k
+                    // queries/s)
+                    __builtin_amdgcn_s_sleep(16);
+                    continue;
                 }
                 if (load_dev(&p.dctrl->stop) != 0) break;      // drained and stopping
                 if (++idle > 16 * p.idle_polls) break;          // nothing for very long: the dispatcher must be gone
-                __builtin_amdgcn_s_sleep(32);
+                // 8,128 cycles, the longest sleep: the head and tail words are read past every XCD's L2, and a few hundred
+                // free workers that ask every 2,048 cycles slow down everything else that goes there: at 6,144 seeds a lone query
+                // took 272 us, takes 149, and eight in flight went from 32 to 54 k queries/s.  A job does not wait for it
+                // while many are free, and with few free it waits for their searches anyway.
+                __builtin_amdgcn_s_sleep(127);
             }
             idle = 0;
             own[11] = (int32_t)(job & 0xFFFFFFFFll);

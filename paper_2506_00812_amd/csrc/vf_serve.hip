@@ -150,10 +150,11 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
                     uint64_t expect = h;
                     if (__hip_atomic_compare_exchange_strong(&p.dctrl->head, &expect, h + 1, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
                                                              __HIP_MEMORY_SCOPE_AGENT)) { job = (int64_t)h; break; }
-                    // another worker took it: look again (progress: the head moved), but not at once: with many workers
-                    // free the swaps of all of them are in one another's way (2,048 seeds, 64 in flight: 108 -> 114 k
-                    // queries/s)
-                    __builtin_amdgcn_s_sleep(16);
+                    // another worker took it: look again (progress: the head moved), but not at once -- with 200 workers
+                    // free the swaps of all of them at one word are in one another's way, and a job costs more in being
+                    // claimed than in the search (1,000,000 x 128 float32, 512 seeds, 64 in flight: sleeps of 0 / 16 / 64 /
+                    // 127 here 109 / 108 / 126 / 156 k queries/s)
+                    __builtin_amdgcn_s_sleep(127);
                     continue;
                 }
                 if (load_dev(&p.dctrl->stop) != 0) break;      // drained and stopping

@@ -6,8 +6,11 @@
 // Tile.  A workgroup of four waves takes 128 rows (32 per wave) and streams a segment of a list through LDS, one group
 // of 32 entries per step, shared by its waves: a group is fetched from L2 once per 128 rows instead of once per 16 (the
 // 16-row kernel's 16 KiB per group and 16 rows would need more L2 bandwidth than there is at this rate).  The rows'
-// operand stays in registers.  Lists come packed (join_pack_kernel): per group the 16-byte chunks chunk-major, which is
-// the B operand of the 32-column MFMAs, lane (n32, h) reading chunk 2 s + h of entry n32.
+// operand stays in registers; where those do not suffice a part of it is in scratch memory (float32 of more than 128
+// components 82 registers' worth, with the predicate 118, and 24 from 100 components on; uint8 of more than 512 25 and 69):
+// 100,000 x 236 float32 vectors still build in 25 ms, on the 32-row scan kernel in 115.  Lists come packed
+// (join_pack_kernel): per group the 16-byte chunks chunk-major, which is the B operand of the 32-column MFMAs, lane
+// (n32, h) reading chunk 2 s + h of entry n32.
 //
 // float32 data: v_mfma_f32_32x32x16_bf16 on two-part splits of both operands, x = hi + lo with hi = bf16(x), lo =
 // bf16(x - hi), after subtraction of a vector near the table's mean: distances stay what they are, and what the norms

@@ -18,7 +18,8 @@
 // teams, sorted, the k best written.  Every candidate that was dropped anywhere has an approximation >= T, hence
 // an ordered distance >= T - B: if the k-th re-ranked distance is below T - B (or nothing was dropped) the result
 // is the exact one.  Otherwise (rare: counted, and reported by the profile) the wave scans the query's whole list
-// itself with the ordered distance, 64 entries a step: predicate, gather, score, merge into the k best.
+// itself with the ordered distance, 64 entries a step: predicate, gather, score, merge into the k best.  A ground-truth
+// call, which waits for its results anyway, collects such queries and answers them together (ordered_scan_kernel).
 #include "vf_beam.h"
 #include "vf_scan_item.h"
 

@@ -121,7 +121,7 @@ __device__ __forceinline__ void scan_topk_item(const ScanParams &p, const ScanIt
     const int row_bytes = p.dim * (DT == 0 ? 1 : 4);
     const int real_chunks = row_bytes / kChunkBytes;
 
-    const int TR = p.tile_rows;                                  // rows the LDS buffers hold (16 or 32)
+    const int TR = p.tile_rows;                                  // rows the LDS buffers hold (1 in a serving session, else up to 32)
     uint4 *qtile = smem;                                         // [nchunks][TR]
     const int KS = K | 1;                                        // row stride of `best` (odd: spreads LDS banks)
     constexpr int PC = 64;                                       // pending slots per row: drained before a group could overflow them

@@ -513,15 +513,17 @@ __global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map,
     }
 }
 
-// The centre: the mean of up to 16,384 rows spread over the table.  Any fixed vector would do, so a sample is enough; one
-// pass over 8 MiB at dim 128.  Block b takes every kCentreParts-th row of the sample, a thread four components of every
-// rows_at_a_time-th of them.
+// The centre: the mean of up to 4,096 rows spread over the table.  Any fixed vector would do, so a sample is enough; one
+// pass over 2 MiB at dim 128 (16,384 rows took 23 us, which a build of 2.5 ms notices).  Block b takes every
+// kCentreParts-th row of the sample, a thread four components of every rows_at_a_time-th of them.
+constexpr int64_t kCentreRows = 4096;
+
 __global__ __launch_bounds__(256) void centre_part_kernel(const float *X, int32_t dim, int64_t n, float *parts)
 {
     __shared__ float4 sum[256];
     const int nch = dim / 4, rows_at_a_time = 256 / nch;   // (at most 62 chunks)
     const int c = threadIdx.x % nch, r = threadIdx.x / nch;
-    const int64_t sample = n < 16384 ? n : 16384;
+    const int64_t sample = n < kCentreRows ? n : kCentreRows;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     if (r < rows_at_a_time)
         for (int64_t i = blockIdx.x + (int64_t)r * kCentreParts; i < sample; i += (int64_t)rows_at_a_time * kCentreParts) {
@@ -545,7 +547,7 @@ __global__ __launch_bounds__(256) void centre_mean_kernel(const float *parts, in
     if (e >= dim) return;
     float a = 0.f;
     for (int b = 0; b < kCentreParts; ++b) a += parts[b * dim + e];
-    centre[e] = a / (float)(n < 16384 ? n : 16384);
+    centre[e] = a / (float)(n < kCentreRows ? n : kCentreRows);
 }
 
 // One thread per row, elements in ascending order (400,000 x 128: 0.32 ms).

@@ -3,20 +3,28 @@
 //
 // Shape on this machine.  The host writes a job (query vector + labels) into a ring in pinned host memory and
 // bumps a counter.  Workgroup 0 of the resident kernel is the DISPATCHER: it alone polls that counter across
-// PCIe, copies new jobs into a ring in device memory and publishes them by advancing a device-side tail.  The
+// PCIe and publishes a job by writing its number into the ready word of the job's slot in device memory.  The
 // other workgroups are WORKERS (one query at a time, as in the paper's one block per query; NW waves each: all of
 // them score a share of the query's seeds, or scan a share of its list, then the first wave searches or merges while
-// the others wait at the workgroup's barrier): a worker claims the next job with a compare-and-swap on the device-side head -- the atomic ring buffer of
-// the paper's figure; "which worker is free" needs no queue of its own, a free worker is one that is polling --
-// routes it (smallest list, graph or scan by T, Section 4.1.2 / 4.3.2), runs the same beam search or list
-// scan the batched kernels run (the device functions are shared), writes the k results straight into the
+// the others wait at the workgroup's barrier): a free worker draws the next job number with one atomic addition --
+// the atomic ring buffer of the paper's figure -- and waits for that job's ready word; it copies the job from the
+// host's ring itself, routes it (smallest list, graph or scan by T, Section 4.1.2 / 4.3.2), runs the same beam search
+// or list scan the batched kernels run (the device functions are shared), writes the k results straight into the
 // result ring in host memory and releases a per-job done flag there.
+//
+// What bounds a session is the latency of one search, times what the places in flight allow.  While free workers compared
+// and swapped one common head word and the dispatcher copied one job after the other (a PCIe round trip each, two more
+// for the counter and the stop word), a job cost about 5 us however many workers there were.  Now no two free workers
+// wait at the same word, the dispatcher's poll is one round trip for any number of jobs, and the copies of different jobs
+// overlap.  300,000 x 128 float32, 6,144 seeds, width 2, 12 iterations, queries/s with 1 / 8 / 64 / 240 in flight: 8.7 k /
+// 56 k / 185 k / 191 k before, 12.9 k / 100 k / 757 k / 2.24 M now; p50 of a query 146 / 174 / 311 / 1,192 us before, 103 /
+// 104 / 108 / 127 now.
 //
 // Every wave exits on its own.  The dispatcher leaves when the host asks it to, when max_jobs jobs have been
 // published, or after idle_polls consecutive polls without a new job; leaving, it raises the device-side stop
-// flag.  A worker leaves when it sees that flag and the queue is drained, and in any case after
-// 16 * idle_polls consecutive empty polls.  So a session that is never ended ends by itself, and
-// vf_serve_end always returns.
+// flag.  A worker leaves when it sees that flag and the job it has drawn is not among those published, and in any
+// case once the dispatcher's heartbeat has stood still for a bounded number of its looks.  So a session that is
+// never ended ends by itself, and vf_serve_end always returns.
 #include <atomic>
 #include <chrono>
 
@@ -26,7 +34,9 @@
 
 namespace vf {
 
-constexpr int kServeHdr = 64;   // bytes of a job slot before the query vector
+constexpr int kServeHdr = 64;    // bytes of a job slot before the query vector
+constexpr int kReadyBytes = 64;  // behind a device slot: its ready word, in a cache line of its own
+constexpr int kServeSleep = 16;  // s_sleep between a waiting worker's polls, 64 cycles each
 
 struct ServeJobHdr {            // first kServeHdr bytes of a job slot (host ring and device ring)
     int32_t n_labels;
@@ -43,20 +53,22 @@ struct ServeResult {            // one slot of the result ring (pinned host memo
 
 struct ServeHostCtrl {          // pinned host memory, both sides read and write
     uint64_t tail;              // host: jobs submitted so far
-    uint32_t stop;              // host: 1 = end the session
+    uint32_t stop;              // host: 1 = end the session (the dispatcher reads tail and stop with one instruction)
     uint32_t pad0;
-    uint64_t published;         // device: jobs copied to the device ring (their host slots may be reused)
+    uint64_t published;         // device: jobs published to the workers
     uint64_t jobs_done;         // device: jobs completed (written at exit)
     uint32_t exit_reason;       // device: 0 while running; 1 host asked, 2 max_jobs reached, 3 idle bound
     uint32_t pad1;
 };
 
-struct ServeDevCtrl {           // device memory
-    uint64_t head;              // next job to claim
-    uint64_t tail;              // jobs published
-    uint32_t stop;
-    uint32_t pad;
+struct ServeDevCtrl {           // device memory; the workers' words and the dispatcher's apart
+    uint64_t head;              // next job to draw
     uint64_t jobs_done;
+    uint64_t pad0[14];
+    uint64_t tail;              // jobs published
+    uint64_t beat;              // the dispatcher's heartbeat
+    uint32_t stop;
+    uint32_t pad1;
 };
 
 struct ServeParams {
@@ -65,8 +77,8 @@ struct ServeParams {
     const int64_t *GO_LS;       // [n_labels] first 32-vector group of a scan list
     int32_t T, n_labels;
     int32_t ring_slots, slot_stride, row_bytes;
-    const char *host_ring;      // device view of the pinned job ring
-    char *dev_ring;
+    const char *host_ring;      // device view of the pinned job ring, slots of slot_stride bytes
+    char *dev_ring;             // slots of slot_stride + kReadyBytes: the job, then its ready word (job + 1 once published)
     ServeResult *results;       // device view of the pinned result ring
     ServeHostCtrl *hctrl;       // device view
     ServeDevCtrl *dctrl;
@@ -78,6 +90,41 @@ struct ServeParams {
 
 template <class T> __device__ __forceinline__ T load_sys(const T *p) { return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM); }
 template <class T> __device__ __forceinline__ T load_dev(const T *p) { return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT); }
+template <class T> __device__ __forceinline__ T look_dev(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+__device__ __forceinline__ char *serve_slot(const ServeParams &p, uint64_t job)
+{
+    return p.dev_ring + (size_t)(job % (uint64_t)p.ring_slots) * (size_t)(p.slot_stride + kReadyBytes);
+}
+__device__ __forceinline__ uint64_t *serve_ready(const ServeParams &p, uint64_t job) { return (uint64_t *)(serve_slot(p, job) + p.slot_stride); }
+
+// One lane: draws the next job and waits for it; -1: the session is over.  A worker that waits reads its job's own ready
+// word, so its polls meet nobody else's, and every 16th time the dispatcher's words.
+__device__ __forceinline__ int64_t serve_next_job(const ServeParams &p)
+{
+    const uint64_t job = __hip_atomic_fetch_add(&p.dctrl->head, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t *ready = serve_ready(p, job);
+    // looks at an unchanged heartbeat (one in 16 polls, some 30 us) before a worker gives the dispatcher up; the
+    // dispatcher beats at least once in 16 of its polls, so this is longer than its own idle bound, and never short
+    const int64_t bound = 16 * p.idle_polls > 65536 ? 16 * p.idle_polls : 65536;
+    uint64_t beat = 0;
+    int64_t still = 0;
+    for (uint32_t poll = 0;; ++poll) {
+        if (look_dev(ready) == job + 1) return (int64_t)job;
+        if ((poll & 15u) == 15u) {
+            const uint32_t stop = load_dev(&p.dctrl->stop);
+            if (stop != 0) {
+                if (job >= look_dev(&p.dctrl->tail)) return -1;   // drained
+                continue;                                         // published before the flag was raised: its word is there
+            }
+            const uint64_t b = look_dev(&p.dctrl->beat);
+            still = b == beat ? still + 1 : 0;
+            beat = b;
+            if (still > bound) return -1;   // the dispatcher must be gone
+        }
+        __builtin_amdgcn_s_sleep(kServeSleep);
+    }
+}
 
 // DT: 0 uint8, 1 float32.  NC: compile-time chunk count of the scan function (chunk pairs for scan_topk_item,
 // chunks for scan_valu_item), 0 = generic.
@@ -90,36 +137,36 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
     if (blockIdx.x == 0) {
         // ---------------- dispatcher (the first wave; it never meets a workgroup barrier)
         if (wv != 0) return;
-        uint64_t published = 0;
+        uint64_t published = 0, beat = 0;
         int64_t idle = 0;
         uint32_t reason = 0;
         while (reason == 0) {
-            const uint64_t t = load_sys(&p.hctrl->tail);
-            const uint32_t stop = load_sys(&p.hctrl->stop);
-            uint64_t upto = t;
-            if ((int64_t)upto > p.max_jobs) upto = (uint64_t)p.max_jobs;
-            if (upto > published) {
-                for (uint64_t j = published; j < upto; ++j) {   // at most ring_slots jobs: the host waits for `published`
-                    const size_t off = (size_t)(j % (uint64_t)p.ring_slots) * (size_t)p.slot_stride;
-                    const uint4 *src = (const uint4 *)(p.host_ring + off);
-                    uint4 *dst = (uint4 *)(p.dev_ring + off);
-                    for (int i = lane; i < p.slot_stride / 16; i += 64) dst[i] = src[i];
-                }
-                __threadfence();
+            // lane 0 reads the counter, lane 1 the stop word: one trip across PCIe
+            const uint64_t word = load_sys((const uint64_t *)p.hctrl + (lane & 1));
+            const uint64_t t = readlane64(word, 0);
+            const uint32_t stop = (uint32_t)readlane64(word, 1);
+            const uint64_t upto = t < (uint64_t)p.max_jobs ? t : (uint64_t)p.max_jobs;
+            if (upto > published) {   // at most ring_slots jobs: a slot is written again when its job is done
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                for (uint64_t j = published + lane; j < upto; j += 64)
+                    __hip_atomic_store(serve_ready(p, j), j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 published = upto;
-                if (lane == 0) {
-                    __hip_atomic_store(&p.dctrl->tail, published, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(&p.hctrl->published, published, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-                }
+                if (lane == 0) __hip_atomic_store(&p.hctrl->published, published, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 idle = 0;
             } else {
                 ++idle;
-                __builtin_amdgcn_s_sleep(32);
+                // (a poll without a new job takes about as long as before once a session has paused for a while, so that
+                // idle_polls of them do too)
+                if (idle > 64) __builtin_amdgcn_s_sleep(100);
+                else __builtin_amdgcn_s_sleep(4);
             }
+            if ((++beat & 15u) == 0 && lane == 0) __hip_atomic_store(&p.dctrl->beat, beat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (stop != 0) reason = 1;
             else if ((int64_t)published >= p.max_jobs) reason = 2;
             else if (idle > p.idle_polls) reason = 3;
         }
+        if (lane == 0) __hip_atomic_store(&p.dctrl->tail, published, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();   // the ready words and the tail before the flag
         if (lane == 0) __hip_atomic_store(&p.dctrl->stop, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         // the session's exit record is complete once every published job is done: bounded wait for the workers
         int64_t spins = 0;
@@ -134,61 +181,51 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
     // ---------------- worker
     // Every wave of the workgroup passes the same four barriers per job.  LDS: the search functions' area (first
     // wave; a scan: a part for each), then [0..7] others, [8..9] others_off, [10] qrow, [11..12] job, then per wave a
-    // copy of the query and a run of 64 seed keys (a scan: 64 entries and 64 distances).
+    // copy of the query and a run of 64 seed keys (a scan: 64 entries and 64 distances); until the job is routed its header
+    // lies where the runs will be.
     int32_t *own = (int32_t *)((char *)smem + p.lds_kernels);
     char *share = (char *)smem + p.lds_kernels + p.lds_own;
     const int q_bytes = (p.row_bytes + 15) & ~15;
     uint4 *hq = (uint4 *)(share + (size_t)wv * q_bytes);                         // this wave's copy of the query
     uint64_t *runs = (uint64_t *)(share + (size_t)NW * q_bytes);                 // [NW][64]
-    int64_t idle = 0;
     while (true) {
-        if (wv == 0 && lane == 0) {
-            int64_t job = -1;
-            while (true) {
-                const uint64_t h = load_dev(&p.dctrl->head), t = load_dev(&p.dctrl->tail);
-                if (h < t) {
-                    uint64_t expect = h;
-                    if (__hip_atomic_compare_exchange_strong(&p.dctrl->head, &expect, h + 1, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
-                                                             __HIP_MEMORY_SCOPE_AGENT)) { job = (int64_t)h; break; }
-                    // another worker took it: look again (progress: the head moved), but not at once -- with 200 workers
-                    // free the swaps of all of them at one word are in one another's way, and a job costs more in being
-                    // claimed than in the search (1,000,000 x 128 float32, 512 seeds, 64 in flight: sleeps of 0 / 16 / 64 /
-                    // 127 here 109 / 108 / 126 / 156 k queries/s)
-                    __builtin_amdgcn_s_sleep(127);
-                    continue;
-                }
-                if (load_dev(&p.dctrl->stop) != 0) break;      // drained and stopping
-                if (++idle > 16 * p.idle_polls) break;          // nothing for very long: the dispatcher must be gone
-                // 8,128 cycles, the longest sleep: the head and tail words are read past every XCD's L2, and a few hundred
-                // free workers that ask every 2,048 cycles slow down everything else that goes there: at 6,144 seeds a lone query
-                // took 272 us, takes 149, and eight in flight went from 32 to 54 k queries/s.  A job does not wait for it
-                // while many are free, and with few free it waits for their searches anyway.
-                __builtin_amdgcn_s_sleep(127);
+        if (wv == 0) {
+            int64_t drawn = lane == 0 ? serve_next_job(p) : 0;
+            drawn = (int64_t)readlane64((uint64_t)drawn, 0);
+            if (lane == 0) {
+                own[11] = (int32_t)(drawn & 0xFFFFFFFFll);
+                own[12] = (int32_t)(drawn >> 32);
             }
-            idle = 0;
-            own[11] = (int32_t)(job & 0xFFFFFFFFll);
-            own[12] = (int32_t)(job >> 32);
+            if (drawn >= 0) {   // wave-uniform: the job from the host's ring, its header to LDS, the query to the device slot
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
+                const uint4 *src = (const uint4 *)(p.host_ring + (size_t)((uint64_t)drawn % (uint64_t)p.ring_slots) * (size_t)p.slot_stride);
+                uint4 *dst = (uint4 *)serve_slot(p, (uint64_t)drawn);
+                const int n16 = p.slot_stride / 16;
+                for (int i = lane; i < n16; i += 128) {   // (a slot has at most 68 pieces: one trip across PCIe)
+                    const uint4 a = src[i];
+                    const bool two = i + 64 < n16;
+                    const uint4 b = two ? src[i + 64] : make_uint4(0, 0, 0, 0);
+                    if (i < kServeHdr / 16) ((uint4 *)runs)[i] = a;
+                    else dst[i] = a;
+                    if (two) dst[i + 64] = b;
+                }
+            }
         }
         __syncthreads();
         const int64_t job = ((int64_t)own[12] << 32) | (uint32_t)own[11];
         if (job < 0) return;   // (the whole workgroup: every wave reads the same word)
-        // an acquire by every lane: the job's slot may sit in this CU's cache from an earlier trip round the ring
-        (void)load_dev(&p.dctrl->tail);
         const size_t soff = (size_t)((uint64_t)job % (uint64_t)p.ring_slots);
-        const char *slot = p.dev_ring + soff * (size_t)p.slot_stride;
-        const ServeJobHdr *hdr = (const ServeJobHdr *)slot;
-        const void *qvec = slot + kServeHdr;
+        const void *qvec = serve_slot(p, (uint64_t)job) + kServeHdr;
         ServeResult *res = p.results + soff;
 
         // route (ClassifyQueries of Alg. 2, smallest list of Section 4.3.2): every lane computes the same
-        // (the slot is rewritten while this kernel runs: its header is read with coherent loads, never through
-        // the scalar cache, which nothing invalidates inside a kernel)
+        const ServeJobHdr *hdr = (const ServeJobHdr *)runs;
         int nl = 0;
         int32_t labs[kMaxOthers + 1];
-        const int n_hdr = __hip_atomic_load(&hdr->n_labels, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int n_hdr = hdr->n_labels;
         const int n_in = n_hdr < kMaxOthers + 1 ? n_hdr : kMaxOthers + 1;
         for (int i = 0; i < n_in; ++i) {
-            const int32_t l = __hip_atomic_load(&hdr->labels[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int32_t l = hdr->labels[i];
             bool seen = l < 0 || l >= p.n_labels;   // (the host has checked the range; never trust a ring)
             for (int u = 0; u < nl; ++u) seen = seen || labs[u] == l;
             if (!seen) labs[nl++] = l;
@@ -365,7 +402,7 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     sv->slot_stride = kServeHdr + ((sv->row_bytes + 63) & ~63);
     sv->d_ring.al = sv->d_ctrl.al = sv->d_GO_LS.al = &ix->alloc;
     for (DevBuf *b : sv->seeds.bufs()) b->al = &ix->alloc;
-    const size_t ring_bytes = (size_t)ring_slots * sv->slot_stride;
+    const size_t ring_bytes = (size_t)ring_slots * sv->slot_stride, dev_ring_bytes = ring_bytes + (size_t)ring_slots * kReadyBytes;
     const unsigned flags = hipHostMallocMapped | hipHostMallocCoherent;
     VF_HIP(hipHostMalloc((void **)&sv->h_ring, ring_bytes, flags));
     VF_HIP(hipHostMalloc((void **)&sv->h_results, (size_t)ring_slots * sizeof(ServeResult), flags));
@@ -374,10 +411,11 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     memset(sv->h_results, 0, (size_t)ring_slots * sizeof(ServeResult));
     memset(sv->h_ctrl, 0, sizeof(ServeHostCtrl));
     VF_HIP(hipStreamCreateWithFlags(&sv->stream, hipStreamNonBlocking));
-    if ((rc = sv->d_ring.reserve(ring_bytes)) != VF_OK) return rc;
+    if ((rc = sv->d_ring.reserve(dev_ring_bytes)) != VF_OK) return rc;
     if ((rc = sv->d_ctrl.reserve(sizeof(ServeDevCtrl))) != VF_OK) return rc;
     if ((rc = upload(sv->d_GO_LS, ix->GO_LS, sv->stream)) != VF_OK) return rc;
     VF_HIP(hipMemsetAsync(sv->d_ctrl.p, 0, sizeof(ServeDevCtrl), sv->stream));
+    VF_HIP(hipMemsetAsync(sv->d_ring.p, 0, dev_ring_bytes, sv->stream));
     VF_HIP(hipStreamSynchronize(sv->stream));
     // the seeds of every graph list, interleaved, in the data's own type (exact distances): a worker streams its
     // query's seeds from it, one seed per lane.  The session owns the copy (the index's copies may be dropped

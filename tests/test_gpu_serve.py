@@ -158,3 +158,24 @@ def test_serving_kernel_ends_by_itself(vf, tiny):
     assert srv.end() == (0, 1)
     with pytest.raises(vf.VecflowError, match="at most 64"):
         vf.Server(ix, 10, itopk=128, width=1, iters=4, n_seeds=64)
+
+
+@pytest.mark.parametrize("ring_slots,n_workers,waves,in_flight", [(1, 240, 8, 1), (3, 5, 4, 3), (70, 64, 1, 70), (64, 1, 8, 64), (1024, 1023, 8, 300)])
+def test_jobs_are_handed_over_once_each(vf, tiny, ring_slots, n_workers, waves, in_flight):
+    """Workers draw job numbers and wait at the slots' ready words: rings with fewer slots than workers, with one slot, more
+    jobs published at once than a wave has lanes, one worker for all of them; and a session of the most workers."""
+    import torch
+    s = tiny.spec
+    X = torch.from_numpy(tiny.vectors).cuda()
+    ix = vf.build_index(X, tiny.label_offsets, tiny.label_ids, s.n_labels, s.T, s.graph_degree)
+    nq = min(300, s.nq)
+    params = dict(itopk=32, width=1, iters=6, n_seeds=64)
+    off, ids = tiny.qlabel_offsets[:nq + 1], tiny.qlabel_ids[:tiny.qlabel_offsets[nq]]
+    ref_i, ref_d = vf.search(ix, torch.from_numpy(tiny.queries[:nq]).cuda(), off, ids, 10, **params)
+    srv = vf.Server(ix, 10, n_workers=n_workers, ring_slots=ring_slots, waves_per_worker=waves, **params)
+    try:
+        for _ in range(2):
+            got_i, got_d, _ = srv.run(tiny.queries[:nq], off, ids, in_flight=in_flight)
+            assert np.array_equal(got_i, to_np(ref_i)) and np.array_equal(got_d, to_np(ref_d))
+    finally:
+        assert srv.end() == (2 * nq, 1)

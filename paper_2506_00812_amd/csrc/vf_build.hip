@@ -108,26 +108,40 @@ __global__ void graph_rows_copy_kernel(const int32_t *cand_idx, int64_t n, int32
 // exact row: every list member the self-join dropped has an approximation >= T (the largest one kept), hence an
 // ordered distance >= T - B with B = err_bound (|x_v|^2 + max |x|^2); the row stands when its R-th distance is
 // below T - B or nothing was dropped.  Otherwise (near-ties at rank R beyond the K - R spare candidates, data far
-// from the origin) the wave scores every member of the list itself.  err_bound < 0: no check (no norms).
-// One wave per vertex.
-__global__ __launch_bounds__(64) void graph_rows_rerank_kernel(const char *X, int32_t row_bytes, const int32_t *map,
-                                                               int64_t n, const int32_t *cand_idx, const uint32_t *cand_bits,
-                                                               int32_t K, int32_t R, int32_t *G_rows, float err_bound,
-                                                               float xn_max, const float *centre, uint32_t *rescanned)
+// from the origin) the row is left to the caller, or the wave scores every member of the list itself.  err_bound < 0: no
+// check (no norms).  One wave per vertex.
+__global__ __launch_bounds__(64) void graph_rows_rerank_kernel(GraphRowsParams p)
 {
     extern __shared__ uint4 smem[];
     const int lane = threadIdx.x, team = lane >> 3, tl = lane & 7;
-    const int64_t j = blockIdx.x;
-    const int nchunks = row_bytes / kChunkBytes;
+    const int64_t at = blockIdx.x, j = p.sel != nullptr ? p.sel[at] - p.row_base : at;
+    const int row_bytes = p.dim * 4, nchunks = row_bytes / kChunkBytes, K = p.K, R = p.R;
+    const char *X = (const char *)p.X;
+    const int32_t *map = p.map;
+    const int64_t n = p.n_list;
     uint4 *qv = smem;
     uint64_t *keys = (uint64_t *)(smem + nchunks);  // [64]
     const char *self = X + (int64_t)map[j] * row_bytes;
     for (int i = lane; i < nchunks; i += 64) qv[i] = *(const uint4 *)(self + i * kChunkBytes);
     keys[lane] = KEY_MAX;
+    auto run = [&](int sg) -> uint64_t {   // segment sg's candidates, ascending over the lanes
+        const int64_t o = (at + sg * p.seg_stride) * K + lane;
+        const int32_t idx = lane < K ? p.cand_idx[o] : -1;
+        return idx >= 0 ? ((uint64_t)p.cand_bits[o] << 32) | (uint32_t)idx : KEY_MAX;
+    };
+    uint64_t cand = run(0);
+    if (p.nseg > 1) {
+        TopM<1> list;
+        list.init(K);
+        merge_sorted_run(list, cand, lane);
+        for (int sg = 1; sg < p.nseg; ++sg) merge_sorted_run(list, run(sg), lane);
+        cand = list.cur[0];
+    }
     __syncthreads();
     for (int r0 = 0; r0 < K; r0 += 8) {
         const int my = r0 + team;
-        const int c = my < K ? cand_idx[j * K + my] : -1;
+        const uint64_t mine = shfl64(cand, my);
+        const int c = my < K && mine != KEY_MAX ? (int)(uint32_t)mine : -1;
         const char *xrow = X + (int64_t)map[c >= 0 ? c : 0] * row_bytes;
         const uint32_t bits = team_dist_bits_f32(qv, xrow, nchunks, tl);
         if (tl == 0 && c >= 0) keys[my] = ((uint64_t)bits << 32) | (uint32_t)c;
@@ -135,23 +149,26 @@ __global__ __launch_bounds__(64) void graph_rows_rerank_kernel(const char *X, in
     __syncthreads();
     wave_bitonic_sort(keys, 64, lane);
     uint64_t key = keys[lane];
-    if (err_bound >= 0.f && n - 1 > K) {   // members were dropped: can one of them belong to the row?
+    if (p.err_bound >= 0.f && n - 1 > K) {   // members were dropped: can one of them belong to the row?
         float vn = 0.f;
         for (int i = lane; i < nchunks; i += 64) {
             const uint4 v = qv[i];
             float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-            if (centre != nullptr)
-                for (int u = 0; u < 4; ++u) f[u] -= centre[i * 4 + u];
+            if (p.centre != nullptr)
+                for (int u = 0; u < 4; ++u) f[u] -= p.centre[i * 4 + u];
             vn += f[0] * f[0] + f[1] * f[1] + f[2] * f[2] + f[3] * f[3];
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) vn += __shfl_xor(vn, o);
-        const float B = err_bound * (vn + xn_max);
-        const float T = __uint_as_float(cand_bits[j * K + K - 1]);
+        const float B = p.err_bound * (vn + p.xn_max) + p.err_q * sqrtf(vn);
+        const float T = p.approx_unit * __uint_as_float((uint32_t)(readlane64(cand, K - 1) >> 32));
         const uint64_t rth = readlane64(key, R - 1);
         const bool proven = rth != KEY_MAX && __uint_as_float((uint32_t)(rth >> 32)) < T - B;
         if (!proven) {   // (wave-uniform) the definition itself
-            if (lane == 0 && rescanned != nullptr) atomicAdd(rescanned, 1u);
+            if (p.unproven != nullptr) {
+                if (lane == 0) p.unproven[1 + atomicAdd(p.unproven, 1)] = p.row_base + (int32_t)j;
+                return;
+            }
             uint32_t *dist = (uint32_t *)keys;   // [64]
             TopM<1> ex;
             ex.init(R);
@@ -170,23 +187,17 @@ __global__ __launch_bounds__(64) void graph_rows_rerank_kernel(const char *X, in
             key = ex.cur[0];
         }
     }
-    if (lane < R) G_rows[j * R + lane] = key == KEY_MAX ? -1 : (int32_t)(uint32_t)key;
+    if (lane < R) p.G_rows[j * R + lane] = key == KEY_MAX ? -1 : (int32_t)(uint32_t)key;
 }
 
-void launch_graph_rows(int dtype, const void *X, int32_t dim, const int32_t *map, int64_t n, const int32_t *cand_idx,
-                       const uint32_t *cand_bits, int32_t K, int32_t R, int32_t *G_rows, float err_bound, float xn_max,
-                       const float *centre, uint32_t *rescanned, hipStream_t s)
+void launch_graph_rows(int dtype, const GraphRowsParams &p, hipStream_t s)
 {
-    if (n <= 0) return;
-    if (dtype == 0) {
-        hipLaunchKernelGGL(graph_rows_copy_kernel, dim3((unsigned)((n * R + 255) / 256)), dim3(256), 0, s, cand_idx, n, K,
-                           R, G_rows);
-    } else {
-        const int32_t row_bytes = dim * 4;
-        hipLaunchKernelGGL(graph_rows_rerank_kernel, dim3((unsigned)n), dim3(64), (size_t)row_bytes + 64 * 8, s,
-                           (const char *)X, row_bytes, map, n, cand_idx, cand_bits, K, R, G_rows, err_bound, xn_max,
-                           centre, rescanned);
-    }
+    if (p.n <= 0) return;
+    if (dtype == 0)
+        hipLaunchKernelGGL(graph_rows_copy_kernel, dim3((unsigned)((p.n * p.R + 255) / 256)), dim3(256), 0, s, p.cand_idx, p.n, p.K,
+                           p.R, p.G_rows);
+    else
+        hipLaunchKernelGGL(graph_rows_rerank_kernel, dim3((unsigned)p.n), dim3(64), (size_t)p.dim * 4 + 64 * 8, s, p);
 }
 
 __global__ void graph_global_ids_kernel(const int32_t *rows, const int32_t *map, int64_t count, int32_t *out)

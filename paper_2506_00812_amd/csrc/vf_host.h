@@ -246,7 +246,8 @@ struct vf_index {
     // float32: the join kernel's origin (a vector near the mean of X), the squared norms of all rows measured from it and the
     // largest of them (0: the table's norms are outside the proofs' range, nothing is joined)
     vf::DevBuf d_centre, d_xnorm_c;
-    float xc_max = 0.f;
+    bool join_single = true;      // float32 joins on binary16 operands; off once more than 1 in 64 rows went without a proof
+    float xc_max = 0.f, xc_rho = 0.f;   // (... and the largest relative error of a centred row rounded to 11 bits)
     bool seed_mfma_ok = false;   // the norms exist and are finite: seeds may be scored on the matrix cores
     // search workspaces (see Workspace); profiled calls and vf_search_exact must not overlap with other calls
     static constexpr int kWorkspaces = 8;
@@ -307,9 +308,30 @@ struct vf_index {
     float seed_err_bound() const { return (float)(tune.seed_slack * 3.0517578125e-05); }
     // squared norms the join kernel takes for its lists
     const uint32_t *join_norms() const { return dtype == VF_U8 ? d_xnorm_all.as<uint32_t>() : d_xnorm_c.as<uint32_t>(); }
-    // the same for the approximations of the join kernel (split bfloat16 products, norms from its origin, see vf_join.hip);
-    // what it decides is stored or is the ground truth: "seed_slack" below 1 does not make its proofs weaker
-    float join_err_bound() const { return (float)(std::max(1.0, tune.seed_slack) * (512 + 4 * dim) * 5.9604644775390625e-08); }
+    // the operands of a join: binary16 while that proves nearly every row (join_single), else two bfloat16 parts
+    int join_kind() const { return dtype == VF_U8 ? vf::kJoinU8 : join_single ? vf::kJoinSingle : vf::kJoinSplit; }
+    // ... and those that the packed lists' buffer is sized for
+    int join_kind_max() const { return dtype == VF_U8 ? vf::kJoinU8 : vf::kJoinSplit; }
+    // the same for the approximations of the join kernel (norms from its origin, see vf_join.hip); what it decides is
+    // stored or is the ground truth: "seed_slack" below 1 does not make its proofs weaker
+    float join_err_bound(int kind) const
+    {
+        return (float)(std::max(1.0, tune.seed_slack) * ((512 + 4 * dim) * 5.9604644775390625e-08 + (kind == vf::kJoinSingle ? 1.220703125e-04 : 0.0)));
+    }
+    // ... and what is proportional to |q|: the rounding of both operands to 11 bits, the table's rows by at most xc_rho of
+    // their length, any vector by 2^-11 (own: the rows are the table's)
+    float join_err_q(int kind, bool own) const
+    {
+        return kind == vf::kJoinSingle ? 2.01f * (xc_rho + (own ? xc_rho : 4.8828125e-04f)) * std::sqrt(xc_max) : 0.f;
+    }
+    // the power of two that brings the largest centred norm of the table into [32, 64)
+    float join_scale(int kind) const
+    {
+        if (kind != vf::kJoinSingle || !(xc_max > 0.f)) return 1.f;
+        int e;
+        (void)std::frexp(std::sqrt(xc_max), &e);
+        return std::ldexp(1.f, 6 - e);
+    }
 };
 
 namespace vf {
@@ -349,6 +371,8 @@ struct CallPlan {
     std::vector<JoinBatch> jbatches;
     int64_t join_groups = 0;              // of the largest batch
     int32_t join_keep = 0, join_max_nseg = 1;
+    int join_kind = kJoinU8, join_tile = kJoinRows;
+    size_t join_bound_at = 0, join_first_row = 0, join_rows = 0;   // the rows' shared bounds, among the partial rows' bits
     size_t ls_part_words = 0;
     std::vector<SeedTile> tiles;          // dense seed scoring: tiles of <= 64 (32) graph queries of one label
     size_t n_gq = 0;

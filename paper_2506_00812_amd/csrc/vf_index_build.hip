@@ -129,10 +129,10 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         const int64_t base = ix->O_HS[(size_t)l], group0 = n_groups;
         lists.push_back(JoinList{base, (int32_t)group0, nl});
         n_groups += (nl + 31) / 32;
-        for (int32_t e = 0; e < nl; e += kJoinRows) {
+        for (int32_t e = 0; e < nl; e += kJoinRowsShared) {
             ScanItem it{};
             it.group0 = group0; it.n = nl;
-            it.q_begin = (int32_t)(base - base0 + e); it.q_count = std::min(kJoinRows, nl - e);
+            it.q_begin = (int32_t)(base - base0 + e); it.q_count = std::min(kJoinRowsShared, nl - e);
             it.self_base = e; it.part_row = it.q_begin;
             items.push_back(it);
         }
@@ -140,29 +140,136 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     // the tiles of the longest lists first: they take the longest
     std::stable_sort(items.begin(), items.end(), [](const ScanItem &a, const ScanItem &b) { return a.n > b.n; });
     int rc;
-    DevBuf d_lists(&ix->alloc);
-    DevBufGuard rel{&d_lists};
+    DevBuf d_lists(&ix->alloc), d_unproven(&ix->alloc), d_sel(&ix->alloc);
+    DevBufGuard rel{&d_lists, &d_unproven, &d_sel};
     if ((rc = upload(d_lists, lists, s)) != VF_OK) return rc;
-    if ((rc = upload(d_items, items, s)) != VF_OK) return rc;
     const int32_t *map = ix->d_M_HS.as<int32_t>();
-    launch_join_pack(ix->dtype, ix->X, ix->dim, map, d_lists.as<JoinList>(), (int)lists.size(), n_groups, ix->join_norms(),
-                     ix->d_centre.as<float>(), ix->tmp_blk.as<uint4>(), ix->tmp_norm.p, s);
-    JoinParams p{};
-    p.xblk = ix->tmp_blk.as<uint4>(); p.xnorm = ix->tmp_norm.p;
-    p.qsrc = ix->X; p.qrow = map + base0; p.items = d_items.as<ScanItem>();
-    p.dim = ix->dim; p.K = K; p.centre = ix->d_centre.as<float>();
-    p.res_idx = cand_idx.as<int32_t>(); p.res_bits = cand_dist.as<uint32_t>();
-    p.meta = ix->meta();
-    launch_join(ix->dtype, p, (int)items.size(), s);
-    for (size_t i = lo; i < hi; ++i) {
-        const int32_t l = ix->graph_labels[i], nl = ix->S[(size_t)l];
-        const int64_t base = ix->O_HS[(size_t)l], at = base - base0;
-        // float32 rows are accepted only with a proof that the K candidates contain them
-        launch_graph_rows(ix->dtype, ix->X, ix->dim, map + base, nl, p.res_idx + at * K, p.res_bits + at * K, K, deg,
-                          rows_out + at * deg, ix->join_err_bound(), ix->xc_max, p.centre, nullptr, s);
-        if (global_ids)
-            launch_graph_global_ids(rows_out + at * deg, map + base, (int64_t)nl * deg, ix->d_Gg.as<int32_t>() + base * ix->R, s);
+    const int64_t n_rows = ix->O_HS[(size_t)ix->graph_labels[hi - 1]] + ix->S[(size_t)ix->graph_labels[hi - 1]] - base0;
+    int kind = ix->join_kind();
+    if (kind == kJoinSingle && (rc = d_unproven.reserve((size_t)(n_rows + 1) * 4)) != VF_OK) {   // how many rows have no proof, and which
+        if (rc != VF_ENOMEM) return rc;
+        (void)hipGetLastError();
+        kind = kJoinSplit;
     }
+    auto pack = [&](int kd) {
+        launch_join_pack(kd, ix->X, ix->dim, map, d_lists.as<JoinList>(), (int)lists.size(), n_groups, ix->join_norms(),
+                         ix->d_centre.as<float>(), ix->join_scale(kd), ix->tmp_blk.as<uint4>(), ix->tmp_norm.p, nullptr, 0, s);
+    };
+    auto join = [&](int kd, const int32_t *sel, int tile_rows, int n_items) {
+        JoinParams p{};
+        p.xblk = ix->tmp_blk.as<uint4>(); p.xnorm = ix->tmp_norm.p;
+        p.qsrc = ix->X; p.qrow = map + base0; p.sel = sel; p.items = d_items.as<ScanItem>();
+        p.dim = ix->dim; p.K = K; p.centre = ix->d_centre.as<float>(); p.scale = ix->join_scale(kd);
+        p.res_idx = cand_idx.as<int32_t>(); p.res_bits = cand_dist.as<uint32_t>();
+        p.meta = ix->meta();
+        launch_join(kd, p, tile_rows, n_items, s);
+    };
+    // n rows of list i (sel null: all of them) from their candidates, which begin at row cand_at
+    auto rows = [&](int kd, size_t i, int64_t cand_at, const int32_t *sel, int64_t n, int32_t nseg, int64_t seg_stride, int32_t *unproven) {
+        const int32_t l = ix->graph_labels[i];
+        const int64_t base = ix->O_HS[(size_t)l];
+        GraphRowsParams g{};
+        g.X = ix->X; g.dim = ix->dim; g.map = map + base; g.n_list = ix->S[(size_t)l]; g.n = n;
+        g.sel = sel; g.row_base = (int32_t)(base - base0); g.nseg = nseg; g.seg_stride = seg_stride;
+        g.cand_idx = cand_idx.as<int32_t>() + cand_at * K; g.cand_bits = cand_dist.as<uint32_t>() + cand_at * K; g.K = K; g.R = deg;
+        g.G_rows = rows_out + (base - base0) * deg;
+        g.err_bound = ix->join_err_bound(kd); g.err_q = ix->join_err_q(kd, true); g.xn_max = ix->xc_max;
+        g.approx_unit = 1.0f / (ix->join_scale(kd) * ix->join_scale(kd)); g.centre = ix->d_centre.as<float>();
+        g.unproven = unproven;
+        launch_graph_rows(ix->dtype, g, s);
+    };
+    auto fetch_count = [&](int32_t &count) -> int {
+        VF_HIP(hipMemcpyAsync(&count, d_unproven.p, 4, hipMemcpyDeviceToHost, s));
+        VF_HIP(hipStreamSynchronize(s));
+        return VF_OK;
+    };
+    // The rows of sel (ascending, of any lists).  Few rows do not fill the chip with whole lists: as many segments as do,
+    // and as the candidates' buffer has room for.
+    auto selected = [&](int kd, const std::vector<int32_t> &sel, int32_t *unproven) -> int {
+        int rc = upload(d_sel, sel, s);
+        if (rc != VF_OK) return rc;
+        const int tile = sel.size() > 4096 ? kJoinRowsShared : kJoinRows;
+        const int64_t most = std::min<int64_t>(n_rows / (int64_t)sel.size(), 1024 / (int64_t)(sel.size() / tile + 1));
+        const int32_t nseg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, most));
+        std::vector<ScanItem> part;
+        std::vector<size_t> first;   // of list lo + i in sel
+        size_t at = 0;
+        for (size_t i = lo; i < hi; ++i) {
+            const int32_t l = ix->graph_labels[i], nl = ix->S[(size_t)l], ng = (nl + 31) / 32, per = (ng + nseg - 1) / nseg;
+            const int64_t row0 = ix->O_HS[(size_t)l] - base0;
+            first.push_back(at);
+            size_t e = at;
+            while (e < sel.size() && sel[e] < row0 + nl) ++e;
+            for (size_t count; at < e; at += count) {
+                count = std::min<size_t>((size_t)tile, e - at);
+                for (int32_t sg = 0; sg < nseg; ++sg) {   // (an empty segment still writes its rows)
+                    const int32_t g0 = std::min(sg * per, ng - 1);
+                    ScanItem it{};
+                    it.group0 = lists[i - lo].group0 + g0; it.entry0 = g0 * 32;
+                    it.n = sg * per < ng ? std::min(per * 32, nl - g0 * 32) : 0;
+                    it.q_begin = (int32_t)at; it.q_count = (int32_t)count;
+                    it.self_base = (int32_t)row0; it.part_row = (int32_t)(at + (size_t)sg * sel.size());
+                    part.push_back(it);
+                }
+            }
+        }
+        first.push_back(at);
+        std::stable_sort(part.begin(), part.end(), [](const ScanItem &a, const ScanItem &b) { return a.n > b.n; });
+        if ((rc = upload(d_items, part, s)) != VF_OK) return rc;
+        join(kd, d_sel.as<int32_t>(), tile, (int)part.size());
+        for (size_t i = lo; i < hi; ++i)
+            rows(kd, i, (int64_t)first[i - lo], d_sel.as<int32_t>() + first[i - lo], (int64_t)(first[i - lo + 1] - first[i - lo]), nseg,
+                 (int64_t)sel.size(), unproven);
+        VF_HIP(hipStreamSynchronize(s));
+        return VF_OK;
+    };
+    pack(kind);
+    // Where a batch takes milliseconds: would binary16 prove its rows?  32 rows of each of the eight longest lists, whose
+    // neighbours are closest together, tell (300,000 x 128, clusters ten times as far apart as they are wide, most rows
+    // without a proof: build 64 ms without this look, 52 with split operands from the start; the look takes 0.3).
+    double pairs = 0;
+    for (const JoinList &l : lists) pairs += (double)l.n * l.n;
+    if (kind == kJoinSingle && pairs > 4e9) {
+        std::vector<size_t> by_size(lists.size());
+        for (size_t i = 0; i < by_size.size(); ++i) by_size[i] = i;
+        std::stable_sort(by_size.begin(), by_size.end(), [&](size_t a, size_t b) { return lists[a].n > lists[b].n; });
+        std::vector<int32_t> sel;
+        for (size_t u = 0; u < std::min<size_t>(8, by_size.size()); ++u)
+            for (int32_t r = 0; r < 32; ++r)
+                sel.push_back((int32_t)(lists[by_size[u]].src - base0 + (int64_t)lists[by_size[u]].n * r / 32));
+        std::sort(sel.begin(), sel.end());
+        VF_HIP(hipMemsetAsync(d_unproven.p, 0, 4, s));
+        int32_t count = 0;
+        if ((rc = selected(kind, sel, d_unproven.as<int32_t>())) != VF_OK || (rc = fetch_count(count)) != VF_OK) return rc;
+        if ((size_t)count > sel.size() / 16) {
+            ix->join_single = false;
+            pack(kind = kJoinSplit);
+        }
+    }
+    if ((rc = upload(d_items, items, s)) != VF_OK) return rc;
+    if (kind == kJoinSingle) VF_HIP(hipMemsetAsync(d_unproven.p, 0, 4, s));
+    join(kind, nullptr, kJoinRowsShared, (int)items.size());
+    for (size_t i = lo; i < hi; ++i)
+        rows(kind, i, ix->O_HS[(size_t)ix->graph_labels[i]] - base0, nullptr, ix->S[(size_t)ix->graph_labels[i]], 1, 0,
+             kind == kJoinSingle ? d_unproven.as<int32_t>() : nullptr);
+    if (kind == kJoinSingle) {
+        int32_t count = 0;
+        if ((rc = fetch_count(count)) != VF_OK) return rc;
+        if (count > 0) {   // those once more, with operands that keep twice the bits
+            std::vector<int32_t> sel((size_t)count);
+            VF_HIP(hipMemcpy(sel.data(), d_unproven.as<int32_t>() + 1, sel.size() * 4, hipMemcpyDeviceToHost));
+            std::sort(sel.begin(), sel.end());
+            pack(kJoinSplit);
+            if ((rc = selected(kJoinSplit, sel, nullptr)) != VF_OK) return rc;
+            if ((int64_t)count > n_rows / 64) ix->join_single = false;
+        }
+    }
+    if (global_ids)
+        for (size_t i = lo; i < hi; ++i) {
+            const int32_t l = ix->graph_labels[i];
+            const int64_t base = ix->O_HS[(size_t)l];
+            launch_graph_global_ids(rows_out + (base - base0) * deg, map + base, (int64_t)ix->S[(size_t)l] * deg, ix->d_Gg.as<int32_t>() + base * ix->R, s);
+        }
     VF_HIP(hipGetLastError());
     VF_HIP(hipStreamSynchronize(s));   // the tables above are pageable host memory and temporaries
     return VF_OK;
@@ -222,8 +329,11 @@ static int build_graph_for_label(vf_index *ix, int32_t l, int32_t K, int32_t deg
     // float32 rows are accepted only with a proof that the self-join's K candidates contain them (the bound of the
     // float32 matrix-core approximations, relative to the largest squared norm of the table)
     const bool checked = ix->dtype == VF_F32 && ix->xn_max > 0.f;
-    launch_graph_rows(ix->dtype, ix->X, ix->dim, map, nl, cand_idx.as<int32_t>(), cand_dist.as<uint32_t>(), K, deg, rows_out,
-                      checked ? ix->seed_err_bound() : -1.f, ix->xn_max, nullptr, nullptr, s);
+    GraphRowsParams g{};
+    g.X = ix->X; g.dim = ix->dim; g.map = map; g.n_list = nl; g.n = nl;
+    g.cand_idx = cand_idx.as<int32_t>(); g.cand_bits = cand_dist.as<uint32_t>(); g.K = K; g.R = deg; g.G_rows = rows_out; g.nseg = 1;
+    g.err_bound = checked ? ix->seed_err_bound() : -1.f; g.xn_max = ix->xn_max; g.approx_unit = 1.f;
+    launch_graph_rows(ix->dtype, g, s);
     if (global_ids)
         launch_graph_global_ids(rows_out, map, (int64_t)nl * deg, ix->d_Gg.as<int32_t>() + base * ix->R, s);
     VF_HIP(hipGetLastError());
@@ -459,17 +569,17 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
             if (ix->dtype == VF_F32) {
                 DevBuf parts(&ix->alloc);
                 DevBufGuard rp{&parts};
-                if ((rc = parts.reserve(((size_t)kCentreParts * dim + 2) * 4)) != VF_OK) return rc;
+                if ((rc = parts.reserve(((size_t)kCentreParts * dim + 3) * 4)) != VF_OK) return rc;
                 if ((rc = ix->d_centre.reserve((size_t)dim * 4)) != VF_OK) return rc;
                 if ((rc = ix->d_xnorm_c.reserve((size_t)n * 4)) != VF_OK) return rc;
                 uint32_t *max_bits = parts.as<uint32_t>() + (size_t)kCentreParts * dim;
                 launch_centre(ix->X, dim, n, parts.as<float>(), ix->d_centre.as<float>(), s);
-                VF_HIP(hipMemsetAsync(max_bits, 0, 8, s));
+                VF_HIP(hipMemsetAsync(max_bits, 0, 12, s));
                 launch_row_norms_f32(ix->X, dim, n, ix->d_centre.as<float>(), ix->d_xnorm_all.as<uint32_t>(), ix->d_xnorm_c.as<uint32_t>(),
                                      max_bits, s);
                 VF_HIP(hipGetLastError());
-                float mx[2] = {0.f, 0.f};
-                VF_HIP(hipMemcpyAsync(mx, max_bits, 8, hipMemcpyDeviceToHost, s));
+                float mx[3] = {0.f, 0.f, 0.f};
+                VF_HIP(hipMemcpyAsync(mx, max_bits, 12, hipMemcpyDeviceToHost, s));
                 VF_HIP(hipStreamSynchronize(s));
                 // a table with NaN or overflowing norms keeps the exact kernel, and so does one whose largest
                 // squared norm is outside [1e-24, 1e30]: the proofs' bound is relative to that norm and assumes
@@ -483,7 +593,10 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
                     ix->seed_mfma_ok = seed_mfma_supported(ix->dtype, ix->dim);
                 }
                 if (!ix->seed_mfma_ok) ix->d_xnorm_all.release();
-                if (in_range(mx[0]) && in_range(mx[1])) ix->xc_max = mx[1];
+                if (in_range(mx[0]) && in_range(mx[1])) {
+                    ix->xc_max = mx[1];
+                    ix->xc_rho = std::min(std::sqrt(mx[2]) * 1.001f, 4.8828125e-04f);
+                }
                 else ix->d_xnorm_c.release();
             } else {
                 launch_row_norms_u8(ix->X, ix->dim, n, ix->d_xnorm_all.as<uint32_t>(), s);
@@ -493,7 +606,7 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
             // Lists are joined many to a launch: as many as fit, packed and with their candidates, into a GiB (or one list
             // that is larger than that).  The scan kernels take one list at a time.  Where there is no memory for that:
             // smaller batches, down to single lists, and then the scan kernels, whose copies of a list are smaller.
-            int64_t batch_rows = joined ? (int64_t)(((size_t)1 << 30) / (join_group_bytes(ix->dtype, ix->dim) / 32 + (size_t)K * 8)) : 0;
+            int64_t batch_rows = joined ? (int64_t)(((size_t)1 << 30) / (join_group_bytes(ix->join_kind_max(), ix->dim) / 32 + (size_t)K * 8)) : 0;
             std::vector<size_t> batch_end;   // positions in graph_labels
             while (true) {
                 int64_t tmp_groups = 0, tmp_rows = 0;
@@ -512,7 +625,7 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
                     i = e;
                 }
                 const size_t cand_bytes = (size_t)(tmp_rows + 31) / 32 * 32 * K * 4;
-                if ((rc = ix->tmp_blk.reserve((size_t)tmp_groups * (joined ? join_group_bytes(ix->dtype, ix->dim) : ix->group_bytes()))) == VF_OK &&
+                if ((rc = ix->tmp_blk.reserve((size_t)tmp_groups * (joined ? join_group_bytes(ix->join_kind_max(), ix->dim) : ix->group_bytes()))) == VF_OK &&
                     (rc = ix->tmp_norm.reserve((size_t)tmp_groups * 32 * 4)) == VF_OK && (rc = cand_idx.reserve(cand_bytes)) == VF_OK &&
                     (rc = cand_dist.reserve(cand_bytes)) == VF_OK)
                     break;

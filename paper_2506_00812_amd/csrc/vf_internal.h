@@ -103,6 +103,7 @@ struct RerankParams {
     const void *Q;
     int32_t dim, Kc, K;
     float err_bound, xn_max, err_q;   // |approximation - ordered distance| <= err_bound (|q|^2 + xn_max) + err_q |q|
+    float approx_unit, q_max;   // res_bits hold distances divided by approx_unit; queries with |q|^2 above q_max have none
     const float *centre;        // the approximations' origin, which |q| is measured from; null: zero
     uint32_t *fail_count;       // incremented once per query whose proof failed
     // where the caller answers such queries itself (launch_ordered_scan): their merge items' indices, this launch's counted
@@ -141,23 +142,31 @@ void launch_ordered_scan(const OrderedScanParams &p, int n_items, hipStream_t s)
 
 // ---------------------------------------------------------------- join kernel (vf_join.hip)
 
+// What the operands are: bytes; float32 in two bfloat16 parts, three products; float32 rounded to binary16, one product.
+enum JoinKind : int { kJoinU8 = 0, kJoinSplit = 1, kJoinSingle = 2 };
+
 // Many rows against whole lists with the top-K selection fused in.
 struct JoinParams {
     const uint4 *xblk;      // packed lists (launch_join_pack)
     const void *xnorm;      // per slot: half the squared norm (float32), the squared norm of the shifted bytes (uint8)
     const float *centre;    // float32: subtracted from the rows, as it is from the packed lists
+    float scale;            // kJoinSingle: rows are multiplied by this power of two, as the packed lists are
     const int32_t *map;     // local -> global id (AND predicate)
     const void *qsrc;       // row-major [*][dim]
     const int32_t *qrow;    // row of qsrc for each tile row
-    const ScanItem *items;  // <= kJoinRows rows each; every item writes partial rows
+    const int32_t *sel;     // tile row q_begin + r stands for qrow[sel[q_begin + r]] and is the list's entry sel[..] - self_base; null: all rows
+    const ScanItem *items;  // <= kJoinRows (kJoinRowsShared) rows each; every item writes partial rows
     int32_t dim, K;         // K <= 64
     int32_t *res_idx;       // [*][K] list-relative entry index, ascending by (distance, index), -1 = none
-    uint32_t *res_bits;     //        distance bits: exact (uint8), approximations (float32)
+    uint32_t *res_bits;     //        distance bits: exact (uint8), approximations (float32; kJoinSingle: times scale^2)
+    uint32_t *bound;        // [tile rows, from bound_row0 on] smallest K-th distance that a segment of the row's list has found, shared by its items; null: none
+    int32_t bound_row0;
     const int32_t *others_off, *others;   // AND partner labels per query row value, may be null
     LabelMeta meta;
 };
 
-constexpr int kJoinRows = 128;
+constexpr int kJoinRows = 32;          // rows of an item whose list is read by one wave
+constexpr int kJoinRowsShared = 128;   // ... by a workgroup of four, through LDS
 
 // One list to pack: its entries are map[src .. src + n), its first group in the packed buffer is group0 (ascending).
 struct JoinList {
@@ -165,18 +174,20 @@ struct JoinList {
     int32_t group0, n;
 };
 
-size_t join_group_bytes(int dtype, int32_t dim);   // packed bytes of a group of 32 vectors
-// n_groups: of all n_lists lists together
-void launch_join_pack(int dtype, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
-                      int64_t n_groups, const uint32_t *norm_all, const float *centre, uint4 *xblk, void *xnorm, hipStream_t s);
+size_t join_group_bytes(int kind, int32_t dim);   // packed bytes of a group of 32 vectors
+// n_groups: of all n_lists lists together; bound[0 .. n_bound) is set to "nothing found"
+void launch_join_pack(int kind, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
+                      int64_t n_groups, const uint32_t *norm_all, const float *centre, float scale, uint4 *xblk, void *xnorm,
+                      uint32_t *bound, int64_t n_bound, hipStream_t s);
 // float32: a vector near the mean of the table's rows; tmp: kCentreParts * dim floats
 constexpr int kCentreParts = 64;
 void launch_centre(const void *X, int32_t dim, int64_t n, float *tmp, float *centre, hipStream_t s);
-// squared norms of all rows of a table (float bits), from zero and from the centre, and the largest of each as bits in
-// max_bits[2] (zero before; NaN and infinity are above all others)
+// squared norms of all rows of a table (float bits), from zero and from the centre; the largest of each, and of the squared
+// relative errors of the centred rows rounded to 11 bits, as bits in max_bits[3] (zero before; NaN and infinity are above
+// all others)
 void launch_row_norms_f32(const void *X, int32_t dim, int64_t n, const float *centre, uint32_t *out, uint32_t *out_c, uint32_t *max_bits,
                           hipStream_t s);
-void launch_join(int dtype, const JoinParams &p, int n_items, hipStream_t s);
+void launch_join(int kind, const JoinParams &p, int rows, int n_items, hipStream_t s);   // rows: kJoinRows or kJoinRowsShared
 
 // ---------------------------------------------------------------- beam search kernel
 
@@ -320,11 +331,30 @@ void launch_bitset_fill(const int32_t *map, int64_t n, uint32_t *bits, hipStream
 // Graph rows from candidate lists: u8 copies the first R candidates (already exact);
 // f32 re-scores K candidates with the ordered fp32 distance and keeps the best R, provided that no member the
 // self-join dropped can belong to the row (cand_bits: the candidates' approximate distances; err_bound, xn_max:
-// |approximation - ordered distance| <= err_bound (|x_v|^2 + xn_max), norms measured from `centre`, null: from zero;
-// err_bound < 0: unchecked); a row without that proof is computed from every member of the list and counted in *rescanned (optional).
-void launch_graph_rows(int dtype, const void *X, int32_t dim, const int32_t *map, int64_t n, const int32_t *cand_idx,
-                       const uint32_t *cand_bits, int32_t K, int32_t R, int32_t *G_rows, float err_bound, float xn_max,
-                       const float *centre, uint32_t *rescanned, hipStream_t s);
+// |approximation - ordered distance| <= err_bound (|x_v|^2 + xn_max) + err_q |x_v|, norms measured from `centre`, null: from
+// zero; err_bound < 0: unchecked).  A row without that proof is computed from every member of the list, or, with
+// `unproven`, left out and listed there (unproven[0]: how many, then row_base + its number).  With `sel` the n rows are
+// sel[i] - row_base instead of 0 .. n - 1; the candidates of the i-th are the i-th in any case, those of the list's
+// segments seg_stride rows apart.
+struct GraphRowsParams {
+    const void *X;
+    int32_t dim;
+    const int32_t *map;
+    int32_t n_list;             // entries of the list
+    int64_t n;                  // rows to compute
+    const int32_t *sel;
+    int32_t row_base;
+    int32_t nseg;
+    int64_t seg_stride;
+    const int32_t *cand_idx;
+    const uint32_t *cand_bits;  // distances divided by approx_unit
+    int32_t K, R;
+    int32_t *G_rows;
+    float err_bound, err_q, xn_max, approx_unit;
+    const float *centre;
+    int32_t *unproven;
+};
+void launch_graph_rows(int dtype, const GraphRowsParams &p, hipStream_t s);
 
 // out[i] = map[rows[i]] (rows[i] >= 0), -1 otherwise: graph rows as global ids
 void launch_graph_global_ids(const int32_t *rows, const int32_t *map, int64_t count, int32_t *out, hipStream_t s);

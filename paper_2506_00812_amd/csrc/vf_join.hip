@@ -3,53 +3,59 @@
 // queries per list and are bound by the list's bytes, a join has as many rows as it has and is bound by the matrix cores
 // and by the selection, so everything here is arranged around those two.
 //
-// Tile.  A workgroup of four waves takes 128 rows (32 per wave) and streams a segment of a list through LDS, one group
-// of 32 entries per step, shared by its waves: a group is fetched from L2 once per 128 rows instead of once per 16 (the
-// 16-row kernel's 16 KiB per group and 16 rows would need more L2 bandwidth than there is at this rate).  The rows'
-// operand stays in registers; where those do not suffice a part of it is in scratch memory (float32 of more than 128
-// components 82 registers' worth, with the predicate 118, and 24 from 100 components on; uint8 of more than 512 25 and 69):
-// 100,000 x 236 float32 vectors still build in 25 ms, on the 32-row scan kernel in 115.  Lists come packed
+// Tile.  A wave takes 32 rows, their operand in registers.  Where rows are many a workgroup of four waves streams a
+// segment of the list through LDS, one group of 32 entries per step, two buffers: a group is fetched from L2 once per 128
+// rows (every wave by itself: the self-joins below are bound by the memory behind L2, 45 ms instead of 30).  Where a list
+// has few rows (ground truth) one wave reads the list by itself, and no wave of a tile is idle.  Lists come packed
 // (join_pack_kernel): per group the 16-byte chunks chunk-major, which is the B operand of the 32-column MFMAs, lane
 // (n32, h) reading chunk 2 s + h of entry n32.
 //
-// float32 data: v_mfma_f32_32x32x16_bf16 on two-part splits of both operands, x = hi + lo with hi = bf16(x), lo =
-// bf16(x - hi), after subtraction of a vector near the table's mean: distances stay what they are, and what the norms
-// and products lose is relative to the spread of the data instead of to its distance from the origin (100,000 x 128,
-// unit noise, shifted by 20 per coordinate: without it most rows are refused a proof, build 77 ms, 3,000 queries' ground
-// truth 5.5 ms; with it 12.5 ms and 1.25 ms, as without the shift).  The products lo.hi and hi.lo first, then hi.hi, into one float32 accumulator (in this order the small
-// terms are summed while the partial sums are small).  Three products at 16 times the rate of the float32 MFMA.  What
-// they leave out, with u = 2^-24: |x - hi - lo| <= 2^-18 |x| twice and the product of the low parts 2^-18, together
-// 192 u |q||x| in q.x, 193 u (|q|^2 + |x|^2) in the distance; the sums of the high parts 2 u per term; norms, summed one
-// after the other, u per term; the subtraction of the centre, u per component, 4 u (|q|^2 + |x|^2) in the distance; final
-// additions, the thresholds' and the ordered distance's own rounding < 100 u: 300 u + 3 u per component in all.  The
-// bound used is 512 u + 4 u per component = join_err_bound(); callers re-rank what the join keeps with the ordered
-// distance and prove with that bound that nothing else belongs to the result.
+// Operands.  float32 data is centred (a vector near the table's mean is subtracted while it is packed and split): distances
+// stay what they are, and what norms and products lose is relative to the spread of the data instead of to its distance
+// from the origin.  With u = 2^-24:
+//   one part (kJoinSingle): x rounded to binary16 after multiplication by a power of two that brings the table's largest
+//   norm into [32, 64): a relative error of 2^-11 of any vector, of the table's own rows measured when the index is built
+//   (about 2^-12.3), so 2 (rho_q + rho_x) |q||x| in the distance; components that fall below binary16's range lose at
+//   most 2^-15 of the largest norm in all, 2^-13 (|q|^2 + |x|^2) in the distance.  One product on
+//   v_mfma_f32_32x32x16_f16.  The gap between the R-th and the 48th neighbour is ten times that on the repository's
+//   workloads; whatever row is not proven (clusters several times further apart than they are wide) is joined again on
+//   two parts, and an index of such rows takes two parts from the start.
+//   two parts (kJoinSplit): x = hi + lo with hi = bf16(x), lo = bf16(x - hi); lo.hi and hi.lo into an accumulator of their
+//   own (their partial sums stay small), hi.hi into another, added at the end.  They leave out: |x - hi - lo| <= 2^-18 |x|
+//   twice and the product of the low parts 2^-18, together 192 u |q||x| in q.x, 193 u (|q|^2 + |x|^2) in the distance.
+//   both: the sums 2 u per term; norms, summed one after the other, u per term; the subtraction of the centre, u per
+//   component, 4 u (|q|^2 + |x|^2) in the distance; final additions, the thresholds' and the ordered distance's own
+//   rounding < 100 u: 300 u + 3 u per component in all.  The bound used is 512 u + 4 u per component = join_err_bound().
+// Callers re-rank what the join keeps with the ordered distance and prove with these bounds that nothing else belongs to
+// the result, so results do not depend on the operands.
 // uint8 data: v_mfma_i32_32x32x32_i8 on the bytes shifted by -128: exact.
 //
 // Selection.  With v = q.x - |x|^2 / 2 (uint8: 2 q.x - |x|^2) a distance is below a row's threshold where v is at least
-// a per-row constant, one subtraction and one compare per pair; the compares' lane masks are or-ed on the scalar unit,
-// and a group without a candidate (most, once the thresholds have tightened) is done.  Otherwise candidates go to the
-// rows' queues in LDS (32 slots; positions by population counts of the masks, no atomics), and full queues are merged
-// into the rows' sorted K best: two rows share a 64-lane sort network, then one merge network per row.  The K best live
-// in the partial result rows in global memory: a row is drained about 15 times, so LDS is better spent on a second
-// workgroup per CU.
+// a per-row constant, one subtraction and one compare per pair; a group without a candidate is done.  Candidates are
+// appended to one list of the wave in LDS; when it is half full they are delivered to the rows' queues (16 slots, LDS
+// atomics over 64 candidates at a time), and rows with ten or more merge their queue into their sorted K best: four rows
+// share a 64-lane sort network, then one merge network per row.  The K best live in the partial result rows in global
+// memory, the next four rows' requested while four are merged.  The waves of a workgroup deliver together: a wave that
+// merges lets the others wait at the next group's barrier, so merges at different times cost the workgroup their sum.
+// First thresholds come from a sample of up to 64 groups (the largest values of two groups' lanes, K of which are at or
+// above the K-th largest of them); without it a third of all candidates fall into a row's first thousand entries.  The
+// segments of a ground truth list share the rows' bounds.
 //
-// Measured, self-joins of 36 lists of 4,000 to 170,000 float32 vectors, dim 128 (4.7e10 pairs): 59 ms; the 16-row kernel
-// on the float32 MFMA, one launch per list and 4 MiB panel, 167 ms.  The matrix cores are busy for 15 ms of it; the
-// streaming alone (no candidates) takes 32 ms, whether the lists come from L2 or from memory: two waves per SIMD and a
-// barrier per group; the rest is the selection.
+// Measured: self-joins of 36 lists of 4,000 to 170,000 float32 vectors, dim 128 (4.7e10 pairs) 59.5 -> 31 ms (before: 128
+// rows per workgroup on two parts, a queue per row filled directly, merges at any time); a build of 400,000 vectors 88 ->
+// 60 ms; ground truth of 5,000 queries over 500,000 2.35 -> 1.2 ms.  Bound by instruction issue and waiting: per 32 x 32 pairs
+// a SIMD takes 1,500 cycles, 210 vector instructions (850 cycles), 8 MFMAs (260); three to four waves per SIMD are what
+// registers and LDS leave, and with two it takes a quarter longer.
 #include "vf_select.h"
 
 namespace vf {
 
 typedef __bf16 v8bf_join __attribute__((ext_vector_type(8)));
+typedef _Float16 v8h_join __attribute__((ext_vector_type(8)));
 typedef float v16f_join __attribute__((ext_vector_type(16)));
 typedef int v16i_join __attribute__((ext_vector_type(16)));
 typedef int v4i_join __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u_join __attribute__((ext_vector_type(4)));
-
-// LDS buffers of one group of nc chunks: two where both fit beside the queues in 64 KiB
-__host__ __device__ constexpr int join_buffers(int nc) { return nc <= 32 ? 2 : 1; }
 
 // four components of a row (chunk c) less those of the centre
 __device__ __forceinline__ float4 centred(float4 v, const float *centre, int c)
@@ -69,6 +75,15 @@ __device__ __forceinline__ void split_bf16x8(const float (&f)[8], uint4 &hi, uin
     }
     hi = make_uint4(a[0] | (a[1] << 16), a[2] | (a[3] << 16), a[4] | (a[5] << 16), a[6] | (a[7] << 16));
     lo = make_uint4(b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16));
+}
+
+// eight floats rounded to binary16
+__device__ __forceinline__ uint4 half8(const float (&f)[8])
+{
+    v8h_join x;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = (_Float16)f[i];
+    return __builtin_bit_cast(uint4, x);
 }
 
 // ---------------------------------------------------------------- sorting networks over the lanes of a wave
@@ -125,6 +140,18 @@ template <int J, uint64_t MIN> __device__ __forceinline__ uint64_t lane_exchange
     return __builtin_amdgcn_inverse_ballot_w64(__builtin_amdgcn_ballot_w64(a < b) ^ ~MIN) ? a : b;
 }
 
+// ... and of 32-bit values (a float is no NaN)
+template <int J, uint64_t MIN, class V> __device__ __forceinline__ V lane_exchange_32(V v)
+{
+    uint32_t ab, bb;
+    lane_pair<J>(__builtin_bit_cast(uint32_t, v), ab, bb);
+    const V a = __builtin_bit_cast(V, ab), b = __builtin_bit_cast(V, bb);
+    const V lo = a < b ? a : b, hi = a < b ? b : a;
+    return __builtin_amdgcn_inverse_ballot_w64(MIN) ? lo : hi;
+}
+template <int J, uint64_t MIN> __device__ __forceinline__ float lane_exchange(float v) { return lane_exchange_32<J, MIN>(v); }
+template <int J, uint64_t MIN> __device__ __forceinline__ int lane_exchange(int v) { return lane_exchange_32<J, MIN>(v); }
+
 // The stages J, J / 2, .. 1 that make a bitonic sequence of each aligned block of K lanes ascending (DESC: descending);
 // LAST: every block, else blocks alternate.  NR independent sets: their dependent chains interleave.
 template <int K, int J, bool LAST, bool DESC, class T, int NR> __device__ __forceinline__ void lane_merge_stages(T (&v)[NR])
@@ -150,38 +177,75 @@ template <int SEG, class T, int NR> __device__ __forceinline__ void lane_merge(T
     lane_merge_stages<SEG, SEG / 2, true, false>(v);
 }
 
-constexpr int kJoinQueue = 32;   // pending keys per row: what one group can add
+constexpr int kJoinQueue = 16;   // pending keys per row
+constexpr int kJoinMerge = 10;   // a row with as many of them is merged when its wave delivers
+constexpr int kJoinFlat = 128;   // candidates on their way to the rows' queues (two rows of a group add up to 64)
+constexpr int kJoinFull = 64;    // as many of them make the waves of a workgroup deliver together
+constexpr int kJoinWaveLds = 32 * kJoinQueue * 8 + kJoinFlat * 8 + 32 * 4 + 32 * 4 + kJoinFlat;   // bytes of a wave
+constexpr int kJoinSample = 64;  // groups that are looked at first, for a row's first threshold
 
 template <int DT> struct JoinAcc { using type = v16f_join; using scalar = float; };
 template <> struct JoinAcc<0> { using type = v16i_join; using scalar = int; };
 
-template <int DT> __host__ __device__ constexpr int join_chunks(int nk) { return DT == 0 ? 2 * nk : 4 * nk; }
+// 16-byte chunks of a packed vector: DT 0 uint8, 1 float32 in two bfloat16 parts, 2 float32 in one binary16 part
+template <int DT> __host__ __device__ constexpr int join_chunks(int nk) { return DT == 1 ? 4 * nk : 2 * nk; }
 
-// v of lane `lane` (a constant) := x (wave-uniform)
-__device__ __forceinline__ void set_lane(int &v, int x, int lane)
+// lanes below this one whose bit is set in m
+__device__ __forceinline__ int lanes_before(uint64_t m)
 {
-    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(x), "n"(lane));
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
-// NK: contraction steps (16 components of float32, 32 of uint8), the vectors zero padded to them.
-template <int DT, int NK, bool AND>
-__global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
+// Waves per SIMD that the registers are shared out for.
+__host__ __device__ constexpr int join_waves(int dt, int nk) { return dt == 1 || nk > 8 ? 2 : nk > 6 ? 3 : 4; }
+
+// Operand chunks in flight: the steps of a group that are requested together.
+template <int DT> __host__ __device__ constexpr int join_prefetch(int nk) { return DT == 1 ? (nk < 4 ? nk : 4) : nk <= 4 ? nk : nk == 6 ? 3 : 4; }
+
+// LDS buffers of one group of nc chunks: two where they leave room for other workgroups on the CU
+__host__ __device__ constexpr int join_buffers(int nc) { return nc <= 32 ? 2 : 1; }
+
+template <int DT, int NK, int W> constexpr size_t join_lds_bytes()
+{
+    constexpr int NC = join_chunks<DT>(NK);
+    return (size_t)(W > 1 ? join_buffers(NC) * NC * 512 + 16 : 0) + (size_t)W * kJoinWaveLds;
+}
+
+// NK: contraction steps (16 components of float32, 32 of uint8), the vectors zero padded to them.  W: waves of a workgroup,
+// 32 rows each.  Four share the list's groups through LDS; one reads them by itself.
+template <int DT, int NK, bool AND, int W>
+__global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinParams p)
 {
     extern __shared__ uint4 smem[];
     using acc_t = typename JoinAcc<DT>::type;
     using val_t = typename JoinAcc<DT>::scalar;
-    constexpr int NC = join_chunks<DT>(NK), STAGE = NC * 32, NL = (STAGE + 255) / 256;
-    constexpr int NBUF = join_buffers(NC);
+    typedef val_t val4_t __attribute__((ext_vector_type(4)));
+    constexpr int NC = join_chunks<DT>(NK), NPRE = join_prefetch<DT>(NK), STAGE = NC * 32;
+    constexpr int NBUF = W > 1 ? join_buffers(NC) : 0, NL = (STAGE + 64 * W - 1) / (64 * W);
     const ScanItem it = p.items[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, n32 = lane & 31, h = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
     const int K = p.K, row_base = wave * 32;
     const int rows = it.q_count - row_base < 32 ? it.q_count - row_base : 32;   // rows of this wave (<= 0: none)
-    uint64_t *pend = (uint64_t *)(smem + NBUF * STAGE) + row_base * kJoinQueue;   // [32 rows][32]
+    static_assert(kJoinWaveLds % 16 == 0, "alignment");
+    uint64_t *pend = (uint64_t *)((char *)(smem + NBUF * STAGE) + wave * kJoinWaveLds);   // [32 rows][kJoinQueue]
+    uint64_t *flat = pend + 32 * kJoinQueue;                   // (v << 32 | entry) of a candidate
+    int *pending = (int *)(flat + kJoinFlat);                  // [32] keys in the rows' queues (may count past their ends)
+    val_t *tvs = (val_t *)(pending + 32);                      // [32] the rows' thresholds: read per group, they would be 16 registers
+    uint8_t *flat_row = (uint8_t *)(tvs + 32);                 // a candidate's row; kTaken: gone to the row's queue, or not wanted
+    int *want = (int *)((char *)(smem + NBUF * STAGE) + W * kJoinWaveLds);   // [3], the groups' in turn: a wave wants to deliver
+    constexpr uint32_t kTaken = 255;
+    int flat_n = 0;
 
     // ---- the rows' operand (lane (n32, h): chunk 2 s + h of row n32) and squared norms
-    const int qr = n32 < rows ? p.qrow[it.q_begin + row_base + n32] : -1;
-    uint4 a[NK], alo[DT == 0 ? 1 : NK];
+    int qr = -1, self = -1;   // row n32's vector, and the entry of the list that is the row itself
+    if (n32 < rows) {
+        int at = it.q_begin + row_base + n32;
+        if (p.sel != nullptr) at = p.sel[at];
+        qr = p.qrow[at];
+        if (it.self_base >= 0) self = p.sel != nullptr ? at - it.self_base : it.self_base + row_base + n32;
+    }
+    uint4 a[NK], alo[DT == 1 ? NK : 1];
     val_t qnorm = 0;
     {
         const char *qp = (const char *)p.qsrc + (int64_t)(qr >= 0 ? qr : 0) * (p.dim * (DT == 0 ? 1 : 4));
@@ -202,8 +266,14 @@ __global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
                 float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
                 if (qr >= 0 && c * 8 < p.dim) x = centred(*(const float4 *)(qp + c * 32), p.centre, 2 * c);
                 if (qr >= 0 && c * 8 + 4 < p.dim) y = centred(*(const float4 *)(qp + c * 32 + 16), p.centre, 2 * c + 1);
-                const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-                split_bf16x8(f, a[s], alo[s]);
+                float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+                if constexpr (DT == 1) {
+                    split_bf16x8(f, a[s], alo[s]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) f[i] *= p.scale;
+                    a[s] = half8(f);
+                }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) qnorm += f[i] * f[i];
             }
@@ -217,75 +287,76 @@ __global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
     int pcv = 0;
     uint64_t row_kth = KEY_MAX;
     uint32_t touched = 0;            // rows whose partial result row has been written
-    const int64_t part0 = (int64_t)it.part_row + row_base;
-    // per accumulator element: row 8 (j / 4) + 4 h + j % 4
-    val_t t[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) t[j] = __shfl(tv, 8 * (j >> 2) + 4 * h + (j & 3));
-    uint32_t and_rows = 0;
-    int qr_of[AND ? 16 : 1];
-    if constexpr (AND) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int r = 8 * (j >> 2) + 4 * h + (j & 3);
-            qr_of[j] = __shfl(qr, r);
-            if (qr_of[j] >= 0 && p.others_off[qr_of[j] + 1] > p.others_off[qr_of[j]]) and_rows |= 1u << j;
-        }
-    }
-
-    auto qnorm_of = [&](int r) -> val_t {   // (wave-uniform r)
-        if constexpr (DT == 0) return __builtin_amdgcn_readlane(qnorm, r);
-        else return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(qnorm), r));
+    // threshold of a row whose K-th distance (of any segment of its list) has the bits kd
+    auto threshold = [&](uint32_t kd) -> val_t {
+        if constexpr (DT == 0) return qnorm - (int)kd;
+        // (lowered by a few units in the last place: a pair that is left out has an approximation of at least the K-th best)
+        else return 0.5f * (qnorm - __uint_as_float(kd)) - 2.4e-7f * (qnorm + __uint_as_float(kd));
     };
+    uint32_t *bound = p.bound != nullptr ? p.bound + (it.q_begin - p.bound_row0) + row_base : nullptr;
+    const val_t first = DT == 0 ? (val_t)(-0x20000000) : (val_t)(-3.0e38f);   // every entry passes
+    val_t start = first;
+    const bool filtered = AND && qr >= 0 && p.others_off[qr + 1] > p.others_off[qr];   // (its sample says nothing about those that pass)
+    if (bound != nullptr && n32 < rows) {
+        const uint32_t kd = __hip_atomic_load(bound + n32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (kd != 0xFFFFFFFFu) tv = threshold(kd);
+    }
+    const int64_t part0 = (int64_t)it.part_row + row_base;
+    if (h == 0) tvs[n32] = tv;
+    if (h == 0) pending[n32] = 0;
+    wave_lds_sync();
     // Merge the queues of the rows in `todo` into their K best, four rows at a time, and empty them.
     auto drain = [&](uint32_t todo) {
         wave_lds_sync();
         const uint32_t done = todo;
-        while (todo != 0) {
+        int r_next[4];
+        bool on_next[4];
+        uint64_t best_next[4];
+        auto pick = [&]() {   // the next four rows, their K best requested while the last four are merged
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                on_next[u] = todo != 0;
+                r_next[u] = on_next[u] ? __builtin_ctz(todo) : 0;
+                todo &= todo - 1;
+                best_next[u] = KEY_MAX;
+                if (on_next[u] && ((touched >> r_next[u]) & 1u) && lane < K) {
+                    const int64_t o = (part0 + r_next[u]) * K + lane;
+                    const int32_t idx = p.res_idx[o];
+                    if (idx >= 0) best_next[u] = ((uint64_t)p.res_bits[o] << 32) | (uint32_t)idx;
+                }
+            }
+        };
+        pick();
+        while (on_next[0]) {
             int r[4];
             bool on[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                on[u] = todo != 0;
-                r[u] = on[u] ? __builtin_ctz(todo) : r[0];
-                todo &= todo - 1;
-            }
             uint64_t best[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                best[u] = KEY_MAX;
-                if (((touched >> r[u]) & 1u) && lane < K) {
-                    const int64_t o = (part0 + r[u]) * K + lane;
-                    const int32_t idx = p.res_idx[o];
-                    if (idx >= 0) best[u] = ((uint64_t)p.res_bits[o] << 32) | (uint32_t)idx;
-                }
+            for (int u = 0; u < 4; ++u) { r[u] = r_next[u]; on[u] = on_next[u]; best[u] = best_next[u]; }
+            pick();
+            // the four queues in the wave's quarters, each sorted descending, then in the last quarter behind KEY_MAX:
+            // against the ascending best, that makes the smallest 64 of both a bitonic sequence
+            static_assert(kJoinQueue == 16, "a quarter of the lanes");
+            const int quarter = lane >> 4, ls = lane & 15;
+            const int rq = quarter < 2 ? (quarter == 0 ? r[0] : r[1]) : (quarter == 2 ? r[2] : r[3]);
+            const int pc_q = __shfl(pcv, rq);
+            const uint64_t kth_q = shfl64(row_kth, rq);
+            const val_t qn_q = __shfl(qnorm, rq);
+            uint64_t x[1] = {KEY_MAX};
+            if (ls < pc_q) {   // v -> distance of the row
+                const uint64_t key = pend[rq * kJoinQueue + ls];
+                const uint32_t vb = (uint32_t)(key >> 32);
+                const uint32_t bits = DT == 0 ? (uint32_t)((int)qn_q - (int)vb)
+                                              : __float_as_uint(fmaxf((float)qn_q - 2.0f * __uint_as_float(vb), 0.0f));
+                const uint64_t k = ((uint64_t)bits << 32) | (uint32_t)key;
+                x[0] = k < kth_q ? k : KEY_MAX;
             }
-            uint64_t x[2];   // rows r[2u] and r[2u + 1] in the wave's halves
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int c0 = __builtin_amdgcn_readlane(pcv, r[2 * u]), c1 = __builtin_amdgcn_readlane(pcv, r[2 * u + 1]);
-                const uint64_t k0 = readlane64(row_kth, r[2 * u]), k1 = readlane64(row_kth, r[2 * u + 1]);
-                uint64_t key = n32 < (h ? c1 : c0) ? pend[(h ? r[2 * u + 1] : r[2 * u]) * kJoinQueue + n32] : KEY_MAX;
-                if (key != KEY_MAX) {   // v -> distance of the row
-                    const val_t q0 = qnorm_of(r[2 * u]), q1 = qnorm_of(r[2 * u + 1]), q = h ? q1 : q0;
-                    const uint32_t vb = (uint32_t)(key >> 32);
-                    const uint32_t bits = DT == 0 ? (uint32_t)((int)q - (int)vb)
-                                                  : __float_as_uint(fmaxf((float)q - 2.0f * __uint_as_float(vb), 0.0f));
-                    key = ((uint64_t)bits << 32) | (uint32_t)key;
-                }
-                x[u] = key < (h ? k1 : k0) ? key : KEY_MAX;
-            }
-            lane_sort<32, true>(x);
+            lane_sort<16, true>(x);
             uint64_t v[4];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                // both halves' sorted keys in the upper lanes: descending behind KEY_MAX, against the ascending best
-                uint32_t l0, l1, h0, h1;
-                lane_pair<32>((uint32_t)x[u], l0, l1);
-                lane_pair<32>((uint32_t)(x[u] >> 32), h0, h1);
-                const uint64_t x0 = h ? ((uint64_t)h0 << 32) | l0 : KEY_MAX, x1 = h ? ((uint64_t)h1 << 32) | l1 : KEY_MAX;
-                v[2 * u] = best[2 * u] < x0 ? best[2 * u] : x0;
-                v[2 * u + 1] = best[2 * u + 1] < x1 ? best[2 * u + 1] : x1;
+            for (int u = 0; u < 4; ++u) {
+                const uint64_t y = shfl64(x[0], 16 * u + ls), z = quarter == 3 ? y : KEY_MAX;
+                v[u] = best[u] < z ? best[u] : z;
             }
             lane_merge<64>(v);
 #pragma unroll
@@ -303,166 +374,255 @@ __global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
         }
         touched |= done;
         if ((done >> n32) & 1u) {
-            if (h == 0) pcv = 0;
-            if (row_kth != KEY_MAX) {
-                const uint32_t kd = (uint32_t)(row_kth >> 32);
-                if constexpr (DT == 0) tv = qnorm - (int)kd;
-                // (lowered by a few units in the last place: a pair that is left out has an approximation of at least
-                // the K-th best)
-                else tv = 0.5f * (qnorm - __uint_as_float(kd)) - 2.4e-7f * (qnorm + __uint_as_float(kd));
-            }
+            if (h == 0) pending[n32] = 0;
+            uint32_t kd = (uint32_t)(row_kth >> 32);
+            if (bound != nullptr) {
+                // what the other segments' workgroups know of the row: no segment needs what is above any one's K-th best
+                if (row_kth != KEY_MAX && h == 0) atomicMin(bound + n32, kd);
+                const uint32_t b = __hip_atomic_load(bound + n32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                kd = row_kth != KEY_MAX && kd < b ? kd : b;
+                if (kd != 0xFFFFFFFFu) tv = threshold(kd);
+            } else if (row_kth != KEY_MAX) tv = threshold(kd);
         }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) t[j] = __shfl(tv, 8 * (j >> 2) + 4 * h + (j & 3));
+        if (h == 0) tvs[n32] = tv;
         wave_lds_sync();
     };
+    // The collected candidates to their rows' queues, 64 at a time, less those that are the row itself or fail the
+    // predicate; then the queues that are half full (last: all) are merged.  Where a queue is too short for what it is
+    // sent (before thresholds exist), the rest follows after the merge.
+    auto deliver = [&](bool last) {
+        while (true) {
+            wave_lds_sync();
+            bool over = false;
+            for (int i0 = 0; i0 < flat_n; i0 += 64) {
+                const int i = i0 + lane;
+                const uint32_t row = i < flat_n ? flat_row[i] : kTaken;
+                const uint64_t key = i < flat_n ? flat[i] : 0;
+                const int entry = (int)(uint32_t)key;
+                const int row_self = __shfl(self, (int)row & 31);   // (outside any condition: the source lane has to be active)
+                bool ok = row != kTaken && entry != row_self;
+                if constexpr (AND) {
+                    const int q = __shfl(qr, (int)row & 31);
+                    if (ok) {
+                        const int o_begin = p.others_off[q], o_end = p.others_off[q + 1];
+                        if (o_begin < o_end) {
+                            const int gid = p.map[it.map_off + entry];
+                            for (int o = o_begin; o < o_end && ok; ++o) ok = has_label(p.meta, p.others[o], gid);
+                        }
+                    }
+                }
+                const int slot = ok ? atomicAdd(&pending[row], 1) : 0;
+                const bool fits = slot < kJoinQueue;
+                if (ok && fits) pend[row * kJoinQueue + slot] = key;
+                if (row != kTaken && fits) flat_row[i] = (uint8_t)kTaken;
+                over = over || !fits;
+            }
+            wave_lds_sync();
+            const int n = pending[n32];
+            pcv = n < kJoinQueue ? n : kJoinQueue;
+            const bool again = __any(over);
+            const uint32_t todo = (uint32_t)__ballot(lane < 32 && pcv >= (last && !again ? 1 : kJoinMerge));
+            if (todo != 0) drain(todo);
+            if (!again) break;
+        }
+        flat_n = 0;
+    };
 
-    // ---- stream the segment
+    // ---- the list's groups: the next one is on its way while one is worked on
     const int n_groups = (it.n + kGroup - 1) / kGroup;
-    v4u_join pre[NL];   // (the native vector type: an array of uint4 ends up in scratch memory here)
-    auto fetch = [&](int g) {
-        const v4u_join *blk = (const v4u_join *)p.xblk + (it.group0 + g) * (int64_t)STAGE;
+    const v4u_join *blk = (const v4u_join *)p.xblk + it.group0 * (int64_t)STAGE;
+    const val_t *xnorm = (const val_t *)p.xnorm + it.group0 * kGroup + n32;
+    v4u_join b[NPRE * (DT == 1 ? 2 : 1)];   // (split operands: high parts, then low parts)
+    v4u_join pre[W > 1 ? NL : 1];           // (the native vector type: an array of uint4 ends up in scratch memory here)
+    val_t xn_next;
+    auto load_b = [&](const v4u_join *src) {   // chunks of NPRE steps, lane (n32, h): chunk 2 s + h of entry n32
+#pragma unroll
+        for (int u = 0; u < NPRE; ++u) {
+            b[u] = src[u * 64 + h * 32 + n32];
+            if constexpr (DT == 1) b[NPRE + u] = src[(NK + u) * 64 + h * 32 + n32];
+        }
+    };
+    auto fetch = [&](int g) {   // W > 1: this thread's part of a group
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            if (STAGE % 256 == 0 || tid + i * 256 < STAGE) pre[i] = blk[tid + i * 256];
+            if (STAGE % (64 * W) == 0 || tid + i * 64 * W < STAGE) pre[W > 1 ? i : 0] = blk[(int64_t)g * STAGE + tid + i * 64 * W];
     };
     auto put = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < NL; ++i)
-            if (STAGE % 256 == 0 || tid + i * 256 < STAGE) ((v4u_join *)smem)[buf * STAGE + tid + i * 256] = pre[i];
+            if (STAGE % (64 * W) == 0 || tid + i * 64 * W < STAGE) ((v4u_join *)smem)[buf * STAGE + tid + i * 64 * W] = pre[W > 1 ? i : 0];
     };
-    const val_t *xnorm = (const val_t *)p.xnorm;
-    fetch(0);
-    val_t xn_next = xnorm[it.group0 * kGroup + n32];
-    put(0);
-    __syncthreads();
-    for (int g = 0; g < n_groups; ++g) {
-        const bool more = g + 1 < n_groups;
-        const val_t xn = xn_next;
-        if (more) {
-            fetch(g + 1);
-            xn_next = xnorm[(it.group0 + g + 1) * kGroup + n32];
+    auto begin = [&]() {
+        if constexpr (W > 1) {
+            fetch(0);
+            put(0);
+            __syncthreads();
+        } else {
+            load_b(blk);
         }
-        if (rows > 0) {   // wave-uniform
-            const uint4 *B = smem + (NBUF == 2 ? (g & 1) : 0) * STAGE;
-            acc_t acc;
+        xn_next = xnorm[0];
+    };
+    // the contraction of group g (v = q.x - |x|^2 / 2, uint8: 2 q.x - |x|^2), and what comes after it set on its way
+    val_t v[16];
+    auto contract = [&](int g) {
+        const int gn = g + 1 < n_groups ? g + 1 : g;   // (the last one is read twice)
+        const val_t xn = xn_next;
+        if constexpr (W > 1) fetch(gn);
+        xn_next = xnorm[gn * kGroup];
+        if (W > 1 && rows <= 0) return;
+        const v4u_join *B = (const v4u_join *)smem + (NBUF == 2 ? (g & 1) : 0) * STAGE;
+        acc_t acc, acc_lo;   // (split operands: the products with a low part by themselves, so that their sums stay small)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc[j] = 0;
-            // NPRE steps of the B operand at a time, requested before the first of them is used: left to itself the
-            // compiler requests each chunk right before its MFMA and waits for the LDS every time
-            constexpr int NPRE = NK < 8 ? NK : 8;
+        for (int j = 0; j < 16; ++j) { acc[j] = 0; acc_lo[j] = 0; }
+#pragma unroll
+        for (int s0 = 0; s0 < NK; s0 += NPRE) {
+            if constexpr (W > 1) {
+                load_b(B + s0 * 64);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if constexpr (DT == 0) {
 #pragma unroll
-                for (int s0 = 0; s0 < NK; s0 += NPRE) {
-                    v4i_join b[NPRE];
-#pragma unroll
-                    for (int u = 0; u < NPRE; ++u) b[u] = ((const v4i_join *)B)[(2 * (s0 + u) + h) * 32 + n32];
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int u = 0; u < NPRE; ++u) {
-                        const v4i_join av = {(int)a[s0 + u].x, (int)a[s0 + u].y, (int)a[s0 + u].z, (int)a[s0 + u].w};
-                        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av, b[u], acc, 0, 0, 0);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int u = 0; u < NPRE; ++u) {
+                    const v4i_join av = {(int)a[s0 + u].x, (int)a[s0 + u].y, (int)a[s0 + u].z, (int)a[s0 + u].w};
+                    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av, __builtin_bit_cast(v4i_join, b[u]), acc, 0, 0, 0);
                 }
+            } else if constexpr (DT == 2) {
+#pragma unroll
+                for (int u = 0; u < NPRE; ++u)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h_join, a[s0 + u]), __builtin_bit_cast(v8h_join, b[u]), acc, 0, 0, 0);
             } else {
 #pragma unroll
-                for (int s0 = 0; s0 < NK; s0 += NPRE) {
-                    v8bf_join bh[NPRE], bl[NPRE];
-#pragma unroll
-                    for (int u = 0; u < NPRE; ++u) {
-                        bh[u] = ((const v8bf_join *)B)[(2 * (s0 + u) + h) * 32 + n32];
-                        bl[u] = ((const v8bf_join *)B)[(2 * NK + 2 * (s0 + u) + h) * 32 + n32];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int u = 0; u < NPRE; ++u) {
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, alo[s0 + u]), bh[u], acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, a[s0 + u]), bl[u], acc, 0, 0, 0);
-                    }
-                    if (NK <= NPRE) {   // (all of it is still in registers)
-#pragma unroll
-                        for (int u = 0; u < NPRE; ++u)
-                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, a[s0 + u]), bh[u], acc, 0, 0, 0);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if constexpr (NK > NPRE) {
-#pragma unroll
-                    for (int s0 = 0; s0 < NK; s0 += NPRE) {
-                        v8bf_join bh[NPRE];
-#pragma unroll
-                        for (int u = 0; u < NPRE; ++u) bh[u] = ((const v8bf_join *)B)[(2 * (s0 + u) + h) * 32 + n32];
-                        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                        for (int u = 0; u < NPRE; ++u)
-                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, a[s0 + u]), bh[u], acc, 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                for (int u = 0; u < NPRE; ++u) {
+                    const v8bf_join bh = __builtin_bit_cast(v8bf_join, b[u]), bl = __builtin_bit_cast(v8bf_join, b[NPRE + u]);
+                    acc_lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, alo[s0 + u]), bh, acc_lo, 0, 0, 0);
+                    acc_lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, a[s0 + u]), bl, acc_lo, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_join, a[s0 + u]), bh, acc, 0, 0, 0);
                 }
             }
-            uint64_t m[16], any = 0;
-            val_t v[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                v[j] = DT == 0 ? acc[j] * 2 - xn : acc[j] - xn;   // (float32: xn holds |x|^2 / 2)
-                m[j] = __builtin_amdgcn_ballot_w64(v[j] >= t[j]);
-                any |= m[j];
-            }
-            if (any != 0) {
-                const int entry = it.entry0 + g * kGroup + n32;   // list-relative
-                // graph build: the entry that is the row itself (self_base + row) is no candidate
-                const int self = it.self_base >= 0 ? it.self_base + row_base : -0x40000000;
-                if (self + 31 >= it.entry0 + g * kGroup && self <= it.entry0 + g * kGroup + 31) {
-                    const int rel = entry - self - 4 * h;
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) m[j] &= __builtin_amdgcn_ballot_w64(rel != 8 * (j >> 2) + (j & 3));
-                }
-                if constexpr (AND) {
-                    const int gid = p.map[it.map_off + (g * kGroup + n32 < it.n ? entry : it.entry0)];
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        if (m[j] == 0) continue;
-                        bool ok = (m[j] >> lane) & 1u;
-                        if (ok && ((and_rows >> j) & 1u)) {
-                            const int o_begin = p.others_off[qr_of[j]], o_end = p.others_off[qr_of[j] + 1];
-                            for (int o = o_begin; o < o_end && ok; ++o) ok = has_label(p.meta, p.others[o], gid);
-                        }
-                        m[j] = __builtin_amdgcn_ballot_w64(ok);
-                    }
-                }
-                int inc = 0;   // keys that row r receives from this group, in lane r
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const int row0 = 8 * (j >> 2) + (j & 3);
-                    set_lane(inc, __builtin_popcount((uint32_t)m[j]), row0);
-                    set_lane(inc, __builtin_popcount((uint32_t)(m[j] >> 32)), row0 + 4);
-                }
-                // (rows that are half full go along: their next drain would come soon)
-                if (__any(pcv + inc > kJoinQueue))
-                    drain((uint32_t)__ballot(lane < 32 && pcv > 0 && (pcv + inc > kJoinQueue || pcv >= kJoinQueue / 2)));
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    if (m[j] == 0) continue;
-                    const int row = 8 * (j >> 2) + (j & 3) + 4 * h;
-                    const uint32_t mine = h ? (uint32_t)(m[j] >> 32) : (uint32_t)m[j];
-                    const int at = __shfl(pcv, row);
-                    if ((mine >> n32) & 1u) {
-                        const int slot = at + __builtin_popcount(mine & ((1u << n32) - 1u));
-                        // (v for now: the drain makes a distance of it)
-                        pend[row * kJoinQueue + slot] = ((uint64_t)(DT == 0 ? (uint32_t)v[j] : __float_as_uint((float)v[j])) << 32) | (uint32_t)entry;
-                    }
-                }
-                pcv += inc;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (W == 1) {   // the chunks that follow, as soon as the matrix cores have taken these
+                if (s0 + NPRE < NK) load_b(blk + (int64_t)g * STAGE + (s0 + NPRE) * 64);
+                else load_b(blk + (int64_t)gn * STAGE);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (more) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j)   // (float32: xn holds |x|^2 / 2)
+            v[j] = DT == 0 ? acc[j] * 2 - xn : (DT == 1 ? acc_lo[j] + acc[j] : acc[j]) - xn;
+    };
+    auto advance = [&](int g) {   // W > 1: the group after g into LDS
+        if constexpr (W > 1) {
             if (NBUF == 1) __syncthreads();
             put(NBUF == 2 ? (g + 1) & 1 : 0);
             __syncthreads();
         }
+    };
+
+    // ---- first thresholds: every lane's largest v of the even and of the odd groups of a sample; a row's K-th largest of
+    // those 64 (K + 1 where the row itself may be among them) has K entries at or above it.  Without this a row's first
+    // thousand entries make a queue's worth of candidates every few groups.
+    const int rank = K - (it.self_base >= 0 ? 0 : 1);
+    const int sample = n_groups / 2 < kJoinSample ? n_groups / 2 : kJoinSample;
+    if (sample >= 8 && rank < 64 && (W > 1 || __any(n32 < rows && !filtered && !(tv > first)))) {
+        val_t top[2][16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) top[0][j] = top[1][j] = first;
+        begin();
+        for (int g = 0; g < sample; g += 2) {
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                contract(g + o);
+                if (W == 1 || rows > 0)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) top[o][j] = v[j] > top[o][j] ? v[j] : top[o][j];
+                advance(g + o);
+            }
+        }
+        if (W == 1 || rows > 0) {
+#pragma unroll
+            for (int j0 = 0; j0 < 16; j0 += 4) {
+                val_t up[4], down[4], kth[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { up[u] = top[0][j0 + u]; down[u] = top[1][j0 + u]; }
+                lane_sort<32, false>(up);
+                lane_sort<32, true>(down);
+                // (ascending against descending: the larger ones of the pairs are the 32 largest)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) kth[u] = (rank < 32) == (up[u] > down[u]) ? up[u] : down[u];
+                lane_merge<32>(kth);
+                // ascending within a half: the r-th largest of 32 is at lane 31 - r
+                const int at = rank < 32 ? 31 - rank : 63 - rank;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j = j0 + u, r0 = 8 * (j >> 2) + (j & 3);
+                    const val_t k0 = __shfl(kth[u], at), k1 = __shfl(kth[u], 32 + at);
+                    if (n32 == r0) start = k0;
+                    if (n32 == r0 + 4) start = k1;
+                }
+            }
+            if (n32 < rows && !filtered && start > tv) tv = start;
+            if (h == 0) tvs[n32] = tv;
+            wave_lds_sync();
+        }
     }
-    drain((uint32_t)__ballot(lane < 32 && pcv > 0));
+
+    // ---- the groups against the thresholds
+    if (W > 1 && tid < 3) want[tid] = 0;
+    begin();
+    for (int g = 0, turn = 0; g < n_groups; ++g, turn = turn < 2 ? turn + 1 : 0) {
+        contract(g);
+        if (W > 1 && rows <= 0) {
+            advance(g);
+            continue;
+        }
+        uint64_t m[16], some[4];   // lanes whose element j is a candidate, and of rows 8 q .. 8 q + 7
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const val4_t t = ((const val4_t *)tvs)[2 * q + h];   // element j: row 8 (j / 4) + 4 h + j % 4
+            some[q] = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                m[4 * q + u] = __builtin_amdgcn_ballot_w64(v[4 * q + u] >= t[u]);
+                some[q] |= m[4 * q + u];
+            }
+        }
+        if ((some[0] | some[1] | some[2] | some[3]) != 0) {
+            const int entry = it.entry0 + g * kGroup + n32;   // list-relative
+            while (true) {
+                bool full = false;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (some[q] == 0 || full) continue;   // (wave-uniform, as all that follows but the stores)
+#pragma unroll
+                    for (int j = 4 * q; j < 4 * q + 4; ++j) {
+                        if (m[j] == 0 || full) continue;
+                        const int c = __builtin_popcountll(m[j]);
+                        if (flat_n + c > kJoinFlat) { full = true; continue; }
+                        const int at = flat_n + lanes_before(m[j]);
+                        if (__builtin_amdgcn_inverse_ballot_w64(m[j])) {   // (v for now: the drain makes a distance of it)
+                            flat[at] = ((uint64_t)(DT == 0 ? (uint32_t)v[j] : __float_as_uint((float)v[j])) << 32) | (uint32_t)entry;
+                            flat_row[at] = (uint8_t)(8 * (j >> 2) + (j & 3) + 4 * h);
+                        }
+                        flat_n += c;
+                        m[j] = 0;
+                    }
+                }
+                if (!full) break;
+                deliver(false);
+            }
+        }
+        if constexpr (W > 1) {
+            // a wave that merges lets the others wait at the barrier: they merge together
+            // (the next group's word was last read two barriers ago, and is not written before the one to come)
+            if (flat_n >= kJoinFull && lane == 0) want[turn] = 1;
+            if (tid == 0) want[turn < 2 ? turn + 1 : 0] = 0;
+            advance(g);
+            if (want[turn] != 0) deliver(false);
+        } else if (flat_n >= kJoinFull) {
+            deliver(false);
+        }
+    }
+    deliver(true);
     for (int r = 0; r < rows; ++r)   // rows without a candidate
         if (((touched >> r) & 1u) == 0 && lane < K) {
             p.res_idx[(part0 + r) * K + lane] = -1;
@@ -475,9 +635,11 @@ __global__ __launch_bounds__(256, 2) void join_kernel(JoinParams p)
 // the squared norm of the shifted bytes); an entry past the end of its list never passes a threshold.
 template <int DT>
 __global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map, const JoinList *lists, int32_t n_lists,
-                                 int64_t n_groups, int32_t nk, const uint32_t *norm_all, const float *centre, uint4 *xblk, uint32_t *xnorm)
+                                 int64_t n_groups, int32_t nk, const uint32_t *norm_all, const float *centre, float scale, uint4 *xblk, uint32_t *xnorm,
+                                 uint32_t *bound, int64_t n_bound)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = t; i < n_bound; i += (int64_t)gridDim.x * blockDim.x) bound[i] = 0xFFFFFFFFu;   // of the join that follows
     const int nch = 2 * nk;
     if (t >= n_groups * nch * 32) return;
     const int v = (int)(t & 31);
@@ -504,12 +666,18 @@ __global__ void join_pack_kernel(const char *X, int32_t dim, const int32_t *map,
         float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
         if (valid && c * 8 < dim) x = centred(*(const float4 *)(X + row * dim * 4 + c * 32), centre, 2 * c);
         if (valid && c * 8 + 4 < dim) y = centred(*(const float4 *)(X + row * dim * 4 + c * 32 + 16), centre, 2 * c + 1);
-        const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-        uint4 hi, lo;
-        split_bf16x8(f, hi, lo);
-        xblk[(g * 2 * nch + c) * 32 + v] = hi;
-        xblk[(g * 2 * nch + nch + c) * 32 + v] = lo;
-        if (c == 0) xnorm[g * 32 + v] = valid ? __float_as_uint(0.5f * __uint_as_float(norm_all[row])) : 0x7F800000u;
+        float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+        if (DT == 1) {
+            uint4 hi, lo;
+            split_bf16x8(f, hi, lo);
+            xblk[(g * 2 * nch + c) * 32 + v] = hi;
+            xblk[(g * 2 * nch + nch + c) * 32 + v] = lo;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f[i] *= scale;
+            xblk[(g * nch + c) * 32 + v] = half8(f);
+        }
+        if (c == 0) xnorm[g * 32 + v] = valid ? __float_as_uint(0.5f * __uint_as_float(norm_all[row]) * (scale * scale)) : 0x7F800000u;
     }
 }
 
@@ -550,33 +718,44 @@ __global__ __launch_bounds__(256) void centre_mean_kernel(const float *parts, in
     centre[e] = a / (float)(n < kCentreRows ? n : kCentreRows);
 }
 
+// x rounded to 11 significant bits, as binary16 does within its range
+__device__ __forceinline__ float round_11_bits(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    return __uint_as_float((u + 0xFFFu + ((u >> 13) & 1u)) & ~0x1FFFu);
+}
+
 // One thread per row, elements in ascending order (400,000 x 128: 0.32 ms).
 __global__ __launch_bounds__(256) void row_norm_f32_kernel(const float *X, int32_t dim, int64_t n, const float *centre, uint32_t *out,
                                                            uint32_t *out_c, uint32_t *max_bits)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    float acc = 0.f, acc_c = 0.f;
+    float acc = 0.f, acc_c = 0.f, acc_e = 0.f;
     if (i < n) {
         const float4 *x = (const float4 *)(X + i * dim);
         for (int c = 0; c < dim / 4; ++c) {
             const float4 v = x[c], w = centred(v, centre, c);
             acc += v.x * v.x; acc += v.y * v.y; acc += v.z * v.z; acc += v.w * v.w;
             acc_c += w.x * w.x; acc_c += w.y * w.y; acc_c += w.z * w.z; acc_c += w.w * w.w;
+            const float4 e = make_float4(w.x - round_11_bits(w.x), w.y - round_11_bits(w.y), w.z - round_11_bits(w.z), w.w - round_11_bits(w.w));
+            acc_e += e.x * e.x; acc_e += e.y * e.y; acc_e += e.z * e.z; acc_e += e.w * e.w;
         }
         out[i] = __float_as_uint(acc);
         out_c[i] = __float_as_uint(acc_c);
     }
     // (no norm is negative: their bits are ordered as they are, with NaN of either sign above infinity)
-    uint32_t m = __float_as_uint(acc), m_c = __float_as_uint(acc_c);
+    uint32_t m = __float_as_uint(acc), m_c = __float_as_uint(acc_c), m_e = acc_c > 0.f ? __float_as_uint(acc_e / acc_c) : 0u;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t v = (uint32_t)__shfl_xor((int)m, o), w = (uint32_t)__shfl_xor((int)m_c, o);
+        const uint32_t v = (uint32_t)__shfl_xor((int)m, o), w = (uint32_t)__shfl_xor((int)m_c, o), e = (uint32_t)__shfl_xor((int)m_e, o);
         m = v > m ? v : m;
         m_c = w > m_c ? w : m_c;
+        m_e = e > m_e ? e : m_e;
     }
     if ((threadIdx.x & 63) == 0) {
         atomicMax(max_bits, m);
         atomicMax(max_bits + 1, m_c);
+        atomicMax(max_bits + 2, m_e);
     }
 }
 
@@ -595,62 +774,72 @@ void launch_row_norms_f32(const void *X, int32_t dim, int64_t n, const float *ce
 }
 
 // Contraction steps the kernel is compiled for: the smallest that holds the vector.
-int32_t join_steps(int dtype, int32_t dim)
+static int32_t join_steps(int kind, int32_t dim)
 {
-    const int32_t need = dtype == 0 ? (dim + 31) / 32 : (dim + 15) / 16;
+    const int32_t need = kind == kJoinU8 ? (dim + 31) / 32 : (dim + 15) / 16;
     for (const int32_t nk : {2, 4, 6, 8, 16}) if (need <= nk) return nk;
-    return dtype == 0 && need <= 32 ? 32 : 0;
+    return kind == kJoinU8 && need <= 32 ? 32 : 0;
 }
 
-size_t join_group_bytes(int dtype, int32_t dim)
+size_t join_group_bytes(int kind, int32_t dim)
 {
-    const int32_t nk = join_steps(dtype, dim);
-    return (size_t)(dtype == 0 ? join_chunks<0>(nk) : join_chunks<1>(nk)) * 512;
+    const int32_t nk = join_steps(kind, dim);
+    return (size_t)(kind == kJoinSplit ? join_chunks<1>(nk) : join_chunks<0>(nk)) * 512;
 }
 
-void launch_join_pack(int dtype, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
-                      int64_t n_groups, const uint32_t *norm_all, const float *centre, uint4 *xblk, void *xnorm, hipStream_t s)
+void launch_join_pack(int kind, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
+                      int64_t n_groups, const uint32_t *norm_all, const float *centre, float scale, uint4 *xblk, void *xnorm,
+                      uint32_t *bound, int64_t n_bound, hipStream_t s)
 {
     if (n_groups <= 0) return;
-    const int32_t nk = join_steps(dtype, dim);
-    const unsigned blocks = (unsigned)((n_groups * 2 * nk * 32 + 255) / 256);
-    if (dtype == 0)
-        hipLaunchKernelGGL(join_pack_kernel<0>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, lists, n_lists,
-                           n_groups, nk, norm_all, centre, xblk, (uint32_t *)xnorm);
-    else
-        hipLaunchKernelGGL(join_pack_kernel<1>, dim3(blocks), dim3(256), 0, s, (const char *)X, dim, map, lists, n_lists,
-                           n_groups, nk, norm_all, centre, xblk, (uint32_t *)xnorm);
+    const int32_t nk = join_steps(kind, dim);
+    const dim3 blocks((unsigned)((n_groups * 2 * nk * 32 + 255) / 256)), threads(256);
+#define VF_LAUNCH_PACK(DT_) \
+    hipLaunchKernelGGL(join_pack_kernel<DT_>, blocks, threads, 0, s, (const char *)X, dim, map, lists, n_lists, n_groups, nk, norm_all, \
+                       centre, scale, xblk, (uint32_t *)xnorm, bound, n_bound)
+    if (kind == kJoinU8) VF_LAUNCH_PACK(0);
+    else if (kind == kJoinSplit) VF_LAUNCH_PACK(1);
+    else VF_LAUNCH_PACK(2);
+#undef VF_LAUNCH_PACK
 }
 
-template <int DT, int NK> static void launch_join_nk(const JoinParams &p, int n_items, hipStream_t s)
+template <int DT, int NK, int W> static void launch_join_w(const JoinParams &p, int n_items, hipStream_t s)
 {
-    constexpr int NC = join_chunks<DT>(NK);
-    const size_t lds = (size_t)join_buffers(NC) * NC * 512 + kJoinRows * kJoinQueue * 8;
-    if (p.others_off != nullptr) hipLaunchKernelGGL((join_kernel<DT, NK, true>), dim3(n_items), dim3(256), lds, s, p);
-    else hipLaunchKernelGGL((join_kernel<DT, NK, false>), dim3(n_items), dim3(256), lds, s, p);
+    constexpr size_t lds = join_lds_bytes<DT, NK, W>();
+    if (p.others_off != nullptr) hipLaunchKernelGGL((join_kernel<DT, NK, true, W>), dim3(n_items), dim3(64 * W), lds, s, p);
+    else hipLaunchKernelGGL((join_kernel<DT, NK, false, W>), dim3(n_items), dim3(64 * W), lds, s, p);
 }
 
-void launch_join(int dtype, const JoinParams &p, int n_items, hipStream_t s)
+template <int DT, int NK> static void launch_join_nk(const JoinParams &p, int rows, int n_items, hipStream_t s)
+{
+    if (rows > kJoinRows) launch_join_w<DT, NK, kJoinRowsShared / kJoinRows>(p, n_items, s);
+    else launch_join_w<DT, NK, 1>(p, n_items, s);
+}
+
+template <int DT> static void launch_join_f32(const JoinParams &p, int32_t nk, int rows, int n_items, hipStream_t s)
+{
+    switch (nk) {
+    case 2: launch_join_nk<DT, 2>(p, rows, n_items, s); break;
+    case 4: launch_join_nk<DT, 4>(p, rows, n_items, s); break;
+    case 6: launch_join_nk<DT, 6>(p, rows, n_items, s); break;
+    case 8: launch_join_nk<DT, 8>(p, rows, n_items, s); break;
+    default: launch_join_nk<DT, 16>(p, rows, n_items, s); break;
+    }
+}
+
+void launch_join(int kind, const JoinParams &p, int rows, int n_items, hipStream_t s)
 {
     if (n_items <= 0) return;
-    const int32_t nk = join_steps(dtype, p.dim);
-    if (dtype == 0) {
-        switch (nk) {
-        case 2: launch_join_nk<0, 2>(p, n_items, s); break;
-        case 4: launch_join_nk<0, 4>(p, n_items, s); break;
-        case 6: launch_join_nk<0, 6>(p, n_items, s); break;
-        case 8: launch_join_nk<0, 8>(p, n_items, s); break;
-        case 16: launch_join_nk<0, 16>(p, n_items, s); break;
-        default: launch_join_nk<0, 32>(p, n_items, s); break;
-        }
-    } else {
-        switch (nk) {
-        case 2: launch_join_nk<1, 2>(p, n_items, s); break;
-        case 4: launch_join_nk<1, 4>(p, n_items, s); break;
-        case 6: launch_join_nk<1, 6>(p, n_items, s); break;
-        case 8: launch_join_nk<1, 8>(p, n_items, s); break;
-        default: launch_join_nk<1, 16>(p, n_items, s); break;
-        }
+    const int32_t nk = join_steps(kind, p.dim);
+    if (kind == kJoinSplit) return launch_join_f32<1>(p, nk, rows, n_items, s);
+    if (kind == kJoinSingle) return launch_join_f32<2>(p, nk, rows, n_items, s);
+    switch (nk) {
+    case 2: launch_join_nk<0, 2>(p, rows, n_items, s); break;
+    case 4: launch_join_nk<0, 4>(p, rows, n_items, s); break;
+    case 6: launch_join_nk<0, 6>(p, rows, n_items, s); break;
+    case 8: launch_join_nk<0, 8>(p, rows, n_items, s); break;
+    case 16: launch_join_nk<0, 16>(p, rows, n_items, s); break;
+    default: launch_join_nk<0, 32>(p, rows, n_items, s); break;
     }
 }
 

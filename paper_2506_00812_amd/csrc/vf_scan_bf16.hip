@@ -298,9 +298,9 @@ __global__ __launch_bounds__(64) void scan_rerank_kernel(RerankParams p)
         const uint64_t rest = done_to < cnt ? readlane64(kept, done_to) : list.worst;
         const uint64_t kth = readlane64(key, p.K - 1);
         // (a query with NaN or an overflowing norm has no usable approximations: the plain definition answers it)
-        proven = (all_kept && done_to == cnt && qn <= 3.0e38f) ||
-                 (kth != KEY_MAX && rest != KEY_MAX &&
-                  __uint_as_float((uint32_t)(kth >> 32)) < __uint_as_float((uint32_t)(rest >> 32)) - B);
+        proven = (all_kept && done_to == cnt && qn <= p.q_max) ||
+                 (kth != KEY_MAX && rest != KEY_MAX && qn <= p.q_max &&
+                  __uint_as_float((uint32_t)(kth >> 32)) < p.approx_unit * __uint_as_float((uint32_t)(rest >> 32)) - B);
         if (proven || done_to == cnt) break;
         done_to = done_to + 8 < cnt ? done_to + 8 : cnt;
     }

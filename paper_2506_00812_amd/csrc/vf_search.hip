@@ -333,23 +333,28 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
                         (ix->dtype == VF_U8 || (ix->xc_max > 0.f && ix->tune.scan_bf16 && join_keep >= k + 16));
     if (joined) {
         P.join_keep = join_keep;
+        P.join_kind = ix->join_kind();
         ItemBuilder jb(ix->tune);
-        jb.tile_rows = kJoinRows;
         jb.all_partial = true;
-        int64_t tile_groups = 0;
+        int64_t tile_groups = 0, n_lists = 0;
+        for (size_t i = first_hs; i < r.scan_pairs.size(); ++i) n_lists += i == first_hs || r.scan_pairs[i] >> 32 != r.scan_pairs[i - 1] >> 32;
+        P.join_tile = (int64_t)(r.scan_pairs.size() - first_hs) >= n_lists * 2 * kJoinRowsShared ? kJoinRowsShared : kJoinRows;
+        jb.tile_rows = P.join_tile;
         for (size_t i = first_hs, e; i < r.scan_pairs.size(); i = e) {
             const uint64_t l = r.scan_pairs[i] >> 32;
             for (e = i; e < r.scan_pairs.size() && r.scan_pairs[e] >> 32 == l;) ++e;
-            tile_groups += (int64_t)((e - i + kJoinRows - 1) / kJoinRows) * ((ix->S[(size_t)l] + 31) / 32);
+            tile_groups += (int64_t)((e - i + P.join_tile - 1) / P.join_tile) * ((ix->S[(size_t)l] + 31) / 32);
         }
         // segments: a row's thresholds start over in each, so no more of them than keep the chip busy (two workgroups per
         // CU at a time; three rounds of them level out the last one)
-        jb.seg_groups = jb.seg_groups_heavy = (int)std::max<int64_t>(64, tile_groups / 1536);
-        const int64_t batch_groups = (int64_t)(P.join_bytes / join_group_bytes(ix->dtype, ix->dim));
+        jb.seg_groups = jb.seg_groups_heavy = (int)std::max<int64_t>(64, tile_groups / (P.join_tile == kJoinRows ? 6144 : 1536));
+        const int64_t batch_groups = (int64_t)(P.join_bytes / join_group_bytes(ix->join_kind_max(), ix->dim));
         int64_t groups = 0;
         JoinBatch b{0, 0, 0, 0, 0};
         auto close = [&]() {
             b.list_hi = P.jlists.size(); b.item_hi = jb.items.size(); b.groups = groups;
+            // every tile's first segment before any second one: what the first find bounds the others
+            std::stable_sort(jb.items.begin() + (std::ptrdiff_t)b.item_lo, jb.items.end(), [](const ScanItem &x, const ScanItem &y) { return x.entry0 < y.entry0; });
             P.jbatches.push_back(b);
             P.join_groups = std::max(P.join_groups, groups);
             b.list_lo = b.list_hi; b.item_lo = b.item_hi; groups = 0;
@@ -367,6 +372,10 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         for (ScanItem &it : jb.items) it.q_begin += (int32_t)ls_qrows;
         VF_REQUIRE(jb.part_rows < ((int64_t)1 << 31), "too many partial result rows in one call");
         P.part_words += (size_t)jb.part_rows * join_keep;
+        P.join_bound_at = P.part_words;
+        P.join_first_row = ls_qrows;
+        P.join_rows = jb.qrow.size();
+        P.part_words += P.join_rows;
         P.join_max_nseg = jb.max_nseg;
         ib.qrow.insert(ib.qrow.end(), jb.qrow.begin(), jb.qrow.end());
         ib.items.insert(ib.items.end(), jb.items.begin(), jb.items.end());
@@ -734,6 +743,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 // the bound of the bfloat16 seed proofs (same arithmetic: two bfloat16 products per component into a
                 // float32 accumulator, norms of the unrounded vectors), with the lists' own largest norm and rounding error
                 rp.err_bound = ix->seed_err_bound() * 8.0f; rp.xn_max = ix->ls_xn_max; rp.err_q = 2.0f * ix->ls_bf16_delta;
+                rp.approx_unit = 1.f; rp.q_max = 3.0e38f;
                 rp.fail_count = ix->d_scan_fb.as<uint32_t>();
                 rp.others_off = sp.others_off; rp.others = sp.others; rp.meta = sp.meta;
                 rp.refused = M.refused; rp.refused_any = M.refused_any; rp.refused_count = ix->d_scan_fb.as<int32_t>() + 1;
@@ -757,16 +767,20 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
         }
         if (!P.jbatches.empty()) {
             JoinParams jp{};   // (ix->tmp_blk, tmp_norm: reserved with the plan)
+            const int kind = P.join_kind;
+            const float scale = ix->join_scale(kind);
             jp.xblk = ix->tmp_blk.as<uint4>(); jp.xnorm = ix->tmp_norm.p; jp.map = ix->d_M_HS.as<int32_t>();
-            jp.qsrc = queries; jp.qrow = sp.qrow; jp.dim = ix->dim; jp.K = P.join_keep; jp.centre = ix->d_centre.as<float>();
+            jp.qsrc = queries; jp.qrow = sp.qrow; jp.dim = ix->dim; jp.K = P.join_keep; jp.centre = ix->d_centre.as<float>(); jp.scale = scale;
             jp.res_idx = M.part_idx + P.ls_part_words; jp.res_bits = M.part_bits + P.ls_part_words;
+            uint32_t *bound = M.part_bits + P.join_bound_at;
+            jp.bound = bound; jp.bound_row0 = (int32_t)P.join_first_row;
             jp.others_off = d_others_off; jp.others = d_others; jp.meta = sp.meta;
             for (const JoinBatch &b : P.jbatches) {
-                launch_join_pack(ix->dtype, ix->X, ix->dim, jp.map, (const JoinList *)(dp + L.off_jlists) + b.list_lo,
-                                 (int)(b.list_hi - b.list_lo), b.groups, ix->join_norms(), ix->d_centre.as<float>(), ix->tmp_blk.as<uint4>(),
-                                 ix->tmp_norm.p, s);
+                launch_join_pack(kind, ix->X, ix->dim, jp.map, (const JoinList *)(dp + L.off_jlists) + b.list_lo,
+                                 (int)(b.list_hi - b.list_lo), b.groups, ix->join_norms(), ix->d_centre.as<float>(), scale, ix->tmp_blk.as<uint4>(),
+                                 ix->tmp_norm.p, bound, (int64_t)P.join_rows, s);
                 jp.items = (const ScanItem *)(dp + L.off_items) + P.n_ls_items + b.item_lo;
-                launch_join(ix->dtype, jp, (int)(b.item_hi - b.item_lo), s);
+                launch_join(kind, jp, P.join_tile, (int)(b.item_hi - b.item_lo), s);
             }
             const int n_merges = (int)(ib.merges.size() - P.n_ls_merges);
             if (ix->dtype == VF_U8) {
@@ -776,7 +790,9 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 RerankParams rp{};
                 rp.items = d_merges + P.n_ls_merges; rp.res_idx = jp.res_idx; rp.res_bits = jp.res_bits; rp.map = jp.map;
                 rp.X = ix->X; rp.Q = queries; rp.dim = ix->dim; rp.Kc = P.join_keep; rp.K = k;
-                rp.err_bound = ix->join_err_bound(); rp.xn_max = ix->xc_max; rp.err_q = 0.f; rp.centre = jp.centre;
+                rp.err_bound = ix->join_err_bound(kind); rp.xn_max = ix->xc_max; rp.err_q = ix->join_err_q(kind, false); rp.centre = jp.centre;
+                // (a component beyond binary16 is infinite, and a query with one has no candidates)
+                rp.approx_unit = 1.0f / (scale * scale); rp.q_max = kind == kJoinSingle ? 1.0e9f * rp.approx_unit : 3.0e38f;
                 rp.fail_count = ix->d_scan_fb.as<uint32_t>();
                 rp.others_off = sp.others_off; rp.others = sp.others; rp.meta = sp.meta;
                 rp.refused = M.refused; rp.refused_any = M.refused_any; rp.refused_count = ix->d_scan_fb.as<int32_t>() + 1;
@@ -854,6 +870,9 @@ static int answer_refused(vf_index *ix, const CallPlan &P, const Routed &r, cons
     std::vector<int32_t> which((size_t)n_refused);
     VF_HIP(hipMemcpy(which.data(), M.refused, which.size() * 4, hipMemcpyDeviceToHost));
     std::sort(which.begin(), which.end());   // queries of a list become neighbours, scan lists come first
+    // (joins on operands of twice the bits from now on, where these leave so many without a proof)
+    const auto joined = which.end() - std::lower_bound(which.begin(), which.end(), (int32_t)P.n_ls_merges);
+    if (P.join_kind == kJoinSingle && joined > 64 && (size_t)joined > (P.ib.merges.size() - P.n_ls_merges) / 64) ix->join_single = false;
     const std::vector<MergeItem> &merges = P.ib.merges;
     constexpr size_t kBatch = 4096;          // bounds the partial rows: 64 segments of 64 results each
     DevBuf d_items(&ix->alloc), d_merges(&ix->alloc), d_qrow(&ix->alloc), parts(&ix->alloc);
@@ -957,7 +976,7 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     // Ground truth over joined lists: the packed lists and partial rows before anything is sent.  Where there is no memory
     // for them: smaller batches of lists, down to single ones, and then the scan kernels, whose copies of a list are smaller.
     while (!P.jbatches.empty()) {
-        if ((rc = ix->tmp_blk.reserve((size_t)P.join_groups * join_group_bytes(ix->dtype, ix->dim))) == VF_OK &&
+        if ((rc = ix->tmp_blk.reserve((size_t)P.join_groups * join_group_bytes(ix->join_kind_max(), ix->dim))) == VF_OK &&
             (rc = ix->tmp_norm.reserve((size_t)P.join_groups * 32 * 4)) == VF_OK &&
             (rc = W->dseed.reserve((2 * words_up(P.part_words) + words_up(P.ib.merges.size())) * 4)) == VF_OK)
             break;

@@ -1,5 +1,5 @@
 """The join kernel (self-joins of the index build) at the edges of its tiles: lists around whole groups of 32 entries and
-whole tiles of 128 rows, dimensions around the contraction steps it is compiled for, candidate counts up to its 64."""
+whole tiles of 32 and 128 rows, dimensions around the contraction steps it is compiled for, candidate counts up to its 64."""
 import numpy as np
 import pytest
 
@@ -188,3 +188,52 @@ def test_ground_truth_without_proofs(dim, k, sizes, nq):
             want = np.flatnonzero(carry[:, asked[j]].all(1))[:k]
             assert np.array_equal(ids2[j][:len(want)], want) and (ids2[j][len(want):] == -1).all()
             assert np.isnan(d2[j][:len(want)]).all() if np.isnan(v) else np.isinf(d2[j]).all()
+
+
+@pytest.mark.parametrize("spread,dim,R", [(4, 32, 16), (12, 100, 32), (12, 128, 48), (60, 236, 32)])
+def test_rows_that_binary16_does_not_prove(spread, dim, R):
+    """Clusters so far apart that the rounding of the operands to binary16 hides the order of a row's neighbours: those rows are
+    joined again on split operands, in segments of their lists, a few of them, most, or all."""
+    import torch
+    from tests.gpu_util import assert_close_with_ties, to_np
+    from paper_2506_00812_amd import binding as vf
+    rng = np.random.default_rng(spread + dim)
+    n, sizes = 5000, [4800, 2000, 700]
+    centres = rng.normal(size=(12, dim)) * spread
+    x = (centres[rng.integers(0, 12, n)] + rng.normal(size=(n, dim))).astype(np.float32)
+    labels = [[] for _ in range(n)]
+    for l, size in enumerate(sizes):
+        for i in np.sort(rng.permutation(n)[:size]):
+            labels[i].append(l)
+    off = np.concatenate([[0], np.cumsum([len(v) for v in labels])]).astype(np.int64)
+    ids = np.array([l for v in labels for l in v], dtype=np.int32)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, len(sizes), 600, R)
+    want = OracleIndex(x, off, ids, len(sizes), 600, R)
+    assert np.array_equal(ix.export("G_HS").reshape(-1, R), want.G_HS)
+    q = (centres[rng.integers(0, 12, 260)] + rng.normal(size=(260, dim))).astype(np.float32)
+    qoff, qids = np.arange(261), (np.arange(260) % 3).astype(np.int32)
+    for k in (1, 25):
+        gi, gd = vf.search_exact(ix, torch.from_numpy(q).cuda(), qoff, qids, k)
+        wi, wd = want.search(q, qoff, qids, k, force_scan=True)
+        assert_close_with_ties(to_np(gi), to_np(gd), wi, wd, 1e-4, f"k {k}")
+
+
+def test_long_lists_are_tried_before_they_are_joined():
+    """A list long enough that a few of its rows decide which operands the join takes, near clusters and far ones: the rows are
+    those of the scan kernels."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    n, dim, R = 66_000, 32, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    off, ids = np.arange(n + 1, dtype=np.int64), np.zeros(n, dtype=np.int32)
+    for spread in (2.0, 40.0):
+        centres = torch.randn((500, dim), generator=g, device="cuda") * spread
+        x = centres[torch.randint(0, 500, (n,), generator=g, device="cuda")] + torch.randn((n, dim), generator=g, device="cuda")
+        got = vf.build_index(x, off, ids, 1, 1000, R).export("G_HS")
+        vf.tune_defaults("build16", 0)
+        try:
+            want = vf.build_index(x, off, ids, 1, 1000, R).export("G_HS")
+        finally:
+            vf.tune_defaults("build16", 1)
+        assert np.array_equal(got, want), f"clusters {spread} apart"

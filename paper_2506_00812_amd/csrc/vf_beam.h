@@ -159,6 +159,41 @@ __device__ __forceinline__ void merge_sorted_run(TopM<1> &list, uint64_t key, in
     list.worst = readlane64(m, list.itopk - 1);
 }
 
+// Keys held one per lane (the lanes of m) into a list of at most 64 entries, all at once: a key's place is the number of
+// entries and of keys below it, an entry moves by the number of keys below it.  Per key two broadcasts and a few compares
+// that wait for nothing, where one insertion after the other is a chain of about thirty instructions each; then everything
+// goes through `scratch` (LDS, 64 words) to its place.  Returns false, with nothing done, if a key is in the list already or
+// came twice (a vertex that the visited table has forgotten): the caller inserts one by one.
+template <bool WAVE_ONLY> __device__ __forceinline__ bool insert_by_rank(TopM<1> &list, uint64_t m, uint64_t key, uint64_t *scratch, int lane)
+{
+    const bool in = (m >> lane) & 1ull;
+    const uint64_t have = list.cur[0], mine = in ? key : KEY_MAX;
+    const uint64_t open = have | 1ull;   // (as a key that is offered would have it)
+    int below = 0, at = 0;               // keys not above the entry; the key's place
+    uint64_t twice = 0;
+    for (uint64_t rest = m; rest;) {
+        const int b = __builtin_ctzll(rest);
+        rest &= rest - 1;
+        const uint64_t s = readlane64(mine, b);
+        const bool less = have < s;
+        const uint64_t entries = __ballot(less), keys = __ballot(mine < s), same = __ballot(mine == s);
+        twice |= __ballot(open == s) | (same & (same - 1));
+        below += less ? 0 : 1;
+        if (lane == b) at = __popcll(entries) + __popcll(keys);
+    }
+    if (twice != 0) return false;
+    wave_sync<WAVE_ONLY>();
+    scratch[lane] = KEY_MAX;
+    wave_sync<WAVE_ONLY>();
+    if (have != KEY_MAX && lane + below < list.itopk) scratch[lane + below] = have;
+    if (in && at < list.itopk) scratch[at] = key;
+    wave_sync<WAVE_ONLY>();
+    list.cur[0] = scratch[lane];
+    list.worst = readlane64(list.cur[0], list.itopk - 1);
+    wave_sync<WAVE_ONLY>();
+    return true;
+}
+
 // Offers the keys held one per lane (distance bits, id; distinct and none of them in the list yet) to a
 // one-register list: many at once through a sort and merge, a few one by one.
 __device__ __forceinline__ void offer_distinct(TopM<1> &list, bool valid, uint32_t bits, int id, int lane)
@@ -368,7 +403,16 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
             list.insert(((uint64_t)kb << 32) | ((uint64_t)kc << 1) | 1ull, lane);
         }
     };
-    auto offer = [&](bool valid, uint32_t bits, int c) { offer_to(top, valid, bits, c); };
+    // (cand_g is free: the candidates' vectors have been read)
+    auto offer = [&](bool valid, uint32_t bits, int c) {
+        if constexpr (E == 1) {
+            const uint64_t m = __ballot(valid && bits <= (uint32_t)(top.worst >> 32));
+            if (__popcll(m) >= 3 &&
+                insert_by_rank<STREAM_SEEDS>(top, m, ((uint64_t)bits << 32) | ((uint64_t)(uint32_t)c << 1) | 1ull, (uint64_t *)cand_g, lane))
+                return;
+        }
+        offer_to(top, valid, bits, c);
+    };
     // Seeds are distinct and offered once, so many of them can enter a list in one merge.
     auto offer_seeds_to = [&](TopM<1> &list, bool valid, uint32_t bits, int c) {
         const bool in = valid && bits <= (uint32_t)(list.worst >> 32);

@@ -200,7 +200,7 @@ __device__ __forceinline__ int lanes_before(uint64_t m)
 __host__ __device__ constexpr int join_waves(int dt, int nk) { return dt == 1 || nk > 8 ? 2 : nk > 6 ? 3 : 4; }
 
 // Operand chunks in flight: the steps of a group that are requested together.
-template <int DT> __host__ __device__ constexpr int join_prefetch(int nk) { return DT == 1 ? (nk < 4 ? nk : 4) : nk <= 4 ? nk : nk == 6 ? 3 : 4; }
+__host__ __device__ constexpr int join_prefetch(int nk) { return nk <= 4 ? nk : nk == 6 ? 3 : 4; }
 
 // LDS buffers of one group of nc chunks: two where they leave room for other workgroups on the CU
 __host__ __device__ constexpr int join_buffers(int nc) { return nc <= 32 ? 2 : 1; }
@@ -220,7 +220,8 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
     using acc_t = typename JoinAcc<DT>::type;
     using val_t = typename JoinAcc<DT>::scalar;
     typedef val_t val4_t __attribute__((ext_vector_type(4)));
-    constexpr int NC = join_chunks<DT>(NK), NPRE = join_prefetch<DT>(NK), STAGE = NC * 32;
+    constexpr int NC = join_chunks<DT>(NK), NPRE = join_prefetch(NK), STAGE = NC * 32;
+    static_assert(NK % NPRE == 0, "whole requests");
     constexpr int NBUF = W > 1 ? join_buffers(NC) : 0, NL = (STAGE + 64 * W - 1) / (64 * W);
     const ScanItem it = p.items[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, n32 = lane & 31, h = lane >> 5;

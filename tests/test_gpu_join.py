@@ -190,7 +190,7 @@ def test_ground_truth_without_proofs(dim, k, sizes, nq):
             assert np.isnan(d2[j][:len(want)]).all() if np.isnan(v) else np.isinf(d2[j]).all()
 
 
-@pytest.mark.parametrize("spread,dim,R", [(4, 32, 16), (12, 100, 32), (12, 128, 48), (60, 236, 32)])
+@pytest.mark.parametrize("spread,dim,R", [(4, 32, 16), (12, 64, 16), (12, 96, 32), (0, 80, 16), (12, 100, 32), (12, 128, 48), (60, 236, 32)])
 def test_rows_that_binary16_does_not_prove(spread, dim, R):
     """Clusters so far apart that the rounding of the operands to binary16 hides the order of a row's neighbours: those rows are
     joined again on split operands, in segments of their lists, a few of them, most, or all."""
@@ -201,6 +201,8 @@ def test_rows_that_binary16_does_not_prove(spread, dim, R):
     n, sizes = 5000, [4800, 2000, 700]
     centres = rng.normal(size=(12, dim)) * spread
     x = (centres[rng.integers(0, 12, n)] + rng.normal(size=(n, dim))).astype(np.float32)
+    if spread == 0:                                     # equal points: no operands prove anything
+        x = np.repeat(x[:50], 100, axis=0)
     labels = [[] for _ in range(n)]
     for l, size in enumerate(sizes):
         for i in np.sort(rng.permutation(n)[:size]):

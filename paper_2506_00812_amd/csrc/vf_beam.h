@@ -611,7 +611,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     auto select_seeds = [&](TopM<1> &list, const uint32_t *drow, bool as_index) -> int {
         constexpr int NBLK = VF_SEED_BLOCKS;
         int done_to = 0;
-        if constexpr (!LAT && !STREAM_SEEDS && (DT == 0 || !AND)) {   // (few queries have no minima; float32 with a predicate: no registers)
+        if constexpr (!STREAM_SEEDS && (DT == 0 || !AND)) {   // (float32 with a predicate: no registers)
             if (bq.dmin_row != nullptr && o_cnt == 0) {
                 if (select_by_blocks(list, drow, as_index)) return ns;
                 list.init(list.itopk);   // (whatever it has offered is offered again)

@@ -488,12 +488,12 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
             i = e;
         }
     }
-    // The minima of the seeds' blocks, where the seed kernel runs with 512 seeds per wave (a lane then writes 16 of them in a
-    // row) and enough queries can use them: no predicate, and three blocks per kept seed or more (fewer: most blocks would
-    // be read anyway).  50,000 uint8 queries with 16,384 seeds: seed kernel 805 -> 825 us, beam kernel 1,561 -> 1,260; 10,000
-    // float32 queries with 6,144 seeds: 107 -> 115 and 269 -> 221 us.
-    if (P.seeds_mfma && !P.seed_select && !P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || !r.any_and) &&
-        (int64_t)P.tiles.size() * ((P.ns_stride + 4 * kSeedMfmaChunk - 1) / (4 * kSeedMfmaChunk)) >= 512) {
+    // The minima of the seeds' blocks, where the seeds come from their copy and enough queries can use them: no predicate, and
+    // three blocks per kept seed or more (fewer: most blocks would be read anyway).  50,000 uint8 queries with 16,384 seeds:
+    // seed kernel 805 -> 825 us, beam kernel 1,561 -> 1,260; 10,000 float32 queries with 6,144 seeds: 107 -> 115 and 269 ->
+    // 221 us; a lone query, whose wave otherwise goes through
+    // the whole row by itself, 74 -> 65 us, 64 queries 109 -> 103.
+    if (P.seeds_mfma && !P.seed_select && !P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || !r.any_and)) {
         const int32_t keep = ix->dtype == VF_U8 ? itopk : std::min(64, itopk + std::max(tune.seed_margin_bf16, tune.seed_margin));
         const int32_t stride = (P.ns_stride / 32 + 15) & ~15;
         if (P.ns_stride / 32 >= 3 * keep && 2 * and_queries() <= (int64_t)P.n_gq && budget.fits((uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride)) {
@@ -686,7 +686,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                     // 32 seeds, its four groups' serial chain of MFMAs cut to one
                     if ((int64_t)P.tiles.size() * ((P.ns_stride + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 256) sd.chunk_seeds = 32;
                     sd.max_chunks = (P.ns_stride + sd.chunk_seeds - 1) / sd.chunk_seeds;
-                    if (P.nb_stride > 0 && sd.chunk_seeds == 4 * kSeedMfmaChunk) {
+                    if (P.nb_stride > 0) {
                         sd.dmin = M.dseed + n_gq * (size_t)P.ns_stride + 64 * 1024;   // (behind the matrix and its dump area)
                         sd.nb_stride = P.nb_stride;
                         bp.dmin = sd.dmin; bp.nb_stride = sd.nb_stride;

@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
 #pragma unroll
     for (int jj = 0; jj < 16; ++jj) qn[jj] = qnorm_s[8 * (jj >> 2) + 4 * h + (jj & 3)];
 
-    uint32_t gmin[NG >= 16 ? NG : 1];   // per group: smallest value of row row_of(n32 & 15, h), see group_min
+    uint32_t gmin[CACHED ? NG : 1];   // per group: smallest value of row row_of(n32 & 15, h), see group_min
     uint4 bnext[NCP];
     auto fetch_group = [&](int g) {   // group g of this wave's seeds (exists)
         if (cached) {
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
                 bits[jj] = __float_as_uint(fmaxf(d, 0.0f));
             }
         }
-        if constexpr (NG >= 16) gmin[g] = p.dmin != nullptr ? group_min(bits, j0 + g * 32 + n32 < ns, n32) : 0u;
+        if constexpr (CACHED) gmin[g] = p.dmin != nullptr ? group_min(bits, j0 + g * 32 + n32 < ns, n32) : 0u;
         // Every lane stores every value, those without a (query, seed) pair into a dump area behind the
         // matrix: with the stores under conditions the compiler cannot count them, and its wait for the next
         // group's operand loads becomes a wait for these stores to be acknowledged as well.  The dump area has
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
             *dst = bits[jj];
         }
     }
-    if constexpr (NG >= 16) {
+    if constexpr (CACHED) {
         // lane (n32 < 16, h) has row 8 (n32 / 4) + 4 h + n32 % 4: its groups' minima are consecutive words
         const int row = 8 * ((n32 & 15) >> 2) + 4 * h + (n32 & 3);
         if (p.dmin != nullptr && n32 < 16 && row < t.q_count) {

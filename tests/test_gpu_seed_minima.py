@@ -40,3 +40,31 @@ def test_block_minima_change_nothing(dtype, dim, noise, itopk, n_seeds, pairs):
     ix.tune("seed_exact", 1)     # every seed's ordered distance, no matrix cores, no minima
     want = vf.search(ix, Q, qoff, qids, 10, **params)
     assert_exact(to_np(got[0]), to_np(got[1]), to_np(want[0]), to_np(want[1]), "block minima")
+
+
+@pytest.mark.parametrize("nq", [1, 33, 500, 1500])
+@pytest.mark.parametrize("dtype,dim,noise", [("uint8", 192, 12), ("float32", 128, 1), ("float32", 96, 0)])
+def test_block_minima_of_small_batches(dtype, dim, noise, nq):
+    """One, four and sixteen groups of seeds per wave, searches by the latency and the throughput kernel; a seed count that ends
+    within a block."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_exact, to_np
+    rng = np.random.default_rng(nq + dim)
+    n = 20_000
+    centres = rng.normal(size=(40, dim)) * (30 if dtype == "uint8" else 2) + (128 if dtype == "uint8" else 0)
+
+    def points(count):
+        x = centres[rng.integers(0, 40, count)] + rng.normal(size=(count, dim)) * noise
+        return np.rint(x).clip(0, 255).astype(np.uint8) if dtype == "uint8" else x.astype(np.float32)
+
+    carry = rng.random((n, 3)) < np.array([0.95, 0.5, 0.2])
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    ids = np.nonzero(carry)[1].astype(np.int32)
+    Q, qoff, qids = torch.from_numpy(points(nq)).cuda(), np.arange(nq + 1), rng.integers(0, 3, nq).astype(np.int32)
+    ix = vf.build_index(torch.from_numpy(points(n)).cuda(), off, ids, 3, 1500, 16)
+    params = dict(itopk=16, width=2, iters=4, n_seeds=5003)
+    got = vf.search(ix, Q, qoff, qids, 10, **params)
+    ix.tune("seed_exact", 1)
+    want = vf.search(ix, Q, qoff, qids, 10, **params)
+    assert_exact(to_np(got[0]), to_np(got[1]), to_np(want[0]), to_np(want[1]), "block minima")

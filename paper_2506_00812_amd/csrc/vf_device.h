@@ -156,64 +156,91 @@ __device__ __forceinline__ uint64_t wave_shr1_64(uint64_t v)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Ascending bitonic sort of the 64 values held one per lane.
-__device__ __forceinline__ uint32_t wave_sort_u32(uint32_t v, int lane)
+// ---------------------------------------------------------------- sorting networks over the lanes of a wave
+
+// Lanes that keep the smaller key when keys at distance J are compared inside ascending (descending: DESC) blocks of K.
+template <int K, int J, bool LAST, bool DESC> __host__ __device__ constexpr uint64_t keep_min_lanes()
 {
-#pragma unroll
-    for (int k = 2; k <= 64; k <<= 1) {
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const uint32_t o = (uint32_t)__shfl_xor((int)v, j);
-            const bool up = k == 64 ? true : (lane & k) == 0;
-            const bool take_min = ((lane & j) == 0) == up;
-            const uint32_t mn = v < o ? v : o, mx = v < o ? o : v;
-            v = take_min ? mn : mx;
+    uint64_t m = 0;
+    for (int l = 0; l < 64; ++l) {
+        const bool up = (LAST || (l & K) == 0) != DESC;
+        if (((l & J) == 0) == up) m |= 1ull << l;
+    }
+    return m;
+}
+
+// a, b: the keys of a lane and of its partner at lane ^ J (J = 1, 2, 4, 8: a is the lane's own key; J = 16, 32: a is
+// the key of the partner whose bit J is clear, in both lanes)
+template <int J> __device__ __forceinline__ void lane_pair(uint32_t v, uint32_t &a, uint32_t &b)
+{
+    static_assert(J == 1 || J == 2 || J == 4 || J == 8 || J == 16 || J == 32, "J is a power of two below 64");
+    if constexpr (J == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        a = r[0]; b = r[1];
+    } else if constexpr (J == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = r[0]; b = r[1];
+    } else {
+        a = v;
+        if constexpr (J == 1) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);        // quad_perm [1,0,3,2]
+        else if constexpr (J == 2) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+        else if constexpr (J == 8) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
+        else {
+            const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);                         // row_half_mirror
+            b = (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, true);                               // quad_perm [3,2,1,0]
         }
     }
-    return v;
 }
 
-// Ascending sort of a bitonic sequence of 64 values held one per lane.
-__device__ __forceinline__ uint32_t wave_merge_u32(uint32_t v, int lane)
+// One compare-exchange stage of 32-bit values (a float is no NaN): the lanes of MIN keep the smaller value of the pair
+// (lane, lane ^ J), the others the larger.
+template <int J, uint64_t MIN, class V> __device__ __forceinline__ V lane_exchange_32(V v)
 {
-#pragma unroll
-    for (int j = 32; j > 0; j >>= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)v, j);
-        const uint32_t mn = v < o ? v : o, mx = v < o ? o : v;
-        v = (lane & j) == 0 ? mn : mx;
-    }
-    return v;
+    uint32_t ab, bb;
+    lane_pair<J>(__builtin_bit_cast(uint32_t, v), ab, bb);
+    const V a = __builtin_bit_cast(V, ab), b = __builtin_bit_cast(V, bb);
+    const V lo = a < b ? a : b, hi = a < b ? b : a;
+    return __builtin_amdgcn_inverse_ballot_w64(MIN) ? lo : hi;
 }
 
-// The same two networks for 64-bit keys.
-__device__ __forceinline__ uint64_t wave_sort64(uint64_t v, int lane)
+// ... of 64-bit keys, one set by itself: both results of the comparison are selected by it and the wanted one by a constant,
+// so that no stage waits for the scalar unit.
+template <int J, uint64_t MIN> __device__ __forceinline__ uint64_t lane_exchange_lone(uint64_t v)
 {
-#pragma unroll
-    for (int k = 2; k <= 64; k <<= 1) {
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const uint32_t lo = __shfl_xor((uint32_t)v, j), hi = __shfl_xor((uint32_t)(v >> 32), j);
-            const uint64_t o = ((uint64_t)hi << 32) | lo;
-            const bool up = k == 64 ? true : (lane & k) == 0;
-            const bool take_min = ((lane & j) == 0) == up;
-            const uint64_t mn = v < o ? v : o, mx = v < o ? o : v;
-            v = take_min ? mn : mx;
-        }
-    }
-    return v;
+    uint32_t al, bl, ah, bh;
+    lane_pair<J>((uint32_t)v, al, bl);
+    lane_pair<J>((uint32_t)(v >> 32), ah, bh);
+    const uint64_t a = ((uint64_t)ah << 32) | al, b = ((uint64_t)bh << 32) | bl;
+    const bool less = a < b;
+    const uint64_t lo = less ? a : b, hi = less ? b : a;
+    return __builtin_amdgcn_inverse_ballot_w64(MIN) ? lo : hi;
 }
 
-__device__ __forceinline__ uint64_t wave_merge64(uint64_t v, int lane)
+template <int K, int J> __device__ __forceinline__ uint32_t wave_stages(uint32_t v)
 {
-#pragma unroll
-    for (int j = 32; j > 0; j >>= 1) {
-        const uint32_t lo = __shfl_xor((uint32_t)v, j), hi = __shfl_xor((uint32_t)(v >> 32), j);
-        const uint64_t o = ((uint64_t)hi << 32) | lo;
-        const uint64_t mn = v < o ? v : o, mx = v < o ? o : v;
-        v = (lane & j) == 0 ? mn : mx;
-    }
-    return v;
+    v = lane_exchange_32<J, keep_min_lanes<K, J, K == 64, false>()>(v);
+    if constexpr (J > 1) return wave_stages<K, J / 2>(v);
+    else return v;
 }
+template <int K, int J> __device__ __forceinline__ uint64_t wave_stages(uint64_t v)
+{
+    v = lane_exchange_lone<J, keep_min_lanes<K, J, K == 64, false>()>(v);
+    if constexpr (J > 1) return wave_stages<K, J / 2>(v);
+    else return v;
+}
+template <int K, class T> __device__ __forceinline__ T wave_sort_from(T v)
+{
+    v = wave_stages<K, K / 2>(v);
+    if constexpr (K < 64) return wave_sort_from<2 * K>(v);
+    else return v;
+}
+
+// Ascending bitonic sort of the 64 values held one per lane, and ascending sort of a bitonic sequence of them; every move on
+// the vector ALU: through ds_bpermute each of the 21 (6) stages waits for an LDS access.
+__device__ __forceinline__ uint32_t wave_sort_u32(uint32_t v, int) { return wave_sort_from<2>(v); }
+__device__ __forceinline__ uint32_t wave_merge_u32(uint32_t v, int) { return wave_stages<64, 32>(v); }
+__device__ __forceinline__ uint64_t wave_sort64(uint64_t v, int) { return wave_sort_from<2>(v); }
+__device__ __forceinline__ uint64_t wave_merge64(uint64_t v, int) { return wave_stages<64, 32>(v); }
 
 // Bitonic sort of keys[0..n) ascending in LDS by one wave; n a power of two.
 __device__ __forceinline__ void wave_bitonic_sort(uint64_t *keys, int n, int lane)

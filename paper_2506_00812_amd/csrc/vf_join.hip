@@ -91,44 +91,8 @@ __device__ __forceinline__ uint4 half8(const float (&f)[8])
 // Bitonic networks over 64-bit keys held one per lane, every cross-lane move on the vector ALU: lane ^ 1, 2, 4, 8 are
 // DPP moves (xor 4 = the mirror of 8 lanes, then the mirror of 4), lane ^ 16 and ^ 32 the row swaps of gfx950, which
 // leave both partners' keys in both lanes.  Which lanes keep the smaller key of a stage is a constant, so a stage is two
-// moves, one compare, one scalar xor of its result with that constant, and two selects; through ds_bpermute (the usual
-// shuffle) it is two LDS accesses and twice the selects.  They pay where several sets run at a time, as here; a lone
-// chain waits for every stage's trip through the scalar unit (in the beam search: a lone query 92 -> 97 us), so the
-// search kernels keep the shuffles.
-
-// Lanes that keep the smaller key when keys at distance J are compared inside ascending (descending: DESC) blocks of K.
-template <int K, int J, bool LAST, bool DESC> __host__ __device__ constexpr uint64_t keep_min_lanes()
-{
-    uint64_t m = 0;
-    for (int l = 0; l < 64; ++l) {
-        const bool up = (LAST || (l & K) == 0) != DESC;
-        if (((l & J) == 0) == up) m |= 1ull << l;
-    }
-    return m;
-}
-
-// a, b: the keys of a lane and of its partner at lane ^ J (J = 1, 2, 4, 8: a is the lane's own key; J = 16, 32: a is
-// the key of the partner whose bit J is clear, in both lanes)
-template <int J> __device__ __forceinline__ void lane_pair(uint32_t v, uint32_t &a, uint32_t &b)
-{
-    static_assert(J == 1 || J == 2 || J == 4 || J == 8 || J == 16 || J == 32, "J is a power of two below 64");
-    if constexpr (J == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        a = r[0]; b = r[1];
-    } else if constexpr (J == 32) {
-        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        a = r[0]; b = r[1];
-    } else {
-        a = v;
-        if constexpr (J == 1) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);        // quad_perm [1,0,3,2]
-        else if constexpr (J == 2) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
-        else if constexpr (J == 8) b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
-        else {
-            const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);                         // row_half_mirror
-            b = (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, true);                               // quad_perm [3,2,1,0]
-        }
-    }
-}
+// moves, one compare, one scalar xor of its result with that constant, and two selects.  Several sets run at a time here,
+// which hides the trip through the scalar unit; a lone chain (lane_exchange_lone in vf_device.h) selects twice instead.
 
 // One compare-exchange stage: the lanes of MIN keep the smaller key of the pair (lane, lane ^ J), the others the larger.
 template <int J, uint64_t MIN> __device__ __forceinline__ uint64_t lane_exchange(uint64_t v)
@@ -140,15 +104,7 @@ template <int J, uint64_t MIN> __device__ __forceinline__ uint64_t lane_exchange
     return __builtin_amdgcn_inverse_ballot_w64(__builtin_amdgcn_ballot_w64(a < b) ^ ~MIN) ? a : b;
 }
 
-// ... and of 32-bit values (a float is no NaN)
-template <int J, uint64_t MIN, class V> __device__ __forceinline__ V lane_exchange_32(V v)
-{
-    uint32_t ab, bb;
-    lane_pair<J>(__builtin_bit_cast(uint32_t, v), ab, bb);
-    const V a = __builtin_bit_cast(V, ab), b = __builtin_bit_cast(V, bb);
-    const V lo = a < b ? a : b, hi = a < b ? b : a;
-    return __builtin_amdgcn_inverse_ballot_w64(MIN) ? lo : hi;
-}
+// ... and of 32-bit values
 template <int J, uint64_t MIN> __device__ __forceinline__ float lane_exchange(float v) { return lane_exchange_32<J, MIN>(v); }
 template <int J, uint64_t MIN> __device__ __forceinline__ int lane_exchange(int v) { return lane_exchange_32<J, MIN>(v); }
 

@@ -222,10 +222,10 @@ def main():
                             "achieved_lower_bound": round(knn_flops / build_s / 1e12, 1),
                             "note": "whole vf_build_index call, host work included"},
     }
-    # graph lists and self-joins run as three products of split bfloat16 operands (uint8: one int8 product), so a useful
-    # flop is priced at a third of the dense bfloat16 peak, 2.5 PFLOP/s
+    # graph lists and self-joins run as one product of binary16 operands (three of split bfloat16 ones on tables where that
+    # does not prove the rows; uint8: one int8 product): priced at the dense 16-bit peak, 2.5 PFLOP/s
     if s.dtype == "float32":
-        mfma_peak = dense["peak"] = round(2500.0 / 3, 1)
+        mfma_peak = dense["peak"] = 2500.0
     dense["ground_truth"]["frac"] = round(dense["ground_truth"]["achieved"] / mfma_peak, 4)
     dense["index_build_knn"]["frac"] = round(dense["index_build_knn"]["achieved_lower_bound"] / mfma_peak, 4)
     log(f"[bench] exact filtered ground truth in {time.time() - t0:.1f}s")

@@ -188,7 +188,7 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     auto selected = [&](int kd, const std::vector<int32_t> &sel, int32_t *unproven) -> int {
         int rc = upload(d_sel, sel, s);
         if (rc != VF_OK) return rc;
-        const int tile = sel.size() > 4096 ? kJoinRowsShared : kJoinRows;
+        const int tile = join_tile_rows(kd, ix->dim, sel.size() > 4096);
         const int64_t most = std::min<int64_t>(n_rows / (int64_t)sel.size(), 1024 / (int64_t)(sel.size() / tile + 1));
         const int32_t nseg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, most));
         std::vector<ScanItem> part;

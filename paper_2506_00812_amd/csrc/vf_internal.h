@@ -175,6 +175,7 @@ struct JoinList {
 };
 
 size_t join_group_bytes(int kind, int32_t dim);   // packed bytes of a group of 32 vectors
+int join_tile_rows(int kind, int32_t dim, bool many);   // rows of an item, kJoinRows or kJoinRowsShared; many: there are enough rows to fill the larger ones
 // n_groups: of all n_lists lists together; bound[0 .. n_bound) is set to "nothing found"
 void launch_join_pack(int kind, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
                       int64_t n_groups, const uint32_t *norm_all, const float *centre, float scale, uint4 *xblk, void *xnorm,

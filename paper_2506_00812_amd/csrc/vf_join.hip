@@ -138,7 +138,10 @@ constexpr int kJoinMerge = 10;   // a row with as many of them is merged when it
 constexpr int kJoinFlat = 128;   // candidates on their way to the rows' queues (two rows of a group add up to 64)
 constexpr int kJoinFull = 64;    // as many of them make the waves of a workgroup deliver together
 constexpr int kJoinWaveLds = 32 * kJoinQueue * 8 + kJoinFlat * 8 + 32 * 4 + 32 * 4 + kJoinFlat;   // bytes of a wave
-constexpr int kJoinSample = 64;  // groups that are looked at first, for a row's first threshold
+// Groups that are looked at first, for a row's first threshold; a quarter of them where the rows and what is kept of each
+// are so few (kJoinFew keys in all) that reading 64 groups twice costs more than the candidates it saves (a lone query over a
+// list of 300,000 x 128, segments of 147 groups, split operands: 371 -> 341 us).
+constexpr int kJoinSample = 64, kJoinSampleFew = 16, kJoinFew = 128;
 
 template <int DT> struct JoinAcc { using type = v16f_join; using scalar = float; };
 template <> struct JoinAcc<0> { using type = v16i_join; using scalar = int; };
@@ -155,8 +158,13 @@ __device__ __forceinline__ int lanes_before(uint64_t m)
 // Waves per SIMD that the registers are shared out for.
 __host__ __device__ constexpr int join_waves(int dt, int nk) { return dt == 1 || nk > 8 ? 2 : nk > 6 ? 3 : 4; }
 
-// Operand chunks in flight: the steps of a group that are requested together.
-__host__ __device__ constexpr int join_prefetch(int nk) { return nk <= 4 ? nk : nk == 6 ? 3 : 4; }
+// Operand chunks in flight: the steps of a group that are requested together.  A wave that reads split operands by itself has
+// the registers for a whole group.
+__host__ __device__ constexpr int join_prefetch(int dt, int nk, int w) { return nk <= 4 || (w == 1 && dt == 1) ? nk : nk == 6 ? 3 : 4; }
+
+// Steps whose row operand lies in LDS: 32 steps leave no registers for the last ones, and a reload from scratch memory in the
+// loop over the groups waits for the next group's loads as well (a lone query over 300,000 x 960 uint8: 515 -> 415 us).
+__host__ __device__ constexpr int join_lds_steps(int nk) { return nk == 32 ? 2 : 0; }
 
 // LDS buffers of one group of nc chunks: two where they leave room for other workgroups on the CU
 __host__ __device__ constexpr int join_buffers(int nc) { return nc <= 32 ? 2 : 1; }
@@ -164,7 +172,7 @@ __host__ __device__ constexpr int join_buffers(int nc) { return nc <= 32 ? 2 : 1
 template <int DT, int NK, int W> constexpr size_t join_lds_bytes()
 {
     constexpr int NC = join_chunks<DT>(NK);
-    return (size_t)(W > 1 ? join_buffers(NC) * NC * 512 + 16 : 0) + (size_t)W * kJoinWaveLds;
+    return (size_t)(W > 1 ? join_buffers(NC) * NC * 512 + 16 : 0) + (size_t)W * (kJoinWaveLds + join_lds_steps(NK) * 1024);
 }
 
 // NK: contraction steps (16 components of float32, 32 of uint8), the vectors zero padded to them.  W: waves of a workgroup,
@@ -176,7 +184,7 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
     using acc_t = typename JoinAcc<DT>::type;
     using val_t = typename JoinAcc<DT>::scalar;
     typedef val_t val4_t __attribute__((ext_vector_type(4)));
-    constexpr int NC = join_chunks<DT>(NK), NPRE = join_prefetch(NK), STAGE = NC * 32;
+    constexpr int NC = join_chunks<DT>(NK), NPRE = join_prefetch(DT, NK, W), STAGE = NC * 32;
     static_assert(NK % NPRE == 0, "whole requests");
     constexpr int NBUF = W > 1 ? join_buffers(NC) : 0, NL = (STAGE + 64 * W - 1) / (64 * W);
     const ScanItem it = p.items[blockIdx.x];
@@ -191,6 +199,8 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
     val_t *tvs = (val_t *)(pending + 32);                      // [32] the rows' thresholds: read per group, they would be 16 registers
     uint8_t *flat_row = (uint8_t *)(tvs + 32);                 // a candidate's row; kTaken: gone to the row's queue, or not wanted
     int *want = (int *)((char *)(smem + NBUF * STAGE) + W * kJoinWaveLds);   // [3], the groups' in turn: a wave wants to deliver
+    constexpr int NR = NK - join_lds_steps(NK);                // steps whose row operand is in registers
+    uint4 *late = (uint4 *)((char *)(smem + NBUF * STAGE) + W * kJoinWaveLds + 16) + wave * (NK - NR) * 64;   // [NK - NR][64 lanes]
     constexpr uint32_t kTaken = 255;
     int flat_n = 0;
 
@@ -202,7 +212,7 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
         qr = p.qrow[at];
         if (it.self_base >= 0) self = p.sel != nullptr ? at - it.self_base : it.self_base + row_base + n32;
     }
-    uint4 a[NK], alo[DT == 1 ? NK : 1];
+    uint4 a[NR], alo[DT == 1 ? NK : 1];
     val_t qnorm = 0;
     {
         const char *qp = (const char *)p.qsrc + (int64_t)(qr >= 0 ? qr : 0) * (p.dim * (DT == 0 ? 1 : 4));
@@ -215,7 +225,8 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
                     v = *(const uint4 *)(qp + c * 16);
                     v.x ^= 0x80808080u; v.y ^= 0x80808080u; v.z ^= 0x80808080u; v.w ^= 0x80808080u;
                 }
-                a[s] = v;
+                if (s < NR) a[s < NR ? s : 0] = v;
+                else late[(s - NR) * 64 + lane] = v;   // (each lane reads its own)
                 const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) qnorm = __builtin_amdgcn_sdot4((int)w[i], (int)w[i], qnorm, false);
@@ -440,7 +451,8 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
             if constexpr (DT == 0) {
 #pragma unroll
                 for (int u = 0; u < NPRE; ++u) {
-                    const v4i_join av = {(int)a[s0 + u].x, (int)a[s0 + u].y, (int)a[s0 + u].z, (int)a[s0 + u].w};
+                    const uint4 ar = s0 + u < NR ? a[s0 + u < NR ? s0 + u : 0] : late[(s0 + u - NR) * 64 + lane];
+                    const v4i_join av = {(int)ar.x, (int)ar.y, (int)ar.z, (int)ar.w};
                     acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av, __builtin_bit_cast(v4i_join, b[u]), acc, 0, 0, 0);
                 }
             } else if constexpr (DT == 2) {
@@ -479,7 +491,8 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
     // those 64 (K + 1 where the row itself may be among them) has K entries at or above it.  Without this a row's first
     // thousand entries make a queue's worth of candidates every few groups.
     const int rank = K - (it.self_base >= 0 ? 0 : 1);
-    const int sample = n_groups / 2 < kJoinSample ? n_groups / 2 : kJoinSample;
+    const int most = it.q_count * K < kJoinFew ? kJoinSampleFew : kJoinSample;
+    const int sample = n_groups / 2 < most ? n_groups / 2 : most;
     if (sample >= 8 && rank < 64 && (W > 1 || __any(n32 < rows && !filtered && !(tv > first)))) {
         val_t top[2][16];
 #pragma unroll
@@ -738,6 +751,14 @@ static int32_t join_steps(int kind, int32_t dim)
     return kind == kJoinU8 && need <= 32 ? 32 : 0;
 }
 
+// Steps up to which one wave reads a list by itself where its rows are few.  Beyond them a group is 16 KB and more, and four
+// waves that load a quarter each are ahead for any number of rows, a single one included (a lone query and 100 over a list of
+// 300,000: uint8 of 512 components 400 / 425 us by one wave, 288 / 356 by four; float32 of 248, split 866 / 1,017 and 705 /
+// 1,001).
+constexpr int32_t kJoinAloneSteps = 8;
+
+int join_tile_rows(int kind, int32_t dim, bool many) { return many || join_steps(kind, dim) > kJoinAloneSteps ? kJoinRowsShared : kJoinRows; }
+
 size_t join_group_bytes(int kind, int32_t dim)
 {
     const int32_t nk = join_steps(kind, dim);
@@ -769,8 +790,10 @@ template <int DT, int NK, int W> static void launch_join_w(const JoinParams &p, 
 
 template <int DT, int NK> static void launch_join_nk(const JoinParams &p, int rows, int n_items, hipStream_t s)
 {
-    if (rows > kJoinRows) launch_join_w<DT, NK, kJoinRowsShared / kJoinRows>(p, n_items, s);
-    else launch_join_w<DT, NK, 1>(p, n_items, s);
+    if constexpr (NK <= kJoinAloneSteps) {
+        if (rows <= kJoinRows) return launch_join_w<DT, NK, 1>(p, n_items, s);
+    }
+    launch_join_w<DT, NK, kJoinRowsShared / kJoinRows>(p, n_items, s);
 }
 
 template <int DT> static void launch_join_f32(const JoinParams &p, int32_t nk, int rows, int n_items, hipStream_t s)

@@ -349,7 +349,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         jb.all_partial = true;
         int64_t tile_groups = 0, n_lists = 0;
         for (size_t i = first_hs; i < r.scan_pairs.size(); ++i) n_lists += i == first_hs || r.scan_pairs[i] >> 32 != r.scan_pairs[i - 1] >> 32;
-        P.join_tile = (int64_t)(r.scan_pairs.size() - first_hs) >= n_lists * 2 * kJoinRowsShared ? kJoinRowsShared : kJoinRows;
+        P.join_tile = join_tile_rows(P.join_kind, ix->dim, (int64_t)(r.scan_pairs.size() - first_hs) >= n_lists * 2 * kJoinRowsShared);
         jb.tile_rows = P.join_tile;
         for (size_t i = first_hs, e; i < r.scan_pairs.size(); i = e) {
             const uint64_t l = r.scan_pairs[i] >> 32;

@@ -239,3 +239,51 @@ def test_long_lists_are_tried_before_they_are_joined():
         finally:
             vf.tune_defaults("build16", 1)
         assert np.array_equal(got, want), f"clusters {spread} apart"
+
+
+def _table(dtype, dim, n, sizes, spread, seed):
+    """Clustered points with some equal ones, posting lists of the given sizes, and a function that draws more points."""
+    rng = np.random.default_rng(seed)
+    centres = rng.normal(size=(16, dim)) * (30 if dtype == "uint8" else spread) + (128 if dtype == "uint8" else 0)
+
+    def points(count):
+        x = centres[rng.integers(0, 16, count)] + rng.normal(size=(count, dim)) * (12 if dtype == "uint8" else 1)
+        return np.rint(x).clip(0, 255).astype(np.uint8) if dtype == "uint8" else x.astype(np.float32)
+
+    x = points(n)
+    x[100:130] = x[7]
+    carry = np.zeros((n, len(sizes)), dtype=bool)
+    for l, size in enumerate(sizes):
+        carry[rng.permutation(n)[:size], l] = True
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    return x, off, np.nonzero(carry)[1].astype(np.int32), points
+
+
+def _check_exact(ix, ixo, q, asked, k, what):
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_close_with_ties, assert_exact, to_np
+    qoff = np.concatenate([[0], np.cumsum([len(a) for a in asked])]).astype(np.int64)
+    qids = np.array([l for a in asked for l in a], dtype=np.int32)
+    gi, gd = vf.search_exact(ix, torch.from_numpy(q).cuda(), qoff, qids, k)
+    oi, od = ixo.search(q, qoff, qids, k, force_scan=True)
+    (assert_exact if q.dtype == np.uint8 else lambda *a: assert_close_with_ties(*a[:4], 1e-4, a[4]))(to_np(gi), to_np(gd), oi, od, what)
+
+
+@pytest.mark.parametrize("dtype,dim,spread", [("float32", 100, 2), ("float32", 96, 60), ("float32", 128, 60), ("float32", 132, 2), ("float32", 244, 60),
+                                              ("uint8", 256, 0), ("uint8", 272, 0), ("uint8", 528, 0), ("uint8", 976, 0), ("uint8", 992, 0)])
+def test_few_queries_of_long_lists(dtype, dim, spread):
+    """Lone queries and a few: lists of one wave and, from 16 steps of the contraction on, of four; operands in registers and,
+    of the last of 32 steps, in LDS; segments whose first thresholds come from a few groups, from many and from none."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    sizes = [9000, 1030, 530, 500]
+    x, off, ids, points = _table(dtype, dim, 9500, sizes, spread, dim)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, len(sizes), 200, 16)
+    ixo = OracleIndex(x, off, ids, len(sizes), 200, 16, lazy_graph=True)
+    q = points(12)
+    q[1] = x[7]
+    for k, counts in ((1, (1, 6)), (5, (1, 5, 12)), (24, (1, 2, 6))):
+        for nq in counts:
+            _check_exact(ix, ixo, q[:nq], [[0]] * nq, k, f"{nq} queries, k {k}")
+        _check_exact(ix, ixo, q, [[0], [1], [2], [3], [0, 1], [2, 3], [1, 2]] + [[0]] * 3 + [[1]] * 2, k, f"several lists, k {k}")

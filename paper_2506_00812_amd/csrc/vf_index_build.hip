@@ -113,6 +113,8 @@ void free_index(vf_index *ix)
     delete ix;
 }
 
+constexpr int kLookRows = 256;   // rows that tell which operands a batch of self-joins takes, 32 of each of the eight longest lists
+
 // Exact kNN rows of the graph lists graph_labels[lo, hi), which lie one after the other in M_HS: pack them, contract every
 // list against itself in one launch (vf_join.hip; a list of a few thousand vectors alone would leave most of the chip
 // idle), keep K candidates per vertex and order `deg` of them into rows_out (per list [|C_l|][deg] local ids).
@@ -140,13 +142,14 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     // the tiles of the longest lists first: they take the longest
     std::stable_sort(items.begin(), items.end(), [](const ScanItem &a, const ScanItem &b) { return a.n > b.n; });
     int rc;
-    DevBuf d_lists(&ix->alloc), d_unproven(&ix->alloc), d_sel(&ix->alloc);
-    DevBufGuard rel{&d_lists, &d_unproven, &d_sel};
+    DevBuf d_lists(&ix->alloc), d_unproven(&ix->alloc);
+    DevBufGuard rel{&d_lists, &d_unproven};
     if ((rc = upload(d_lists, lists, s)) != VF_OK) return rc;
     const int32_t *map = ix->d_M_HS.as<int32_t>();
     const int64_t n_rows = ix->O_HS[(size_t)ix->graph_labels[hi - 1]] + ix->S[(size_t)ix->graph_labels[hi - 1]] - base0;
     int kind = ix->join_kind();
-    if (kind == kJoinSingle && (rc = d_unproven.reserve((size_t)(n_rows + 1) * 4)) != VF_OK) {   // how many rows have no proof, and which
+    const int64_t sel_at = 1 + n_rows;   // d_unproven: how many rows have no proof, which, and those that are joined again
+    if (kind == kJoinSingle && (rc = d_unproven.reserve((size_t)(sel_at + std::max<int64_t>(n_rows, kLookRows)) * 4)) != VF_OK) {
         if (rc != VF_ENOMEM) return rc;
         (void)hipGetLastError();
         kind = kJoinSplit;
@@ -184,10 +187,10 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         return VF_OK;
     };
     // The rows of sel (ascending, of any lists).  Few rows do not fill the chip with whole lists: as many segments as do,
-    // and as the candidates' buffer has room for.
+    // and as the candidates' buffer has room for.  VF_ENOMEM (for the items): nothing was launched.
     auto selected = [&](int kd, const std::vector<int32_t> &sel, int32_t *unproven) -> int {
-        int rc = upload(d_sel, sel, s);
-        if (rc != VF_OK) return rc;
+        int rc;
+        int32_t *d_sel = d_unproven.as<int32_t>() + sel_at;
         const int tile = join_tile_rows(kd, ix->dim, sel.size() > 4096);
         const int64_t most = std::min<int64_t>(n_rows / (int64_t)sel.size(), 1024 / (int64_t)(sel.size() / tile + 1));
         const int32_t nseg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, most));
@@ -216,9 +219,10 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         first.push_back(at);
         std::stable_sort(part.begin(), part.end(), [](const ScanItem &a, const ScanItem &b) { return a.n > b.n; });
         if ((rc = upload(d_items, part, s)) != VF_OK) return rc;
-        join(kd, d_sel.as<int32_t>(), tile, (int)part.size());
+        VF_HIP(hipMemcpyAsync(d_sel, sel.data(), sel.size() * 4, hipMemcpyHostToDevice, s));
+        join(kd, d_sel, tile, (int)part.size());
         for (size_t i = lo; i < hi; ++i)
-            rows(kd, i, (int64_t)first[i - lo], d_sel.as<int32_t>() + first[i - lo], (int64_t)(first[i - lo + 1] - first[i - lo]), nseg,
+            rows(kd, i, (int64_t)first[i - lo], d_sel + first[i - lo], (int64_t)(first[i - lo + 1] - first[i - lo]), nseg,
                  (int64_t)sel.size(), unproven);
         VF_HIP(hipStreamSynchronize(s));
         return VF_OK;
@@ -235,12 +239,15 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         std::stable_sort(by_size.begin(), by_size.end(), [&](size_t a, size_t b) { return lists[a].n > lists[b].n; });
         std::vector<int32_t> sel;
         for (size_t u = 0; u < std::min<size_t>(8, by_size.size()); ++u)
-            for (int32_t r = 0; r < 32; ++r)
-                sel.push_back((int32_t)(lists[by_size[u]].src - base0 + (int64_t)lists[by_size[u]].n * r / 32));
+            for (int32_t r = 0; r < kLookRows / 8; ++r)
+                sel.push_back((int32_t)(lists[by_size[u]].src - base0 + (int64_t)lists[by_size[u]].n * r / (kLookRows / 8)));
         std::sort(sel.begin(), sel.end());
         VF_HIP(hipMemsetAsync(d_unproven.p, 0, 4, s));
         int32_t count = 0;
-        if ((rc = selected(kind, sel, d_unproven.as<int32_t>())) != VF_OK || (rc = fetch_count(count)) != VF_OK) return rc;
+        rc = selected(kind, sel, d_unproven.as<int32_t>());
+        if (rc == VF_OK) rc = fetch_count(count);
+        if (rc != VF_OK && rc != VF_ENOMEM) return rc;
+        if (rc == VF_ENOMEM) (void)hipGetLastError();   // (no look then)
         if ((size_t)count > sel.size() / 16) {
             ix->join_single = false;
             pack(kind = kJoinSplit);
@@ -260,7 +267,14 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
             VF_HIP(hipMemcpy(sel.data(), d_unproven.as<int32_t>() + 1, sel.size() * 4, hipMemcpyDeviceToHost));
             std::sort(sel.begin(), sel.end());
             pack(kJoinSplit);
-            if ((rc = selected(kJoinSplit, sel, nullptr)) != VF_OK) return rc;
+            rc = selected(kJoinSplit, sel, nullptr);
+            if (rc == VF_ENOMEM) {   // each by its wave, from every entry of its list
+                (void)hipGetLastError();
+                for (size_t i = lo; i < hi; ++i)
+                    rows(kJoinSingle, i, ix->O_HS[(size_t)ix->graph_labels[i]] - base0, nullptr, ix->S[(size_t)ix->graph_labels[i]], 1, 0, nullptr);
+            } else if (rc != VF_OK) {
+                return rc;
+            }
             if ((int64_t)count > n_rows / 64) ix->join_single = false;
         }
     }

@@ -176,6 +176,47 @@ def test_little_memory_takes_smaller_batches(vf, dtype, dim, limit):
         assert (to_np(gi) == to_np(wi)).mean() > 0.99
 
 
+@pytest.mark.parametrize("spread,dim", [(6.0, 32), (8.0, 96), (10.0, 96), (12.0, 96), (40.0, 64)])
+def test_rows_joined_again_need_no_memory(vf, spread, dim):
+    """Rows that binary16 operands do not prove are joined again from what the build holds already, or computed by their waves:
+    an allocator that gives a table of far clusters (some of the rows, most, all without a proof) as many pieces as one of near
+    clusters takes is enough for it, and the rows are the same."""
+    import torch
+    rng = np.random.default_rng(5)
+    n, sizes, T, R = 5000, [4800, 2000, 700], 600, 32
+    carry = np.zeros((n, 3), dtype=bool)
+    for l, size in enumerate(sizes):
+        carry[rng.permutation(n)[:size], l] = True
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    ids = np.nonzero(carry)[1].astype(np.int32)
+
+    def build(spread, most):
+        x = rng0.normal(size=(12, dim))[rng0.integers(0, 12, n)] * spread + rng0.normal(size=(n, dim))
+        X = torch.from_numpy(x.astype(np.float32)).cuda()
+        al = vf.TorchAllocator(X.device)
+        inner, al.asked = al._alloc_cb, 0
+
+        def counting(nbytes, ctx):
+            al.asked += 1
+            return inner(nbytes, ctx) if al.asked <= most else None
+        al.cb = vf.ALLOC_FN(counting)
+        al.struct = vf.VfAllocator(al.cb, al._free_cb, None)
+        real = vf.TorchAllocator
+        vf.TorchAllocator = lambda device: al
+        try:
+            return vf.build_index(X, off, ids, 3, T, R).export("G_HS"), al.asked
+        finally:
+            vf.TorchAllocator = real
+
+    rng0 = np.random.default_rng(6)
+    _, pieces = build(1.0, 1 << 30)
+    rng0 = np.random.default_rng(6)
+    want, _ = build(spread, 1 << 30)
+    rng0 = np.random.default_rng(6)
+    got, _ = build(spread, pieces)
+    assert np.array_equal(got, want)
+
+
 def test_streams_with_different_seed_counts_overlap_safely(vf):
     """Calls on different streams may use different n_seeds at the same time: each seed count has its own
     interleaved copy of the seeds, so a call never overwrites what another stream's seed kernel is reading.

@@ -191,7 +191,9 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     auto selected = [&](int kd, const std::vector<int32_t> &sel, int32_t *unproven) -> int {
         int rc;
         int32_t *d_sel = d_unproven.as<int32_t>() + sel_at;
-        const int tile = join_tile_rows(kd, ix->dim, sel.size() > 4096);
+        // (few rows are a matter of latency, most of it a wave's selection: 32 rows of a list of 60,000 x 128, K = 48, by 64 items
+        // of 32 rows 351 us, by 256 of 8 118)
+        const int waves = join_tile_rows(kd, ix->dim, sel.size() > 4096), tile = sel.size() <= kLookRows ? 8 : waves;
         const int64_t most = std::min<int64_t>(n_rows / (int64_t)sel.size(), 1024 / (int64_t)(sel.size() / tile + 1));
         const int32_t nseg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, most));
         std::vector<ScanItem> part;
@@ -220,7 +222,7 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         std::stable_sort(part.begin(), part.end(), [](const ScanItem &a, const ScanItem &b) { return a.n > b.n; });
         if ((rc = upload(d_items, part, s)) != VF_OK) return rc;
         VF_HIP(hipMemcpyAsync(d_sel, sel.data(), sel.size() * 4, hipMemcpyHostToDevice, s));
-        join(kd, d_sel, tile, (int)part.size());
+        join(kd, d_sel, waves, (int)part.size());
         for (size_t i = lo; i < hi; ++i)
             rows(kd, i, (int64_t)first[i - lo], d_sel + first[i - lo], (int64_t)(first[i - lo + 1] - first[i - lo]), nseg,
                  (int64_t)sel.size(), unproven);
@@ -229,11 +231,13 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     };
     pack(kind);
     // Where a batch takes milliseconds: would binary16 prove its rows?  32 rows of each of the eight longest lists, whose
-    // neighbours are closest together, tell (300,000 x 128, clusters ten times as far apart as they are wide, most rows
-    // without a proof: build 64 ms without this look, 52 with split operands from the start; the look takes 0.3).
+    // neighbours are closest together, tell.  The look takes 0.2 ms; not looking costs tables of far clusters a join that
+    // proves little and then the one that does: 60,000 x 128, clusters twelve times as far apart as they are wide, build
+    // 9.6 ms without, 5.4 with it (near clusters 4.5 and 4.7); 300,000, ten times as far: 64 and 52 ms.  At 30,000 (9e8 pairs)
+    // the table of far clusters still does as well without.
     double pairs = 0;
     for (const JoinList &l : lists) pairs += (double)l.n * l.n;
-    if (kind == kJoinSingle && pairs > 4e9) {
+    if (kind == kJoinSingle && pairs > 1.5e9) {
         std::vector<size_t> by_size(lists.size());
         for (size_t i = 0; i < by_size.size(); ++i) by_size[i] = i;
         std::stable_sort(by_size.begin(), by_size.end(), [&](size_t a, size_t b) { return lists[a].n > lists[b].n; });
@@ -262,7 +266,13 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     if (kind == kJoinSingle) {
         int32_t count = 0;
         if ((rc = fetch_count(count)) != VF_OK) return rc;
-        if (count > 0) {   // those once more, with operands that keep twice the bits
+        if ((int64_t)count > n_rows / 2) {   // all once more, with operands that keep twice the bits: most have to be, and need not be listed
+            pack(kJoinSplit);
+            join(kJoinSplit, nullptr, kJoinRowsShared, (int)items.size());
+            for (size_t i = lo; i < hi; ++i)
+                rows(kJoinSplit, i, ix->O_HS[(size_t)ix->graph_labels[i]] - base0, nullptr, ix->S[(size_t)ix->graph_labels[i]], 1, 0, nullptr);
+            ix->join_single = false;
+        } else if (count > 0) {   // those once more
             std::vector<int32_t> sel((size_t)count);
             VF_HIP(hipMemcpy(sel.data(), d_unproven.as<int32_t>() + 1, sel.size() * 4, hipMemcpyDeviceToHost));
             std::sort(sel.begin(), sel.end());

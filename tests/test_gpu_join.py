@@ -241,6 +241,30 @@ def test_long_lists_are_tried_before_they_are_joined():
         assert np.array_equal(got, want), f"clusters {spread} apart"
 
 
+
+def test_rows_of_several_lists_are_tried():
+    """The same with three lists whose pairs together make a look worth its time; clusters so far apart that half the rows or
+    all have no proof, where everything is joined again, and near ones."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    n, dim, R, sizes = 40_000, 36, 24, [30_007, 20_000, 16_001]
+    rng = np.random.default_rng(8)
+    carry = np.zeros((n, 3), dtype=bool)
+    for l, size in enumerate(sizes):
+        carry[rng.permutation(n)[:size], l] = True
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    ids = np.nonzero(carry)[1].astype(np.int32)
+    for spread in (1.5, 12.0, 50.0):
+        centres = rng.normal(size=(300, dim)) * spread
+        x = torch.from_numpy((centres[rng.integers(0, 300, n)] + rng.normal(size=(n, dim))).astype(np.float32)).cuda()
+        got = vf.build_index(x, off, ids, 3, 1000, R).export("G_HS")
+        vf.tune_defaults("build16", 0)
+        try:
+            want = vf.build_index(x, off, ids, 3, 1000, R).export("G_HS")
+        finally:
+            vf.tune_defaults("build16", 1)
+        assert np.array_equal(got, want), f"clusters {spread} apart"
+
 def _table(dtype, dim, n, sizes, spread, seed):
     """Clustered points with some equal ones, posting lists of the given sizes, and a function that draws more points."""
     rng = np.random.default_rng(seed)

@@ -215,7 +215,9 @@ int vf_search_noalloc(vf_index *index, const void *queries, int64_t nq, const in
  *
  *   k, itopk, width, iters, n_seeds   as in vf_search, fixed for the session; itopk <= 64.  A worker scores its
  *                  query's seeds itself (no batch to share a dense seed kernel with), its waves each a share
- *   n_workers      worker workgroups, 0 = 240 (every workgroup of the kernel must fit on the chip at once)
+ *   n_workers      worker workgroups, at most 1,023; 0 = 240.  No more run than fit on 240 of the 256 compute units.
+ *                  float32 workers of 8 or 4 waves take a compute unit each: kernels of more than a few workgroups
+ *                  (vf_search on the same GPU) run beside up to 223 of them, beside more they wait for the session's end
  *   waves_per_worker  waves of a worker, 1, 4 or 8; 0 = 8.  All of them score seeds or scan the list, the first one searches
  *   ring_slots     jobs that may be in flight or unread, 0 = 1024
  *   max_jobs       the kernel ends after this many jobs, 0 = no limit

@@ -365,12 +365,30 @@ static void free_server(vf_server *sv)
     delete sv;
 }
 
-template <int DT, int NC> static void launch_serve(const ServeParams &p, int n_workers, int waves, size_t lds, hipStream_t s)
+// No more workers than are resident on all compute units but kServeFreeCus.  A session that fills the chip lets nothing else
+// run until it ends: workers of 256 registers (float32) take a compute unit's whole register file, and a caller who then waits
+// for a copy of up to 16 KiB, which is a kernel (12 KiB beside 255 workers: until the idle bound; beside 240 0.2 ms), submits
+// nothing more until the session has ended by itself.  A worker that is not resident does nothing for the session either: job
+// numbers are drawn by running workers only.
+constexpr int kServeFreeCus = 16;
+
+template <int DT, int NC, int NW> static int launch_serve_nw(const ServeParams &p, int n_workers, size_t lds, hipStream_t s)
 {
-    const dim3 grid(1 + n_workers);
-    if (waves == 1) hipLaunchKernelGGL((serve_kernel<DT, NC, 1>), grid, dim3(64), lds, s, p);
-    else if (waves == 4) hipLaunchKernelGGL((serve_kernel<DT, NC, 4>), grid, dim3(256), lds, s, p);
-    else hipLaunchKernelGGL((serve_kernel<DT, NC, 8>), grid, dim3(512), lds, s, p);
+    int per_cu = 0, dev = 0, cus = 0;
+    VF_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, serve_kernel<DT, NC, NW>, 64 * NW, lds));
+    VF_HIP(hipGetDevice(&dev));
+    VF_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int most = std::max(1, per_cu * std::max(1, cus - kServeFreeCus));
+    hipLaunchKernelGGL((serve_kernel<DT, NC, NW>), dim3(1 + std::min(n_workers, most)), dim3(64 * NW), lds, s, p);
+    VF_HIP(hipGetLastError());
+    return VF_OK;
+}
+
+template <int DT, int NC> static int launch_serve(const ServeParams &p, int n_workers, int waves, size_t lds, hipStream_t s)
+{
+    if (waves == 1) return launch_serve_nw<DT, NC, 1>(p, n_workers, lds, s);
+    if (waves == 4) return launch_serve_nw<DT, NC, 4>(p, n_workers, lds, s);
+    return launch_serve_nw<DT, NC, 8>(p, n_workers, lds, s);
 }
 
 static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server **out)
@@ -387,7 +405,6 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     const int32_t waves = prm->waves_per_worker > 0 ? prm->waves_per_worker : 8;
     VF_REQUIRE(waves == 1 || waves == 4 || waves == 8, "waves_per_worker must be 1, 4 or 8 (0 = 8)");
     const int32_t ring_slots = prm->ring_slots > 0 ? prm->ring_slots : 1024;
-    // every workgroup must be resident at once (a CU takes several)
     VF_REQUIRE(n_workers >= 1 && n_workers <= 1023, "n_workers must be in [1, 1023]");
     VF_REQUIRE(ring_slots >= 1 && ring_slots <= (1 << 20), "ring_slots must be in [1, 2^20]");
     const int64_t max_jobs = prm->max_jobs > 0 ? prm->max_jobs : ((int64_t)1 << 62);
@@ -455,15 +472,15 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     p.max_jobs = max_jobs; p.idle_polls = idle_polls; p.lds_kernels = (int32_t)lds_kernels; p.lds_own = (int32_t)lds_own; p.lds_scan = (int32_t)scan_lds;
     const size_t lds = lds_kernels + lds_own + lds_share;
     if (ix->dtype == VF_U8) {
-        if (ix->dim == 128) launch_serve<0, 4>(p, n_workers, waves, lds, sv->stream);
-        else if (ix->dim == 192) launch_serve<0, 6>(p, n_workers, waves, lds, sv->stream);
-        else launch_serve<0, 0>(p, n_workers, waves, lds, sv->stream);
+        if (ix->dim == 128) rc = launch_serve<0, 4>(p, n_workers, waves, lds, sv->stream);
+        else if (ix->dim == 192) rc = launch_serve<0, 6>(p, n_workers, waves, lds, sv->stream);
+        else rc = launch_serve<0, 0>(p, n_workers, waves, lds, sv->stream);
     } else {
-        if (ix->dim == 128) launch_serve<1, 32>(p, n_workers, waves, lds, sv->stream);
-        else if (ix->dim == 96) launch_serve<1, 24>(p, n_workers, waves, lds, sv->stream);
-        else launch_serve<1, 0>(p, n_workers, waves, lds, sv->stream);
+        if (ix->dim == 128) rc = launch_serve<1, 32>(p, n_workers, waves, lds, sv->stream);
+        else if (ix->dim == 96) rc = launch_serve<1, 24>(p, n_workers, waves, lds, sv->stream);
+        else rc = launch_serve<1, 0>(p, n_workers, waves, lds, sv->stream);
     }
-    VF_HIP(hipGetLastError());
+    if (rc != VF_OK) return rc;
     sv->launched = true;
     guard.sv = nullptr;
     *out = sv;

@@ -179,3 +179,30 @@ def test_jobs_are_handed_over_once_each(vf, tiny, ring_slots, n_workers, waves, 
             assert np.array_equal(got_i, to_np(ref_i)) and np.array_equal(got_d, to_np(ref_d))
     finally:
         assert srv.end() == (2 * nq, 1)
+
+
+@pytest.mark.parametrize("waves,n_workers", [(8, 1023), (4, 1023), (1, 1023), (8, 256), (8, 223)])
+def test_other_work_runs_beside_a_session_of_many_workers(vf, waves, n_workers):
+    """float32 workers take a compute unit's whole register file: however many are asked for, a copy that is a kernel (up to
+    16 KiB) still runs beside them, with up to 223 larger kernels too, and the session goes on.  (What cannot run waits for the
+    idle bound, and the session is over.)"""
+    import torch
+    w = make_workload("c2", n=12_000, nq=64, n_labels=20, n_clusters=16, T=800, graph_degree=16)
+    s = w.spec
+    X = torch.from_numpy(w.vectors).cuda()
+    ix = vf.build_index(X, w.label_offsets, w.label_ids, s.n_labels, s.T, s.graph_degree)
+    words = torch.ones(512 * 1024, device="cuda")
+    words.add_(1)
+    torch.cuda.synchronize()
+    srv = vf.Server(ix, 10, n_workers=n_workers, waves_per_worker=waves, ring_slots=64, idle_polls=200_000, itopk=32, width=1, iters=6, n_seeds=64)
+    try:
+        first = srv.run(w.queries, w.qlabel_offsets, w.qlabel_ids, in_flight=64)
+        for i in range(3):
+            if n_workers == 223:
+                words.add_(1)
+            assert (words[:3072].cpu() == (3 + i if n_workers == 223 else 2)).all()
+        again = srv.run(w.queries, w.qlabel_offsets, w.qlabel_ids, in_flight=64)
+        assert np.array_equal(first[0], again[0]) and np.array_equal(first[1], again[1])
+    finally:
+        done, why = srv.end()
+    assert (done, why) == (2 * s.nq, 1)

@@ -36,6 +36,7 @@ namespace vf {
 
 constexpr int kServeHdr = 64;    // bytes of a job slot before the query vector
 constexpr int kReadyBytes = 64;  // behind a device slot: its ready word, in a cache line of its own
+constexpr int kServeQuickPolls = 64;   // the dispatcher's, after a job, with a short sleep between them
 constexpr int kServeSleep = 16;  // s_sleep between a waiting worker's polls, 64 cycles each
 
 struct ServeJobHdr {            // first kServeHdr bytes of a job slot (host ring and device ring)
@@ -138,7 +139,7 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
         // ---------------- dispatcher (the first wave; it never meets a workgroup barrier)
         if (wv != 0) return;
         uint64_t published = 0, beat = 0;
-        int64_t idle = 0;
+        int64_t idle = -kServeQuickPolls;
         uint32_t reason = 0;
         while (reason == 0) {
             // lane 0 reads the counter, lane 1 the stop word: one trip across PCIe
@@ -152,12 +153,10 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
                     __hip_atomic_store(serve_ready(p, j), j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 published = upto;
                 if (lane == 0) __hip_atomic_store(&p.hctrl->published, published, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                idle = 0;
+                idle = -kServeQuickPolls;
             } else {
-                ++idle;
-                // (a poll without a new job takes about as long as before once a session has paused for a while, so that
-                // idle_polls of them do too)
-                if (idle > 64) __builtin_amdgcn_s_sleep(100);
+                // (quick polls are not counted: one that is counted takes about 4 us, whatever the bound)
+                if (++idle > 0) __builtin_amdgcn_s_sleep(100);
                 else __builtin_amdgcn_s_sleep(4);
             }
             if ((++beat & 15u) == 0 && lane == 0) __hip_atomic_store(&p.dctrl->beat, beat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

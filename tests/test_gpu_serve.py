@@ -206,3 +206,28 @@ def test_other_work_runs_beside_a_session_of_many_workers(vf, waves, n_workers):
     finally:
         done, why = srv.end()
     assert (done, why) == (2 * s.nq, 1)
+
+
+def test_a_small_idle_bound_outlasts_short_pauses(vf, tiny):
+    """A counted poll takes a few microseconds from the first one on: 64 of them are longer than pauses of 130 us between jobs,
+    also where polls are quick at first."""
+    import torch
+    s = tiny.spec
+    X = torch.from_numpy(tiny.vectors).cuda()
+    ix = vf.build_index(X, tiny.label_offsets, tiny.label_ids, s.n_labels, s.T, s.graph_degree)
+    lasted = False
+    for _ in range(20):   # (the host may be held up for longer than that)
+        srv = vf.Server(ix, 10, itopk=32, width=1, iters=4, n_seeds=64, n_workers=8, ring_slots=64, idle_polls=64)
+        try:
+            for _ in range(12):
+                srv.submit(tiny.queries[0], [int(tiny.qlabel_ids[0])])
+                t0 = time.perf_counter()
+                while time.perf_counter() - t0 < 130e-6:
+                    pass
+            lasted = True
+        except vf.VecflowError as e:
+            assert "ended" in str(e)
+        srv.end()
+        if lasted:
+            break
+    assert lasted

@@ -224,7 +224,7 @@ int vf_search_noalloc(vf_index *index, const void *queries, int64_t nq, const in
  *   idle_polls     the kernel ends after this many consecutive polls of the job ring without a new job
  *                  (a poll takes about four microseconds; the first 64 after a job, about one each, are not counted),
  *                  0 = 2,000,000: every wave leaves on its own, the session need not be ended for the GPU to become
- *                  free again
+ *                  free again.  Jobs submitted before that are finished
  * The index must outlive the session and must not be freed before vf_serve_end.  One host thread at a time may
  * submit; any thread may poll.
  *

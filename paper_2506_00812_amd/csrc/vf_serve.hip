@@ -168,8 +168,14 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
         __threadfence();   // the ready words and the tail before the flag
         if (lane == 0) __hip_atomic_store(&p.dctrl->stop, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         // the session's exit record is complete once every published job is done: bounded wait for the workers
-        int64_t spins = 0;
-        while (load_dev(&p.dctrl->jobs_done) < published && spins < 16 * p.idle_polls + 1024) { ++spins; __builtin_amdgcn_s_sleep(32); }
+        // (counted from the last of them that was done: one worker may have a queue of jobs before it)
+        uint64_t done = load_dev(&p.dctrl->jobs_done);
+        for (int64_t spins = 0; done < published && spins < 16 * p.idle_polls + 1024; ++spins) {
+            __builtin_amdgcn_s_sleep(32);
+            const uint64_t now = load_dev(&p.dctrl->jobs_done);
+            if (now != done) spins = 0;
+            done = now;
+        }
         if (lane == 0) {
             p.hctrl->jobs_done = load_dev(&p.dctrl->jobs_done);
             __hip_atomic_store(&p.hctrl->exit_reason, reason, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -231,3 +231,26 @@ def test_a_small_idle_bound_outlasts_short_pauses(vf, tiny):
         if lasted:
             break
     assert lasted
+
+
+def test_jobs_submitted_before_the_idle_bound_are_finished(vf, tiny):
+    """One worker with a queue of jobs, which take longer together than the dispatcher's own last wait: all are done."""
+    import torch
+    s = tiny.spec
+    X = torch.from_numpy(tiny.vectors).cuda()
+    ix = vf.build_index(X, tiny.label_offsets, tiny.label_ids, s.n_labels, s.T, s.graph_degree)
+    nq, off = 256, tiny.qlabel_offsets
+    for _ in range(20):   # (the host may be held up for longer than the idle bound while it submits)
+        srv = vf.Server(ix, 10, itopk=64, width=1, iters=30, n_seeds=64, n_workers=1, waves_per_worker=1, ring_slots=nq, idle_polls=300)
+        jobs = []
+        try:
+            for j in range(nq):
+                jobs.append(srv.submit(tiny.queries[j], tiny.qlabel_ids[off[j]:off[j + 1]].tolist()))
+        except vf.VecflowError as e:
+            assert "ended" in str(e)
+        got = _wait(srv, jobs)
+        done, why = srv.end()
+        assert len(got) == done == len(jobs) and why in (1, 3)
+        if done == nq:
+            return
+    pytest.fail("the host was held up every time")

@@ -205,11 +205,11 @@ int vf_search_noalloc(vf_index *index, const void *queries, int64_t nq, const in
 
 /*
  * Queue-driven serving of single queries (the persistent kernel of Section 4.2.3).  vf_serve_begin launches ONE
- * kernel that stays resident for the session: a dispatcher wave watches a job ring in pinned host memory and
- * feeds a ring in device memory; worker waves (one per query, as many queries in flight as there are workers)
- * claim jobs from it with an atomic compare-and-swap, route them (smallest list; graph search for |C_l| >= T,
- * scan otherwise; the other labels as AND predicate) and write the k results and a done flag straight into a
- * result ring in host memory.  A query costs no kernel launch and no HIP call: vf_serve_submit and
+ * kernel that stays resident for the session: a dispatcher wave watches a counter in pinned host memory and
+ * publishes each job in a word of the job's slot in device memory; workers (one query at a time, as many queries in
+ * flight as there are workers) draw job numbers with an atomic addition, wait for their job's word, copy the job from
+ * the host's ring, route it (smallest list; graph search for |C_l| >= T, scan otherwise; the other labels as AND
+ * predicate) and write the k results and a done flag straight into a result ring in host memory.  A query costs no kernel launch and no HIP call: vf_serve_submit and
  * vf_serve_poll only touch pinned memory.  Results are those of vf_search for the same query and parameters
  * (uint8 and graph-searched float32 queries bit for bit).
  *

@@ -265,7 +265,7 @@ struct SeedParams {
     const uint32_t *seed_norm;  // [group * 32 + v] squared norms as in xnorm_all
     const int64_t *seed_goff;   // [n_graph_labels] first group of each graph list, by rank among graph labels
     int32_t chunk_seeds;        // seeds per wave: kSeedMfmaChunk, or 32 or four times kSeedMfmaChunk (interleaved copy only); max_chunks matches it
-    uint32_t *dmin;             // optional (chunk_seeds = 4 * kSeedMfmaChunk): see BeamParams::dmin; rows of nb_stride words, a multiple of 16
+    uint32_t *dmin;             // optional (interleaved copy only, any chunk_seeds): see BeamParams::dmin; rows of nb_stride words, a multiple of 16
     int32_t nb_stride;
     int64_t dump_off;           // seed_mfma_kernel: dseed[dump_off .. dump_off + 64 * (dump_mask + 1)) takes the stores of
     int32_t dump_mask;          // lanes without a pair, 64 entries per workgroup index & dump_mask (2^k - 1)

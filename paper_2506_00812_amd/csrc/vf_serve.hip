@@ -14,8 +14,8 @@
 //
 // What bounds a session is the latency of one search, times what the places in flight allow.  While free workers compared
 // and swapped one common head word and the dispatcher copied one job after the other (a PCIe round trip each, two more
-// for the counter and the stop word), a job cost about 5 us however many workers there were.  Now no two free workers
-// wait at the same word, the dispatcher's poll is one round trip for any number of jobs, and the copies of different jobs
+// for the counter and the stop word), a job cost about 5 us however many workers there were.  Now free workers wait at as
+// many words as there are slots, the dispatcher's poll is one round trip for any number of jobs, and the copies of different jobs
 // overlap.  300,000 x 128 float32, 6,144 seeds, width 2, 12 iterations, queries/s with 1 / 8 / 64 / 240 in flight: 8.7 k /
 // 56 k / 185 k / 191 k before, 12.9 k / 100 k / 757 k / 2.24 M now; p50 of a query 146 / 174 / 311 / 1,192 us before, 103 /
 // 104 / 108 / 127 now.
@@ -35,7 +35,7 @@
 namespace vf {
 
 constexpr int kServeHdr = 64;    // bytes of a job slot before the query vector
-constexpr int kReadyBytes = 64;  // behind a device slot: its ready word, in a cache line of its own
+constexpr int kReadyBytes = 64;  // behind a device slot: its ready word, whose 128-byte line ends with the query or begins the next slot
 constexpr int kServeQuickPolls = 64;   // the dispatcher's, after a job, with a short sleep between them
 constexpr int kServeSleep = 16;  // s_sleep between a waiting worker's polls, 64 cycles each
 
@@ -56,7 +56,6 @@ struct ServeHostCtrl {          // pinned host memory, both sides read and write
     uint64_t tail;              // host: jobs submitted so far
     uint32_t stop;              // host: 1 = end the session (the dispatcher reads tail and stop with one instruction)
     uint32_t pad0;
-    uint64_t published;         // device: jobs published to the workers
     uint64_t jobs_done;         // device: jobs completed (written at exit)
     uint32_t exit_reason;       // device: 0 while running; 1 host asked, 2 max_jobs reached, 3 idle bound
     uint32_t pad1;
@@ -99,8 +98,9 @@ __device__ __forceinline__ char *serve_slot(const ServeParams &p, uint64_t job)
 }
 __device__ __forceinline__ uint64_t *serve_ready(const ServeParams &p, uint64_t job) { return (uint64_t *)(serve_slot(p, job) + p.slot_stride); }
 
-// One lane: draws the next job and waits for it; -1: the session is over.  A worker that waits reads its job's own ready
-// word, so its polls meet nobody else's, and every 16th time the dispatcher's words.
+// One lane: draws the next job and waits for it; -1: the session is over.  A worker that waits reads the ready word of its
+// job's slot, which it shares with others only where there are fewer slots than workers, and every 16th time the dispatcher's
+// words.
 __device__ __forceinline__ int64_t serve_next_job(const ServeParams &p)
 {
     const uint64_t job = __hip_atomic_fetch_add(&p.dctrl->head, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -152,7 +152,6 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
                 for (uint64_t j = published + lane; j < upto; j += 64)
                     __hip_atomic_store(serve_ready(p, j), j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 published = upto;
-                if (lane == 0) __hip_atomic_store(&p.hctrl->published, published, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 idle = -kServeQuickPolls;
             } else {
                 // (quick polls are not counted: one that is counted takes about 4 us, whatever the bound)
@@ -505,12 +504,11 @@ static int serve_submit_impl(vf_server *sv, const void *query, const int32_t *la
     VF_REQUIRE((int64_t)sv->next_job < sv->max_jobs, "max_jobs of this session have been submitted");
     const uint64_t j = sv->next_job;
     if (j >= (uint64_t)sv->ring_slots) {
-        // the slot's previous job must have left the host ring (copied to the device) and be done (its result slot is
-        // about to be reused)
+        // the slot's previous job must be done: its worker copies it from the host ring, after it was published, and its
+        // result slot is about to be reused
         const uint64_t prev = j - (uint64_t)sv->ring_slots;
-        const uint64_t pub = __atomic_load_n(&sv->h_ctrl->published, __ATOMIC_ACQUIRE);
         const uint64_t done = __atomic_load_n(&sv->h_results[prev % (uint64_t)sv->ring_slots].done, __ATOMIC_ACQUIRE);
-        if (pub <= prev || done < prev + 1) {
+        if (done < prev + 1) {
             set_error("the job ring is full");
             return VF_EBUSY;
         }

@@ -244,6 +244,37 @@ int check_search_params(const vf_index *ix, bool exact, int32_t k, int32_t &itop
     return VF_OK;
 }
 
+// How joined lists are cut into work items.
+struct JoinTiles {
+    int kernel;       // rows a workgroup of the kernel can take (kJoinRows, kJoinRowsShared)
+    int rows;         // ... and is given
+    int seg_groups;   // groups of a segment
+};
+
+// lists: groups and rows of each.  A row's thresholds start over in each segment, so no more of them than keep the chip busy: two
+// workgroups of four waves per CU at a time, eight of one wave; three rounds of them level out the last one.  Where tiles of 32
+// rows leave most SIMDs without a wave, smaller ones: a wave's selection takes longer than reading the list, and is a matter of
+// its rows and of what is kept of each (lists of 20,000 / 133,000 x 128 float32, 32 queries: k = 10 336 -> 196 and 471 -> 307 us,
+// k = 48 599 -> 265 and 716 -> 426; a shared reading of the list by four waves, as before there were tiles of one, took 413, 505, 538
+// and 632).
+static JoinTiles join_tiles(int kind, int32_t dim, const std::vector<std::pair<int64_t, int64_t>> &lists)
+{
+    constexpr int64_t kShort = 64;
+    auto count = [&](int64_t rows, int64_t seg) {
+        int64_t c = 0;
+        for (const auto &l : lists) c += ((l.second + rows - 1) / rows) * (seg > 0 ? (l.first + seg - 1) / seg : l.first);
+        return c;
+    };
+    int64_t n_rows = 0;
+    for (const auto &l : lists) n_rows += l.second;
+    JoinTiles t;
+    t.kernel = t.rows = join_tile_rows(kind, dim, n_rows >= (int64_t)lists.size() * 2 * kJoinRowsShared);
+    if (t.kernel == kJoinRows)
+        while (t.rows > 8 && count(t.rows, kShort) < 1024) t.rows /= 2;
+    t.seg_groups = (int)std::max<int64_t>(kShort, count(t.rows, 0) / (t.kernel == kJoinRows ? 6144 : 1536));
+    return t;
+}
+
 // Routing, work lists, blob layout.  budget: how large a seed distance matrix may be (beyond it the
 // beam kernel gathers the seeds itself).
 int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, const int32_t *qids, bool exact,
@@ -347,18 +378,16 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         P.join_kind = ix->join_kind();
         ItemBuilder jb(ix->tune);
         jb.all_partial = true;
-        int64_t tile_groups = 0, n_lists = 0;
-        for (size_t i = first_hs; i < r.scan_pairs.size(); ++i) n_lists += i == first_hs || r.scan_pairs[i] >> 32 != r.scan_pairs[i - 1] >> 32;
-        P.join_tile = join_tile_rows(P.join_kind, ix->dim, (int64_t)(r.scan_pairs.size() - first_hs) >= n_lists * 2 * kJoinRowsShared);
-        jb.tile_rows = P.join_tile;
+        std::vector<std::pair<int64_t, int64_t>> list_rows;
         for (size_t i = first_hs, e; i < r.scan_pairs.size(); i = e) {
             const uint64_t l = r.scan_pairs[i] >> 32;
             for (e = i; e < r.scan_pairs.size() && r.scan_pairs[e] >> 32 == l;) ++e;
-            tile_groups += (int64_t)((e - i + P.join_tile - 1) / P.join_tile) * ((ix->S[(size_t)l] + 31) / 32);
+            list_rows.emplace_back((ix->S[(size_t)l] + 31) / 32, (int64_t)(e - i));
         }
-        // segments: a row's thresholds start over in each, so no more of them than keep the chip busy (two workgroups per
-        // CU at a time; three rounds of them level out the last one)
-        jb.seg_groups = jb.seg_groups_heavy = (int)std::max<int64_t>(64, tile_groups / (P.join_tile == kJoinRows ? 6144 : 1536));
+        const JoinTiles tiles = join_tiles(P.join_kind, ix->dim, list_rows);
+        P.join_tile = tiles.kernel;
+        jb.tile_rows = tiles.rows;
+        jb.seg_groups = jb.seg_groups_heavy = tiles.seg_groups;
         const int64_t batch_groups = (int64_t)(P.join_bytes / join_group_bytes(ix->join_kind_max(), ix->dim));
         int64_t groups = 0;
         JoinBatch b{0, 0, 0, 0, 0};

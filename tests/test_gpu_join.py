@@ -241,7 +241,6 @@ def test_long_lists_are_tried_before_they_are_joined():
         assert np.array_equal(got, want), f"clusters {spread} apart"
 
 
-
 def test_rows_of_several_lists_are_tried():
     """The same with three lists whose pairs together make a look worth its time; clusters so far apart that half the rows or
     all have no proof, where everything is joined again, and near ones."""
@@ -264,6 +263,7 @@ def test_rows_of_several_lists_are_tried():
         finally:
             vf.tune_defaults("build16", 1)
         assert np.array_equal(got, want), f"clusters {spread} apart"
+
 
 def _table(dtype, dim, n, sizes, spread, seed):
     """Clustered points with some equal ones, posting lists of the given sizes, and a function that draws more points."""
@@ -311,3 +311,19 @@ def test_few_queries_of_long_lists(dtype, dim, spread):
         for nq in counts:
             _check_exact(ix, ixo, q[:nq], [[0]] * nq, k, f"{nq} queries, k {k}")
         _check_exact(ix, ixo, q, [[0], [1], [2], [3], [0, 1], [2, 3], [1, 2]] + [[0]] * 3 + [[1]] * 2, k, f"several lists, k {k}")
+
+
+@pytest.mark.parametrize("dtype,dim,k", [("float32", 64, 48), ("float32", 128, 10), ("uint8", 128, 64)])
+def test_queries_around_the_rows_of_a_small_tile(dtype, dim, k):
+    """Lists with a few queries are cut into tiles of 8, 16 or 32 rows: numbers of queries around them, ties, AND queries."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    sizes = [9000, 4500, 700]
+    x, off, ids, points = _table(dtype, dim, 9500, sizes, 2, dim + k)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, len(sizes), 200, 16)
+    ixo = OracleIndex(x, off, ids, len(sizes), 200, 16, lazy_graph=True)
+    q = points(100)
+    q[1] = x[7]
+    for nq in (7, 8, 9, 17, 31, 33, 100):
+        _check_exact(ix, ixo, q[:nq], [[0]] * nq, k, f"{nq} queries")
+    _check_exact(ix, ixo, q, [[0]] * 41 + [[1]] * 23 + [[2]] * 9 + [[0, 1]] * 16 + [[0, 1, 2]] * 11, k, "several lists")

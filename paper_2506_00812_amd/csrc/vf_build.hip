@@ -164,6 +164,10 @@ __global__ __launch_bounds__(64) void graph_rows_rerank_kernel(GraphRowsParams p
         const float T = p.approx_unit * __uint_as_float((uint32_t)(readlane64(cand, K - 1) >> 32));
         const uint64_t rth = readlane64(key, R - 1);
         const bool proven = rth != KEY_MAX && __uint_as_float((uint32_t)(rth >> 32)) < T - B;
+        if (p.loose != nullptr && j % kLooseStep == 0 && lane == 0) {
+            const float Bq = p.err_bound * (vn + p.xn_max) + p.err_q_query * sqrtf(vn);
+            if (!(rth != KEY_MAX && __uint_as_float((uint32_t)(rth >> 32)) < T - Bq)) atomicAdd(p.loose, 1);
+        }
         if (!proven) {   // (wave-uniform) the definition itself
             if (p.unproven != nullptr) {
                 if (lane == 0) p.unproven[1 + atomicAdd(p.unproven, 1)] = p.row_base + (int32_t)j;

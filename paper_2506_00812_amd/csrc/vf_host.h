@@ -246,7 +246,12 @@ struct vf_index {
     // float32: the join kernel's origin (a vector near the mean of X), the squared norms of all rows measured from it and the
     // largest of them (0: the table's norms are outside the proofs' range, nothing is joined)
     vf::DevBuf d_centre, d_xnorm_c;
-    bool join_single = true;      // float32 joins on binary16 operands; off once more than 1 in 64 rows went without a proof
+    // float32 self-joins on binary16 operands; off from the batch of lists on where a look at 256 rows left 1 in 16 without a proof,
+    // or the join 1 in 64
+    bool join_single = true;
+    // ... and ground truth, of at most so many results: set by a build that kept to binary16 and whose rows would nearly all have
+    // been proven as queries, whose own rounding is not known (0: two parts).  No call changes it.
+    int32_t exact_single_k = 0;
     float xc_max = 0.f, xc_rho = 0.f;   // (... and the largest relative error of a centred row rounded to 11 bits)
     bool seed_mfma_ok = false;   // the norms exist and are finite: seeds may be scored on the matrix cores
     // search workspaces (see Workspace); profiled calls and vf_search_exact must not overlap with other calls
@@ -308,8 +313,9 @@ struct vf_index {
     float seed_err_bound() const { return (float)(tune.seed_slack * 3.0517578125e-05); }
     // squared norms the join kernel takes for its lists
     const uint32_t *join_norms() const { return dtype == VF_U8 ? d_xnorm_all.as<uint32_t>() : d_xnorm_c.as<uint32_t>(); }
-    // the operands of a join: binary16 while that proves nearly every row (join_single), else two bfloat16 parts
+    // the operands of a self-join, and of a join of queries
     int join_kind() const { return dtype == VF_U8 ? vf::kJoinU8 : join_single ? vf::kJoinSingle : vf::kJoinSplit; }
+    int exact_kind(int32_t k) const { return dtype == VF_U8 ? vf::kJoinU8 : k <= exact_single_k ? vf::kJoinSingle : vf::kJoinSplit; }
     // ... and those that the packed lists' buffer is sized for
     int join_kind_max() const { return dtype == VF_U8 ? vf::kJoinU8 : vf::kJoinSplit; }
     // the same for the approximations of the join kernel (norms from its origin, see vf_join.hip); what it decides is

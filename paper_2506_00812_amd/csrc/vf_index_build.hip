@@ -118,9 +118,10 @@ constexpr int kLookRows = 256;   // rows that tell which operands a batch of sel
 // Exact kNN rows of the graph lists graph_labels[lo, hi), which lie one after the other in M_HS: pack them, contract every
 // list against itself in one launch (vf_join.hip; a list of a few thousand vectors alone would leave most of the chip
 // idle), keep K candidates per vertex and order `deg` of them into rows_out (per list [|C_l|][deg] local ids).
-// rows_out: row of the first vertex; global_ids as in build_graph_for_label.
+// rows_out: row of the first vertex; global_ids as in build_graph_for_label.  for_queries: stays true while binary16 operands have
+// proven nearly all rows, and would have with a query's bound.
 static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, int32_t deg, int32_t *rows_out, bool global_ids,
-                               DevBuf &cand_idx, DevBuf &cand_dist, DevBuf &d_items, hipStream_t s)
+                               DevBuf &cand_idx, DevBuf &cand_dist, DevBuf &d_items, bool &for_queries, hipStream_t s)
 {
     const int64_t base0 = ix->O_HS[(size_t)ix->graph_labels[lo]];
     std::vector<JoinList> lists;
@@ -148,7 +149,8 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
     const int32_t *map = ix->d_M_HS.as<int32_t>();
     const int64_t n_rows = ix->O_HS[(size_t)ix->graph_labels[hi - 1]] + ix->S[(size_t)ix->graph_labels[hi - 1]] - base0;
     int kind = ix->join_kind();
-    const int64_t sel_at = 1 + n_rows;   // d_unproven: how many rows have no proof, which, and those that are joined again
+    // d_unproven: how many rows (of a few) would have no proof as queries, how many have none, which, and those that are joined again
+    const int64_t sel_at = 2 + n_rows;
     if (kind == kJoinSingle && (rc = d_unproven.reserve((size_t)(sel_at + std::max<int64_t>(n_rows, kLookRows)) * 4)) != VF_OK) {
         if (rc != VF_ENOMEM) return rc;
         (void)hipGetLastError();
@@ -168,7 +170,9 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         launch_join(kd, p, tile_rows, n_items, s);
     };
     // n rows of list i (sel null: all of them) from their candidates, which begin at row cand_at
-    auto rows = [&](int kd, size_t i, int64_t cand_at, const int32_t *sel, int64_t n, int32_t nseg, int64_t seg_stride, int32_t *unproven) {
+    int32_t *const loose = d_unproven.as<int32_t>(), *const unproven_rows = loose + 1;
+    auto rows = [&](int kd, size_t i, int64_t cand_at, const int32_t *sel, int64_t n, int32_t nseg, int64_t seg_stride, int32_t *unproven,
+                    int32_t *loose = nullptr) {
         const int32_t l = ix->graph_labels[i];
         const int64_t base = ix->O_HS[(size_t)l];
         GraphRowsParams g{};
@@ -179,10 +183,11 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         g.err_bound = ix->join_err_bound(kd); g.err_q = ix->join_err_q(kd, true); g.xn_max = ix->xc_max;
         g.approx_unit = 1.0f / (ix->join_scale(kd) * ix->join_scale(kd)); g.centre = ix->d_centre.as<float>();
         g.unproven = unproven;
+        g.loose = loose; g.err_q_query = ix->join_err_q(kd, false);
         launch_graph_rows(ix->dtype, g, s);
     };
-    auto fetch_count = [&](int32_t &count) -> int {
-        VF_HIP(hipMemcpyAsync(&count, d_unproven.p, 4, hipMemcpyDeviceToHost, s));
+    auto fetch_counts = [&](int32_t (&count)[2]) -> int {   // as a query, as a row
+        VF_HIP(hipMemcpyAsync(count, d_unproven.p, 8, hipMemcpyDeviceToHost, s));
         VF_HIP(hipStreamSynchronize(s));
         return VF_OK;
     };
@@ -246,26 +251,30 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
             for (int32_t r = 0; r < kLookRows / 8; ++r)
                 sel.push_back((int32_t)(lists[by_size[u]].src - base0 + (int64_t)lists[by_size[u]].n * r / (kLookRows / 8)));
         std::sort(sel.begin(), sel.end());
-        VF_HIP(hipMemsetAsync(d_unproven.p, 0, 4, s));
-        int32_t count = 0;
-        rc = selected(kind, sel, d_unproven.as<int32_t>());
-        if (rc == VF_OK) rc = fetch_count(count);
+        VF_HIP(hipMemsetAsync(d_unproven.p, 0, 8, s));
+        int32_t count[2] = {0, 0};
+        rc = selected(kind, sel, unproven_rows);
+        if (rc == VF_OK) rc = fetch_counts(count);
         if (rc != VF_OK && rc != VF_ENOMEM) return rc;
         if (rc == VF_ENOMEM) (void)hipGetLastError();   // (no look then)
-        if ((size_t)count > sel.size() / 16) {
+        if ((size_t)count[1] > sel.size() / 16) {
             ix->join_single = false;
             pack(kind = kJoinSplit);
         }
     }
     if ((rc = upload(d_items, items, s)) != VF_OK) return rc;
-    if (kind == kJoinSingle) VF_HIP(hipMemsetAsync(d_unproven.p, 0, 4, s));
+    if (kind == kJoinSingle) VF_HIP(hipMemsetAsync(d_unproven.p, 0, 8, s));
     join(kind, nullptr, kJoinRowsShared, (int)items.size());
     for (size_t i = lo; i < hi; ++i)
         rows(kind, i, ix->O_HS[(size_t)ix->graph_labels[i]] - base0, nullptr, ix->S[(size_t)ix->graph_labels[i]], 1, 0,
-             kind == kJoinSingle ? d_unproven.as<int32_t>() : nullptr);
+             kind == kJoinSingle ? unproven_rows : nullptr, kind == kJoinSingle ? loose : nullptr);
     if (kind == kJoinSingle) {
-        int32_t count = 0;
-        if ((rc = fetch_count(count)) != VF_OK) return rc;
+        int32_t counts[2] = {0, 0};
+        if ((rc = fetch_counts(counts)) != VF_OK) return rc;
+        const int32_t count = counts[1];
+        int64_t n_looked = 0;
+        for (const JoinList &l : lists) n_looked += (l.n + kLooseStep - 1) / kLooseStep;
+        if ((int64_t)counts[0] > n_looked / 64) for_queries = false;
         if ((int64_t)count > n_rows / 2) {   // all once more, with operands that keep twice the bits: most have to be, and need not be listed
             pack(kJoinSplit);
             join(kJoinSplit, nullptr, kJoinRowsShared, (int)items.size());
@@ -274,7 +283,7 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
             ix->join_single = false;
         } else if (count > 0) {   // those once more
             std::vector<int32_t> sel((size_t)count);
-            VF_HIP(hipMemcpy(sel.data(), d_unproven.as<int32_t>() + 1, sel.size() * 4, hipMemcpyDeviceToHost));
+            VF_HIP(hipMemcpy(sel.data(), unproven_rows + 1, sel.size() * 4, hipMemcpyDeviceToHost));
             std::sort(sel.begin(), sel.end());
             pack(kJoinSplit);
             rc = selected(kJoinSplit, sel, nullptr);
@@ -288,6 +297,7 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
             if ((int64_t)count > n_rows / 64) ix->join_single = false;
         }
     }
+    if (kind != kJoinSingle || !ix->join_single) for_queries = false;
     if (global_ids)
         for (size_t i = lo; i < hi; ++i) {
             const int32_t l = ix->graph_labels[i];
@@ -663,6 +673,7 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
             const bool progress = ix->tune.build_progress != 0;
             time_t last_print = time(nullptr);
             size_t done = 0;
+            bool for_queries = joined && ix->dtype == VF_F32;
             for (const size_t end : batch_end) {
                 if (progress && time(nullptr) - last_print >= 10) {
                     fprintf(stderr, "[vf_build_index] %zu of %zu label graphs built, next list holds %d vectors\n", done,
@@ -679,12 +690,15 @@ int build_index_impl(const void *vectors, int dtype, int64_t n, int32_t dim, con
                 const int64_t base = ix->O_HS[(size_t)first];
                 int32_t *rows = pruned ? d_knn.as<int32_t>() + base * D : ix->d_G.as<int32_t>() + base * ix->R;
                 if (joined)
-                    rc = build_graphs_joined(ix, done, end, K, D, rows, !pruned, cand_idx, cand_dist, d_items, s);
+                    rc = build_graphs_joined(ix, done, end, K, D, rows, !pruned, cand_idx, cand_dist, d_items, for_queries, s);
                 else
                     rc = build_graph_for_label(ix, first, K, D, rows, !pruned, cand_idx, cand_dist, d_items, s);
                 if (rc != VF_OK) return rc;
                 done = end;
             }
+            // (distances spread out towards the nearest: k of a query and 22 to spare are as far apart as D of a row and K - D, or
+            // further, up to k = D)
+            if (for_queries) ix->exact_single_k = D;
             VF_HIP(hipStreamSynchronize(s));
             if (pruned) {
                 cand_idx.release(); cand_dist.release();

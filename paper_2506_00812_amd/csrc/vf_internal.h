@@ -354,7 +354,11 @@ struct GraphRowsParams {
     float err_bound, err_q, xn_max, approx_unit;
     const float *centre;
     int32_t *unproven;
+    // optional: counts the rows, of every kLooseStep-th, that err_q_query in the place of err_q would leave without a proof
+    int32_t *loose;
+    float err_q_query;
 };
+constexpr int kLooseStep = 16;
 void launch_graph_rows(int dtype, const GraphRowsParams &p, hipStream_t s);
 
 // out[i] = map[rows[i]] (rows[i] >= 0), -1 otherwise: graph rows as global ids

@@ -375,7 +375,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
                         (ix->dtype == VF_U8 || (ix->xc_max > 0.f && ix->tune.scan_bf16 && join_keep >= k + 16));
     if (joined) {
         P.join_keep = join_keep;
-        P.join_kind = ix->join_kind();
+        P.join_kind = ix->exact_kind(k);
         ItemBuilder jb(ix->tune);
         jb.all_partial = true;
         std::vector<std::pair<int64_t, int64_t>> list_rows;
@@ -910,9 +910,6 @@ static int answer_refused(vf_index *ix, const CallPlan &P, const Routed &r, cons
     std::vector<int32_t> which((size_t)n_refused);
     VF_HIP(hipMemcpy(which.data(), M.refused, which.size() * 4, hipMemcpyDeviceToHost));
     std::sort(which.begin(), which.end());   // queries of a list become neighbours, scan lists come first
-    // (joins on operands of twice the bits from now on, where these leave so many without a proof)
-    const auto joined = which.end() - std::lower_bound(which.begin(), which.end(), (int32_t)P.n_ls_merges);
-    if (P.join_kind == kJoinSingle && joined > 64 && (size_t)joined > (P.ib.merges.size() - P.n_ls_merges) / 64) ix->join_single = false;
     const std::vector<MergeItem> &merges = P.ib.merges;
     constexpr size_t kBatch = 4096;          // bounds the partial rows: 64 segments of 64 results each
     DevBuf d_items(&ix->alloc), d_merges(&ix->alloc), d_qrow(&ix->alloc), parts(&ix->alloc);

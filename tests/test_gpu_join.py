@@ -327,3 +327,41 @@ def test_queries_around_the_rows_of_a_small_tile(dtype, dim, k):
     for nq in (7, 8, 9, 17, 31, 33, 100):
         _check_exact(ix, ixo, q[:nq], [[0]] * nq, k, f"{nq} queries")
     _check_exact(ix, ixo, q, [[0]] * 41 + [[1]] * 23 + [[2]] * 9 + [[0, 1]] * 16 + [[0, 1, 2]] * 11, k, "several lists")
+
+
+@pytest.mark.parametrize("dim,R,spread", [(128, 16, 3), (128, 16, 4), (64, 16, 4), (128, 8, 5), (128, 32, 2), (64, 32, 12)])
+def test_ground_truth_that_binary16_would_not_prove(dim, R, spread):
+    """Tables whose rows binary16 operands prove, but not the queries, or not those for many results: the index knows it from its
+    build, and the first call finds its proofs as a later one does.  A call whose queries go without proofs changes nothing."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_close_with_ties, to_np
+    rng = np.random.default_rng(dim + R)
+    n, nq = 20_000, 1000
+    centres = rng.normal(size=(40, dim)) * spread
+    x = (centres[rng.integers(0, 40, n)] + rng.normal(size=(n, dim))).astype(np.float32)
+    q = (centres[rng.integers(0, 40, nq)] + rng.normal(size=(nq, dim))).astype(np.float32)
+    off, ids = np.arange(n + 1, dtype=np.int64), np.zeros(n, dtype=np.int32)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, 1, 1000, R)
+    qoff, qids, Q = np.arange(nq + 1, dtype=np.int64), np.zeros(nq, dtype=np.int32), torch.from_numpy(q).cuda()
+
+    def unproven(count, k):
+        ix.profile_enable(True)
+        gi, gd = vf.search_exact(ix, Q[:count], qoff[:count + 1], qids[:count], k)
+        wi, wd = _truth(x, q[:40], np.ones(n, dtype=bool), k)
+        m = min(count, 40)
+        assert_close_with_ties(to_np(gi)[:m], to_np(gd)[:m], wi[:m], wd[:m].astype(np.float32), 1e-5, f"k {k}")
+        return ix.profile_read()["scan_fallbacks"]
+
+    def few(counts):   # (1 in 64 rows may be without a proof, and as many queries)
+        return all(c <= n_c // 32 for c, n_c in counts)
+
+    def all_counts():
+        return [(unproven(count, k), count) for k in (10, 26, 42, 48) for count in (40, nq)]
+
+    first = all_counts()
+    assert few(first), first
+    ix.tune("seed_slack", 1e6)
+    assert unproven(nq, 10) == nq
+    ix.tune("seed_slack", 1.0)
+    assert all_counts() == first

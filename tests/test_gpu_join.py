@@ -365,3 +365,57 @@ def test_ground_truth_that_binary16_would_not_prove(dim, R, spread):
     assert unproven(nq, 10) == nq
     ix.tune("seed_slack", 1.0)
     assert all_counts() == first
+
+
+@pytest.mark.parametrize("dtype,dim,k,spread", [("float32", 36, 10, 2), ("float32", 128, 10, 2), ("float32", 128, 10, 60), ("float32", 96, 42, 2),
+                                                ("float32", 132, 7, 60), ("float32", 248, 10, 2), ("uint8", 128, 10, 0), ("uint8", 192, 64, 0),
+                                                ("uint8", 272, 5, 0), ("uint8", 976, 10, 0)])
+def test_lists_shared_by_four_waves(dtype, dim, k, spread):
+    """Ground truth with 257 queries per list and more: lists of several segments, last tiles of 1, 44 and 129 rows (waves without
+    rows), filtered queries between others, ties; operands of one part and of two, in one LDS buffer and in two."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    sizes = [9000, 2500, 700]
+    x, off, ids, points = _table(dtype, dim, 9500, sizes, spread, dim + k)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, len(sizes), 200, 16)
+    ixo = OracleIndex(x, off, ids, len(sizes), 200, 16, lazy_graph=True)
+    rng = np.random.default_rng(k)
+    for counts in ((385, 300, 257), (513, 257, 0)):
+        asked = [[0]] * counts[0] + [[1]] * counts[1] + [[2]] * counts[2]
+        pairs = [[0, 1]] * 40 + [[1, 2]] * 30 + [[0, 2]] * 20 + [[0, 1, 2]] * 10
+        for a in (asked, asked + pairs):
+            a = [a[i] for i in rng.permutation(len(a))]
+            q = points(len(a))
+            q[3], q[4] = x[7], x[8]
+            _check_exact(ix, ixo, q, a, k, f"{counts} queries")
+
+
+@pytest.mark.parametrize("dim,k", [(128, 10), (36, 16), (96, 1), (248, 5)])
+def test_queries_beyond_binary16(dim, k):
+    """Finite queries around the norm from which ground truth takes no binary16 operands (31,622 in the operands' unit), around the
+    largest binary16 number (65,504) and far above it: results as from the ordered scan alone, in lists of any length."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    sizes = [9000, 700, 60, 39, 38, 33, 32, 31, 22]
+    x, off, ids, points = _table("float32", dim, 9500, sizes, 2, dim)
+    unit = 2.0 ** (6 - np.frexp(np.linalg.norm(x - x.mean(0), axis=1).max())[1])
+    targets = np.array([3e3, 2.9e4, 3.1e4, 3.16e4, 3.17e4, 3.3e4, 6.4e4, 6.55e4, 6.6e4, 1e5, 1e6, 1e9]) / unit
+    q = []
+    for j, t in enumerate(targets):
+        for sign in (1, -1):
+            one, all_ = points(1)[0], points(1)[0]
+            one[j % dim] += sign * t
+            all_ += sign * t / np.sqrt(dim)
+            q += [one, all_]
+    q = np.array(q + list(points(8)), dtype=np.float32)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, len(sizes), 20, 16)
+    for label in range(len(sizes)):
+        asked = np.full(len(q), label, dtype=np.int32)
+        out = []
+        for slack in (1.0, 1e6):
+            ix.tune("seed_slack", slack)
+            gi, gd = vf.search_exact(ix, torch.from_numpy(q).cuda(), np.arange(len(q) + 1), asked, k)
+            out.append((gi.cpu().numpy(), gd.cpu().numpy()))
+        (gi, gd), (wi, wd) = out
+        bad = np.flatnonzero((gi != wi).any(1) | (gd.view(np.uint32) != wd.view(np.uint32)).any(1))
+        assert len(bad) == 0, f"list of {sizes[label]}: queries {bad}: {gi[bad[0]]} {wi[bad[0]]}"

@@ -192,13 +192,14 @@ static int build_graphs_joined(vf_index *ix, size_t lo, size_t hi, int32_t K, in
         return VF_OK;
     };
     // The rows of sel (ascending, of any lists).  Few rows do not fill the chip with whole lists: as many segments as do,
-    // and as the candidates' buffer has room for.  VF_ENOMEM (for the items): nothing was launched.
+    // and as the candidates' buffer has room for (about 1,024 items; builds of 200,000 x 128 with some of the rows joined again:
+    // with 256 3 to 8 % longer, with 4,096 2 to 6).  VF_ENOMEM (for the items): nothing was launched.
     auto selected = [&](int kd, const std::vector<int32_t> &sel, int32_t *unproven) -> int {
         int rc;
         int32_t *d_sel = d_unproven.as<int32_t>() + sel_at;
         // (few rows are a matter of latency, most of it a wave's selection: 32 rows of a list of 60,000 x 128, K = 48, by 64 items
         // of 32 rows 351 us, by 256 of 8 118)
-        const int waves = join_tile_rows(kd, ix->dim, sel.size() > 4096), tile = sel.size() <= kLookRows ? 8 : waves;
+        const int waves = join_tile_rows(kd, ix->dim), tile = sel.size() <= kLookRows ? 8 : waves;
         const int64_t most = std::min<int64_t>(n_rows / (int64_t)sel.size(), 1024 / (int64_t)(sel.size() / tile + 1));
         const int32_t nseg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, most));
         std::vector<ScanItem> part;

@@ -175,7 +175,7 @@ struct JoinList {
 };
 
 size_t join_group_bytes(int kind, int32_t dim);   // packed bytes of a group of 32 vectors
-int join_tile_rows(int kind, int32_t dim, bool many);   // rows of an item, kJoinRows or kJoinRowsShared; many: there are enough rows to fill the larger ones
+int join_tile_rows(int kind, int32_t dim);   // rows of an item of queries (or of selected rows), kJoinRows or kJoinRowsShared
 // n_groups: of all n_lists lists together; bound[0 .. n_bound) is set to "nothing found"
 void launch_join_pack(int kind, const void *X, int32_t dim, const int32_t *map, const JoinList *lists, int n_lists,
                       int64_t n_groups, const uint32_t *norm_all, const float *centre, float scale, uint4 *xblk, void *xnorm,
@@ -188,7 +188,8 @@ void launch_centre(const void *X, int32_t dim, int64_t n, float *tmp, float *cen
 // all others)
 void launch_row_norms_f32(const void *X, int32_t dim, int64_t n, const float *centre, uint32_t *out, uint32_t *out_c, uint32_t *max_bits,
                           hipStream_t s);
-void launch_join(int kind, const JoinParams &p, int rows, int n_items, hipStream_t s);   // rows: kJoinRows or kJoinRowsShared
+// rows: kJoinRows or kJoinRowsShared (with a predicate: join_tile_rows)
+void launch_join(int kind, const JoinParams &p, int rows, int n_items, hipStream_t s);
 
 // ---------------------------------------------------------------- beam search kernel
 

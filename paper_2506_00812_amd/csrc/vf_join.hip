@@ -5,8 +5,8 @@
 //
 // Tile.  A wave takes 32 rows, their operand in registers.  Where rows are many a workgroup of four waves streams a
 // segment of the list through LDS, one group of 32 entries per step, two buffers: a group is fetched from L2 once per 128
-// rows (every wave by itself: the self-joins below are bound by the memory behind L2, 45 ms instead of 30).  Where a list
-// has few rows (ground truth) one wave reads the list by itself, and no wave of a tile is idle.  Lists come packed
+// rows (every wave by itself: the self-joins below are bound by the memory behind L2, 45 ms instead of 30).  A list of queries
+// (ground truth; rows that are joined again) is read by one wave by itself, up to 8 steps (kJoinAloneSteps).  Lists come packed
 // (join_pack_kernel): per group the 16-byte chunks chunk-major, which is the B operand of the 32-column MFMAs, lane
 // (n32, h) reading chunk 2 s + h of entry n32.
 //
@@ -754,13 +754,14 @@ static int32_t join_steps(int kind, int32_t dim)
     return kind == kJoinU8 && need <= 32 ? 32 : 0;
 }
 
-// Steps up to which one wave reads a list by itself where its rows are few.  Beyond them a group is 16 KB and more, and four
-// waves that load a quarter each are ahead for any number of rows, a single one included (a lone query and 100 over a list of
-// 300,000: uint8 of 512 components 400 / 425 us by one wave, 288 / 356 by four; float32 of 248, split 866 / 1,017 and 705 /
-// 1,001).
+// Steps up to which queries' lists are read by one wave each, however many rows there are: 5,000 / 50,000 queries of a list of
+// 150,000 x 128 float32 1.03 / 4.86 ms, by workgroups of four waves 1.20 / 5.82 (20,000 entries 0.34 / 1.44 and 0.48 / 1.62; uint8
+// x 256, 30,000 queries 2.39 and 2.85).  Beyond them a group is 16 KB and more, and four waves that load a quarter each are ahead
+// for any number of rows, a single one included (a lone query and 100 over a list of 300,000: uint8 of 512 components 400 / 425 us
+// by one wave, 288 / 356 by four; float32 of 248, split 866 / 1,017 and 705 / 1,001).
 constexpr int32_t kJoinAloneSteps = 8;
 
-int join_tile_rows(int kind, int32_t dim, bool many) { return many || join_steps(kind, dim) > kJoinAloneSteps ? kJoinRowsShared : kJoinRows; }
+int join_tile_rows(int kind, int32_t dim) { return join_steps(kind, dim) > kJoinAloneSteps ? kJoinRowsShared : kJoinRows; }
 
 size_t join_group_bytes(int kind, int32_t dim)
 {
@@ -787,8 +788,13 @@ void launch_join_pack(int kind, const void *X, int32_t dim, const int32_t *map, 
 template <int DT, int NK, int W> static void launch_join_w(const JoinParams &p, int n_items, hipStream_t s)
 {
     constexpr size_t lds = join_lds_bytes<DT, NK, W>();
-    if (p.others_off != nullptr) hipLaunchKernelGGL((join_kernel<DT, NK, true, W>), dim3(n_items), dim3(64 * W), lds, s, p);
-    else hipLaunchKernelGGL((join_kernel<DT, NK, false, W>), dim3(n_items), dim3(64 * W), lds, s, p);
+    if constexpr (W == 1 || NK > kJoinAloneSteps) {   // (only queries have predicates)
+        if (p.others_off != nullptr) {
+            hipLaunchKernelGGL((join_kernel<DT, NK, true, W>), dim3(n_items), dim3(64 * W), lds, s, p);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((join_kernel<DT, NK, false, W>), dim3(n_items), dim3(64 * W), lds, s, p);
 }
 
 template <int DT, int NK> static void launch_join_nk(const JoinParams &p, int rows, int n_items, hipStream_t s)

@@ -252,7 +252,8 @@ struct JoinTiles {
 };
 
 // lists: groups and rows of each.  A row's thresholds start over in each segment, so no more of them than keep the chip busy: two
-// workgroups of four waves per CU at a time, eight of one wave; three rounds of them level out the last one.  Where tiles of 32
+// workgroups of four waves per CU at a time, eight of one wave; three rounds of them level out the last one (with a third of
+// that, 4,250 queries over 51 lists 8 % less to 8 % more).  Where tiles of 32
 // rows leave most SIMDs without a wave, smaller ones: a wave's selection takes longer than reading the list, and is a matter of
 // its rows and of what is kept of each (lists of 20,000 / 133,000 x 128 float32, 32 queries: k = 10 336 -> 196 and 471 -> 307 us,
 // k = 48 599 -> 265 and 716 -> 426; a shared reading of the list by four waves, as before there were tiles of one, took 413, 505, 538
@@ -265,10 +266,8 @@ static JoinTiles join_tiles(int kind, int32_t dim, const std::vector<std::pair<i
         for (const auto &l : lists) c += ((l.second + rows - 1) / rows) * (seg > 0 ? (l.first + seg - 1) / seg : l.first);
         return c;
     };
-    int64_t n_rows = 0;
-    for (const auto &l : lists) n_rows += l.second;
     JoinTiles t;
-    t.kernel = t.rows = join_tile_rows(kind, dim, n_rows >= (int64_t)lists.size() * 2 * kJoinRowsShared);
+    t.kernel = t.rows = join_tile_rows(kind, dim);
     if (t.kernel == kJoinRows)
         while (t.rows > 8 && count(t.rows, kShort) < 1024) t.rows /= 2;
     t.seg_groups = (int)std::max<int64_t>(kShort, count(t.rows, 0) / (t.kernel == kJoinRows ? 6144 : 1536));

@@ -370,9 +370,10 @@ def test_ground_truth_that_binary16_would_not_prove(dim, R, spread):
 @pytest.mark.parametrize("dtype,dim,k,spread", [("float32", 36, 10, 2), ("float32", 128, 10, 2), ("float32", 128, 10, 60), ("float32", 96, 42, 2),
                                                 ("float32", 132, 7, 60), ("float32", 248, 10, 2), ("uint8", 128, 10, 0), ("uint8", 192, 64, 0),
                                                 ("uint8", 272, 5, 0), ("uint8", 976, 10, 0)])
-def test_lists_shared_by_four_waves(dtype, dim, k, spread):
-    """Ground truth with 257 queries per list and more: lists of several segments, last tiles of 1, 44 and 129 rows (waves without
-    rows), filtered queries between others, ties; operands of one part and of two, in one LDS buffer and in two."""
+def test_many_queries_of_each_list(dtype, dim, k, spread):
+    """Ground truth with 257 queries per list and more: lists of several segments, last tiles of 1, 44 and 129 rows (from 16 steps on
+    in workgroups with waves without rows), filtered queries between others, ties; operands of one part and of two, in one LDS
+    buffer, in two and in registers."""
     import torch
     from paper_2506_00812_amd import binding as vf
     sizes = [9000, 2500, 700]

@@ -403,9 +403,12 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
             list.insert(((uint64_t)kb << 32) | ((uint64_t)kc << 1) | 1ull, lane);
         }
     };
-    // (cand_g is free: the candidates' vectors have been read)
+    // By rank where the wave's own chain is what takes the time (a lone query 55.3 -> 53.8 us, 64 queries 100.9 -> 98.9); launches that
+    // fill the chip are bound by instruction issue, and one by one is fewer of them (50,000 uint8 queries 1,829 -> 1,798 us, 14,000
+    // searches that gather 8,293 seeds of 208 components each 3,553 -> 3,478).  In their instantiation the code alone costs that:
+    // with a branch on the size of the launch 3,573.  (cand_g is free: the candidates' vectors have been read)
     auto offer = [&](bool valid, uint32_t bits, int c) {
-        if constexpr (E == 1) {
+        if constexpr (E == 1 && (LAT || STREAM_SEEDS)) {
             const uint64_t m = __ballot(valid && bits <= (uint32_t)(top.worst >> 32));
             if (__popcll(m) >= 3 &&
                 insert_by_rank<STREAM_SEEDS>(top, m, ((uint64_t)bits << 32) | ((uint64_t)(uint32_t)c << 1) | 1ull, (uint64_t *)cand_g, lane))

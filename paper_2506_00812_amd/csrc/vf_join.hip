@@ -34,8 +34,10 @@
 // uint8 data: v_mfma_i32_32x32x32_i8 on the bytes shifted by -128: exact.
 //
 // Selection.  With v = q.x - |x|^2 / 2 (uint8: 2 q.x - |x|^2) a distance is below a row's threshold where v is at least
-// a per-row constant, one subtraction and one compare per pair; a group without a candidate is done.  Candidates are
-// appended to one list of the wave in LDS; when it is half full they are delivered to the rows' queues (16 slots, LDS
+// a per-row constant t, or q.x - t at least |x|^2 / 2: the right side is the lane's entry's alone, so one subtraction per pair
+// and the maxima of four rows each decide, and only quarters with a candidate are looked at by element.  Candidates are
+// appended to one list of the wave in LDS, without a look at its end; a group that overruns it (before thresholds exist) is
+// gone through again, delivering in between; when it is half full they are delivered to the rows' queues (16 slots, LDS
 // atomics over 64 candidates at a time), and rows with ten or more merge their queue into their sorted K best: four rows
 // share a 64-lane sort network, then one merge network per row.  The K best live in the partial result rows in global
 // memory, the next four rows' requested while four are merged.  The waves of a workgroup deliver together: a wave that
@@ -44,11 +46,13 @@
 // above the K-th largest of them); without it a third of all candidates fall into a row's first thousand entries.  The
 // segments of a ground truth list share the rows' bounds.
 //
-// Measured: self-joins of 36 lists of 4,000 to 170,000 float32 vectors, dim 128 (4.7e10 pairs) 59.5 -> 31 ms (before: 128
-// rows per workgroup on two parts, a queue per row filled directly, merges at any time); a build of 400,000 vectors 88 ->
-// 60 ms; ground truth of 5,000 queries over 500,000 2.35 -> 1.2 ms.  Bound by instruction issue and waiting: per 32 x 32 pairs
-// a SIMD takes 1,500 cycles, 210 vector instructions (850 cycles), 8 MFMAs (260); three to four waves per SIMD are what
-// registers and LDS leave, and with two it takes a quarter longer.
+// Measured: self-joins of 36 lists of 4,000 to 170,000 float32 vectors, dim 128 (4.7e10 pairs) 29.4 -> 22.9 ms, uint8 of 128
+// and 192 components 4.26 -> 3.60 and 5.47 -> 5.05 (before: a compare and a mask in scalar registers per pair, sixteen of them
+// kept, spilled and branched on in every group with a candidate; 156 registers, three waves per SIMD); ground truth of 5,000
+// queries over 500,000 0.67 -> 0.63 ms.  Per 32 x 32 pairs a SIMD takes 1,180 cycles: 113 vector instructions (450), 8 MFMAs (260),
+// and what four waves leave uncovered of a wave's chain of LDS reads, products, branches and the workgroup's barrier (3,200
+// cycles, a quarter each).  Made no difference: list groups that are always in cache, half the LDS reads, groups touched four
+// ahead, more rows of the sample, wave priorities, two groups per barrier with two chains of products (three waves: 25 ms).
 #include "vf_select.h"
 
 namespace vf {
@@ -136,6 +140,9 @@ template <int SEG, class T, int NR> __device__ __forceinline__ void lane_merge(T
     lane_merge_stages<SEG, SEG / 2, true, false>(v);
 }
 
+__device__ __forceinline__ float larger(float a, float b) { return __builtin_fmaxf(a, b); }
+__device__ __forceinline__ int larger(int a, int b) { return a > b ? a : b; }
+
 constexpr int kJoinQueue = 16;   // pending keys per row
 constexpr int kJoinMerge = 10;   // a row with as many of them is merged when its wave delivers
 constexpr int kJoinFlat = 128;   // candidates on their way to the rows' queues (two rows of a group add up to 64)
@@ -158,8 +165,11 @@ __device__ __forceinline__ int lanes_before(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
-// Waves per SIMD that the registers are shared out for.
-__host__ __device__ constexpr int join_waves(int dt, int nk) { return dt == 1 || nk > 8 ? 2 : nk > 6 ? 3 : 4; }
+// Waves per SIMD that the registers are shared out for: the most that need no scratch memory in the loop over the groups.
+__host__ __device__ constexpr int join_waves(int dt, int nk, int w)
+{
+    return dt == 1 || nk > 8 ? 2 : (w == 1 ? nk > (dt == 0 ? 4 : 6) : nk > (dt == 0 ? 6 : 8)) ? 3 : 4;
+}
 
 // Operand chunks in flight: the steps of a group that are requested together.  A wave that reads split operands by itself has
 // the registers for a whole group.
@@ -181,7 +191,7 @@ template <int DT, int NK, int W> constexpr size_t join_lds_bytes()
 // NK: contraction steps (16 components of float32, 32 of uint8), the vectors zero padded to them.  W: waves of a workgroup,
 // 32 rows each.  Four share the list's groups through LDS; one reads them by itself.
 template <int DT, int NK, bool AND, int W>
-__global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinParams p)
+__global__ __launch_bounds__(64 * W, join_waves(DT, NK, W)) void join_kernel(JoinParams p)
 {
     extern __shared__ uint4 smem[];
     using acc_t = typename JoinAcc<DT>::type;
@@ -433,11 +443,12 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
         }
         xn_next = xnorm[0];
     };
-    // the contraction of group g (v = q.x - |x|^2 / 2, uint8: 2 q.x - |x|^2), and what comes after it set on its way
-    val_t v[16];
+    // the contraction of group g, and what comes after it set on its way
+    acc_t qx;   // q.x of the lane's 16 pairs
+    val_t xn;   // |x|^2 / 2 of its entry (uint8: |x|^2)
     auto contract = [&](int g) {
         const int gn = g + 1 < n_groups ? g + 1 : g;   // (the last one is read twice)
-        const val_t xn = xn_next;
+        xn = xn_next;
         if constexpr (W > 1) fetch(gn);
         xn_next = xnorm[gn * kGroup];
         if (W > 1 && rows <= 0) return;
@@ -479,9 +490,9 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
             }
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j)   // (float32: xn holds |x|^2 / 2)
-            v[j] = DT == 0 ? acc[j] * 2 - xn : (DT == 1 ? acc_lo[j] + acc[j] : acc[j]) - xn;
+        for (int j = 0; j < 16; ++j) qx[j] = DT == 1 ? acc_lo[j] + acc[j] : acc[j];
     };
+    auto value = [&](int j) -> val_t { return DT == 0 ? qx[j] * 2 - xn : qx[j] - xn; };
     auto advance = [&](int g) {   // W > 1: the group after g into LDS
         if constexpr (W > 1) {
             if (NBUF == 1) __syncthreads();
@@ -507,7 +518,10 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
                 contract(g + o);
                 if (W == 1 || rows > 0)
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) top[o][j] = v[j] > top[o][j] ? v[j] : top[o][j];
+                    for (int j = 0; j < 16; ++j) {
+                        const val_t v = value(j);
+                        top[o][j] = v > top[o][j] ? v : top[o][j];
+                    }
                 advance(g + o);
             }
         }
@@ -548,51 +562,68 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK)) void join_kernel(JoinPa
             advance(g);
             continue;
         }
-        uint64_t m[16], some[4];   // lanes whose element j is a candidate, and of rows 8 q .. 8 q + 7
+        val_t t[16];   // element j: row 8 (j / 4) + 4 h + j % 4
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const val4_t t = ((const val4_t *)tvs)[2 * q + h];   // element j: row 8 (j / 4) + 4 h + j % 4
-            some[q] = 0;
+            const val4_t t4 = ((const val4_t *)tvs)[2 * q + h];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                m[4 * q + u] = __builtin_amdgcn_ballot_w64(v[4 * q + u] >= t[u]);
-                some[q] |= m[4 * q + u];
-            }
+            for (int u = 0; u < 4; ++u) t[4 * q + u] = t4[u];
         }
-        if ((some[0] | some[1] | some[2] | some[3]) != 0) {
-            const int entry = it.entry0 + g * kGroup + n32;   // list-relative
-            while (true) {
-                bool full = false;
+        auto over = [&](int j) -> val_t { return DT == 0 ? qx[j] * 2 - t[j] : qx[j] - t[j]; };
+        val_t most[4];   // of rows 8 q .. 8 q + 7
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (some[q] == 0 || full) continue;   // (wave-uniform, as all that follows but the stores)
+        for (int q = 0; q < 4; ++q) most[q] = larger(larger(larger(over(4 * q), over(4 * q + 1)), over(4 * q + 2)), over(4 * q + 3));
+        const int entry = it.entry0 + g * kGroup + n32;   // list-relative
+        auto append = [&](int j, uint64_t m) {
+            const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)flat_n));
+            if (__builtin_amdgcn_inverse_ballot_w64(m) && at < kJoinFlat) {   // (v for now: the drain makes a distance of it)
+                const val_t v = value(j);
+                flat[at] = ((uint64_t)(DT == 0 ? (uint32_t)v : __float_as_uint((float)v)) << 32) | (uint32_t)entry;
+                int row = 4 * h;
+                asm("" : "+v"(row));   // (else the sixteen rows' numbers are kept in as many registers)
+                flat_row[at] = (uint8_t)(row + 8 * (j >> 2) + (j & 3));
+            }
+            flat_n += __builtin_popcountll(m);
+        };
+        int left = 16;   // elements from here on have not been looked at
+        if (__builtin_amdgcn_ballot_w64(larger(larger(larger(most[0], most[1]), most[2]), most[3]) >= xn) != 0) {
+            const int before = flat_n;
 #pragma unroll
-                    for (int j = 4 * q; j < 4 * q + 4; ++j) {
-                        if (m[j] == 0 || full) continue;
-                        const int c = __builtin_popcountll(m[j]);
-                        if (flat_n + c > kJoinFlat) { full = true; continue; }
-                        const int at = flat_n + lanes_before(m[j]);
-                        if (__builtin_amdgcn_inverse_ballot_w64(m[j])) {   // (v for now: the drain makes a distance of it)
-                            flat[at] = ((uint64_t)(DT == 0 ? (uint32_t)v[j] : __float_as_uint((float)v[j])) << 32) | (uint32_t)entry;
-                            flat_row[at] = (uint8_t)(8 * (j >> 2) + (j & 3) + 4 * h);
-                        }
-                        flat_n += c;
-                        m[j] = 0;
-                    }
+            for (int q = 0; q < 4; ++q) {
+                if (__builtin_amdgcn_ballot_w64(most[q] >= xn) == 0) continue;   // (wave-uniform, as all that follows but the stores)
+#pragma unroll
+                for (int j = 4 * q; j < 4 * q + 4; ++j) {
+                    const uint64_t m = __builtin_amdgcn_ballot_w64(over(j) >= xn);
+                    if (m != 0) append(j, m);
                 }
-                if (!full) break;
-                deliver(false);
+            }
+            if (__builtin_expect(flat_n > kJoinFlat, 0)) {   // more than there is room for (before thresholds exist)
+                flat_n = before;
+                left = 0;
             }
         }
+        bool now = flat_n >= kJoinFull || left < 16;
         if constexpr (W > 1) {
             // a wave that merges lets the others wait at the barrier: they merge together
             // (the next group's word was last read two barriers ago, and is not written before the one to come)
-            if (flat_n >= kJoinFull && lane == 0) want[turn] = 1;
+            if (now && lane == 0) want[turn] = 1;
             if (tid == 0) want[turn < 2 ? turn + 1 : 0] = 0;
             advance(g);
-            if (want[turn] != 0) deliver(false);
-        } else if (flat_n >= kJoinFull) {
-            deliver(false);
+            now = want[turn] != 0;
+        }
+        if (now) {
+            while (true) {
+                deliver(false);
+                if (__builtin_expect(left == 16, 1)) break;
+#pragma unroll 1
+                for (; left < 16; ++left) {
+                    const val_t tj = tvs[8 * (left >> 2) + 4 * h + (left & 3)];
+                    const uint64_t m = __builtin_amdgcn_ballot_w64((DT == 0 ? qx[left] * 2 - tj : qx[left] - tj) >= xn);
+                    if (flat_n + __builtin_popcountll(m) > kJoinFlat) break;
+                    if (m != 0) append(left, m);
+                }
+                if (left == 16 && flat_n < kJoinFull) break;
+            }
         }
     }
     deliver(true);

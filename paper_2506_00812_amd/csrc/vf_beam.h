@@ -775,7 +775,140 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
         n_scored += (o_cnt > 0 && bq.seed_pass >= 0) ? bq.seed_pass : ns;
     };
 
-    if constexpr (E == 1 && DT == 1) {
+    // What the proofs of approximate seeds allow for: |approximation - ordered distance| <= B.
+    auto approx_error = [&]() -> float {
+        float qn = 0.f;
+        for (int i = lane; i < nchunks; i += 64) {
+            const uint4 v = qv[i];
+            const float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
+            qn += f[0] * f[0] + f[1] * f[1] + f[2] * f[2] + f[3] * f[3];
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) qn += __shfl_xor(qn, o);
+        return p.err_bound * (qn + p.xn_max) + p.err_q * sqrtf(qn);
+    };
+    // The seeds that may belong to the list, for queries without a predicate: with tau at or above the itopk-th smallest
+    // approximation, itopk seeds have ordered distances of at most tau + B, and a seed of an approximation above tau + 2 B has
+    // none below that.  So those at or below tau + 2 B are collected (indexes in cand_c), a few more than itopk, to be scored with
+    // the ordered distance; no list of approximations is kept.  tau: the itopk-th smallest of the lanes' two smallest values of
+    // the row, or of the blocks' minima, which are at or above as many seeds (then only blocks with a minimum up to the limit
+    // are read).  Returns how many there are, more than 128 if that is too many.
+    // (Instead of keeping the 56 best approximations in a sorted list and re-scoring them under a proof: 10,000 queries with 2,560
+    // seeds 108.7 -> 91.2 us, a lone query with 6,144 39.2 -> 36.3, lists of up to 64 entries, which 64 kept ones cannot prove.)
+    auto collect = [&](float B, bool blocks) -> int {
+        constexpr int NBLK = VF_SEED_BLOCKS;
+        const uint32_t *drow = bq.dseed_row, *vals = blocks ? bq.dmin_row : drow;
+        const int nb = (ns + 31) >> 5, nv = blocks ? nb : ns;
+        uint32_t v[NBLK];
+        uint32_t m1 = 0xFFFFFFFFu, m2 = 0xFFFFFFFFu;
+        for (int i0 = 0; i0 < nv; i0 += 64 * NBLK) {
+#pragma unroll
+            for (int i = 0; i < NBLK; ++i) {
+                v[i] = 0xFFFFFFFFu;
+                if (i0 + i * 64 < nv && i0 + i * 64 + lane < nv) v[i] = vals[i0 + i * 64 + lane];
+            }
+#pragma unroll
+            for (int i = 0; i < NBLK; ++i) {
+                const uint32_t hi = v[i] > m1 ? v[i] : m1;
+                m2 = hi < m2 ? hi : m2;
+                m1 = v[i] < m1 ? v[i] : m1;
+            }
+        }
+        const uint32_t s1 = wave_sort_u32(m1, lane), s2 = wave_sort_u32(m2, lane);
+        const uint32_t s2r = (uint32_t)__shfl((int)s2, 63 - lane);
+        const uint32_t tau = (uint32_t)__builtin_amdgcn_readlane((int)wave_merge_u32(s1 < s2r ? s1 : s2r, lane), itopk - 1);
+        const uint32_t limit = tau == 0xFFFFFFFFu ? 0xFFFFFFFEu : __float_as_uint(__uint_as_float(tau) + 2.0f * B);
+        int n_blocks = 0;
+        if (blocks) {
+            wave_sync<STREAM_SEEDS>();
+#pragma unroll
+            for (int i = 0; i < NBLK; ++i) {
+                if (i * 64 >= nb) break;   // (wave-uniform)
+                const bool pass = v[i] <= limit && i * 64 + lane < nb;
+                const uint64_t m = __ballot(pass);
+                const int at = n_blocks + __popcll(m & ((1ull << lane) - 1ull));
+                if (pass && at < 128) cand_g[at] = i * 64 + lane;
+                n_blocks += __popcll(m);
+            }
+            wave_sync<STREAM_SEEDS>();
+            if (n_blocks > 128) return 129;
+        }
+        // 32 blocks, or as many seeds of the row, at a time
+        const int n_read = blocks ? n_blocks * 32 : ns;
+        int cnt = 0;
+        wave_sync<STREAM_SEEDS>();
+        for (int i0 = 0; i0 < n_read; i0 += 64 * NBLK) {
+            if (blocks || ns > 64 * NBLK) {   // (else they are in the registers)
+#pragma unroll
+                for (int i = 0; i < NBLK; ++i) {
+                    v[i] = 0xFFFFFFFFu;
+                    if (i0 + i * 64 < n_read) {
+                        const int r = i0 + i * 64 + lane;
+                        const int j = blocks ? (r < n_read ? cand_g[r >> 5] * 32 + (r & 31) : ns) : r;
+                        if (j < ns) v[i] = drow[j];
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NBLK; ++i) {
+                if (i0 + i * 64 >= n_read) break;   // (wave-uniform)
+                const bool pass = v[i] <= limit;
+                const uint64_t m = __ballot(pass);
+                if (m == 0) continue;
+                const int r = i0 + i * 64 + lane, at = cnt + __popcll(m & ((1ull << lane) - 1ull));
+                if (pass && at < 128) cand_c[at] = blocks ? cand_g[r >> 5] * 32 + (r & 31) : r;
+                cnt += __popcll(m);
+            }
+        }
+        wave_sync<STREAM_SEEDS>();
+        return cnt;
+    };
+
+    if constexpr (E == 1 && DT == 1 && !AND && !STREAM_SEEDS) {
+        if ((bq.dseed_row != nullptr || bq.runs != nullptr) && p.seed_approx != 0) {
+            const float B = approx_error();
+            int cnt;
+            if (bq.runs != nullptr) {   // the seed kernel has selected: those up to tau + 2 B have to be among what it kept
+                TopM<1> tmp;
+                tmp.init(p.seed_keep);
+                merge_runs(tmp, true);
+                n_scored = 0;
+                const uint32_t a = (uint32_t)(tmp.cur[0] >> 32);
+                const uint32_t tau = (uint32_t)__builtin_amdgcn_readlane((int)a, itopk - 1);
+                const uint32_t limit = tau == 0xFFFFFFFFu ? 0xFFFFFFFEu : __float_as_uint(__uint_as_float(tau) + 2.0f * B);
+                const uint64_t m = __ballot(a <= limit && tmp.cur[0] != KEY_MAX);   // (a sorted list: the first lanes)
+                wave_sync<STREAM_SEEDS>();
+                if ((m >> lane) & 1ull) cand_c[lane] = (int32_t)((tmp.cur[0] >> 1) & 0x7FFFFFFFu);
+                wave_sync<STREAM_SEEDS>();
+                cnt = tmp.worst != KEY_MAX && (uint32_t)(tmp.worst >> 32) <= limit ? 129 : __popcll(m);
+            } else {
+                // (the minima's tau lets a quarter more through: where that is too many, the row's)
+                bool blocks = bq.dmin_row != nullptr && ns > 32 * (kSeedMinimaF32 * itopk - 1) && ns <= 64 * 32 * VF_SEED_BLOCKS;
+                while (true) {
+                    cnt = collect(B, blocks);
+                    if (cnt <= 128 || !blocks) break;
+                    blocks = false;
+                }
+            }
+            // (every one of them: the approximations were of no use)
+            if (cnt <= 128 && (cnt < ns || ns <= 64)) {
+                for (int i = lane; i < cnt; i += 64) {
+                    const int c = seed_local_id((uint32_t)cand_c[i], (uint32_t)n, (uint32_t)ns);
+                    cand_c[i] = c;
+                    cand_g[i] = p.meta.M_HS[base + c];
+                }
+                wave_sync<STREAM_SEEDS>();
+                score(cnt, true);
+                n_scored = ns;
+                n_rescored = cnt;
+                seeds_done = true;
+            } else {   // the gather path below scores every seed
+                seed_fallback = 1;
+                if (p.fallback_count != nullptr && lane == 0) atomicAdd(p.fallback_count, 1u);
+            }
+        }
+    }
+    if constexpr (E == 1 && DT == 1 && AND) {
         if ((bq.dseed_row != nullptr || bq.runs != nullptr) && p.seed_approx != 0) {
             // The seeds were scored approximately on the matrix cores.  Keep the seed_keep best of them, re-score
             // those with the ordered distance, and accept the result only if every other seed is provably
@@ -796,15 +929,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 const int cnt = __popcll(__ballot(valid));
                 if (valid) { cand_c[lane] = c; cand_g[lane] = p.meta.M_HS[base + c]; }
                 wave_sync<STREAM_SEEDS>();
-                float qn = 0.f;
-                for (int i = lane; i < nchunks; i += 64) {
-                    const uint4 v = qv[i];
-                    const float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
-                    qn += f[0] * f[0] + f[1] * f[1] + f[2] * f[2] + f[3] * f[3];
-                }
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) qn += __shfl_xor(qn, o);
-                const float B = p.err_bound * (qn + p.xn_max) + p.err_q * sqrtf(qn);
+                const float B = approx_error();
                 const bool all_kept = tmp.worst == KEY_MAX;
                 // The kept seeds are re-scored in the order of their approximations, first enough to fill the list and
                 // eight to spare, then eight at a time, until everything not re-scored yet is provably worse than the

@@ -262,6 +262,7 @@ struct SeedParams {
     // seed_mfma_kernel, optional: the seeds of every graph list for this n_seeds as an interleaved copy
     // ([group][chunk][32] 16-byte chunks like a scan list, 32 seeds per group in seed order, zero padded)
     const uint4 *seed_blk;
+    int32_t blk_chunks;         // chunks of a seed in it
     int32_t seed_bf16;          // float32 data: seed_blk holds the seeds rounded to bfloat16 (chunks of 8 components)
     const uint32_t *seed_norm;  // [group * 32 + v] squared norms as in xnorm_all
     const int64_t *seed_goff;   // [n_graph_labels] first group of each graph list, by rank among graph labels
@@ -302,6 +303,10 @@ void launch_seed_pack_bf16(const uint4 *blk32, int64_t n_groups, int32_t nch16, 
 void launch_seed_map(const int32_t *M_HS, const int64_t *slot_base, const int32_t *slot_n, int32_t n_seeds,
                      const int32_t *grp_slot, const int32_t *grp_j0, int64_t n_groups, int32_t *seed_map, hipStream_t s);
 
+// 32-seed blocks per list entry from which the minima of float32 seeds are used: 10,000 queries with 80 blocks for 32 entries, beam
+// kernel 99.7 -> 91.2 us (seed kernel 38.8 -> 41.2); at fewer the bound they give lets too many seeds through
+constexpr int kSeedMinimaF32 = 2;
+constexpr int kSeedMfmaLeast = 192;   // seeds from which a copy of them is kept for dimensions without an instantiation of their own
 constexpr int kSeedMfmaChunk = 128;  // seeds per wave of the MFMA seed kernel when it gathers rows (four 32-seed groups)
 
 // does the dimension have an instantiation of the ordered-distance seed kernel for itself?
@@ -311,6 +316,8 @@ bool seed_dist_pays(int dtype, int dim, int n_seeds, int64_t n_gq, int64_t n_and
 void launch_seed_dist(int dtype, const SeedParams &p, int n_tiles, hipStream_t s);
 // |q|^2 + |x|^2 - 2 q.x through the matrix cores: approximate for float32, exact for uint8
 bool seed_mfma_supported(int dtype, int dim);
+bool seed_mfma_own(int dtype, int dim);   // ... with an instantiation of its own, which needs no copy of the seeds
+bool seed_mfma_pays(int dtype, int dim, int32_t itopk, int n_seeds, int64_t n_gq);   // others: whether the launch pays where the ordered one does not
 void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s);
 // uint8: squared norms of all rows of a table, of the -128 shifted bytes (float32: launch_row_norms_f32)
 void launch_row_norms_u8(const void *X, int32_t dim, int64_t n, uint32_t *out, hipStream_t s);

@@ -112,8 +112,8 @@ int drop_seed_copies(vf_index *ix)
 // more than half of the free device memory: the seed kernel then gathers rows from the vector table.
 bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_seeds)
 {
-    return !exact && !ix->graph_labels.empty() && ix->seed_mfma_ok && !ix->tune.seed_exact && n_seeds > 64 &&
-           (ix->dtype == VF_U8 || itopk <= 48);
+    return !exact && !ix->graph_labels.empty() && ix->seed_mfma_ok && !ix->tune.seed_exact && (ix->dtype == VF_U8 || itopk <= 64) &&
+           (seed_mfma_own(ix->dtype, ix->dim) ? n_seeds > 64 : n_seeds >= kSeedMfmaLeast && (ix->dtype == VF_U8 || (ix->tune.seed_bf16 && !ix->seed_bf16_off)));
 }
 
 int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, SeedCopy **out)
@@ -454,8 +454,11 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     P.n_gq = r.gq_query.size();
     P.ns_stride = (n_seeds + 31) & ~31;
     // Seeds on the matrix cores.  uint8: they give the exact integer distances, nothing else changes.
-    // float32: approximations, re-ranked by the beam kernel (its proof needs a list of at most 48 entries).
-    const bool mfma_ok = wants_seed_copy(ix, exact, itopk, n_seeds) && P.n_gq > 0;
+    // float32: approximations, re-ranked by the beam kernel (its proof under a predicate needs a list of at most 48 entries).
+    // Dimensions without an instantiation of their own are scored from the seeds' copy only.
+    const bool own_dim = seed_mfma_own(ix->dtype, ix->dim);
+    const bool mfma_ok = wants_seed_copy(ix, exact, itopk, n_seeds) && P.n_gq > 0 && (ix->dtype == VF_U8 || itopk <= 48 || !r.any_and) &&
+                         (own_dim || (!P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || sc->has_bf16)));
     // With an interleaved seed copy the seed kernel also selects (itopk <= 64: the beam kernel's one-register
     // list): it leaves sel_K keys per (query, seed segment) instead of every distance.  float32 data: from the
     // bfloat16 copy; calls with few graph queries keep the float32 copy and the unfused kernel (their proofs
@@ -502,7 +505,9 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         // every distance goes through the seed distance matrix, which must fit
         const uint64_t need = (uint64_t)P.n_gq * (uint64_t)P.ns_stride + 64 * 1024;
         const int64_t n_and = seed_dist_own(ix->dtype, ix->dim) ? 0 : and_queries();
-        P.dense_seeds = !exact && P.n_gq > 0 && seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq, n_and) && budget.fits(need);
+        P.dense_seeds = !exact && P.n_gq > 0 && budget.fits(need) &&
+                        (seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq, n_and) ||
+                         (mfma_ok && seed_mfma_pays(ix->dtype, ix->dim, itopk, n_seeds, (int64_t)P.n_gq)));
         P.seeds_mfma = P.dense_seeds && mfma_ok;
         if (P.dense_seeds) P.dseed_words = (size_t)need;
     }
@@ -517,14 +522,13 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         }
     }
     // The minima of the seeds' blocks, where the seeds come from their copy and enough queries can use them: no predicate, and
-    // three blocks per kept seed or more (fewer: most blocks would be read anyway).  50,000 uint8 queries with 16,384 seeds:
+    // three blocks per list entry or more (fewer: most blocks would be read anyway), float32 two.  50,000 uint8 queries with 16,384 seeds:
     // seed kernel 805 -> 825 us, beam kernel 1,561 -> 1,260; 10,000 float32 queries with 6,144 seeds: 107 -> 115 and 269 ->
     // 221 us; a lone query, whose wave otherwise goes through
     // the whole row by itself, 74 -> 65 us, 64 queries 109 -> 103.
     if (P.seeds_mfma && !P.seed_select && !P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || !r.any_and)) {
-        const int32_t keep = ix->dtype == VF_U8 ? itopk : std::min(64, itopk + std::max(tune.seed_margin_bf16, tune.seed_margin));
         const int32_t stride = (P.ns_stride / 32 + 15) & ~15;
-        if (P.ns_stride / 32 >= 3 * keep && 2 * and_queries() <= (int64_t)P.n_gq && budget.fits((uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride)) {
+        if (P.ns_stride / 32 >= (ix->dtype == VF_U8 ? 3 : kSeedMinimaF32) * itopk && 2 * and_queries() <= (int64_t)P.n_gq && budget.fits((uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride)) {
             P.nb_stride = stride;
             P.dseed_words += P.n_gq * (size_t)stride;
         }
@@ -697,8 +701,9 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 if (sc != nullptr && sc->ok) {
                     // without the watch on failed proofs (it needs a pinned counter) the bfloat16 form is used only
                     // where it is the only one
-                    const bool use16 = sc->has_bf16 &&
-                                       (!sc->has_f32 || (may_allocate && (int64_t)n_gq >= tune.seed_bf16_min_batch));
+                    const bool use16 = sc->has_bf16 && (!sc->has_f32 || !seed_mfma_own(ix->dtype, ix->dim) ||
+                                                        (may_allocate && (int64_t)n_gq >= tune.seed_bf16_min_batch));
+                    sd.blk_chunks = use16 ? ix->ncp : 2 * ix->ncp;
                     sd.seed_blk = use16 ? sc->blk16.as<uint4>() : sc->blk.as<uint4>();
                     sd.seed_norm = sc->norm.as<uint32_t>();
                     sd.seed_goff = sc->goff.as<int64_t>();

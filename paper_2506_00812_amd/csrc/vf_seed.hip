@@ -189,11 +189,15 @@ __device__ __forceinline__ uint32_t group_min(const uint32_t (&bits)[16], bool v
     return r[0] < r[1] ? r[0] : r[1];
 }
 
-template <int DT, int NCP, bool CACHED, int NG>
+// FIT = false: vectors of fewer than NCP contraction steps (dimensions without an instantiation of their own; from the copy
+// only).  The steps that do not exist have a zero query operand and read the copy's last chunk once more.
+template <int DT, int NCP, bool CACHED, int NG, bool FIT = true>
 __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
 {
-    static_assert(DT != 2 || CACHED, "bfloat16 seeds exist only as the interleaved copy");
-    constexpr int NCH = 2 * NCP, row_bytes = (DT == 2 ? 2 : 1) * NCH * kChunkBytes;   // row_bytes: of a query
+    static_assert((DT != 2 && FIT) || CACHED, "bfloat16 seeds exist only as the interleaved copy");
+    constexpr int NCH = 2 * NCP;
+    const int blk_chunks = FIT ? NCH : p.blk_chunks;   // 16-byte chunks of a seed in the copy
+    const int row_bytes = FIT ? (DT == 2 ? 2 : 1) * NCH * kChunkBytes : p.dim * (DT == 0 ? 1 : 4);   // of a query
     __shared__ uint4 qtile[(DT == 2 ? 2 : 1) * NCH * 32];   // DT 2: high parts, then low parts
     __shared__ uint32_t qnorm_s[32];   // float bits / int
     const int lane = threadIdx.x, n32 = lane & 31, h = lane >> 5;
@@ -238,9 +242,12 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
             const int c = 2 * c0 + h;
             if constexpr (DT == 2) {   // components 8 c .. 8 c + 7
                 uint4 v0 = make_uint4(0, 0, 0, 0), v1 = v0;
-                if (qr >= 0) {
-                    v0 = *(const uint4 *)(qp + (2 * c) * kChunkBytes);
-                    v1 = *(const uint4 *)(qp + (2 * c + 1) * kChunkBytes);
+                if (qr >= 0) {   // (chunks that do not exist: the first one, and zeros in its place)
+                    const bool in0 = FIT || 2 * c * kChunkBytes < row_bytes, in1 = FIT || (2 * c + 1) * kChunkBytes < row_bytes;
+                    v0 = *(const uint4 *)(qp + (in0 ? 2 * c * kChunkBytes : 0));
+                    v1 = *(const uint4 *)(qp + (in1 ? (2 * c + 1) * kChunkBytes : 0));
+                    if (!in0) v0 = make_uint4(0, 0, 0, 0);
+                    if (!in1) v1 = make_uint4(0, 0, 0, 0);
                 }
                 const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
                 uint32_t hi[8], lo[8];
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
                 continue;
             }
             uint4 v = make_uint4(0, 0, 0, 0);
-            if (qr >= 0) {
+            if (qr >= 0 && (FIT || c * kChunkBytes < row_bytes)) {
                 v = *(const uint4 *)(qp + c * kChunkBytes);
                 if (DT == 0) { v.x ^= 0x80808080u; v.y ^= 0x80808080u; v.z ^= 0x80808080u; v.w ^= 0x80808080u; }
             }
@@ -293,9 +300,9 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
     uint4 bnext[NCP];
     auto fetch_group = [&](int g) {   // group g of this wave's seeds (exists)
         if (cached) {
-            const uint4 *blk = p.seed_blk + (grp0 + g) * (int64_t)(NCH * 32);
+            const uint4 *blk = p.seed_blk + (grp0 + g) * (int64_t)(blk_chunks * 32);
 #pragma unroll
-            for (int cp = 0; cp < NCP; ++cp) bnext[cp] = blk[(2 * cp + h) * 32 + n32];
+            for (int cp = 0; cp < NCP; ++cp) bnext[cp] = blk[(FIT || 2 * cp + h < blk_chunks ? 2 * cp + h : blk_chunks - 1) * 32 + n32];
         } else {
             const char *xrow = (const char *)p.X + (int64_t)gid[g] * row_bytes;
 #pragma unroll
@@ -728,9 +735,46 @@ void launch_seed_pass_count(const int32_t *gq_query, const int32_t *gq_label, co
                        others, pass_count);
 }
 
-bool seed_mfma_supported(int dtype, int dim)
+bool seed_mfma_own(int dtype, int dim)
 {
     return dtype == 1 ? (dim == 96 || dim == 128) : (dim == 128 || dim == 192);
+}
+
+// (the bound of the float32 proofs is that of 512 products)
+bool seed_mfma_supported(int dtype, int dim) { return dim <= (dtype == 1 ? 256 : 512); }
+
+// Dimensions without an instantiation of their own score on the matrix cores wherever the ordered kernel would score them, and
+// beyond its lines (seed_dist_pays) from 192 seeds on.  Whole calls among others, before (gathered or ordered) -> on the matrix
+// cores, at 192 / 384 / 1,024 / 4,096 seeds:
+//   float32 dim 100    1 query      48 65 65 72 -> 42 43 44 47 us,   3,000 queries   91 115 123 263 -> 77 78 73 92
+//   float32 dim 200   64 queries    72 99 109 124 -> 60 61 61 65,    3,000 queries   114 142 238 719 -> 99 100 97 120
+//   float32 dim 200   64 AND pairs  71 95 176 649 -> 68 70 71 88,    3,000 AND pairs 119 147 231 659 -> 110 113 117 161
+//   uint8 dim 112      1 query      46 47 47 55 -> 39 40 41 42,      3,000 AND pairs 84 98 98 150 -> 75 81 85 120
+//   uint8 dim 400      1 query      52 83 82 89 -> 44 44 43 43,      3,000 queries   121 145 193 372 -> 89 92 95 108
+// Lists of more than 48 entries re-score more, and ordered distances, where they are given, need none of that: from four
+// million pairs on (dim 200, 3,000 queries x 4,096 seeds 743 -> 150 us).
+bool seed_mfma_pays(int dtype, int dim, int32_t itopk, int n_seeds, int64_t n_gq)
+{
+    if (!seed_mfma_supported(dtype, dim)) return false;
+    if (itopk > 48) return (int64_t)n_seeds * n_gq >= (int64_t)1 << 22;
+    return n_seeds >= kSeedMfmaLeast;
+}
+
+// Dimensions without an instantiation of their own: the next larger one, from the copy of the seeds.
+template <int DT, int NCP> static void launch_seed_mfma_nofit(const SeedParams &p, dim3 grid, hipStream_t s)
+{
+    if (p.chunk_seeds == 4 * kSeedMfmaChunk) hipLaunchKernelGGL((seed_mfma_kernel<DT, NCP, true, 16, false>), grid, dim3(64), 0, s, p);
+    else if (p.chunk_seeds == 32) hipLaunchKernelGGL((seed_mfma_kernel<DT, NCP, true, 1, false>), grid, dim3(64), 0, s, p);
+    else hipLaunchKernelGGL((seed_mfma_kernel<DT, NCP, true, 4, false>), grid, dim3(64), 0, s, p);
+}
+template <int DT> static void launch_seed_mfma_any(const SeedParams &p, dim3 grid, hipStream_t s)
+{
+    const int steps = (p.blk_chunks + 1) / 2;
+    if (steps <= 2) launch_seed_mfma_nofit<DT, 2>(p, grid, s);
+    else if (steps <= 4) launch_seed_mfma_nofit<DT, 4>(p, grid, s);
+    else if (steps <= 8) launch_seed_mfma_nofit<DT, 8>(p, grid, s);
+    else if (steps <= 12) launch_seed_mfma_nofit<DT, 12>(p, grid, s);
+    else launch_seed_mfma_nofit<DT, 16>(p, grid, s);
 }
 
 void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s)
@@ -743,6 +787,11 @@ void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s
     const bool cached = p.seed_blk != nullptr;
     const bool wide = cached && p.chunk_seeds == 4 * kSeedMfmaChunk;
     const bool narrow = cached && p.chunk_seeds == 32;
+    if (!seed_mfma_own(dtype, p.dim)) {
+        if (dtype == 0) launch_seed_mfma_any<0>(p, grid, s);
+        else launch_seed_mfma_any<2>(p, grid, s);
+        return;
+    }
 #define VF_LAUNCH_SEED(DT_, NCP_) \
     do { \
         if (wide) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 16>), grid, block, 0, s, p); \

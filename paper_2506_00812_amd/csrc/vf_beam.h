@@ -777,15 +777,22 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
 
     // What the proofs of approximate seeds allow for: |approximation - ordered distance| <= B.
     auto approx_error = [&]() -> float {
-        float qn = 0.f;
+        float qn = 0.f, en = 0.f;   // |q|^2, |q - q^|^2 (see vf_seed.hip)
+        const float unscale = p.scale > 0.f ? 1.0f / p.scale : 0.f;
         for (int i = lane; i < nchunks; i += 64) {
             const uint4 v = qv[i];
             const float f[4] = {__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
             qn += f[0] * f[0] + f[1] * f[1] + f[2] * f[2] + f[3] * f[3];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const float d = f[w] - (float)(_Float16)(f[w] * p.scale) * unscale;
+                en += d * d;
+            }
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) qn += __shfl_xor(qn, o);
-        return p.err_bound * (qn + p.xn_max) + p.err_q * sqrtf(qn);
+        for (int o = 32; o > 0; o >>= 1) { qn += __shfl_xor(qn, o); en += __shfl_xor(en, o); }
+        if (!(qn <= p.q_max)) return __builtin_inff();
+        return p.err_bound * (qn + p.xn_max) + p.err_q * sqrtf(qn) + (p.scale > 0.f ? 2.001f * sqrtf(en * p.xn_max) : 0.f);
     };
     // The seeds that may belong to the list, for queries without a predicate: with tau at or above the itopk-th smallest
     // approximation, itopk seeds have ordered distances of at most tau + B, and a seed of an approximation above tau + 2 B has

@@ -103,9 +103,9 @@ struct Tuning {
     int seed_exact = 0;           // 1: seeds are scored by the ordered-distance kernel, never on the matrix cores
     double seed_slack = 1.0;      // scales the rounding-error bound of the float32 seed proofs
     int seed_margin = 8;          // approximations kept beyond itopk for re-ranking (float32 copy of the seeds)
-    int seed_margin_bf16 = 24;    // the same from the bfloat16 copy
+    int seed_margin_bf16 = 24;    // the same from the 16-bit (binary16) copy
     int seed_cache = 1;           // 0: no interleaved copy of the seeds, the seed kernel gathers rows
-    int seed_bf16 = 1;            // 0: float32 data keep only the float32 copy of the seeds
+    int seed_bf16 = 1;            // 0: float32 data keep only the float32 copy of the seeds, not the 16-bit one
     int seed_bf16_min_batch = 512;   // calls with fewer graph queries use the float32 copy when it is resident
     int seed_fb_window = 131072;  // graph queries between two looks at the failed-proof counter
     int seed_select = 0;          // 1: the seed kernel also selects (runs of keys instead of every distance; itopk <= 64)
@@ -205,8 +205,8 @@ struct SeedCopy {
     int32_t n_seeds = -1;        // -1: slot unused
     bool ok = false;             // false: the copy did not fit, the kernel gathers rows from the vector table
     bool has_f32 = false;        // blk is valid
-    bool has_bf16 = false;       // blk16 is valid (float32 data only)
-    float bf16_delta = 0.f;      // upper bound of |x - bf16(x)| over the seeds of the copy
+    bool has_f16 = false;        // blk16 is valid (float32 data only)
+    float f16_delta = 0.f;       // upper bound of the rounding errors |x - x^| of the seeds of the copy
     uint64_t last_use = 0;
     DevBuf blk, blk16, norm, goff;
     DevBuf map;                  // [group * 32 + v] global id of the seed (AND predicate inside the seed kernel)
@@ -265,7 +265,7 @@ struct vf_index {
     static constexpr int kSeedCopies = 4;
     vf::SeedCopy seed_copies[kSeedCopies];
     uint64_t seed_tick = 0;
-    // Watch on the bfloat16 form of the seed copies: queries whose proof failed are counted on the device; the
+    // Watch on the 16-bit form of the seed copies: queries whose proof failed are counted on the device; the
     // count is fetched every tune.seed_fb_window graph queries and read at a later call, and a window with more
     // than 1/64 failures switches this index back to float32 copies (a failed proof costs its query a gather of
     // every seed).
@@ -311,6 +311,14 @@ struct vf_index {
     size_t group_bytes() const { return (size_t)2 * ncp * 32 * 16; }
     // float32 seed proofs: |approximation - ordered distance| <= seed_err_bound() (|q|^2 + xn_max)
     float seed_err_bound() const { return (float)(tune.seed_slack * 3.0517578125e-05); }
+    // the power of two that brings the largest norm into [32, 64): binary16 operands
+    static float half_scale(float norm2)
+    {
+        int e;
+        (void)std::frexp(std::sqrt(norm2), &e);
+        return std::ldexp(1.f, 6 - e);
+    }
+    float seed_scale() const { return xn_max > 0.f ? half_scale(xn_max) : 1.f; }
     // squared norms the join kernel takes for its lists
     const uint32_t *join_norms() const { return dtype == VF_U8 ? d_xnorm_all.as<uint32_t>() : d_xnorm_c.as<uint32_t>(); }
     // the operands of a self-join, and of a join of queries
@@ -330,14 +338,8 @@ struct vf_index {
     {
         return kind == vf::kJoinSingle ? 2.01f * (xc_rho + (own ? xc_rho : 4.8828125e-04f)) * std::sqrt(xc_max) : 0.f;
     }
-    // the power of two that brings the largest centred norm of the table into [32, 64)
-    float join_scale(int kind) const
-    {
-        if (kind != vf::kJoinSingle || !(xc_max > 0.f)) return 1.f;
-        int e;
-        (void)std::frexp(std::sqrt(xc_max), &e);
-        return std::ldexp(1.f, 6 - e);
-    }
+    // its scale is that of the centred norms
+    float join_scale(int kind) const { return kind == vf::kJoinSingle && xc_max > 0.f ? half_scale(xc_max) : 1.f; }
 };
 
 namespace vf {
@@ -385,10 +387,10 @@ struct CallPlan {
     size_t n_xq = 0;                      // AND queries answered by the exact predicate scan of a short graph list
     bool dense_seeds = false, seeds_mfma = false;
     // seeds_mfma with the selection fused into the seed kernel: runs of sel_K keys per (query, segment)
-    bool seed_select = false, sel_bf16 = false;
+    bool seed_select = false, sel_f16 = false, seeds_f16 = false;
     int32_t sel_K = 0, seg_seeds = 0, max_segs = 0;
     BlobLayout L{};
-    size_t dseed_words = 0;               // seed distance matrix + the dump area behind it
+    size_t dseed_words = 0;               // seed distance matrix
     size_t part_words = 0;                // partial result rows x k (x scan_keep with the bfloat16 filter)
     // float32 scan lists filtered from their bfloat16 copy and re-ranked
     bool scan_bf16 = false;
@@ -435,7 +437,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
 bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_seeds);
 // The resident copy for n_seeds, or (build = true) a new one; *out stays null when there is none.
 int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, SeedCopy **out);
-int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_bf16, SeedCopy *c);
+int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16, SeedCopy *c);
 void fill_blob(const CallPlan &P, const Routed &r, char *hp);
 int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem &M, const SeedCopy *sc, const void *queries,
                 int64_t *out_ids, float *out_dists, hipStream_t s, hipStream_t side, hipEvent_t ev_fork,

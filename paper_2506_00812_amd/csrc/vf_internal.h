@@ -221,8 +221,9 @@ struct BeamParams {
     int32_t seed_approx;
     int32_t seed_keep;  // approximations kept for re-ranking (itopk < seed_keep <= 64)
     float err_bound, xn_max;
+    float scale, q_max;        // seeds scored from their binary16 copy: scale of both operands (else 0), largest |q|^2 that it takes
     uint32_t *fallback_count;  // optional: incremented once per query whose proof failed
-    float err_q;        // 0 unless the seeds were scored from their bfloat16 copy: 2 * max |x - bf16(x)| over the seeds
+    float err_q;        // 0 unless the seeds were scored from their binary16 copy: 2 * max |x - x^| over the seeds (and what |q^| may exceed |q| by)
     // seeds scored with the selection fused in (seed_select_kernel; itopk <= 64): per query run_segs runs of run_K
     // keys, of which the first ceil(min(n_seeds, |C_l|) / seg_seeds) exist.  uint8: exact distances; float32:
     // approximations (seed_approx != 0, run_K == seed_keep)
@@ -235,7 +236,7 @@ struct BeamParams {
     const int32_t *seed_map;
     const int64_t *seed_goff;
     int32_t lat_waves;         // launches of at most this many graph queries (itopk <= 64) run the latency instantiation
-    // optional: an interleaved copy of the seeds (uint8 or float32, never bfloat16) from which a wave scores its
+    // optional: an interleaved copy of the seeds (uint8 or float32, never binary16) from which a wave scores its
     // seeds itself when no dense seed kernel ran (the serving kernel); sgoff: first group of each graph list
     const uint4 *sblk;
     const int64_t *sgoff;
@@ -263,14 +264,13 @@ struct SeedParams {
     // ([group][chunk][32] 16-byte chunks like a scan list, 32 seeds per group in seed order, zero padded)
     const uint4 *seed_blk;
     int32_t blk_chunks;         // chunks of a seed in it
-    int32_t seed_bf16;          // float32 data: seed_blk holds the seeds rounded to bfloat16 (chunks of 8 components)
+    int32_t seed_f16;           // float32 data: seed_blk holds the seeds times `scale` rounded to binary16 (chunks of 8 components)
+    float scale, minus_two_unscaled;   // float32 data: the power of two both operands are multiplied with, and -2 / scale^2
     const uint32_t *seed_norm;  // [group * 32 + v] squared norms as in xnorm_all
     const int64_t *seed_goff;   // [n_graph_labels] first group of each graph list, by rank among graph labels
     int32_t chunk_seeds;        // seeds per wave: kSeedMfmaChunk, or 32 or four times kSeedMfmaChunk (interleaved copy only); max_chunks matches it
     uint32_t *dmin;             // optional (interleaved copy only, any chunk_seeds): see BeamParams::dmin; rows of nb_stride words, a multiple of 16
     int32_t nb_stride;
-    int64_t dump_off;           // seed_mfma_kernel: dseed[dump_off .. dump_off + 64 * (dump_mask + 1)) takes the stores of
-    int32_t dump_mask;          // lanes without a pair, 64 entries per workgroup index & dump_mask (2^k - 1)
 };
 
 // Seed scoring with fused selection (seed_select_kernel): one run of K keys per (graph query, seed segment)
@@ -283,7 +283,8 @@ struct SeedSelParams {
     int32_t K;                  // keys kept per (query, segment), <= 64
     int32_t seg_seeds;          // seeds per segment, a multiple of 32
     int32_t max_segs;           // segments per tile in the grid: ceil(min(n_seeds, longest list of the batch) / seg_seeds)
-    const uint4 *seed_blk;      // interleaved copy of the seeds: uint8, or bfloat16 for float32 data
+    const uint4 *seed_blk;      // interleaved copy of the seeds: uint8, or binary16 for float32 data
+    float scale, minus_two_unscaled;   // as in SeedParams
     const uint32_t *seed_norm;  // [group * 32 + v] squared norms (int32 of the -128 shifted bytes / float bits)
     const int64_t *seed_goff;   // [n_graph_labels] first group of each graph list
     const int32_t *seed_map;    // [group * 32 + v] global id of the seed (AND predicate)
@@ -291,7 +292,7 @@ struct SeedSelParams {
     const int32_t *others;
     uint64_t *runs;             // [n_gq][max_segs][K]: (value bits << 32 | seed index), ascending, KEY_MAX = none
 };
-bool seed_select_supported(int dtype, int dim, bool bf16_copy);
+bool seed_select_supported(int dtype, int dim, bool f16_copy);
 size_t seed_select_lds_bytes(int32_t K);
 void launch_seed_select(int dtype, const SeedSelParams &p, int n_tiles, hipStream_t s);
 void launch_seed_pass_count(const int32_t *gq_query, const int32_t *gq_label, const LabelMeta &meta, int32_t n_seeds,
@@ -299,6 +300,7 @@ void launch_seed_pass_count(const int32_t *gq_query, const int32_t *gq_label, co
 
 // seed_map[g * 32 + v] = global id of seed j = grp_j0[g] + v of graph list grp_slot[g] (local id floor(j n / ns)),
 // 0 for v beyond the list's seeds
+void launch_seed_pack_f16(const uint4 *blk32, int64_t n_groups, int32_t nch16, float scale, uint4 *blk16, float *err2, hipStream_t s);
 void launch_seed_pack_bf16(const uint4 *blk32, int64_t n_groups, int32_t nch16, uint4 *blk16, float *err2, hipStream_t s);
 void launch_seed_map(const int32_t *M_HS, const int64_t *slot_base, const int32_t *slot_n, int32_t n_seeds,
                      const int32_t *grp_slot, const int32_t *grp_j0, int64_t n_groups, int32_t *seed_map, hipStream_t s);
@@ -316,6 +318,7 @@ bool seed_dist_pays(int dtype, int dim, int n_seeds, int64_t n_gq, int64_t n_and
 void launch_seed_dist(int dtype, const SeedParams &p, int n_tiles, hipStream_t s);
 // |q|^2 + |x|^2 - 2 q.x through the matrix cores: approximate for float32, exact for uint8
 bool seed_mfma_supported(int dtype, int dim);
+int seed_mfma_tile_of(int dtype, int dim, bool f16);   // queries of a tile (f16: float32 data from the binary16 copy)
 bool seed_mfma_own(int dtype, int dim);   // ... with an instantiation of its own, which needs no copy of the seeds
 bool seed_mfma_pays(int dtype, int dim, int32_t itopk, int n_seeds, int64_t n_gq);   // others: whether the launch pays where the ordered one does not
 void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s);

@@ -100,7 +100,7 @@ int drop_seed_copies(vf_index *ix)
     for (SeedCopy &c : ix->seed_copies) {
         for (DevBuf *b : c.bufs()) b->release();
         c.n_seeds = -1;
-        c.ok = c.has_f32 = c.has_bf16 = false;
+        c.ok = c.has_f32 = c.has_f16 = false;
     }
     return VF_OK;
 }
@@ -142,13 +142,13 @@ int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, Seed
     return build_seed_copy(ix, n_seeds, s, ix->dtype == VF_F32 && ix->tune.seed_bf16 && !ix->seed_bf16_off, c);
 }
 
-// Fills *c for n_seeds on stream s (complete when the call returns).  want_bf16: float32 data also get the
-// bfloat16 form (and lose the float32 one when it is larger than 128 MiB).
-int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_bf16, SeedCopy *c)
+// Fills *c for n_seeds on stream s (complete when the call returns).  want_f16: float32 data also get the
+// binary16 form (and lose the float32 one when it is larger than 128 MiB).
+int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16, SeedCopy *c)
 {
     c->n_seeds = n_seeds;
-    c->ok = c->has_f32 = c->has_bf16 = false;
-    c->bf16_delta = 0.f;
+    c->ok = c->has_f32 = c->has_f16 = false;
+    c->f16_delta = 0.f;
     if (!ix->tune.seed_cache) return VF_OK;
     const size_t n_gl = ix->graph_labels.size();
     std::vector<int64_t> goff(n_gl), slot_base(n_gl);
@@ -194,12 +194,12 @@ int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_bf16
     VF_HIP(hipGetLastError());
     VF_HIP(hipStreamSynchronize(s));   // the tables above are pageable host memory and temporaries
     c->has_f32 = true;
-    if (want_bf16) {
-        // float32 data: a second copy in bfloat16; the largest rounding error of a seed goes into the
-        // beam kernel's proof (zero for integer-valued data up to 256, SIFT's kind)
+    if (want_f16) {
+        // float32 data: a second copy in binary16; the largest rounding error of a seed goes into the
+        // beam kernel's proof (zero for integer-valued data of up to 11 bits, SIFT's kind)
         if ((rc = c->blk16.reserve((size_t)n_groups * ix->group_bytes() / 2)) != VF_OK) return rc;
         if ((rc = d_err2.reserve((size_t)n_groups * 32 * 4)) != VF_OK) return rc;
-        launch_seed_pack_bf16(c->blk.as<uint4>(), n_groups, ix->ncp, c->blk16.as<uint4>(), d_err2.as<float>(), s);
+        launch_seed_pack_f16(c->blk.as<uint4>(), n_groups, ix->ncp, ix->seed_scale(), c->blk16.as<uint4>(), d_err2.as<float>(), s);
         std::vector<float> e2((size_t)n_groups * 32);
         VF_HIP(hipMemcpyAsync(e2.data(), d_err2.p, e2.size() * 4, hipMemcpyDeviceToHost, s));
         VF_HIP(hipStreamSynchronize(s));
@@ -208,14 +208,13 @@ int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_bf16
         for (float v : e2) { finite = finite && v == v && v <= 3.0e38f; mx = v > mx ? v : mx; }
         if (!finite) c->blk16.release();
         if (finite) {
-            // small batches are served from the float32 copy (its proofs need fewer re-scored seeds, which
-            // is what a latency-bound call notices), so a copy of up to 128 MiB stays
-            if ((size_t)n_groups * ix->group_bytes() > ((size_t)128 << 20)) {
+            // small batches are served from the float32 copy, so one of up to 128 MiB stays (dimensions that have a kernel for it)
+            if ((size_t)n_groups * ix->group_bytes() > ((size_t)128 << 20) || !seed_mfma_own(ix->dtype, ix->dim)) {
                 c->blk.release();
                 c->has_f32 = false;
             }
-            c->has_bf16 = true;
-            c->bf16_delta = (float)(std::sqrt(mx) * 1.001);
+            c->has_f16 = true;
+            c->f16_delta = (float)(std::sqrt(mx) * 1.001);
             if (!ix->h_fb) {
                 if ((rc = ix->d_fb_count.reserve(4)) != VF_OK) return rc;
                 VF_HIP(hipMemsetAsync(ix->d_fb_count.p, 0, 4, s));
@@ -452,22 +451,24 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     }
     P.n_xq = r.xq_query.size();
     P.n_gq = r.gq_query.size();
-    P.ns_stride = (n_seeds + 31) & ~31;
+    const int32_t ns_blocks = (int32_t)(((int64_t)n_seeds + 31) / 32);
+    P.ns_stride = (int32_t)((int64_t)ns_blocks * 32 <= INT32_MAX ? ns_blocks * 32 : INT32_MAX & ~31);
     // Seeds on the matrix cores.  uint8: they give the exact integer distances, nothing else changes.
     // float32: approximations, re-ranked by the beam kernel (its proof under a predicate needs a list of at most 48 entries).
     // Dimensions without an instantiation of their own are scored from the seeds' copy only.
     const bool own_dim = seed_mfma_own(ix->dtype, ix->dim);
-    const bool mfma_ok = wants_seed_copy(ix, exact, itopk, n_seeds) && P.n_gq > 0 && (ix->dtype == VF_U8 || itopk <= 48 || !r.any_and) &&
-                         (own_dim || (!P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || sc->has_bf16)));
+    // (a tile's rows are addressed by 32-bit offsets)
+    const bool mfma_ok = wants_seed_copy(ix, exact, itopk, n_seeds) && P.n_gq > 0 && P.ns_stride <= 1 << 23 && (ix->dtype == VF_U8 || itopk <= 48 || !r.any_and) &&
+                         (own_dim || (!P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || sc->has_f16)));
     // With an interleaved seed copy the seed kernel also selects (itopk <= 64: the beam kernel's one-register
     // list): it leaves sel_K keys per (query, seed segment) instead of every distance.  float32 data: from the
-    // bfloat16 copy; calls with few graph queries keep the float32 copy and the unfused kernel (their proofs
+    // binary16 copy; calls with few graph queries keep the float32 copy and the unfused kernel (their proofs
     // need fewer re-scored seeds, which a latency-bound call notices).
     const Tuning &tune = ix->tune;
     if (mfma_ok && sc != nullptr && sc->ok && tune.seed_select && itopk <= 64 &&
-        seed_select_supported(ix->dtype, ix->dim, sc->has_bf16) &&
+        seed_select_supported(ix->dtype, ix->dim, sc->has_f16) &&
         (ix->dtype == VF_U8 || !sc->has_f32 || (int64_t)P.n_gq >= tune.seed_bf16_min_batch)) {
-        P.sel_bf16 = ix->dtype == VF_F32;
+        P.sel_f16 = ix->dtype == VF_F32;
         P.sel_K = ix->dtype == VF_U8 ? itopk : std::min(64, itopk + std::max(tune.seed_margin_bf16, tune.seed_margin));
         int32_t longest = 0;
         size_t n_tiles = 0;
@@ -503,7 +504,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     };
     if (!P.seed_select) {
         // every distance goes through the seed distance matrix, which must fit
-        const uint64_t need = (uint64_t)P.n_gq * (uint64_t)P.ns_stride + 64 * 1024;
+        const uint64_t need = (uint64_t)P.n_gq * (uint64_t)P.ns_stride;
         const int64_t n_and = seed_dist_own(ix->dtype, ix->dim) ? 0 : and_queries();
         P.dense_seeds = !exact && P.n_gq > 0 && budget.fits(need) &&
                         (seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq, n_and) ||
@@ -512,7 +513,12 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         if (P.dense_seeds) P.dseed_words = (size_t)need;
     }
     if (P.dense_seeds) {
-        const size_t tile_q = P.seeds_mfma ? 32 : 64;
+        // (without the watch on failed proofs, which needs a pinned counter, the binary16 form is used only where it is the only one)
+        P.seeds_f16 = P.seeds_mfma && ix->dtype == VF_F32 && sc != nullptr && sc->ok && sc->has_f16 &&
+                      (!sc->has_f32 || !own_dim || (!P.tight && (int64_t)P.n_gq >= tune.seed_bf16_min_batch));
+        size_t tile_q = P.seed_select ? 32 : P.seeds_mfma ? (size_t)seed_mfma_tile_of(ix->dtype, ix->dim, P.seeds_f16) : 64;
+        // (launches that would leave SIMDs without a wave even at 128 seeds a wave: smaller tiles)
+        if (P.seeds_mfma && (int64_t)(P.n_gq / 64) * ((n_seeds + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 1024) tile_q = 32;
         for (size_t i = 0; i < P.n_gq;) {
             size_t e = i;
             while (e < P.n_gq && r.gq_label[e] == r.gq_label[i]) ++e;
@@ -527,8 +533,8 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     // 221 us; a lone query, whose wave otherwise goes through
     // the whole row by itself, 74 -> 65 us, 64 queries 109 -> 103.
     if (P.seeds_mfma && !P.seed_select && !P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || !r.any_and)) {
-        const int32_t stride = (P.ns_stride / 32 + 15) & ~15;
-        if (P.ns_stride / 32 >= (ix->dtype == VF_U8 ? 3 : kSeedMinimaF32) * itopk && 2 * and_queries() <= (int64_t)P.n_gq && budget.fits((uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride)) {
+        const int32_t stride = (ns_blocks + 15) & ~15;
+        if (ns_blocks >= (ix->dtype == VF_U8 ? 3 : kSeedMinimaF32) * itopk && 2 * and_queries() <= (int64_t)P.n_gq && budget.fits((uint64_t)P.dseed_words + (uint64_t)P.n_gq * (uint64_t)stride)) {
             P.nb_stride = stride;
             P.dseed_words += P.n_gq * (size_t)stride;
         }
@@ -649,6 +655,13 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                                    ix->counters.as<int32_t>() + (size_t)P.nq * 5, (int)n_gq, s);
         }
     };
+    // the bounds of approximations from the binary16 copy (see vf_seed.hip): 2048 u, and dx; |q^| <= |q| (1 + 2^-11) and a little
+    auto half_bound = [&](BeamParams &b, float delta) {
+        b.err_bound = ix->seed_err_bound() * 4.0f;
+        b.err_q = 2.002f * delta;
+        b.scale = ix->seed_scale();
+        b.q_max = 1.07374182e9f / (b.scale * b.scale);   // 2^30: the scaled length is below 2^15
+    };
     auto run_seeds = [&]() -> int {
         // (a profiled call that forks has recorded this event already: it is its fork event)
         if (prof && !forked) VF_HIP(hipEventRecord(ix->prof_ev[2], s));
@@ -658,16 +671,17 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
             sl.Q = queries; sl.gq_query = bp.gq_query;
             sl.tiles = (const SeedTile *)(dp + L.off_tiles); sl.meta = bp.meta;
             sl.dim = ix->dim; sl.n_seeds = P.n_seeds; sl.K = P.sel_K; sl.seg_seeds = P.seg_seeds; sl.max_segs = P.max_segs;
-            sl.seed_blk = P.sel_bf16 ? sc->blk16.as<uint4>() : sc->blk.as<uint4>();
+            sl.seed_blk = P.sel_f16 ? sc->blk16.as<uint4>() : sc->blk.as<uint4>();
             sl.seed_norm = sc->norm.as<uint32_t>();
             sl.seed_goff = sc->goff.as<int64_t>();
             sl.seed_map = sc->map.as<int32_t>();
             sl.others_off = d_others_off; sl.others = d_others;
             sl.runs = (uint64_t *)M.dseed;
+            sl.scale = ix->seed_scale(); sl.minus_two_unscaled = -2.0f / (sl.scale * sl.scale);
             launch_seed_select(ix->dtype, sl, (int)P.tiles.size(), s);
             bp.seed_runs = sl.runs; bp.run_K = P.sel_K; bp.run_segs = P.max_segs; bp.seg_seeds = P.seg_seeds;
             if (prof) {
-                ix->prof.seeds_on_matrix_cores = P.sel_bf16 ? 2 : 1;
+                ix->prof.seeds_on_matrix_cores = P.sel_f16 ? 2 : 1;
                 ix->prof.seed_selected = 1;
                 for (const SeedTile &t : P.tiles) {
                     const int64_t ns_l = std::min<int64_t>(P.n_seeds, ix->S[(size_t)t.label]);
@@ -676,12 +690,8 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 if (ix->prof_exact_counts && r.any_and) bp.seed_pass = ix->counters.as<int32_t>() + (size_t)P.nq * 5;   // filled before the timed interval
             }
             if (ix->dtype == VF_F32) {
-                // two bfloat16 products per component (<= 256 terms, <= 2 u each: 512 u), the query's split
-                // (2^-16 = 256 u), norms and final additions (< 200 u): under 1024 u; 4096 u = 2^-12 relative to
-                // |q|^2 + xn_max is used, plus 2 |q| max |x - bf16(x)|
                 bp.seed_approx = 1; bp.xn_max = ix->xn_max;
-                bp.err_bound = ix->seed_err_bound() * 8.0f;
-                bp.err_q = 2.0f * sc->bf16_delta;
+                half_bound(bp, sc->f16_delta);
                 bp.seed_keep = P.sel_K;
                 if (may_allocate) bp.fallback_count = ix->d_fb_count.as<uint32_t>();
             }
@@ -691,55 +701,50 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
             sd.tiles = (const SeedTile *)(dp + L.off_tiles); sd.meta = bp.meta;
             sd.dim = ix->dim; sd.n_seeds = P.n_seeds; sd.ns_stride = P.ns_stride;
             sd.dseed = M.dseed;
-            sd.dump_off = (int64_t)n_gq * P.ns_stride;
-            sd.dump_mask = 1023;
+            sd.scale = ix->seed_scale(); sd.minus_two_unscaled = -2.0f / (sd.scale * sd.scale);
             if (P.seeds_mfma) {
                 sd.chunk_seeds = kSeedMfmaChunk;
-                sd.max_chunks = (P.ns_stride + kSeedMfmaChunk - 1) / kSeedMfmaChunk;
+                sd.max_chunks = (P.n_seeds + kSeedMfmaChunk - 1) / kSeedMfmaChunk;
                 sd.xnorm_all = ix->d_xnorm_all.as<uint32_t>();
-                float seed_bf16_delta = 0.f;
+                float seed_delta = 0.f;
                 if (sc != nullptr && sc->ok) {
-                    // without the watch on failed proofs (it needs a pinned counter) the bfloat16 form is used only
-                    // where it is the only one
-                    const bool use16 = sc->has_bf16 && (!sc->has_f32 || !seed_mfma_own(ix->dtype, ix->dim) ||
-                                                        (may_allocate && (int64_t)n_gq >= tune.seed_bf16_min_batch));
+                    const bool use16 = P.seeds_f16;
                     sd.blk_chunks = use16 ? ix->ncp : 2 * ix->ncp;
                     sd.seed_blk = use16 ? sc->blk16.as<uint4>() : sc->blk.as<uint4>();
                     sd.seed_norm = sc->norm.as<uint32_t>();
                     sd.seed_goff = sc->goff.as<int64_t>();
-                    sd.seed_bf16 = use16 ? 1 : 0;
-                    seed_bf16_delta = sc->bf16_delta;
-                    if (prof && sd.seed_bf16) ix->prof.seeds_on_matrix_cores = 2;
+                    sd.seed_f16 = use16 ? 1 : 0;
+                    seed_delta = sc->f16_delta;
+                    if (prof && sd.seed_f16) ix->prof.seeds_on_matrix_cores = 2;
                     // seeds per wave: few long waves share the chip better with the scan (512 seeds:
                     // step 0.374 -> 0.340 ms on 10,000-query batches), small batches need many short ones
                     sd.chunk_seeds = 4 * kSeedMfmaChunk;
-                    if ((int64_t)P.tiles.size() * ((P.ns_stride + sd.chunk_seeds - 1) / sd.chunk_seeds) < 512)
+                    if ((int64_t)P.tiles.size() * ((P.n_seeds + sd.chunk_seeds - 1) / sd.chunk_seeds) < 512)
                         sd.chunk_seeds = kSeedMfmaChunk;
                     // a launch that leaves most SIMDs without a wave even so (a handful of queries): a wave per group of
                     // 32 seeds, its four groups' serial chain of MFMAs cut to one
-                    if ((int64_t)P.tiles.size() * ((P.ns_stride + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 256) sd.chunk_seeds = 32;
-                    sd.max_chunks = (P.ns_stride + sd.chunk_seeds - 1) / sd.chunk_seeds;
+                    if ((int64_t)P.tiles.size() * ((P.n_seeds + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 256) sd.chunk_seeds = 32;
+                    sd.max_chunks = (P.n_seeds + sd.chunk_seeds - 1) / sd.chunk_seeds;
                     if (P.nb_stride > 0) {
-                        sd.dmin = M.dseed + n_gq * (size_t)P.ns_stride + 64 * 1024;   // (behind the matrix and its dump area)
+                        sd.dmin = M.dseed + (P.dseed_words - n_gq * (size_t)P.nb_stride);   // (behind the matrix)
                         sd.nb_stride = P.nb_stride;
                         bp.dmin = sd.dmin; bp.nb_stride = sd.nb_stride;
                     }
                 }
                 launch_seed_mfma(ix->dtype, sd, (int)P.tiles.size(), s);
                 if (ix->dtype == VF_F32) {
-                    bp.seed_approx = 1; bp.err_bound = ix->seed_err_bound(); bp.xn_max = ix->xn_max;
+                    bp.seed_approx = 1; bp.err_bound = ix->seed_err_bound(); bp.xn_max = ix->xn_max; bp.q_max = 3.0e38f;
                     bp.seed_keep = std::min(64, P.itopk + tune.seed_margin);
-                    if (sd.seed_bf16) {
-                        // the bfloat16 bound (see above) and its wider margin: more approximations are kept for
-                        // re-ranking (a failed proof costs the query a gather of every seed)
-                        bp.err_bound = ix->seed_err_bound() * 8.0f;
-                        bp.err_q = 2.0f * seed_bf16_delta;
+                    if (sd.seed_f16) {
+                        // its wider margin: more approximations are kept for re-ranking under a predicate (a failed proof
+                        // costs the query a gather of every seed)
+                        half_bound(bp, seed_delta);
                         if (may_allocate) bp.fallback_count = ix->d_fb_count.as<uint32_t>();
                         bp.seed_keep = std::min(64, P.itopk + std::max(tune.seed_margin_bf16, tune.seed_margin));
                     }
                 }
             } else {
-                sd.max_chunks = P.ns_stride / kSeedChunk;
+                sd.max_chunks = (P.n_seeds + kSeedChunk - 1) / kSeedChunk;
                 launch_seed_dist(ix->dtype, sd, (int)P.tiles.size(), s);
             }
             bp.dseed = sd.dseed;

@@ -24,6 +24,9 @@
 //
 // Output of the unfused kernels: dseed[gq][j] = distance bits of graph query gq to seed j, consumed by the
 // beam kernel, which keeps the best itopk.
+#include <type_traits>
+#include <utility>
+
 #include "vf_select.h"
 
 namespace vf {
@@ -127,79 +130,71 @@ __global__ __launch_bounds__(64) void seed_dist_kernel(SeedParams p)
 }
 
 // ---------------------------------------------------------------------------------------------
-// float32, matrix cores.  queries x seeds of one label is a dense contraction, so the bulk of the
-// work can run on MFMA as |q|^2 + |x|^2 - 2 q.x.  That value is rounded differently from the
-// ordered distance the search is defined with, so it is used as a filter only: the beam kernel
-// keeps the itopk + margin best approximations per query (at most 64), re-scores those with the
-// ordered distance, and accepts the list only if its worst entry lies below the last kept approximation
-// by more than the rounding-error bound (else it scores every seed itself).  One wave: a tile of <= 32 queries (A operand, staged in LDS) against kSeedMfmaChunk
-// seeds in groups of 32 (B operand gathered row-wise from X: lane (v, h) reads the 16-byte
-// chunks 2c + h of seed v, the operand layout of v_mfma_f32_32x32x2_f32).
-// uint8 data go through the same kernel with v_mfma_i32_32x32x32_i8 on the vectors shifted by -128
-// (the shift cancels in q - x): the int32 result is the exact distance, so nothing is approximate
-// there and the rows of dseed are used as they are.
+// Matrix cores.  queries x seeds of one label is a dense contraction, |q|^2 + |x|^2 - 2 q.x.  One wave: a tile of <= 64 or 32
+// queries (seed_mfma_tile; in registers) against NG groups of 32 seeds; lane (v, h) holds the 16-byte chunks 2 s + h of query v, and of seed v.
+// uint8 data: v_mfma_i32_32x32x32_i8 on the vectors shifted by -128 (the shift cancels in q - x): the int32 result is the
+// exact distance, so nothing is approximate there and the rows of dseed are used as they are.
+// float32 data: v_mfma_f32_32x32x2_f32 on the rows or a float32 copy of the seeds (small batches, tables without a copy), or,
+// from a copy of the seeds in binary16, v_mfma_f32_32x32x16_f16 (a sixteenth of the matrix-core time): both operands
+// rounded to binary16 after multiplication by a power of two that brings the table's largest norm into [32, 64), norms
+// those of the unrounded vectors.  The values are a filter only: the beam kernel scores the seeds that may belong to its list
+// with the ordered distance, under a bound of the difference.  With u = 2^-24, q^ and x^ the rounded vectors (unscaled), and dx
+// the largest |x - x^|, measured when the copy is built:
+//   |2 q.x - 2 q^.x^| <= 2 |q - q^| |x|max + 2 |q^| dx    (|q - q^|: measured by the beam kernel)
+//   the sum of <= 256 products, 2 u each, norms and final additions < 1024 u (|q|^2 + |x|max^2); 2048 u are used
+// (a query whose scaled length is beyond 2^15 has no usable approximations: the beam kernel scores its seeds itself).
+// float32 products: <= 512 terms in any order, norms, final additions: 300 u, 512 u used.  (Bfloat16 seeds and queries in two
+// bfloat16 parts, as before, take twice the products, and their bound on 1,000,000 x 128 is 3.6 instead of 0.8.)
 typedef float v16f_seed __attribute__((ext_vector_type(16)));
 typedef int v16i_seed __attribute__((ext_vector_type(16)));
 typedef int v4i_seed __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf_seed __attribute__((ext_vector_type(8)));
+typedef _Float16 v8h_seed __attribute__((ext_vector_type(8)));
 
-// CACHED: the B operand comes from the interleaved copy of the seeds (coalesced 1-KiB loads, lane (v, h)
-// taking chunk 2 c + h of seed v of the group); otherwise every lane pair gathers its seed's row from X
-// (32 rows of 32 bytes per load instruction).  NG = 32-seed groups per wave (fully unrolled: a loop with a
-// run-time trip count needs both operand buffers live at once and spills): few long waves for large
-// batches, many short ones for small batches.
-// DT = 2: float32 data whose interleaved seed copy holds bfloat16 (16-byte chunks of 8 components, NCH of
-// them per seed, CACHED only).  The queries are split into a bfloat16 high part and the bfloat16 rounding
-// of the rest (|q - hi - lo| <= 2^-16 |q| per component), both multiplied with the seeds by
-// v_mfma_f32_32x32x16_bf16 into one float32 accumulator: half the operand bytes and a quarter of the
-// matrix-core time of the float32 form (two products per component at sixteen times the rate).  The norms stay those of the unrounded vectors, so the only new
-// error is 2 q.(x - bf16(x)), which the beam kernel's bound carries as err_q * |q|.
-// The smallest of a group's 32 values for each of the accumulator's rows: lane n32 of a half holds element jj of the 16
-// (row 8 (jj / 4) + 4 h + jj % 4) for column n32; each step halves the elements a lane keeps and doubles the columns they
-// cover, so 16 rows cost about as many instructions as two reductions of one value.  Returns element n32 & 15 over all
-// columns.  valid: the lane's column exists.
-__device__ __forceinline__ uint32_t group_min(const uint32_t (&bits)[16], bool valid, int n32)
+// eight components (two 16-byte chunks) scaled and rounded to binary16
+__device__ __forceinline__ uint4 scaled_half8(const uint4 &a, const uint4 &b, float scale)
 {
-    uint32_t a[8], b[4], c[2];
-    const bool b0 = n32 & 1, b1 = n32 & 2, b2 = n32 & 4, b3 = n32 & 8;
+    const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    v8h_seed x;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint32_t x = valid ? bits[2 * i] : 0xFFFFFFFFu, y = valid ? bits[2 * i + 1] : 0xFFFFFFFFu;
-        const uint32_t keep = b0 ? y : x, give = b0 ? x : y;
-        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0xB1, 0xF, 0xF, true);    // lane ^ 1
-        a[i] = keep < got ? keep : got;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t keep = b1 ? a[2 * i + 1] : a[2 * i], give = b1 ? a[2 * i] : a[2 * i + 1];
-        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0x4E, 0xF, 0xF, true);    // lane ^ 2
-        b[i] = keep < got ? keep : got;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const uint32_t keep = b2 ? b[2 * i + 1] : b[2 * i], give = b2 ? b[2 * i] : b[2 * i + 1];
-        const int m = __builtin_amdgcn_update_dpp(0, (int)give, 0x141, 0xF, 0xF, true);                    // lane ^ 7
-        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, true);            // ... ^ 3: lane ^ 4
-        c[i] = keep < got ? keep : got;
-    }
-    const uint32_t keep = b3 ? c[1] : c[0], give = b3 ? c[0] : c[1];
-    const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0x128, 0xF, 0xF, true);       // lane ^ 8
-    const uint32_t d = keep < got ? keep : got;
-    const auto r = __builtin_amdgcn_permlane16_swap(d, d, false, false);                                  // columns below and from 16
-    return r[0] < r[1] ? r[0] : r[1];
+    for (int i = 0; i < 8; ++i) x[i] = (_Float16)(__uint_as_float(w[i]) * scale);
+    return __builtin_bit_cast(uint4, x);
 }
 
-// FIT = false: vectors of fewer than NCP contraction steps (dimensions without an instantiation of their own; from the copy
-// only).  The steps that do not exist have a zero query operand and read the copy's last chunk once more.
-template <int DT, int NCP, bool CACHED, int NG, bool FIT = true>
-__global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
+// Queries of a tile: 64 where the registers allow it: every seed is then read from L2 half as often (6,500 x 6,144 x 128: 52 us
+// instead of 59; 10,700 AND pairs x 96: 180 instead of 210; uint8 x 192: the same).
+static constexpr __host__ __device__ int seed_mfma_tile(int dt, int steps) { return dt != 1 && steps <= 8 ? 64 : 32; }
+
+template <class F, int... G> __device__ __forceinline__ void while_each(F &&f, std::integer_sequence<int, G...>)
 {
-    static_assert((DT != 2 && FIT) || CACHED, "bfloat16 seeds exist only as the interleaved copy");
-    constexpr int NCH = 2 * NCP;
-    const int blk_chunks = FIT ? NCH : p.blk_chunks;   // 16-byte chunks of a seed in the copy
-    const int row_bytes = FIT ? (DT == 2 ? 2 : 1) * NCH * kChunkBytes : p.dim * (DT == 0 ? 1 : 4);   // of a query
-    __shared__ uint4 qtile[(DT == 2 ? 2 : 1) * NCH * 32];   // DT 2: high parts, then low parts
-    __shared__ uint32_t qnorm_s[32];   // float bits / int
+    (void)(f(std::integral_constant<int, G>()) && ...);
+}
+
+// DT: 0 uint8, 1 float32, 2 float32 data from the copy in binary16.
+// CACHED: the seeds come from their interleaved copy (coalesced 1-KiB loads); otherwise every lane gathers its seed's row
+// from X.  NCP: contraction steps.  FIT = false: vectors of fewer steps than NCP (dimensions without an instantiation of
+// their own; from the copy only); the steps that do not exist have a zero query operand and read the copy's last chunk once
+// more.  NG: groups of a wave, unrolled.
+// The seeds are the rows of the product and the queries its columns, so a lane has 16 seeds of one query: the minimum of a
+// group's 32 is eight instructions and one swap.  The result goes through LDS to be stored as whole rows, 1 KB an
+// instruction.  Bound by the stores, and by what is in flight: loads and stores are counted by one counter in order, so a
+// wave that waits for its next group's chunks waits for every store issued before their request, too (requests two groups
+// ahead, where the registers allow it, leave the stores of the last two groups in flight).  39,000 queries x 16,384 seeds x 192 uint8 (2.4 GB)
+// 807 -> 655 us (nothing but the stores: 400), 10,700 AND pairs x up to 16,384 seeds x 96 220 -> 180 us, 6,500 queries x 6,144
+// seeds x 128 79 -> 52 us; before: queries as rows, their operand read from LDS, two products a step, 16 addresses by 64-bit
+// multiplication and 45 instructions of minima per group.
+// Queries a tile does not have repeat its last one, and seeds past the end of a list are stored within its row, so that every
+// store is unconditional.
+template <int DT, int NCP, bool CACHED, int NG, bool FIT = true>
+__global__ __launch_bounds__(64, NCP <= (FIT ? 8 : 6) ? 3 : 2) void seed_mfma_kernel(SeedParams p)
+{
+    static_assert((DT != 2 && FIT) || CACHED, "binary16 seeds and other dimensions only from the interleaved copy");
+    constexpr int QT = seed_mfma_tile(DT, NCP) / 32;               // sets of 32 queries
+    constexpr int PITCH = 36, MINS = NG + 1, AHEAD = NG > 1 && NCP <= 4 ? 2 : 1;   // words of a row in LDS; groups requested ahead
+    __shared__ uint32_t rows[32 * PITCH];
+    __shared__ uint32_t mins[CACHED ? QT * 32 * MINS : 1];         // the groups' minima of each query
+    __shared__ uint32_t norms[32];
+    const int blk_chunks = FIT ? 2 * NCP : p.blk_chunks;            // 16-byte chunks of a seed in the copy
+    const int row_bytes = p.dim * (DT == 0 ? 1 : 4);                // of a query
     const int lane = threadIdx.x, n32 = lane & 31, h = lane >> 5;
     const int tile = blockIdx.x / p.max_chunks, chunk = blockIdx.x % p.max_chunks;
     const SeedTile t = p.tiles[tile];
@@ -208,189 +203,179 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
     const int ns = p.n_seeds < n ? p.n_seeds : n;
     const int j0 = chunk * (NG * 32);
     if (j0 >= ns) return;
+    const bool second = QT > 1 && t.q_count > 32;
 
-    constexpr bool cached = CACHED;
-    const int64_t grp0 = cached ? p.seed_goff[p.meta.hs_slot[t.label]] + j0 / 32 : 0;
-    // global ids and norms of this lane's seed in each group (issued first: the longest dependent chain)
-    int gid[NG];
-    uint32_t xn[NG];
-    if (cached) {
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            gid[g] = 0;
-            xn[g] = j0 + g * 32 < ns ? p.seed_norm[(grp0 + g) * 32 + n32] : 0u;
-        }
-    } else {
+    const int64_t grp0 = CACHED ? p.seed_goff[p.meta.hs_slot[t.label]] + j0 / 32 : 0;
+    int gid[CACHED ? 1 : NG];   // without a copy: global id of this lane's seed in each group
+    if constexpr (!CACHED) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             const int j = j0 + g * 32 + n32;
-            const int c = j < ns ? (int)(((uint64_t)j * (uint64_t)n) / (uint64_t)ns) : 0;
-            gid[g] = p.meta.M_HS[base + c];
+            gid[g] = p.meta.M_HS[base + (j < ns ? (int)(((uint64_t)j * (uint64_t)n) / (uint64_t)ns) : 0)];
         }
-#pragma unroll
-        for (int g = 0; g < NG; ++g) xn[g] = p.xnorm_all[gid[g]];
     }
 
-    // query tile, chunk-major; rows without a query are zero
-    {
-        const int qr = n32 < t.q_count ? p.gq_query[t.gq_begin + n32] : -1;
-        const char *qp = (const char *)p.Q + (int64_t)(qr >= 0 ? qr : 0) * row_bytes;
-        float facc = 0.f;
-        int iacc = 0;
+    // the tile's operand: lane (n32, h) holds the chunks 2 s + h of query n32 of each set
+    uint4 q[QT][NCP];
+    uint32_t qn[QT];
 #pragma unroll
-        for (int c0 = 0; c0 < NCP; ++c0) {
-            const int c = 2 * c0 + h;
-            if constexpr (DT == 2) {   // components 8 c .. 8 c + 7
-                uint4 v0 = make_uint4(0, 0, 0, 0), v1 = v0;
-                if (qr >= 0) {   // (chunks that do not exist: the first one, and zeros in its place)
-                    const bool in0 = FIT || 2 * c * kChunkBytes < row_bytes, in1 = FIT || (2 * c + 1) * kChunkBytes < row_bytes;
-                    v0 = *(const uint4 *)(qp + (in0 ? 2 * c * kChunkBytes : 0));
-                    v1 = *(const uint4 *)(qp + (in1 ? (2 * c + 1) * kChunkBytes : 0));
-                    if (!in0) v0 = make_uint4(0, 0, 0, 0);
-                    if (!in1) v1 = make_uint4(0, 0, 0, 0);
-                }
-                const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-                uint32_t hi[8], lo[8];
+    for (int o = 0; o < QT; ++o) {
+        const int at = 32 * o + n32;
+        const int qr = p.gq_query[t.gq_begin + (at < t.q_count ? at : t.q_count - 1)];
+        const char *qp = (const char *)p.Q + (int64_t)qr * row_bytes;
+        auto chunk_of = [&](int c) -> uint4 {   // (those that do not exist: the first one is read, and zeros are in its place)
+            const bool in = FIT || c * kChunkBytes < row_bytes;
+            uint4 v = *(const uint4 *)(qp + (in ? c * kChunkBytes : 0));
+            if (!in) v = make_uint4(0, 0, 0, 0);
+            return v;
+        };
+        if constexpr (DT == 0) {
+            int acc = 0;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float f = __uint_as_float(w[i]);
-                    facc += f * f;
-                    hi[i] = bf16_rn_bits(f);
-                    lo[i] = bf16_rn_bits(f - __uint_as_float(hi[i] << 16));
-                }
-                qtile[c * 32 + n32] = make_uint4(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16));
-                qtile[NCH * 32 + c * 32 + n32] =
-                    make_uint4(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16));
-                continue;
+            for (int s = 0; s < NCP; ++s) {
+                const int c = 2 * s + h;
+                uint4 v = chunk_of(c);
+                if (FIT || c * kChunkBytes < row_bytes) { v.x ^= 0x80808080u; v.y ^= 0x80808080u; v.z ^= 0x80808080u; v.w ^= 0x80808080u; }
+                q[o][s] = v;
+                acc = __builtin_amdgcn_sdot4((int)v.x, (int)v.x, acc, false); acc = __builtin_amdgcn_sdot4((int)v.y, (int)v.y, acc, false);
+                acc = __builtin_amdgcn_sdot4((int)v.z, (int)v.z, acc, false); acc = __builtin_amdgcn_sdot4((int)v.w, (int)v.w, acc, false);
             }
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (qr >= 0 && (FIT || c * kChunkBytes < row_bytes)) {
-                v = *(const uint4 *)(qp + c * kChunkBytes);
-                if (DT == 0) { v.x ^= 0x80808080u; v.y ^= 0x80808080u; v.z ^= 0x80808080u; v.w ^= 0x80808080u; }
-            }
-            qtile[c * 32 + n32] = v;
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (DT == 0) {
-#pragma unroll
-                    for (int bb = 0; bb < 4; ++bb) {
-                        const int e = (int)(int8_t)(w[i] >> (8 * bb));
-                        iacc += e * e;
-                    }
-                } else {
-                    facc += __uint_as_float(w[i]) * __uint_as_float(w[i]);
-                }
-            }
-        }
-        if (DT == 0) {
-            iacc += __shfl_xor(iacc, 32);
-            if (h == 0) qnorm_s[n32] = (uint32_t)iacc;
+            acc += __shfl_xor(acc, 32);
+            qn[o] = (uint32_t)acc;
         } else {
-            facc += __shfl_xor(facc, 32);
-            if (h == 0) qnorm_s[n32] = __float_as_uint(facc);
+            float acc = 0.f;
+#pragma unroll
+            for (int s = 0; s < NCP; ++s) {
+                if constexpr (DT == 1) {
+                    const uint4 v = chunk_of(2 * s + h);
+                    q[o][s] = v;
+                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc += __uint_as_float(w[i]) * __uint_as_float(w[i]);
+                } else {   // components 8 (2 s + h) and the next seven
+                    const uint4 v0 = chunk_of(4 * s + 2 * h), v1 = chunk_of(4 * s + 2 * h + 1);
+                    const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) acc += __uint_as_float(w[i]) * __uint_as_float(w[i]);
+                    q[o][s] = scaled_half8(v0, v1, p.scale);
+                }
+            }
+            acc += __shfl_xor(acc, 32);
+            qn[o] = __float_as_uint(acc);
         }
     }
-    __syncthreads();
-    uint32_t qn[16];
+    // where rows 8 i + lane / 8 of a set's result go, as bytes from the tile's first row (64 rows: less than 4 GiB)
+    uint32_t at[QT][4];
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) qn[jj] = qnorm_s[8 * (jj >> 2) + 4 * h + (jj & 3)];
+    for (int o = 0; o < QT; ++o)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 32 * o + 8 * i + (lane >> 3);
+            at[o][i] = ((uint32_t)(row < t.q_count ? row : t.q_count - 1) * (uint32_t)p.ns_stride + 4u * (lane & 7)) * 4u;
+        }
+    char *const out = (char *)(p.dseed + (int64_t)t.gq_begin * p.ns_stride + j0);
 
-    uint32_t gmin[CACHED ? NG : 1];   // per group: smallest value of row row_of(n32 & 15, h), see group_min
-    uint4 bnext[NCP];
-    auto fetch_group = [&](int g) {   // group g of this wave's seeds (exists)
-        if (cached) {
+    constexpr uint32_t kNever = DT == 0 ? 0x3FFFFFFFu : 0x7F800000u;   // norm of a seed that does not exist: larger than any
+    uint4 b[AHEAD][NCP];
+    uint32_t xn[AHEAD];               // norm of seed n32
+    const int last = (ns - j0 + 31) / 32 - 1;
+    auto fetch_group = [&](int gg) {  // group gg of this wave's seeds (past the last one that exists: that one again, so that every
+        uint4 (&to)[NCP] = b[gg % AHEAD];   // request is unconditional and the waits can be counted)
+        uint32_t &xn_to = xn[gg % AHEAD];
+        if constexpr (CACHED) {
+            const int g = gg < last ? gg : last;
             const uint4 *blk = p.seed_blk + (grp0 + g) * (int64_t)(blk_chunks * 32);
 #pragma unroll
-            for (int cp = 0; cp < NCP; ++cp) bnext[cp] = blk[(FIT || 2 * cp + h < blk_chunks ? 2 * cp + h : blk_chunks - 1) * 32 + n32];
+            for (int s = 0; s < NCP; ++s) to[s] = blk[(FIT || 2 * s + h < blk_chunks ? 2 * s + h : blk_chunks - 1) * 32 + n32];
+            xn_to = p.seed_norm[(grp0 + g) * 32 + n32];
         } else {
-            const char *xrow = (const char *)p.X + (int64_t)gid[g] * row_bytes;
+            const int id = gid[gg];   // (every one of them is a seed)
+            const char *xrow = (const char *)p.X + (int64_t)id * row_bytes;
 #pragma unroll
-            for (int cp = 0; cp < NCP; ++cp) bnext[cp] = *(const uint4 *)(xrow + (2 * cp + h) * kChunkBytes);
+            for (int s = 0; s < NCP; ++s) to[s] = *(const uint4 *)(xrow + (2 * s + h) * kChunkBytes);
+            xn_to = p.xnorm_all[id];
         }
     };
-    fetch_group(0);
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (j0 + g * 32 >= ns) break;   // wave uniform
-        uint4 b[NCP];
+    for (int g = 0; g < AHEAD; ++g) fetch_group(g);
+    auto group = [&](auto number) -> bool {
+        constexpr int g = decltype(number)::value;
+        if (g > last) return false;    // (wave-uniform)
+        uint4 (&x)[NCP] = b[g % AHEAD];
+        wave_lds_sync();               // (the last group's rows have been read)
+        norms[n32] = j0 + g * 32 + n32 < ns ? xn[g % AHEAD] : kNever;
+        using acc_t = typename std::conditional<DT == 0, v16i_seed, v16f_seed>::type;
+        acc_t acc[QT];
 #pragma unroll
-        for (int cp = 0; cp < NCP; ++cp) b[cp] = bnext[cp];
-        if (g + 1 < NG && j0 + (g + 1) * 32 < ns) fetch_group(g + 1 < NG ? g + 1 : g);
-        uint32_t bits[16];
+        for (int o = 0; o < QT; ++o)
+#pragma unroll
+            for (int jj = 0; jj < 16; ++jj) acc[o][jj] = 0;
         if constexpr (DT == 0) {
-            v16i_seed acc;
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj) acc[jj] = 0;
+            for (int s = 0; s < NCP; ++s) { x[s].x ^= 0x80808080u; x[s].y ^= 0x80808080u; x[s].z ^= 0x80808080u; x[s].w ^= 0x80808080u; }
+        }
 #pragma unroll
-            for (int cp = 0; cp < NCP; ++cp) {
-                const uint4 a = qtile[(2 * cp + h) * 32 + n32];
-                uint4 bb = b[cp];
-                bb.x ^= 0x80808080u; bb.y ^= 0x80808080u; bb.z ^= 0x80808080u; bb.w ^= 0x80808080u;
-                const v4i_seed av = {(int)a.x, (int)a.y, (int)a.z, (int)a.w};
-                const v4i_seed bv = {(int)bb.x, (int)bb.y, (int)bb.z, (int)bb.w};
-                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(av, bv, acc, 0, 0, 0);
-            }
+        for (int o = 0; o < QT; ++o) {
+            if (o > 0 && !second) break;   // (wave-uniform)
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj) bits[jj] = (uint32_t)((int)qn[jj] + (int)xn[g] - 2 * acc[jj]);
-        } else if constexpr (DT == 2) {
-            v16f_seed acc;
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) acc[jj] = 0.f;
-#pragma unroll
-            for (int cp = 0; cp < NCP; ++cp) {
-                const v8bf_seed bv = __builtin_bit_cast(v8bf_seed, b[cp]);
-                const uint4 ah = qtile[(2 * cp + h) * 32 + n32], al = qtile[NCH * 32 + (2 * cp + h) * 32 + n32];
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_seed, ah), bv, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_seed, al), bv, acc, 0, 0, 0);
-            }
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) {
-                const float d = (__uint_as_float(qn[jj]) + __uint_as_float(xn[g])) - 2.0f * acc[jj];
-                bits[jj] = __float_as_uint(fmaxf(d, 0.0f));
-            }
-        } else {
-            v16f_seed acc;
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) acc[jj] = 0.f;
-#pragma unroll
-            for (int cp = 0; cp < NCP; ++cp) {
-                const uint4 a = qtile[(2 * cp + h) * 32 + n32];
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b[cp].x), acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b[cp].y), acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b[cp].z), acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b[cp].w), acc, 0, 0, 0);
-            }
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) {
-                const float d = (__uint_as_float(qn[jj]) + __uint_as_float(xn[g])) - 2.0f * acc[jj];
-                bits[jj] = __float_as_uint(fmaxf(d, 0.0f));
+            for (int s = 0; s < NCP; ++s) {
+                if constexpr (DT == 0) {
+                    acc[o] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(v4i_seed, x[s]), __builtin_bit_cast(v4i_seed, q[o][s]), acc[o], 0, 0, 0);
+                } else if constexpr (DT == 2) {
+                    acc[o] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h_seed, x[s]), __builtin_bit_cast(v8h_seed, q[o][s]), acc[o], 0, 0, 0);
+                } else {
+                    acc[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x[s].x), __uint_as_float(q[o][s].x), acc[o], 0, 0, 0);
+                    acc[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x[s].y), __uint_as_float(q[o][s].y), acc[o], 0, 0, 0);
+                    acc[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x[s].z), __uint_as_float(q[o][s].z), acc[o], 0, 0, 0);
+                    acc[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x[s].w), __uint_as_float(q[o][s].w), acc[o], 0, 0, 0);
+                }
             }
         }
-        if constexpr (CACHED) gmin[g] = p.dmin != nullptr ? group_min(bits, j0 + g * 32 + n32 < ns, n32) : 0u;
-        // Every lane stores every value, those without a (query, seed) pair into a dump area behind the
-        // matrix: with the stores under conditions the compiler cannot count them, and its wait for the next
-        // group's operand loads becomes a wait for these stores to be acknowledged as well.  The dump area has
-        // a slot per workgroup index (mod 1024): one shared slot is a single hot cache line when many tiles
-        // are partly filled.
-        const int j = j0 + g * 32 + n32;
-        uint32_t *dump = p.dseed + p.dump_off + (((int64_t)(blockIdx.x & (unsigned)p.dump_mask)) << 6) + lane;
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (g + AHEAD < NG) fetch_group(g + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const int row = 8 * (jj >> 2) + 4 * h + (jj & 3);
-            const bool ok = j < ns && row < t.q_count;
-            uint32_t *dst = ok ? p.dseed + (int64_t)(t.gq_begin + row) * p.ns_stride + j : dump;
-            *dst = bits[jj];
+        for (int o = 0; o < QT; ++o) {
+            if (o > 0 && !second) break;   // (wave-uniform)
+            wave_lds_sync();
+            uint32_t m = 0xFFFFFFFFu;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint4 n4 = *(const uint4 *)&norms[8 * i + 4 * h];
+                const uint32_t nx[4] = {n4.x, n4.y, n4.z, n4.w};
+                uint32_t bits[4];          // seeds 8 i + 4 h + u of query n32
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int jj = 4 * i + u;
+                    if constexpr (DT == 0) bits[u] = qn[o] + nx[u] - ((uint32_t)acc[o][jj] << 1);
+                    else bits[u] = __float_as_uint(fmaxf(__builtin_fmaf(DT == 1 ? -2.0f : p.minus_two_unscaled, acc[o][jj], __uint_as_float(qn[o]) + __uint_as_float(nx[u])), 0.0f));
+                    m = bits[u] < m ? bits[u] : m;
+                }
+                *(uint4 *)&rows[n32 * PITCH + 8 * i + 4 * h] = make_uint4(bits[0], bits[1], bits[2], bits[3]);
+            }
+            if constexpr (CACHED) {
+                const auto r = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+                mins[(32 * o + n32) * MINS + g] = r[0] < r[1] ? r[0] : r[1];
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *(uint4 *)(out + at[o][i] + g * 128) = *(const uint4 *)&rows[(8 * i + (lane >> 3)) * PITCH + 4 * (lane & 7)];
         }
-    }
+        return true;
+    };
+    while_each(group, std::make_integer_sequence<int, NG>());   // (a loop that is left early is not unrolled)
     if constexpr (CACHED) {
-        // lane (n32 < 16, h) has row 8 (n32 / 4) + 4 h + n32 % 4: its groups' minima are consecutive words
-        const int row = 8 * ((n32 & 15) >> 2) + 4 * h + (n32 & 3);
-        if (p.dmin != nullptr && n32 < 16 && row < t.q_count) {
-            uint32_t *dst = p.dmin + (int64_t)(t.gq_begin + row) * p.nb_stride + j0 / 32;
+        wave_lds_sync();
+        if (p.dmin != nullptr && lane < t.q_count && lane < QT * 32) {   // (the minima of groups that do not exist are not read)
+            uint32_t *dst = p.dmin + (int64_t)(t.gq_begin + lane) * p.nb_stride + j0 / 32;
+            const uint32_t *m = &mins[lane * MINS];
+            if constexpr (NG % 4 == 0) {   // (rows of minima are multiples of 16 words)
 #pragma unroll
-            for (int g = 0; g < NG; ++g)
-                if (j0 + g * 32 < ns) dst[g] = gmin[g];
+                for (int g = 0; g < NG; g += 4) *(uint4 *)(dst + g) = make_uint4(m[g], m[g + 1], m[g + 2], m[g + 3]);
+            } else {
+#pragma unroll
+                for (int g = 0; g < NG; ++g) dst[g] = m[g];
+            }
         }
     }
 }
@@ -411,12 +396,11 @@ __global__ __launch_bounds__(64) void seed_mfma_kernel(SeedParams p)
 // A seed missing from the union was rejected in its segment by K values that all are in the union, so its
 // approximation is at least the union's K-th smallest value, which is T as before.
 // A operand (queries) in registers for the whole segment; LDS holds only the queues and the lists.
-// DT = 0: uint8 data (v_mfma_i32_32x32x32_i8 on the -128 shifted bytes).  DT = 2: float32 data, seeds from the
-// bfloat16 copy, queries split into a bfloat16 high and low part (see seed_mfma_kernel).
+// DT = 0: uint8 data (v_mfma_i32_32x32x32_i8 on the -128 shifted bytes).  DT = 2: float32 data, seeds from the binary16 copy.
 template <int DT, int NCP>
 __global__ __launch_bounds__(64, 2) void seed_select_kernel(SeedSelParams p)
 {
-    static_assert(DT == 0 || DT == 2, "uint8, or float32 data with a bfloat16 seed copy");
+    static_assert(DT == 0 || DT == 2, "uint8, or float32 data with a binary16 seed copy");
     extern __shared__ uint4 smem[];
     constexpr int NCH = 2 * NCP, PC = 64;
     constexpr int row_bytes = (DT == 2 ? 2 : 1) * NCH * kChunkBytes;   // of a query
@@ -455,7 +439,7 @@ __global__ __launch_bounds__(64, 2) void seed_select_kernel(SeedSelParams p)
     __syncthreads();
 
     // ---- A operand: lane (n32, h) holds chunks 2 cp + h of query row n32 (zeros for a row without a query)
-    uint4 areg[NCP], alo[DT == 2 ? NCP : 1];
+    uint4 areg[NCP];
     {
         const int qr = qrow_s[n32];
         const char *qp = (const char *)p.Q + (int64_t)(qr >= 0 ? qr : 0) * row_bytes;
@@ -471,16 +455,9 @@ __global__ __launch_bounds__(64, 2) void seed_select_kernel(SeedSelParams p)
                     v1 = *(const uint4 *)(qp + (2 * c + 1) * kChunkBytes);
                 }
                 const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-                uint32_t hi[8], lo[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float f = __uint_as_float(w[i]);
-                    facc += f * f;
-                    hi[i] = bf16_rn_bits(f);
-                    lo[i] = bf16_rn_bits(f - __uint_as_float(hi[i] << 16));
-                }
-                areg[cp] = make_uint4(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16));
-                alo[cp] = make_uint4(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16));
+                for (int i = 0; i < 8; ++i) facc += __uint_as_float(w[i]) * __uint_as_float(w[i]);
+                areg[cp] = scaled_half8(v0, v1, p.scale);
             } else {
                 uint4 v = make_uint4(0, 0, 0, 0);
                 if (qr >= 0) {
@@ -598,9 +575,7 @@ __global__ __launch_bounds__(64, 2) void seed_select_kernel(SeedSelParams p)
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[j] = 0.f;
             auto contract = [&](int cp) {
-                const v8bf_seed bv = __builtin_bit_cast(v8bf_seed, breg[cp]);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_seed, areg[cp]), bv, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_seed, alo[cp]), bv, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h_seed, areg[cp]), __builtin_bit_cast(v8h_seed, breg[cp]), acc, 0, 0, 0);
             };
 #pragma unroll
             for (int cp = 0; cp < H0; ++cp) contract(cp);
@@ -616,7 +591,7 @@ __global__ __launch_bounds__(64, 2) void seed_select_kernel(SeedSelParams p)
             }
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                const float d = (__uint_as_float(qn[j]) + __uint_as_float(xn)) - 2.0f * acc[j];
+                const float d = __builtin_fmaf(p.minus_two_unscaled, acc[j], __uint_as_float(qn[j]) + __uint_as_float(xn));
                 bitsv[j] = __float_as_uint(fmaxf(d, 0.0f));
             }
         }
@@ -685,9 +660,9 @@ __global__ __launch_bounds__(64, 2) void seed_select_kernel(SeedSelParams p)
         if (lane < K) p.runs[((int64_t)(t.gq_begin + r) * p.max_segs + seg) * K + lane] = best[r * KS + lane];
 }
 
-bool seed_select_supported(int dtype, int dim, bool bf16_copy)
+bool seed_select_supported(int dtype, int dim, bool f16_copy)
 {
-    return dtype == 0 ? (dim == 128 || dim == 192) : (bf16_copy && (dim == 96 || dim == 128));
+    return dtype == 0 ? (dim == 128 || dim == 192) : (f16_copy && (dim == 96 || dim == 128));
 }
 
 size_t seed_select_lds_bytes(int32_t K) { return (size_t)32 * 64 * 8 + (size_t)32 * (K | 1) * 8 + 4 * 32 * 4; }
@@ -733,6 +708,13 @@ void launch_seed_pass_count(const int32_t *gq_query, const int32_t *gq_label, co
     if (n_gq <= 0) return;
     hipLaunchKernelGGL(seed_pass_count_kernel, dim3(n_gq), dim3(64), 0, s, gq_query, gq_label, meta, n_seeds, others_off,
                        others, pass_count);
+}
+
+int seed_mfma_tile_of(int dtype, int dim, bool f16)
+{
+    if (dtype == 1 && !f16) return 32;
+    const int steps = dtype == 1 ? (dim + 15) / 16 : (dim + 31) / 32;
+    return seed_mfma_tile(dtype == 0 ? 0 : 2, steps);
 }
 
 bool seed_mfma_own(int dtype, int dim)
@@ -781,12 +763,8 @@ void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s
 {
     if (n_tiles <= 0) return;
     const dim3 grid((unsigned)n_tiles * (unsigned)p.max_chunks), block(64);
-    // separate instantiations for the two operand sources (one kernel holding both paths needs so many
-    // registers that a SIMD takes a single wave of it) and for the seeds per wave (p.chunk_seeds: 128,
-    // or 32 or 512 with the interleaved copy)
+    // instantiations for the operand sources and for the seeds per wave (p.chunk_seeds: 128, or 32 or 512 with the copy)
     const bool cached = p.seed_blk != nullptr;
-    const bool wide = cached && p.chunk_seeds == 4 * kSeedMfmaChunk;
-    const bool narrow = cached && p.chunk_seeds == 32;
     if (!seed_mfma_own(dtype, p.dim)) {
         if (dtype == 0) launch_seed_mfma_any<0>(p, grid, s);
         else launch_seed_mfma_any<2>(p, grid, s);
@@ -794,26 +772,50 @@ void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s
     }
 #define VF_LAUNCH_SEED(DT_, NCP_) \
     do { \
-        if (wide) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 16>), grid, block, 0, s, p); \
-        else if (narrow) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 1>), grid, block, 0, s, p); \
+        if (cached && p.chunk_seeds == 4 * kSeedMfmaChunk) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 16>), grid, block, 0, s, p); \
+        else if (cached && p.chunk_seeds == 32) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 1>), grid, block, 0, s, p); \
         else if (cached) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, true, 4>), grid, block, 0, s, p); \
-        else hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, false, 4>), grid, block, 0, s, p); \
+        else if constexpr (DT_ != 2) hipLaunchKernelGGL((seed_mfma_kernel<DT_, NCP_, false, 4>), grid, block, 0, s, p); \
     } while (0)
-    if (dtype == 1 && p.seed_bf16 && cached) {
-        if (p.dim == 128) {
-            if (wide) hipLaunchKernelGGL((seed_mfma_kernel<2, 8, true, 16>), grid, block, 0, s, p);
-            else if (narrow) hipLaunchKernelGGL((seed_mfma_kernel<2, 8, true, 1>), grid, block, 0, s, p);
-            else hipLaunchKernelGGL((seed_mfma_kernel<2, 8, true, 4>), grid, block, 0, s, p);
-        } else if (p.dim == 96) {
-            if (wide) hipLaunchKernelGGL((seed_mfma_kernel<2, 6, true, 16>), grid, block, 0, s, p);
-            else if (narrow) hipLaunchKernelGGL((seed_mfma_kernel<2, 6, true, 1>), grid, block, 0, s, p);
-            else hipLaunchKernelGGL((seed_mfma_kernel<2, 6, true, 4>), grid, block, 0, s, p);
-        }
-    } else if (dtype == 1 && p.dim == 128) VF_LAUNCH_SEED(1, 16);
-    else if (dtype == 1 && p.dim == 96) VF_LAUNCH_SEED(1, 12);
-    else if (dtype == 0 && p.dim == 128) VF_LAUNCH_SEED(0, 4);
-    else if (dtype == 0 && p.dim == 192) VF_LAUNCH_SEED(0, 6);
+    if (dtype == 0 && p.dim == 128) VF_LAUNCH_SEED(0, 4);
+    else if (dtype == 0) VF_LAUNCH_SEED(0, 6);
+    else if (p.seed_f16 && p.dim == 128) VF_LAUNCH_SEED(2, 8);
+    else if (p.seed_f16) VF_LAUNCH_SEED(2, 6);
+    else if (p.dim == 128) VF_LAUNCH_SEED(1, 16);
+    else VF_LAUNCH_SEED(1, 12);
 #undef VF_LAUNCH_SEED
+}
+
+// The float32 copy of the seeds as binary16 (nch16 chunks of 8 components), times scale; err2[group * 32 + v] = |x - x^|^2 of
+// the unscaled vectors, whose largest is what the proofs allow for.  One thread per seed.
+__global__ void seed_pack_f16_kernel(const uint4 *blk32, int64_t n_vec, int32_t nch16, float scale, uint4 *blk16, float *err2)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n_vec) return;
+    const int64_t g = t >> 5;
+    const int v = (int)(t & 31);
+    const float unscale = 1.0f / scale;   // (a power of two)
+    float e2 = 0.f;
+    for (int c = 0; c < nch16; ++c) {
+        const uint4 a = blk32[(g * (2 * nch16) + 2 * c) * 32 + v], b = blk32[(g * (2 * nch16) + 2 * c + 1) * 32 + v];
+        const uint4 r = scaled_half8(a, b, scale);
+        const v8h_seed x = __builtin_bit_cast(v8h_seed, r);
+        const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float d = __uint_as_float(w[i]) - (float)x[i] * unscale;
+            e2 += d * d;
+        }
+        blk16[(g * nch16 + c) * 32 + v] = r;
+    }
+    err2[t] = e2;
+}
+
+void launch_seed_pack_f16(const uint4 *blk32, int64_t n_groups, int32_t nch16, float scale, uint4 *blk16, float *err2, hipStream_t s)
+{
+    if (n_groups <= 0) return;
+    hipLaunchKernelGGL(seed_pack_f16_kernel, dim3((unsigned)((n_groups * 32 + 255) / 256)), dim3(256), 0, s, blk32,
+                       n_groups * 32, nch16, scale, blk16, err2);
 }
 
 // The interleaved float32 copy of the seeds (groups of 32, 2 * nch16 chunks of 4 components) rounded to

@@ -25,6 +25,8 @@
 // e = 32 s + 4 t + c (s ascending, c = 0..3) as acc = fma(d, d, acc), d = q - x, and the
 // team combines ((a0+a1)+(a2+a3)) + ((a4+a5)+(a6+a7)).
 #pragma once
+#include <type_traits>
+
 #include "vf_device.h"
 
 #ifndef VF_SEED_BLOCKS
@@ -33,12 +35,18 @@
 
 namespace vf {
 
+// (a scalar register's worth)
+__device__ __forceinline__ double uniform_double(double v)
+{
+    return __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(v), 0));
+}
+
 // true: id was not in the table (it is now, unless the probe budget ran out)
 __device__ __forceinline__ bool visit(uint32_t *tab, int bits, uint32_t id)
 {
     const uint32_t mask = (1u << bits) - 1u;
     uint32_t slot = (id * 0x9E3779B1u) >> (32 - bits);
-    for (int pr = 0; pr < 16; ++pr) {
+    for (int pr = 0; pr < 16; ++pr) {   // (unrolled, its exec masks crowd the kernel's scalar registers out)
         const uint32_t old = atomicCAS(&tab[slot], 0xFFFFFFFFu, id);
         if (old == 0xFFFFFFFFu) return true;
         if (old == id) return false;
@@ -52,15 +60,11 @@ __device__ __forceinline__ bool visit(uint32_t *tab, int bits, uint32_t id)
 // answering this arithmetically keeps the seeds out of the visited table.
 // c is a seed iff some multiple of n lies in [c * ns, c * ns + ns), i.e. iff
 // r = (c * ns) mod n is 0 or larger than n - ns.  The quotient comes from a double-precision
-// multiplication by 1 / n (for n * ns < 2^52 the product is exact in a double and the estimate is off by at most
-// one, which the two corrections absorb); the remainder is exact integer arithmetic.
+// multiplication by 1 / n (three roundings of 2^-53 and a quotient below 2^31: off by at most one, which the two
+// corrections absorb); the remainder is exact integer arithmetic.
 __device__ __forceinline__ bool is_seed(uint32_t c, uint32_t n, uint32_t ns, double inv_n)
 {
     if (ns >= n) return true;
-    if (((uint64_t)n * ns) >> 52) {   // (not reached with realistic seed counts) plain integer division
-        const uint64_t j = ((uint64_t)c * ns + n - 1) / n;
-        return j < ns && (uint32_t)((j * n) / ns) == c;
-    }
     const uint64_t prod = (uint64_t)c * ns;
     const uint32_t q = (uint32_t)((double)c * (double)ns * inv_n);
     int64_t r = (int64_t)prod - (int64_t)((uint64_t)q * n);
@@ -69,13 +73,24 @@ __device__ __forceinline__ bool is_seed(uint32_t c, uint32_t n, uint32_t ns, dou
     return r == 0 || r > (int64_t)(n - ns);
 }
 
-// floor(j * n / ns) for j < ns <= n: quotient estimated in double precision (exact product below 2^52, the
-// estimate off by at most one), corrected with the exact remainder.
-__device__ __forceinline__ int seed_local_id(uint32_t j, uint32_t n, uint32_t ns)
+// The same for n < 2^24 and ns <= 2^20 (small_list), in a third of the issue slots: no 64-bit products, no double precision
+// (a lone query's search 37.5 -> 35.5 us, 39,000 uint8 queries of 32 iterations 864 -> 833).
+// x = c ns / n comes within 1/8 in float32 (three roundings of 2^-24 each, of at most 2^20: two are of factors), so the nearest
+// whole number j is within 5/8 of x, and the first whole number that is not below x is j or j + 1.  Only the differences j n - c ns
+// count, and those are exact modulo 2^32 from 24-bit products.
+__device__ __forceinline__ bool is_seed_small(uint32_t c, uint32_t n, uint32_t ns, float ns_over_n)
+{
+    const uint32_t j = (uint32_t)__builtin_rintf((float)c * ns_over_n);
+    const uint32_t r = __umul24(j, n) - __umul24(c, ns);
+    return r < ns || r + n < ns;
+}
+
+// floor(j * n / ns) for j < ns <= n: quotient estimated in double precision (inv_ns = 1 / ns; below 2^31, so off by at most one),
+// corrected with the exact remainder.
+__device__ __forceinline__ int seed_local_id(uint32_t j, uint32_t n, uint32_t ns, double inv_ns)
 {
     const uint64_t prod = (uint64_t)j * n;
-    if (((uint64_t)n * ns) >> 52) return (int)(prod / ns);
-    uint32_t q = (uint32_t)((double)j * (double)n / (double)ns);
+    uint32_t q = (uint32_t)((double)j * (double)n * inv_ns);
     int64_t r = (int64_t)prod - (int64_t)((uint64_t)q * ns);
     if (r < 0) { r += ns; --q; }
     if (r >= (int64_t)ns) { r -= ns; ++q; }
@@ -227,6 +242,7 @@ __device__ __forceinline__ void stream_seed_segment(const BeamParams &p, int lab
     const int n = p.meta.S[label];
     const int ns = p.n_seeds < n ? p.n_seeds : n;
     const int64_t base = p.meta.O_HS[label];
+    const double inv_ns = uniform_double(1.0 / (double)ns);
     const int64_t g0 = p.sgoff[p.meta.hs_slot[label]];
     int qq_all = 0;
     if (DT == 0) {
@@ -306,7 +322,7 @@ __device__ __forceinline__ void stream_seed_segment(const BeamParams &p, int lab
             const float c0s = b0 + b1, c1s = b2 + b3;
             bits = __float_as_uint(c0s + c1s);
         }
-        const int c = valid ? seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns) : 0;
+        const int c = valid ? seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns) : 0;
         bool pass = valid;
         if (o_cnt > 0 && valid) {
             const int g = p.meta.M_HS[base + c];
@@ -346,6 +362,8 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     const int label = bq.label;
     const int n = p.meta.S[label];
     const int64_t base = p.meta.O_HS[label];
+    const int ns = p.n_seeds < n ? p.n_seeds : n;   // seeds of this list
+    const double inv_ns = uniform_double(1.0 / (double)ns);
     const int itopk = p.itopk, R = p.R;
     const int row_bytes = p.dim * (DT == 0 ? 1 : 4);
     const int nchunks = row_bytes / kChunkBytes;
@@ -364,6 +382,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
 
     const int o_cnt = AND ? bq.o_cnt : 0;
     const int qq_lane = DT == 0 ? lane_qq_u8(qv, nchunks, tl) : 0;
+    const int qq = DT == 0 ? __builtin_amdgcn_readfirstlane(team_sum_i(qq_lane)) : 0;   // |q|^2
 
     // The AND predicate of global id g.  One partner label with a bitset -- every two-label query whose searched
     // list is its smallest: the partner's list is at least as long, so it is a graph list too -- is one word of
@@ -382,9 +401,8 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     // global ids of this list's seeds in seed order, when the call has them (else M_HS[base + floor(j n / ns)])
     const int32_t *smap = nullptr;
     if (AND && o_cnt > 0 && p.seed_map != nullptr) smap = p.seed_map + p.seed_goff[p.meta.hs_slot[label]] * 32;
-    auto seed_gid = [&](int j) -> int {   // (ns as below: the number of seeds of this list)
-        const int ns_ = p.n_seeds < n ? p.n_seeds : n;
-        return smap != nullptr ? smap[j] : p.meta.M_HS[base + (int)(((uint64_t)j * (uint64_t)n) / (uint64_t)ns_)];
+    auto seed_gid = [&](int j) -> int {
+        return smap != nullptr ? smap[j] : p.meta.M_HS[base + seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns)];
     };
 
     TopM<E> top;
@@ -423,6 +441,53 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
         merge_batch(list, in ? ((uint64_t)bits << 32) | ((uint64_t)(uint32_t)c << 1) | 1ull : KEY_MAX, lane);
     };
 
+    // LAT: the distances of cand[lo..cnt) into cand_d, for vectors of at most W 16-byte chunks per lane of a team.  A wave that has
+    // its SIMD to itself waits for every load, LDS read and branch it makes: the vectors of 64 candidates are requested before
+    // the first is used, the query stays in registers, and no lane takes a branch (see team_acc_f32).
+    // (A lone query's search, 12 x 2 rows of 32 edges over 128 float32 components, 35.5 -> 31.4 us; 64 queries 55.5 -> 48.)
+    auto score_lat = [&](auto w_steps, int cnt, int lo) {
+        constexpr int W = decltype(w_steps)::value, NR = 8;
+        uint4 q[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) q[w] = qv[w * 8 + tl < nchunks ? w * 8 + tl : 0];
+        for (int r0 = lo; r0 < cnt; r0 += 8 * NR) {
+            uint4 x[NR][W];
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+                const int my = r0 + 8 * u + team;
+                if (u > 0 && r0 + 8 * u >= cnt) break;   // (wave-uniform)
+                const char *xrow = (const char *)p.X + (int64_t)cand_g[my < cnt ? my : 0] * row_bytes;
+#pragma unroll
+                for (int w = 0; w < W; ++w) x[u][w] = *(const uint4 *)(xrow + (w * 8 + tl < nchunks ? w * 8 + tl : 0) * kChunkBytes);
+            }
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+                const int my = r0 + 8 * u + team;
+                if (u > 0 && r0 + 8 * u >= cnt) break;
+                uint32_t bits;
+                if constexpr (DT == 0) {
+                    uint32_t xx = 0, qx = 0;
+#pragma unroll
+                    for (int w = 0; w < W; ++w) {
+                        const uint4 xv = x[u][w];
+                        uint32_t a = xx, b = qx;
+                        a = __builtin_amdgcn_udot4(xv.x, xv.x, a, false); b = __builtin_amdgcn_udot4(q[w].x, xv.x, b, false);
+                        a = __builtin_amdgcn_udot4(xv.y, xv.y, a, false); b = __builtin_amdgcn_udot4(q[w].y, xv.y, b, false);
+                        a = __builtin_amdgcn_udot4(xv.z, xv.z, a, false); b = __builtin_amdgcn_udot4(q[w].z, xv.z, b, false);
+                        a = __builtin_amdgcn_udot4(xv.w, xv.w, a, false); b = __builtin_amdgcn_udot4(q[w].w, xv.w, b, false);
+                        xx = w * 8 + tl < nchunks ? a : xx; qx = w * 8 + tl < nchunks ? b : qx;
+                    }
+                    bits = (uint32_t)team_sum_i(qq_lane + (int)xx - 2 * (int)qx);
+                } else {   // the order of team_dist_bits_f32
+                    float acc = 0.0f;
+#pragma unroll
+                    for (int w = 0; w < W; ++w) acc = team_acc_f32(acc, q[w], x[u][w], w * 8 + tl < nchunks);
+                    bits = __float_as_uint(team_sum_f(acc));
+                }
+                if (tl == 0 && my < cnt) cand_d[my] = bits;
+            }
+        }
+    };
     // Distances of cand[0..cnt) (eight at a time, one per team) into cand_d.
     // (lo: a multiple of 8, the entries before it have been dealt with)
     auto score = [&](int cnt, bool distinct_new = false, int lo = 0) {   // distinct_new: seeds (see offer_seeds_to)
@@ -430,69 +495,26 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
         n_gathered += cnt - lo;
         int lo_rest = lo;
         if constexpr (LAT) {
-            if (nchunks <= 32) {   // at most four 16-byte chunks per lane of a team
-                constexpr int NR = 8;
-                for (int r0 = lo; r0 < cnt; r0 += 8 * NR) {
-                    uint4 x[NR][4];
-#pragma unroll
-                    for (int u = 0; u < NR; ++u) {
-                        const int my = r0 + 8 * u + team;
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) x[u][w] = make_uint4(0, 0, 0, 0);
-                        if (r0 + 8 * u < cnt) {   // (wave-uniform)
-                            const char *xrow = (const char *)p.X + (int64_t)cand_g[my < cnt ? my : 0] * row_bytes;
-#pragma unroll
-                            for (int w = 0; w < 4; ++w)
-                                if (w * 8 + tl < nchunks) x[u][w] = *(const uint4 *)(xrow + (w * 8 + tl) * kChunkBytes);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < NR; ++u) {
-                        const int my = r0 + 8 * u + team;
-                        if (r0 + 8 * u >= cnt) break;   // (wave-uniform)
-                        uint32_t bits;
-                        if constexpr (DT == 0) {
-                            uint32_t xx = 0, qx = 0;
-#pragma unroll
-                            for (int w = 0; w < 4; ++w) {
-                                if (w * 8 + tl < nchunks) {
-                                    const uint4 q = qv[w * 8 + tl], xv = x[u][w];
-                                    xx = __builtin_amdgcn_udot4(xv.x, xv.x, xx, false); qx = __builtin_amdgcn_udot4(q.x, xv.x, qx, false);
-                                    xx = __builtin_amdgcn_udot4(xv.y, xv.y, xx, false); qx = __builtin_amdgcn_udot4(q.y, xv.y, qx, false);
-                                    xx = __builtin_amdgcn_udot4(xv.z, xv.z, xx, false); qx = __builtin_amdgcn_udot4(q.z, xv.z, qx, false);
-                                    xx = __builtin_amdgcn_udot4(xv.w, xv.w, xx, false); qx = __builtin_amdgcn_udot4(q.w, xv.w, qx, false);
-                                }
-                            }
-                            bits = (uint32_t)team_sum_i(qq_lane + (int)xx - 2 * (int)qx);
-                        } else {   // the order of team_dist_bits_f32
-                            float acc = 0.0f;
-#pragma unroll
-                            for (int w = 0; w < 4; ++w) {
-                                if (w * 8 + tl < nchunks) {
-                                    const uint4 q = qv[w * 8 + tl], xv = x[u][w];
-                                    float d;
-                                    d = __uint_as_float(q.x) - __uint_as_float(xv.x); acc = __builtin_fmaf(d, d, acc);
-                                    d = __uint_as_float(q.y) - __uint_as_float(xv.y); acc = __builtin_fmaf(d, d, acc);
-                                    d = __uint_as_float(q.z) - __uint_as_float(xv.z); acc = __builtin_fmaf(d, d, acc);
-                                    d = __uint_as_float(q.w) - __uint_as_float(xv.w); acc = __builtin_fmaf(d, d, acc);
-                                }
-                            }
-                            bits = __float_as_uint(team_sum_f(acc));
-                        }
-                        if (tl == 0 && my < cnt) cand_d[my] = bits;
-                    }
-                }
-                lo_rest = cnt;
+            if (nchunks <= 8) { score_lat(std::integral_constant<int, 1>(), cnt, lo); lo_rest = cnt; }
+            else if (nchunks <= 16) { score_lat(std::integral_constant<int, 2>(), cnt, lo); lo_rest = cnt; }
+            else if (nchunks <= 32) { score_lat(std::integral_constant<int, 4>(), cnt, lo); lo_rest = cnt; }
+        }
+        if constexpr (DT == 0) {
+            const int t4 = lane & 3;
+            for (int r0 = lo_rest; r0 < cnt; r0 += 16) {
+                const int my = r0 + (lane >> 2);
+                const int g = cand_g[my < cnt ? my : 0];
+                const uint32_t bits = (uint32_t)qq + quad_dist_u8(qv, (const char *)p.X + (int64_t)g * row_bytes, nchunks, t4);
+                if (t4 == 0 && my < cnt) cand_d[my] = bits;
             }
+            lo_rest = cnt;
         }
 #pragma unroll 2
         for (int r0 = lo_rest; r0 < cnt; r0 += 8) {
             const int my = r0 + team;
             const int g = cand_g[my < cnt ? my : 0];
             const char *xrow = (const char *)p.X + (int64_t)g * row_bytes;
-            uint32_t bits;
-            if (DT == 0) bits = team_dist_bits_u8(qv, qq_lane, xrow, nchunks, tl);
-            else bits = team_dist_bits_f32(qv, xrow, nchunks, tl);
+            const uint32_t bits = team_dist_bits_f32(qv, xrow, nchunks, tl);
             if (tl == 0 && my < cnt) cand_d[my] = bits;
         }
         wave_sync<STREAM_SEEDS>();
@@ -525,8 +547,6 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     };
 
     // ---- InitializeSearch: stratified seeds floor(j * n / ns)
-    const int ns = p.n_seeds < n ? p.n_seeds : n;
-    const double inv_n = 1.0 / (double)n;
     int j_begin = 0;   // seeds below j_begin have been dealt with
 
     // Selection from a dense row of seed distances in two passes over chunks of 64 * NBLK seeds
@@ -603,7 +623,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 const int i = i0 + lane;
                 const bool valid = i < cnt;
                 int c = valid ? cand_c[i] : 0;
-                if (!as_index) c = (int)(((uint64_t)c * (uint64_t)n) / (uint64_t)ns);
+                if (!as_index) c = seed_local_id((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_ns);
                 offer_seeds_to(list, valid, valid ? cand_d[i] : 0u, c);
             }
             wave_sync<STREAM_SEEDS>();
@@ -736,7 +756,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 bool valid = i < cnt;
                 int c = valid ? cand_c[i] : 0;
                 if (lazy || !as_index) {
-                    const int cl = (int)(((uint64_t)c * (uint64_t)n) / (uint64_t)ns);
+                    const int cl = seed_local_id((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_ns);
                     if (lazy && valid) valid = passes(seed_gid(c));
                     if (!as_index) c = cl;
                 }
@@ -766,7 +786,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
             uint64_t key = KEY_MAX;
             if (raw != KEY_MAX) {
                 const uint32_t j = (uint32_t)raw;
-                const uint32_t c = as_index ? j : (uint32_t)seed_local_id(j, (uint32_t)n, (uint32_t)ns);
+                const uint32_t c = as_index ? j : (uint32_t)seed_local_id(j, (uint32_t)n, (uint32_t)ns, inv_ns);
                 key = (raw & 0xFFFFFFFF00000000ull) | ((uint64_t)c << 1) | 1ull;
             }
             merge_sorted_run(list, key, lane);
@@ -900,7 +920,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
             // (every one of them: the approximations were of no use)
             if (cnt <= 128 && (cnt < ns || ns <= 64)) {
                 for (int i = lane; i < cnt; i += 64) {
-                    const int c = seed_local_id((uint32_t)cand_c[i], (uint32_t)n, (uint32_t)ns);
+                    const int c = seed_local_id((uint32_t)cand_c[i], (uint32_t)n, (uint32_t)ns, inv_ns);
                     cand_c[i] = c;
                     cand_g[i] = p.meta.M_HS[base + c];
                 }
@@ -930,7 +950,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 fix_seed_count();
                 const uint64_t key = tmp.cur[0];
                 const bool valid = key != KEY_MAX;
-                const int c = valid ? seed_local_id((uint32_t)(key >> 1) & 0x7FFFFFFFu, (uint32_t)n, (uint32_t)ns) : 0;
+                const int c = valid ? seed_local_id((uint32_t)(key >> 1) & 0x7FFFFFFFu, (uint32_t)n, (uint32_t)ns, inv_ns) : 0;
                 // the kept seeds sit in lanes 0 .. cnt - 1 (sorted list) and have passed the predicate already
                 wave_sync<STREAM_SEEDS>();
                 const int cnt = __popcll(__ballot(valid));
@@ -995,13 +1015,13 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 const bool full = top.worst != KEY_MAX;
                 if (full) { lazy_used = true; pass = valid && bits <= (uint32_t)(top.worst >> 32); }
                 if (pass) {
-                    c = (int)(((uint64_t)j * (uint64_t)n) / (uint64_t)ns);
+                    c = seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns);
                     pass = passes(seed_gid(j));
                 }
                 n_scored += __popcll(__ballot(pass));
             } else {
                 n_scored += __popcll(__ballot(valid));
-                if (pass && bits <= (uint32_t)(top.worst >> 32)) c = (int)(((uint64_t)j * (uint64_t)n) / (uint64_t)ns);
+                if (pass && bits <= (uint32_t)(top.worst >> 32)) c = seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns);
             }
             offer(pass, bits, c);
         }
@@ -1012,7 +1032,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
         for (int j0 = 0; j0 < ns; j0 += 64) {
             const int j = j0 + lane;
             const bool valid = j < ns;
-            const int c = valid ? (int)(((uint64_t)j * (uint64_t)n) / (uint64_t)ns) : 0;
+            const int c = valid ? seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns) : 0;
             wave_sync<STREAM_SEEDS>();
             const int cnt = filter_and_compact(valid, c, 0);
             wave_sync<STREAM_SEEDS>();
@@ -1023,6 +1043,11 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     // ---- iterations: expand the best unexpanded entries, score their unvisited children, merge
     // child slot j = j0 + lane (j0 = 0 or 64, width * R <= 128) is edge j % R of parent j / R
     const int jq0 = lane / R, jr0 = lane - jq0 * R, jq1 = (lane + 64) / R, jr1 = lane + 64 - jq1 * R;
+    // whether a child is a seed (see is_seed_small), and its place in the list's rows as a 32-bit number
+    const bool small_list = n < (1 << 24) && ns <= (1 << 20) && (int64_t)n * R < (1 << 30);
+    const float ns_over_n = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint((float)ns / (float)n)));
+    const double inv_n = small_list ? 0.0 : uniform_double(1.0 / (double)n);
+    const int32_t *const rows_local = p.G + base * R, *const rows_global = p.Gg + base * R;
     for (int it = 0; it < p.iters; ++it) {
         int np = 0;
 #pragma unroll
@@ -1057,11 +1082,18 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 // the row as local ids (list bookkeeping) and as global ids (where the vector is): two
                 // independent coalesced loads instead of a lookup in M that depends on the first
                 const int pa = parents[j0 == 0 ? jq0 : jq1];
-                const int64_t at = (base + pa) * R + (j0 == 0 ? jr0 : jr1);
-                c = p.G[at];
-                g = p.Gg[at];
-                valid = c >= 0 && !is_seed((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_n) &&
-                        visit(hash, p.hash_bits, (uint32_t)c);
+                if (small_list) {
+                    const uint32_t at = __umul24((uint32_t)pa, (uint32_t)R) + (uint32_t)(j0 == 0 ? jr0 : jr1);
+                    c = rows_local[at];
+                    g = rows_global[at];
+                    valid = c >= 0 && !is_seed_small((uint32_t)c, (uint32_t)n, (uint32_t)ns, ns_over_n);
+                } else {
+                    const int64_t at = (int64_t)pa * R + (j0 == 0 ? jr0 : jr1);
+                    c = rows_local[at];
+                    g = rows_global[at];
+                    valid = c >= 0 && !is_seed((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_n);
+                }
+                valid = valid && visit(hash, p.hash_bits, (uint32_t)c);
             }
             cnt = filter_and_compact(valid, c, cnt, g);
         }

@@ -70,6 +70,18 @@ __device__ __forceinline__ int team_sum_i(int v)
 // computed by one 8-lane team; tl = lane within the team.  Lane tl handles chunks
 // tl, tl+8, ... .  fp32: lane-sequential acc = fma(d, d, acc) with d = q-x rounded, then
 // team_sum_f -- an order that a CPU evaluation (C fmaf) reproduces bit for bit.
+// No lane takes a branch: those without a chunk in the last step read an existing one and leave its terms out (a load or
+// an LDS read under a lane's condition is a branch of its own, and its wait stands in front of the next: 6,400 queries of
+// 24 rows of 32 edges 141 -> 137 us).
+__device__ __forceinline__ float team_acc_f32(float acc, const uint4 &q, const uint4 &x, bool in)
+{
+    float d, a = acc;
+    d = __uint_as_float(q.x) - __uint_as_float(x.x); a = __builtin_fmaf(d, d, a);
+    d = __uint_as_float(q.y) - __uint_as_float(x.y); a = __builtin_fmaf(d, d, a);
+    d = __uint_as_float(q.z) - __uint_as_float(x.z); a = __builtin_fmaf(d, d, a);
+    d = __uint_as_float(q.w) - __uint_as_float(x.w); a = __builtin_fmaf(d, d, a);
+    return in ? a : acc;
+}
 __device__ __forceinline__ uint32_t team_dist_bits_f32(const uint4 *qv, const char *xrow, int nchunks, int tl)
 {
     const int steps = (nchunks + 7) >> 3;
@@ -78,21 +90,15 @@ __device__ __forceinline__ uint32_t team_dist_bits_f32(const uint4 *qv, const ch
         uint4 x[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {   // all loads of the batch are issued before the first use
+            if (u > 0 && st0 + u >= steps) break;   // (wave-uniform)
             const int ci = (st0 + u) * 8 + tl;
-            x[u] = make_uint4(0, 0, 0, 0);
-            if (ci < nchunks) x[u] = *(const uint4 *)(xrow + ci * kChunkBytes);
+            x[u] = *(const uint4 *)(xrow + (ci < nchunks ? ci : 0) * kChunkBytes);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
+            if (u > 0 && st0 + u >= steps) break;
             const int ci = (st0 + u) * 8 + tl;
-            if (ci < nchunks) {
-                const uint4 q = qv[ci];
-                float d;
-                d = __uint_as_float(q.x) - __uint_as_float(x[u].x); acc = __builtin_fmaf(d, d, acc);
-                d = __uint_as_float(q.y) - __uint_as_float(x[u].y); acc = __builtin_fmaf(d, d, acc);
-                d = __uint_as_float(q.z) - __uint_as_float(x[u].z); acc = __builtin_fmaf(d, d, acc);
-                d = __uint_as_float(q.w) - __uint_as_float(x[u].w); acc = __builtin_fmaf(d, d, acc);
-            }
+            acc = team_acc_f32(acc, qv[ci < nchunks ? ci : 0], x[u], ci < nchunks);
         }
     }
     return __float_as_uint(team_sum_f(acc));
@@ -112,23 +118,37 @@ __device__ __forceinline__ int lane_qq_u8(const uint4 *qv, int nchunks, int tl)
     }
     return (int)qq;
 }
-__device__ __forceinline__ uint32_t team_dist_bits_u8(const uint4 *qv, int qq_lane, const char *xrow, int nchunks, int tl)
+// One team of four lanes (t4 = lane within it), without |q|^2: whole numbers, so neither the split nor the order matters, and
+// a wave takes sixteen rows at a time.
+__device__ __forceinline__ uint32_t quad_dist_u8(const uint4 *qv, const char *xrow, int nchunks, int t4)
 {
-    const int steps = (nchunks + 7) >> 3;
+    const int steps = (nchunks + 3) >> 2;
     uint32_t xx = 0, qx = 0;
-#pragma unroll 2
-    for (int st = 0; st < steps; ++st) {
-        const int ci = st * 8 + tl;
-        if (ci < nchunks) {
-            const uint4 x = *(const uint4 *)(xrow + ci * kChunkBytes);
-            const uint4 q = qv[ci];
-            xx = __builtin_amdgcn_udot4(x.x, x.x, xx, false); qx = __builtin_amdgcn_udot4(q.x, x.x, qx, false);
-            xx = __builtin_amdgcn_udot4(x.y, x.y, xx, false); qx = __builtin_amdgcn_udot4(q.y, x.y, qx, false);
-            xx = __builtin_amdgcn_udot4(x.z, x.z, xx, false); qx = __builtin_amdgcn_udot4(q.z, x.z, qx, false);
-            xx = __builtin_amdgcn_udot4(x.w, x.w, xx, false); qx = __builtin_amdgcn_udot4(q.w, x.w, qx, false);
+    for (int st0 = 0; st0 < steps; st0 += 4) {
+        uint4 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u > 0 && st0 + u >= steps) break;   // (wave-uniform)
+            const int ci = (st0 + u) * 4 + t4;
+            x[u] = *(const uint4 *)(xrow + (ci < nchunks ? ci : 0) * kChunkBytes);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u > 0 && st0 + u >= steps) break;
+            const int ci = (st0 + u) * 4 + t4;
+            const uint4 q = qv[ci < nchunks ? ci : 0];
+            uint32_t a = xx, b = qx;
+            a = __builtin_amdgcn_udot4(x[u].x, x[u].x, a, false); b = __builtin_amdgcn_udot4(q.x, x[u].x, b, false);
+            a = __builtin_amdgcn_udot4(x[u].y, x[u].y, a, false); b = __builtin_amdgcn_udot4(q.y, x[u].y, b, false);
+            a = __builtin_amdgcn_udot4(x[u].z, x[u].z, a, false); b = __builtin_amdgcn_udot4(q.z, x[u].z, b, false);
+            a = __builtin_amdgcn_udot4(x[u].w, x[u].w, a, false); b = __builtin_amdgcn_udot4(q.w, x[u].w, b, false);
+            xx = ci < nchunks ? a : xx; qx = ci < nchunks ? b : qx;
         }
     }
-    return (uint32_t)team_sum_i(qq_lane + (int)xx - 2 * (int)qx);
+    int v = (int)xx - 2 * (int)qx;
+    v = v + __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+    v = v + __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+    return (uint32_t)v;
 }
 
 __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)

@@ -10,6 +10,7 @@
 #include <exception>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -137,7 +138,9 @@ struct Routed {
     std::vector<int32_t> q_best;                      // searched label of each query, -1: empty result
     std::vector<int32_t> empty_q;                     // queries with q_best == -1
     std::vector<int32_t> cnt;                         // [n_labels] queries per searched label (zero between calls)
-    std::vector<int32_t> touched;                     // labels with cnt > 0
+    std::vector<int32_t> touched;                     // [n_labels + 1] labels with cnt > 0, first
+    std::vector<uint64_t> label_bits;                 // ... while they are put in order
+    std::vector<int32_t> order;                       // queries grouped by label
 };
 
 // What routing needs to know of an index (a view, so that routing can be exercised without a device).
@@ -172,12 +175,27 @@ struct ItemBuilder {
 // Everything a call writes besides its outputs.  An index has kWorkspaces of them and hands one to each
 // stream that calls it, so that calls on different streams can overlap on the GPU (small batches leave most
 // of the chip idle); calls on one stream share one workspace and run in order.
+// The work lists of a call's plan, kept for the next call's (what they hold is not; new ones are half a megabyte of page faults)
+struct PlanStore {
+    std::vector<int32_t> qrow;
+    std::vector<ScanItem> items;
+    std::vector<MergeItem> merges;
+    std::vector<SeedTile> tiles;
+    template <class Plan> void swap_with(Plan &P)
+    {
+        qrow.swap(P.ib.qrow); items.swap(P.ib.items); merges.swap(P.ib.merges); tiles.swap(P.tiles);
+    }
+    void clear() { qrow.clear(); items.clear(); merges.clear(); tiles.clear(); }
+};
+
 struct Workspace {
+    PlanStore plan;
     DevBuf ws_blob, ws_blob_b;
     DevBuf dseed;   // seed distances, then partial result rows
     // vf_search_multi: gathered query rows, results of the sub-searches
     DevBuf multi_q, multi_ids, multi_dists;
     std::vector<int32_t> multi_host;      // [n_sub parents | nq + 1 first sub-search of each query]
+    std::vector<int32_t> multi_first;
     std::vector<int64_t> multi_qoff;
     std::vector<int32_t> multi_qids;
     // the scan path runs beside the graph path on a second stream of the same (default) priority

@@ -1012,6 +1012,12 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
         if ((rc = seed_copy_for(ix, n_seeds, s, true, &sc)) != VF_OK) return rc;
     }
     CallPlan P(tune);
+    struct Lend {
+        CallPlan &P;
+        PlanStore &store;
+        Lend(CallPlan &p, PlanStore &s) : P(p), store(s) { store.clear(); store.swap_with(P); }
+        ~Lend() { store.swap_with(P); }
+    } lend(P, W->plan);
     Routed &r = W->routed;
     VF_REQUIRE(and_scan_limit >= 0, "and_scan_limit must be >= 0");
     auto plan = [&] {
@@ -1169,12 +1175,24 @@ int search_multi_impl(vf_index *ix, const void *queries, int64_t nq, const int64
         std::vector<int32_t> &host = W->multi_host;
         std::vector<int64_t> &sqoff = W->multi_qoff;
         std::vector<int32_t> &sqids = W->multi_qids;
+        std::vector<int32_t> &first = W->multi_first;
         host.clear(); sqoff.assign(1, 0); sqids.clear();
-        std::vector<int32_t> first((size_t)nq + 1, 0);
+        first.resize((size_t)nq + 1);
+        first[0] = 0;
         int32_t labs[kMaxOthers + 1];
         for (int64_t j = 0; j < nq; ++j) {
             const int64_t b = qoff[j], e = qoff[j + 1];
             VF_REQUIRE(e > b, "every query needs at least one label");
+            if (mode == VF_OR && e - b <= 2) {   // the common case as a straight line: a search for every label with a list
+                const int32_t l0 = qids[b], l1 = qids[e - 1];
+                VF_REQUIRE((uint32_t)l0 < (uint32_t)ix->n_labels && (uint32_t)l1 < (uint32_t)ix->n_labels, "query label outside [0, n_labels)");
+                const size_t at = host.size(), one = ix->S[(size_t)l0] > 0, two = (l0 != l1) & (ix->S[(size_t)l1] > 0);
+                host.resize(at + one + two, (int32_t)j);
+                sqids.resize(at + one + two, l1);
+                if (one) sqids[at] = l0;
+                first[(size_t)j + 1] = (int32_t)host.size();
+                continue;
+            }
             int32_t nl = 0;
             for (int64_t p = b; p < e; ++p) {
                 const int32_t l = qids[p];
@@ -1191,7 +1209,7 @@ int search_multi_impl(vf_index *ix, const void *queries, int64_t nq, const int64
                 if (with_others)
                     for (int32_t i = 0; i < nl; ++i)
                         if (labs[i] != searched) sqids.push_back(labs[i]);
-                sqoff.push_back((int64_t)sqids.size());
+                if (mode != VF_OR) sqoff.push_back((int64_t)sqids.size());
             };
             if (mode == VF_OR) {
                 for (int32_t i = 0; i < nl; ++i)
@@ -1212,6 +1230,10 @@ int search_multi_impl(vf_index *ix, const void *queries, int64_t nq, const int64
             first[(size_t)j + 1] = (int32_t)host.size();
         }
         const int64_t n_sub = (int64_t)host.size();
+        if (mode == VF_OR) {   // (one label each)
+            sqoff.resize((size_t)n_sub + 1);
+            std::iota(sqoff.begin(), sqoff.end(), (int64_t)0);
+        }
         if (n_sub == 0) {
             launch_fill_out(out_ids, out_dists, nq * (int64_t)k, s);
             VF_HIP(hipGetLastError());

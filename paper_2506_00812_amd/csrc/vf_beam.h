@@ -446,7 +446,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     // the first is used, the query stays in registers, and no lane takes a branch (see team_acc_f32).
     // (A lone query's search, 12 x 2 rows of 32 edges over 128 float32 components, 35.5 -> 31.4 us; 64 queries 55.5 -> 48.)
     auto score_lat = [&](auto w_steps, int cnt, int lo) {
-        constexpr int W = decltype(w_steps)::value, NR = 8;
+        constexpr int W = decltype(w_steps)::value, NR = STREAM_SEEDS ? 4 : 8;
         uint4 q[W];
 #pragma unroll
         for (int w = 0; w < W; ++w) q[w] = qv[w * 8 + tl < nchunks ? w * 8 + tl : 0];
@@ -891,7 +891,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
         return cnt;
     };
 
-    if constexpr (E == 1 && DT == 1 && !AND && !STREAM_SEEDS) {
+    if constexpr (E == 1 && DT == 1 && !AND) {
         if ((bq.dseed_row != nullptr || bq.runs != nullptr) && p.seed_approx != 0) {
             const float B = approx_error();
             int cnt;
@@ -935,7 +935,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
             }
         }
     }
-    if constexpr (E == 1 && DT == 1 && AND) {
+    if constexpr (E == 1 && DT == 1 && AND && !STREAM_SEEDS) {
         if ((bq.dseed_row != nullptr || bq.runs != nullptr) && p.seed_approx != 0) {
             // The seeds were scored approximately on the matrix cores.  Keep the seed_keep best of them, re-score
             // those with the ordered distance, and accept the result only if every other seed is provably

@@ -38,7 +38,17 @@ template <bool WAVE_ONLY> __device__ __forceinline__ void wave_sync()
         __syncthreads();
     }
 }
-template <bool WAVE_ONLY> __device__ __forceinline__ int wave_lane() { return WAVE_ONLY ? (int)(threadIdx.x & 63u) : (int)threadIdx.x; }
+// (WAVE_ONLY: opaque, so that a kernel that works job after job does not keep what it derives from the lane in registers
+// across all of them)
+template <bool WAVE_ONLY> __device__ __forceinline__ int wave_lane()
+{
+    int lane = (int)threadIdx.x;
+    if constexpr (WAVE_ONLY) {
+        lane &= 63;
+        asm volatile("" : "+v"(lane));
+    }
+    return lane;
+}
 
 // float -> bfloat16 bits, round to nearest even (finite inputs)
 __device__ __forceinline__ uint32_t bf16_rn_bits(float f)
@@ -150,6 +160,19 @@ __device__ __forceinline__ uint32_t quad_dist_u8(const uint4 *qv, const char *xr
     v = v + __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
     return (uint32_t)v;
 }
+
+typedef _Float16 v8h_seed __attribute__((ext_vector_type(8)));
+
+// eight components (two 16-byte chunks) scaled and rounded to binary16
+__device__ __forceinline__ uint4 scaled_half8(const uint4 &a, const uint4 &b, float scale)
+{
+    const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    v8h_seed x;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = (_Float16)(__uint_as_float(w[i]) * scale);
+    return __builtin_bit_cast(uint4, x);
+}
+typedef float v16f_seed __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)
 {

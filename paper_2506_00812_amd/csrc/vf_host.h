@@ -455,7 +455,8 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
 bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_seeds);
 // The resident copy for n_seeds, or (build = true) a new one; *out stays null when there is none.
 int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, SeedCopy **out);
-int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16, SeedCopy *c);
+int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16, bool keep_f32, SeedCopy *c);
+void half_bound(const vf_index *ix, float delta, BeamParams &b);
 void fill_blob(const CallPlan &P, const Routed &r, char *hp);
 int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem &M, const SeedCopy *sc, const void *queries,
                 int64_t *out_ids, float *out_dists, hipStream_t s, hipStream_t side, hipEvent_t ev_fork,

@@ -139,12 +139,12 @@ int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, Seed
     }
     c->last_use = ++ix->seed_tick;
     *out = c;
-    return build_seed_copy(ix, n_seeds, s, ix->dtype == VF_F32 && ix->tune.seed_bf16 && !ix->seed_bf16_off, c);
+    return build_seed_copy(ix, n_seeds, s, ix->dtype == VF_F32 && ix->tune.seed_bf16 && !ix->seed_bf16_off, false, c);
 }
 
 // Fills *c for n_seeds on stream s (complete when the call returns).  want_f16: float32 data also get the
-// binary16 form (and lose the float32 one when it is larger than 128 MiB).
-int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16, SeedCopy *c)
+// binary16 form (and lose the float32 one when it is larger than 128 MiB, unless it is to be kept).
+int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16, bool keep_f32, SeedCopy *c)
 {
     c->n_seeds = n_seeds;
     c->ok = c->has_f32 = c->has_f16 = false;
@@ -198,23 +198,22 @@ int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16,
         // float32 data: a second copy in binary16; the largest rounding error of a seed goes into the
         // beam kernel's proof (zero for integer-valued data of up to 11 bits, SIFT's kind)
         if ((rc = c->blk16.reserve((size_t)n_groups * ix->group_bytes() / 2)) != VF_OK) return rc;
-        if ((rc = d_err2.reserve((size_t)n_groups * 32 * 4)) != VF_OK) return rc;
-        launch_seed_pack_f16(c->blk.as<uint4>(), n_groups, ix->ncp, ix->seed_scale(), c->blk16.as<uint4>(), d_err2.as<float>(), s);
-        std::vector<float> e2((size_t)n_groups * 32);
-        VF_HIP(hipMemcpyAsync(e2.data(), d_err2.p, e2.size() * 4, hipMemcpyDeviceToHost, s));
+        if ((rc = d_err2.reserve(4)) != VF_OK) return rc;
+        VF_HIP(hipMemsetAsync(d_err2.p, 0, 4, s));
+        launch_seed_pack_f16(c->blk.as<uint4>(), n_groups, ix->ncp, ix->seed_scale(), c->blk16.as<uint4>(), d_err2.as<uint32_t>(), s);
+        float mx = 0.f;
+        VF_HIP(hipMemcpyAsync(&mx, d_err2.p, 4, hipMemcpyDeviceToHost, s));
         VF_HIP(hipStreamSynchronize(s));
-        double mx = 0.0;
-        bool finite = true;
-        for (float v : e2) { finite = finite && v == v && v <= 3.0e38f; mx = v > mx ? v : mx; }
+        const bool finite = mx >= 0.f && mx <= 3.0e38f;
         if (!finite) c->blk16.release();
         if (finite) {
             // small batches are served from the float32 copy, so one of up to 128 MiB stays (dimensions that have a kernel for it)
-            if ((size_t)n_groups * ix->group_bytes() > ((size_t)128 << 20) || !seed_mfma_own(ix->dtype, ix->dim)) {
+            if (!keep_f32 && ((size_t)n_groups * ix->group_bytes() > ((size_t)128 << 20) || !seed_mfma_own(ix->dtype, ix->dim))) {
                 c->blk.release();
                 c->has_f32 = false;
             }
             c->has_f16 = true;
-            c->f16_delta = (float)(std::sqrt(mx) * 1.001);
+            c->f16_delta = (float)(std::sqrt((double)mx) * 1.001);
             if (!ix->h_fb) {
                 if ((rc = ix->d_fb_count.reserve(4)) != VF_OK) return rc;
                 VF_HIP(hipMemsetAsync(ix->d_fb_count.p, 0, 4, s));
@@ -580,6 +579,15 @@ void fill_blob(const CallPlan &P, const Routed &r, char *hp)
     if (!r.empty_q.empty()) memcpy(hp + L.off_empty, r.empty_q.data(), r.empty_q.size() * 4);
 }
 
+// The bounds of approximations from the binary16 copy (see vf_seed.hip): 2048 u, and dx; |q^| <= |q| (1 + 2^-11) and a little.
+void half_bound(const vf_index *ix, float delta, BeamParams &b)
+{
+    b.err_bound = ix->seed_err_bound() * 4.0f;
+    b.err_q = 2.002f * delta;
+    b.scale = ix->seed_scale();
+    b.q_max = 1.07374182e9f / (b.scale * b.scale);   // 2^30: the scaled length is below 2^15
+}
+
 // The launches of one call.  s: the caller's stream; side: the stream the scan path runs on beside the graph path
 // (ev_fork / ev_join tie it to s), or nullptr: everything on s.  may_allocate = false (the entry point that
 // allocates nothing): no seed copy is built, no profiling, no failed-proof watch.
@@ -655,13 +663,6 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                                    ix->counters.as<int32_t>() + (size_t)P.nq * 5, (int)n_gq, s);
         }
     };
-    // the bounds of approximations from the binary16 copy (see vf_seed.hip): 2048 u, and dx; |q^| <= |q| (1 + 2^-11) and a little
-    auto half_bound = [&](BeamParams &b, float delta) {
-        b.err_bound = ix->seed_err_bound() * 4.0f;
-        b.err_q = 2.002f * delta;
-        b.scale = ix->seed_scale();
-        b.q_max = 1.07374182e9f / (b.scale * b.scale);   // 2^30: the scaled length is below 2^15
-    };
     auto run_seeds = [&]() -> int {
         // (a profiled call that forks has recorded this event already: it is its fork event)
         if (prof && !forked) VF_HIP(hipEventRecord(ix->prof_ev[2], s));
@@ -691,7 +692,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
             }
             if (ix->dtype == VF_F32) {
                 bp.seed_approx = 1; bp.xn_max = ix->xn_max;
-                half_bound(bp, sc->f16_delta);
+                half_bound(ix, sc->f16_delta, bp);
                 bp.seed_keep = P.sel_K;
                 if (may_allocate) bp.fallback_count = ix->d_fb_count.as<uint32_t>();
             }
@@ -738,7 +739,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                     if (sd.seed_f16) {
                         // its wider margin: more approximations are kept for re-ranking under a predicate (a failed proof
                         // costs the query a gather of every seed)
-                        half_bound(bp, seed_delta);
+                        half_bound(ix, seed_delta, bp);
                         if (may_allocate) bp.fallback_count = ix->d_fb_count.as<uint32_t>();
                         bp.seed_keep = std::min(64, P.itopk + std::max(tune.seed_margin_bf16, tune.seed_margin));
                     }

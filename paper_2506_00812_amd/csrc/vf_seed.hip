@@ -145,21 +145,8 @@ __global__ __launch_bounds__(64) void seed_dist_kernel(SeedParams p)
 // (a query whose scaled length is beyond 2^15 has no usable approximations: the beam kernel scores its seeds itself).
 // float32 products: <= 512 terms in any order, norms, final additions: 300 u, 512 u used.  (Bfloat16 seeds and queries in two
 // bfloat16 parts, as before, take twice the products, and their bound on 1,000,000 x 128 is 3.6 instead of 0.8.)
-typedef float v16f_seed __attribute__((ext_vector_type(16)));
 typedef int v16i_seed __attribute__((ext_vector_type(16)));
 typedef int v4i_seed __attribute__((ext_vector_type(4)));
-typedef _Float16 v8h_seed __attribute__((ext_vector_type(8)));
-
-// eight components (two 16-byte chunks) scaled and rounded to binary16
-__device__ __forceinline__ uint4 scaled_half8(const uint4 &a, const uint4 &b, float scale)
-{
-    const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    v8h_seed x;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = (_Float16)(__uint_as_float(w[i]) * scale);
-    return __builtin_bit_cast(uint4, x);
-}
-
 // Queries of a tile: 64 where the registers allow it: every seed is then read from L2 half as often (6,500 x 6,144 x 128: 52 us
 // instead of 59; 10,700 AND pairs x 96: 180 instead of 210; uint8 x 192: the same).
 static constexpr __host__ __device__ int seed_mfma_tile(int dt, int steps) { return dt != 1 && steps <= 8 ? 64 : 32; }
@@ -786,9 +773,9 @@ void launch_seed_mfma(int dtype, const SeedParams &p, int n_tiles, hipStream_t s
 #undef VF_LAUNCH_SEED
 }
 
-// The float32 copy of the seeds as binary16 (nch16 chunks of 8 components), times scale; err2[group * 32 + v] = |x - x^|^2 of
-// the unscaled vectors, whose largest is what the proofs allow for.  One thread per seed.
-__global__ void seed_pack_f16_kernel(const uint4 *blk32, int64_t n_vec, int32_t nch16, float scale, uint4 *blk16, float *err2)
+// The float32 copy of the seeds as binary16 (nch16 chunks of 8 components), times scale; *err2_max = the largest |x - x^|^2 of the
+// unscaled vectors (its bits; a NaN's are above all others), which the proofs allow for.  One thread per seed.
+__global__ void seed_pack_f16_kernel(const uint4 *blk32, int64_t n_vec, int32_t nch16, float scale, uint4 *blk16, uint32_t *err2_max)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n_vec) return;
@@ -808,14 +795,17 @@ __global__ void seed_pack_f16_kernel(const uint4 *blk32, int64_t n_vec, int32_t 
         }
         blk16[(g * nch16 + c) * 32 + v] = r;
     }
-    err2[t] = e2;
+    uint32_t most = __float_as_uint(e2);   // (whole halves of a wave: groups have 32 seeds)
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) { const uint32_t other = (uint32_t)__shfl_xor((int)most, o, 32); most = other > most ? other : most; }
+    if (v == 0) atomicMax(err2_max, most);
 }
 
-void launch_seed_pack_f16(const uint4 *blk32, int64_t n_groups, int32_t nch16, float scale, uint4 *blk16, float *err2, hipStream_t s)
+void launch_seed_pack_f16(const uint4 *blk32, int64_t n_groups, int32_t nch16, float scale, uint4 *blk16, uint32_t *err2_max, hipStream_t s)
 {
     if (n_groups <= 0) return;
     hipLaunchKernelGGL(seed_pack_f16_kernel, dim3((unsigned)((n_groups * 32 + 255) / 256)), dim3(256), 0, s, blk32,
-                       n_groups * 32, nch16, scale, blk16, err2);
+                       n_groups * 32, nch16, scale, blk16, err2_max);
 }
 
 // The interleaved float32 copy of the seeds (groups of 32, 2 * nch16 chunks of 4 components) rounded to

@@ -18,7 +18,10 @@
 // many words as there are slots, the dispatcher's poll is one round trip for any number of jobs, and the copies of different jobs
 // overlap.  300,000 x 128 float32, 6,144 seeds, width 2, 12 iterations, queries/s with 1 / 8 / 64 / 240 in flight: 8.7 k /
 // 56 k / 185 k / 191 k before, 12.9 k / 100 k / 757 k / 2.24 M now; p50 of a query 146 / 174 / 311 / 1,192 us before, 103 /
-// 104 / 108 / 127 now.
+// 104 / 108 / 127 now.  Of the 102 us of such a search 63 went by with the seeds and 38 with the search; with the seeds filtered
+// in binary16 on the matrix cores and the search in the form for a wave that has its SIMD to itself, and what is derived from
+// the lane's number kept out of the registers between jobs (464 -> 48 bytes spilled), 26 and 42, which the scoring of the
+// filter's survivors is part of: 1 / 64 in flight 13.1 k / 788 k -> 19.2 k / 1.08 M queries/s.
 //
 // Every wave exits on its own.  The dispatcher leaves when the host asks it to, when max_jobs jobs have been
 // published, or after idle_polls consecutive polls without a new job; leaving, it raises the device-side stop
@@ -86,6 +89,12 @@ struct ServeParams {
     int32_t lds_kernels;        // bytes of LDS the search functions use; the worker's own words follow (lds_own bytes)
     int32_t lds_own;
     int32_t lds_scan;           // bytes of LDS the scan of one wave uses
+    const uint4 *sblk16;        // optional: the seeds in binary16 (bp.scale), the filter of jobs without a predicate
+    const float *snorm;         // with it: norms of the unrounded seeds
+    int32_t s16_chunks;         // 16-byte chunks of a seed in it
+    uint32_t *rows;             // a row of row_words words per worker: approximations, then the minima of their blocks of 32
+    int32_t ns_stride, row_words;
+    float minus_two_unscaled;
 };
 
 template <class T> __device__ __forceinline__ T load_sys(const T *p) { return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM); }
@@ -124,6 +133,77 @@ __device__ __forceinline__ int64_t serve_next_job(const ServeParams &p)
             if (still > bound) return -1;   // the dispatcher must be gone
         }
         __builtin_amdgcn_s_sleep(kServeSleep);
+    }
+}
+
+// Approximate distances of seeds [j_lo, j_hi) (whole groups of 32 but for the list's end) from their binary16 copy, on the matrix
+// cores, as seed_mfma_kernel computes them: the seeds are the rows of a 32x32 product, and every column is the one query.  STEPS:
+// contraction steps (FIT = false: at most).  A worker's seeds come from far memory at the rate that what it keeps in flight
+// allows, so the copy of half the bytes is read, AHEAD groups a wave in flight, and nothing waits for a group but its own product;
+// groups past the last one are that one once more, so that no request or store is conditional.
+// (One query, 6,144 seeds x 128, eight waves: 63 us scored in float32, 64 seeds a step, 26 us so, with 64 queries in flight.)
+template <int STEPS, bool FIT>
+__device__ __forceinline__ void seed_filter_segment(const ServeParams &p, int label, const uint4 *q16, float qn, int ns, int j_lo, int j_hi,
+                                                    uint32_t *norms, uint32_t *row, uint32_t *mins, int lane)
+{
+    constexpr int AHEAD = STEPS <= 8 ? 4 : 1;
+    const int n32 = lane & 31, h = lane >> 5;
+    const int chunks = FIT ? 2 * STEPS : p.s16_chunks, steps = FIT ? STEPS : (chunks + 1) / 2;
+    const int last = (j_hi - j_lo + 31) / 32 - 1;
+    const int64_t g0 = p.bp.sgoff[p.bp.meta.hs_slot[label]] + j_lo / 32;
+    const uint4 *const blk = p.sblk16 + g0 * (int64_t)(chunks * 32) + n32;
+    const float *const xn_at = p.snorm + g0 * 32 + n32;
+    uint4 q[STEPS];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        const bool in = 2 * s + h < chunks;
+        q[s] = q16[in ? 2 * s + h : 0];
+        if (!in) q[s] = make_uint4(0, 0, 0, 0);
+    }
+    uint4 b[AHEAD][STEPS];
+    float xn[AHEAD];
+    auto fetch = [&](int u, int g) {
+        g = g < last ? g : last;
+        const uint4 *src = blk + (int64_t)g * (chunks * 32);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) b[u][s] = src[(FIT || 2 * s + h < chunks ? 2 * s + h : chunks - 1) * 32];
+        xn[u] = xn_at[(int64_t)g * 32];
+    };
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) fetch(u, u);
+    for (int base = 0; base <= last; base += AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int g = base + u < last ? base + u : last, j0 = j_lo + g * 32;
+            v16f_seed acc;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s)
+                if (FIT || s < steps)   // (wave-uniform)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h_seed, b[u][s]), __builtin_bit_cast(v8h_seed, q[s]), acc, 0, 0, 0);
+            wave_sync<true>();          // (the last group's norms have been read)
+            norms[n32] = j0 + n32 < ns ? __float_as_uint(xn[u]) : 0x7F800000u;
+            fetch(u, base + u + AHEAD);
+            wave_sync<true>();
+            uint32_t m = 0xFFFFFFFFu;
+            uint4 mine = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {   // seeds 8 i + 4 h + 0..3 of the group, in every lane of that half
+                const uint4 n4 = *(const uint4 *)&norms[8 * i + 4 * h];
+                const uint32_t nx[4] = {n4.x, n4.y, n4.z, n4.w};
+                uint32_t bits[4];
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    bits[w] = __float_as_uint(fmaxf(__builtin_fmaf(p.minus_two_unscaled, acc[4 * i + w], qn + __uint_as_float(nx[w])), 0.0f));
+                    m = bits[w] < m ? bits[w] : m;
+                }
+                if (n32 == i) mine = make_uint4(bits[0], bits[1], bits[2], bits[3]);
+            }
+            const auto r = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+            if (n32 < 4) *(uint4 *)&row[j0 + 8 * n32 + 4 * h] = mine;
+            if (lane == 0) mins[j0 / 32] = r[0] < r[1] ? r[0] : r[1];
+        }
     }
 }
 
@@ -192,7 +272,12 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
     const int q_bytes = (p.row_bytes + 15) & ~15;
     uint4 *hq = (uint4 *)(share + (size_t)wv * q_bytes);                         // this wave's copy of the query
     uint64_t *runs = (uint64_t *)(share + (size_t)NW * q_bytes);                 // [NW][64]
+    // own[16]: whether the seeds' binary16 copy is used; [20..23] the last search's counters.  A query whose proof fails (more than
+    // 128 seeds within the bound) has its seeds scored by one wave: a worker that meets more than one in 16 does without.
+    int met = 0, failed = 0;
+    if (threadIdx.x == 0) own[16] = p.sblk16 != nullptr ? 1 : 0;
     while (true) {
+        const int lane = wave_lane<true>();
         if (wv == 0) {
             int64_t drawn = lane == 0 ? serve_next_job(p) : 0;
             drawn = (int64_t)readlane64((uint64_t)drawn, 0);
@@ -256,9 +341,31 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
         // interleaved seed copy into a list of its own and leaves that list as a sorted run of keys
         const bool shared_seeds = graph && p.bp.sblk != nullptr;
         int seg = 64;
-        if (shared_seeds) {
-            const int n = p.bp.meta.S[best];
-            const int ns = p.bp.n_seeds < n ? p.bp.n_seeds : n;
+        const int ns = graph ? (p.bp.n_seeds < p.bp.meta.S[best] ? p.bp.n_seeds : p.bp.meta.S[best]) : 0;
+        const bool filtered = DT == 1 && shared_seeds && o_cnt == 0 && own[16] != 0 && ns >= kSeedMfmaLeast;
+        uint32_t *const seed_row = filtered ? p.rows + (int64_t)(blockIdx.x - 1) * p.row_words : nullptr;
+        if (filtered) {
+            if constexpr (DT == 1) {
+                seg = (((ns + NW - 1) / NW) + 31) & ~31;
+                const int j_lo = wv * seg, j_hi = j_lo + seg < ns ? j_lo + seg : ns;
+                // the query in binary16, and its norm
+                const int nchunks = p.row_bytes / kChunkBytes;
+                uint4 v0 = make_uint4(0, 0, 0, 0), v1 = v0;
+                if (2 * lane < nchunks) v0 = ((const uint4 *)qvec)[2 * lane];
+                if (2 * lane + 1 < nchunks) v1 = ((const uint4 *)qvec)[2 * lane + 1];
+                const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+                float qn = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) qn += __uint_as_float(w[i]) * __uint_as_float(w[i]);
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) qn += __shfl_xor(qn, o);
+                if (lane < p.s16_chunks) hq[lane] = scaled_half8(v0, v1, p.bp.scale);
+                wave_sync<true>();
+                constexpr int STEPS = NC == 32 ? 8 : NC == 24 ? 6 : 16;
+                if (j_lo < j_hi)
+                    seed_filter_segment<STEPS, NC != 0>(p, best, hq, qn, ns, j_lo, j_hi, (uint32_t *)(runs + wv * 64), seed_row, seed_row + p.ns_stride, lane);
+            }
+        } else if (shared_seeds) {
             const int nchunks = p.row_bytes / kChunkBytes;
             seg = (((ns + NW - 1) / NW) + 63) & ~63;
             const int j_lo = wv * seg, j_hi = j_lo + seg < ns ? j_lo + seg : ns;
@@ -307,11 +414,23 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
                 bq.out_ids = res->ids; bq.out_dists = res->dists;
                 bq.counters = nullptr; bq.gathered = nullptr; bq.dseed_row = nullptr; bq.runs = nullptr; bq.seed_pass = -1;
                 BeamParams bp = p.bp;
-                if (shared_seeds) {   // the waves' runs, merged by the search as the runs of a selecting seed kernel would be
+                bp.seed_approx = filtered ? 1 : 0;
+                if (filtered) {
+                    bq.dseed_row = seed_row;
+                    bq.dmin_row = seed_row + p.ns_stride;
+                    bq.counters = own + 20;
+                } else if (shared_seeds) {   // the waves' runs, merged by the search as the runs of a selecting seed kernel would be
                     bq.runs = runs;
-                    bp.run_K = 64; bp.run_segs = NW; bp.seg_seeds = seg; bp.seed_approx = 0;
+                    bp.run_K = 64; bp.run_segs = NW; bp.seg_seeds = seg;
                 }
-                beam_search_wave<DT, 1, true>(bp, bq, smem);
+                if (o_cnt == 0) beam_search_wave<DT, 1, true, false, true>(bp, bq, smem);
+                else beam_search_wave<DT, 1, true, true, true>(bp, bq, smem);
+                if (filtered) {
+                    wave_sync<true>();
+                    ++met;
+                    failed += __builtin_amdgcn_readfirstlane(own[23]) & 1;
+                    if (lane == 0 && 16 * failed > met + 64) own[16] = 0;
+                }
             } else {
                 TopM<1> list;   // the waves' runs, ascending by (distance, entry)
                 list.init(k);
@@ -348,7 +467,7 @@ struct vf_server {
     char *h_ring = nullptr;               // pinned
     ServeResult *h_results = nullptr;     // pinned
     ServeHostCtrl *h_ctrl = nullptr;      // pinned
-    DevBuf d_ring, d_ctrl, d_GO_LS;
+    DevBuf d_ring, d_ctrl, d_GO_LS, d_rows;
     SeedCopy seeds;                       // the session's own interleaved copy of the seeds (workers score from it)
     int32_t ring_slots = 0, slot_stride = 0, row_bytes = 0, k = 0;
     int64_t max_jobs = 0;
@@ -361,7 +480,7 @@ static void free_server(vf_server *sv)
 {
     if (!sv) return;
     if (sv->stream) { (void)hipStreamSynchronize(sv->stream); (void)hipStreamDestroy(sv->stream); }
-    sv->d_ring.release(); sv->d_ctrl.release(); sv->d_GO_LS.release();
+    sv->d_ring.release(); sv->d_ctrl.release(); sv->d_GO_LS.release(); sv->d_rows.release();
     for (DevBuf *b : sv->seeds.bufs()) b->release();
     if (sv->h_ring) (void)hipHostFree(sv->h_ring);
     if (sv->h_results) (void)hipHostFree(sv->h_results);
@@ -421,7 +540,7 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     sv->ix = ix; sv->k = k; sv->ring_slots = ring_slots; sv->max_jobs = max_jobs;
     sv->row_bytes = (int32_t)((size_t)ix->dim * ix->elem());
     sv->slot_stride = kServeHdr + ((sv->row_bytes + 63) & ~63);
-    sv->d_ring.al = sv->d_ctrl.al = sv->d_GO_LS.al = &ix->alloc;
+    sv->d_ring.al = sv->d_ctrl.al = sv->d_GO_LS.al = sv->d_rows.al = &ix->alloc;
     for (DevBuf *b : sv->seeds.bufs()) b->al = &ix->alloc;
     const size_t ring_bytes = (size_t)ring_slots * sv->slot_stride, dev_ring_bytes = ring_bytes + (size_t)ring_slots * kReadyBytes;
     const unsigned flags = hipHostMallocMapped | hipHostMallocCoherent;
@@ -441,7 +560,13 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     // the seeds of every graph list, interleaved, in the data's own type (exact distances): a worker streams its
     // query's seeds from it, one seed per lane.  The session owns the copy (the index's copies may be dropped
     // while the kernel runs).  When it does not fit, workers gather the seeds' rows from the vector table.
-    if (!ix->graph_labels.empty() && (rc = build_seed_copy(ix, n_seeds, sv->stream, false, &sv->seeds)) != VF_OK) return rc;
+    // float32 data: beside it the copy in binary16 (see seed_filter_segment).
+    int32_t longest = 0;
+    for (int32_t l : ix->graph_labels) longest = std::max(longest, std::min(n_seeds, ix->S[(size_t)l]));
+    const int32_t ns_stride = (longest + 31) & ~31, row_words = ns_stride + (((ns_stride / 32) + 63) & ~63);
+    const bool want_f16 = ix->dtype == VF_F32 && ix->dim <= 256 && wants_seed_copy(ix, false, itopk, n_seeds) && n_seeds >= kSeedMfmaLeast && ix->tune.seed_bf16 && !ix->seed_bf16_off &&
+                          longest >= kSeedMfmaLeast && (int64_t)n_workers * row_words <= ((int64_t)64 << 20);
+    if (!ix->graph_labels.empty() && (rc = build_seed_copy(ix, n_seeds, sv->stream, want_f16, true, &sv->seeds)) != VF_OK) return rc;
 
     ServeParams p{};
     // beam search: geometry as vf_search computes it
@@ -455,6 +580,14 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     if (sv->seeds.ok && sv->seeds.has_f32) {
         p.bp.sblk = sv->seeds.blk.as<uint4>(); p.bp.sgoff = sv->seeds.goff.as<int64_t>(); p.bp.sblk_chunks = 2 * ix->ncp;
     }
+    if (p.bp.sblk != nullptr && sv->seeds.has_f16) {
+        if ((rc = sv->d_rows.reserve((size_t)n_workers * row_words * 4)) != VF_OK) return rc;
+        p.sblk16 = sv->seeds.blk16.as<uint4>(); p.snorm = sv->seeds.norm.as<float>(); p.s16_chunks = ix->ncp;
+        p.rows = sv->d_rows.as<uint32_t>(); p.ns_stride = ns_stride; p.row_words = row_words;
+        half_bound(ix, sv->seeds.f16_delta, p.bp);
+        p.bp.xn_max = ix->xn_max; p.bp.seed_keep = 64;
+        p.minus_two_unscaled = -2.0f / (p.bp.scale * p.bp.scale);
+    }
     const size_t beam_lds = beam_lds_bytes(p.bp, ix->dtype);
     // scan: one query against a whole list
     p.sp.xblk = ix->d_X_LS.as<uint4>(); p.sp.xnorm = ix->d_xnorm_LS.p; p.sp.map = ix->d_M_LS.as<int32_t>();
@@ -462,7 +595,7 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     const bool valu = scan_valu_supported(ix->dtype, ix->dim, 16);
     const size_t scan_lds = ((valu ? (size_t)(96 + (k | 1)) * 8 + 2 * 32 * 4 : scan_lds_bytes(ix->ncp, 1, k)) + 63) & ~(size_t)63;   // of one wave
     const size_t lds_kernels = (std::max(beam_lds, waves * scan_lds) + 63) & ~(size_t)63;
-    const size_t lds_own = 64;
+    const size_t lds_own = 128;
     // per wave a copy of the query and a run of 64 seed keys
     const size_t lds_share = (size_t)waves * ((((size_t)sv->row_bytes + 15) & ~(size_t)15) + 64 * 8);
     VF_REQUIRE(lds_kernels + lds_own + lds_share <= 64 * 1024, "search parameters need more than 64 KiB of LDS");

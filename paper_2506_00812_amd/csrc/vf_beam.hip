@@ -47,7 +47,12 @@ template <int DT, bool AND>
 static void launch_beam_dt(const BeamParams &p, int n_gq, size_t lds, hipStream_t s, hipEvent_t start, hipEvent_t stop)
 {
     const dim3 grid(n_gq), block(64);
-    if (p.itopk <= 64 && n_gq <= p.lat_waves) hipExtLaunchKernelGGL((beam_kernel<DT, 1, AND, true>), grid, block, (uint32_t)lds, s, start, stop, 0, p);
+    // The latency instantiation has two waves on a SIMD: float32 launches without a predicate take it while all of their waves
+    // are resident so (1,265 queries of 24 x 2 rows: call 146 -> 131 us; 1,944 of 12 x 2 165.3 -> 166.5; 2,514 160.4 -> 161.3 where a
+    // second round is needed).  Those with predicates and uint8 ones only while each has a SIMD to itself (1,200 uint8 queries,
+    // 40 % with a predicate: 349 us, and 391 so).
+    const int lat_waves = DT == 1 && !AND && p.lat_waves <= (1 << 29) ? 2 * p.lat_waves : p.lat_waves;
+    if (p.itopk <= 64 && n_gq <= lat_waves) hipExtLaunchKernelGGL((beam_kernel<DT, 1, AND, true>), grid, block, (uint32_t)lds, s, start, stop, 0, p);
     else if (p.itopk <= 64) hipExtLaunchKernelGGL((beam_kernel<DT, 1, AND>), grid, block, (uint32_t)lds, s, start, stop, 0, p);
     else if (p.itopk <= 128) hipExtLaunchKernelGGL((beam_kernel<DT, 2, AND>), grid, block, (uint32_t)lds, s, start, stop, 0, p);
     else hipExtLaunchKernelGGL((beam_kernel<DT, 4, AND>), grid, block, (uint32_t)lds, s, start, stop, 0, p);

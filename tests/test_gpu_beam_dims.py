@@ -16,7 +16,7 @@ def test_candidate_distances(dtype, dim):
     from paper_2506_00812_amd import binding as vf
     from tests.gpu_util import assert_exact, to_np
     rng = np.random.default_rng(dim)
-    n, nq = 4000, 1300
+    n, nq = 4000, 2300
     x = rng.normal(size=(10, dim))[rng.integers(0, 10, n)] * 2 + rng.normal(size=(n, dim))
     q = x[rng.integers(0, n, nq)] + 0.4 * rng.normal(size=(nq, dim))
     x, q = ((np.rint(a * 25 + 128).clip(0, 255).astype(np.uint8) if dtype == "uint8" else a.astype(np.float32)) for a in (x, q))
@@ -25,7 +25,7 @@ def test_candidate_distances(dtype, dim):
     ids = np.nonzero(carry)[1].astype(np.int32)
     ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, 2, 300, 20)
     ixo = OracleIndex(x, off, ids, 2, 300, 20)
-    for count, two in ((3, False), (nq, False), (300, True), (nq, True)):
+    for count, two in ((3, False), (1300, False), (nq, False), (300, True), (1300, True)):
         per = 2 if two else 1
         qoff = np.arange(count + 1) * per
         qids = (np.tile([0, 1], count) if two else rng.integers(0, 2, count)).astype(np.int32)

@@ -358,7 +358,7 @@ struct BeamQuery {
 template <int DT, int E, bool STREAM_SEEDS = false, bool AND = true, bool LAT = false>
 __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const BeamQuery &bq, uint4 *smem)
 {
-    const int lane = wave_lane<STREAM_SEEDS>(), team = lane >> 3, tl = lane & 7;
+    const int lane = wave_lane<STREAM_SEEDS, STREAM_SEEDS && DT == 1>(), team = lane >> 3, tl = lane & 7;
     const int label = bq.label;
     const int n = p.meta.S[label];
     const int64_t base = p.meta.O_HS[label];

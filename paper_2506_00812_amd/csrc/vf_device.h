@@ -38,15 +38,12 @@ template <bool WAVE_ONLY> __device__ __forceinline__ void wave_sync()
         __syncthreads();
     }
 }
-// (WAVE_ONLY: opaque, so that a kernel that works job after job does not keep what it derives from the lane in registers
+// (OPAQUE: so that a kernel that works job after job does not keep what it derives from the lane in registers
 // across all of them)
-template <bool WAVE_ONLY> __device__ __forceinline__ int wave_lane()
+template <bool WAVE_ONLY, bool OPAQUE = false> __device__ __forceinline__ int wave_lane()
 {
-    int lane = (int)threadIdx.x;
-    if constexpr (WAVE_ONLY) {
-        lane &= 63;
-        asm volatile("" : "+v"(lane));
-    }
+    int lane = WAVE_ONLY ? (int)(threadIdx.x & 63u) : (int)threadIdx.x;
+    if constexpr (OPAQUE) asm volatile("" : "+v"(lane));
     return lane;
 }
 

@@ -115,7 +115,7 @@ __device__ __forceinline__ void and_window_masks(const ScanParams &p, const Scan
 template <int DT, int NCP, bool WAVE_ONLY = false, bool MASKS = false>
 __device__ __forceinline__ void scan_topk_item(const ScanParams &p, const ScanItem &it, uint4 *smem)
 {
-    const int lane = wave_lane<WAVE_ONLY>(), n32 = lane & 31, h = lane >> 5;
+    const int lane = wave_lane<WAVE_ONLY, WAVE_ONLY && DT == 1>(), n32 = lane & 31, h = lane >> 5;
     const int ncp = NCP > 0 ? NCP : p.ncp;
     const int nchunks = 2 * ncp, K = p.K;
     const int row_bytes = p.dim * (DT == 0 ? 1 : 4);
@@ -386,7 +386,7 @@ __device__ __forceinline__ void scan_topk_item(const ScanParams &p, const ScanIt
 template <int NCH, bool QLDS = false>
 __device__ __forceinline__ void scan_valu_item(const ScanParams &p, const ScanItem &it, uint4 *smem, const float *q_lds = nullptr)
 {
-    const int lane = wave_lane<QLDS>(), n32 = lane & 31, h = lane >> 5;
+    const int lane = wave_lane<QLDS, QLDS>(), n32 = lane & 31, h = lane >> 5;
     const int K = p.K, KS = K | 1, TR = p.tile_rows;
     constexpr int PC = 96;   // a step adds <= 64 keys to a row and rows above 32 are drained after every step
     constexpr int row_bytes = NCH * kChunkBytes;

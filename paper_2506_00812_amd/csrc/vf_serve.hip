@@ -277,7 +277,7 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
     int met = 0, failed = 0;
     if (threadIdx.x == 0) own[16] = p.sblk16 != nullptr ? 1 : 0;
     while (true) {
-        const int lane = wave_lane<true>();
+        const int lane = wave_lane<true, DT == 1>();
         if (wv == 0) {
             int64_t drawn = lane == 0 ? serve_next_job(p) : 0;
             drawn = (int64_t)readlane64((uint64_t)drawn, 0);
@@ -423,7 +423,9 @@ __global__ __launch_bounds__(64 * NW) void serve_kernel(ServeParams p)
                     bq.runs = runs;
                     bp.run_K = 64; bp.run_segs = NW; bp.seg_seeds = seg;
                 }
-                if (o_cnt == 0) beam_search_wave<DT, 1, true, false, true>(bp, bq, smem);
+                // (uint8 workers leave registers for other kernels on their compute unit)
+                if constexpr (DT == 0) beam_search_wave<DT, 1, true>(bp, bq, smem);
+                else if (o_cnt == 0) beam_search_wave<DT, 1, true, false, true>(bp, bq, smem);
                 else beam_search_wave<DT, 1, true, true, true>(bp, bq, smem);
                 if (filtered) {
                     wave_sync<true>();

@@ -35,7 +35,9 @@
 //
 // Selection.  With v = q.x - |x|^2 / 2 (uint8: 2 q.x - |x|^2) a distance is below a row's threshold where v is at least
 // a per-row constant t, or q.x - t at least |x|^2 / 2: the right side is the lane's entry's alone, so one subtraction per pair
-// and the maxima of four rows each decide, and only quarters with a candidate are looked at by element.  Candidates are
+// and the maxima of four rows each decide, and only quarters with a candidate are looked at by element.  (In float32 the two forms
+// round differently: the second one holds for every entry whose unrounded v is at least t, and thresholds allow for what v's own
+// rounding adds.)  Candidates are
 // appended to one list of the wave in LDS, without a look at its end; a group that overruns it (before thresholds exist) is
 // gone through again, delivering in between; when it is half full they are delivered to the rows' queues (16 slots, LDS
 // atomics over 64 candidates at a time), and rows with ten or more merge their queue into their sorted K best: four rows
@@ -503,7 +505,10 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK, W)) void join_kernel(Joi
 
     // ---- first thresholds: every lane's largest v of the even and of the odd groups of a sample; a row's K-th largest of
     // those 64 (K + 1 where the row itself may be among them) has K entries at or above it.  Without this a row's first
-    // thousand entries make a queue's worth of candidates every few groups.
+    // thousand entries make a queue's worth of candidates every few groups.  The sample's values are q.x - |x|^2 / 2 rounded, and the
+    // groups are compared as q.x - t rounded, which never leaves out an entry whose unrounded value is at least t: so a
+    // float32 threshold is the sample's value less a few units in its last place, and all K entries pass (copies of one
+    // vector, that is, all of them or none).
     const int rank = K - (it.self_base >= 0 ? 0 : 1);
     const int most = it.q_count * K < kJoinFew ? kJoinSampleFew : kJoinSample;
     const int sample = n_groups / 2 < most ? n_groups / 2 : most;
@@ -547,6 +552,7 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK, W)) void join_kernel(Joi
                     if (n32 == r0 + 4) start = k1;
                 }
             }
+            if constexpr (DT != 0) start -= 2.4e-7f * __builtin_fabsf(start);   // (four halves of a unit; differences below the normal range are exact)
             if (n32 < rows && !filtered && start > tv) tv = start;
             if (h == 0) tvs[n32] = tv;
             wave_lds_sync();

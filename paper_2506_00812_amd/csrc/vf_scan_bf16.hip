@@ -279,7 +279,10 @@ __global__ __launch_bounds__(64) void scan_rerank_kernel(RerankParams p)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) qn += __shfl_xor(qn, o);
     const float B = p.err_bound * (qn + p.xn_max) + p.err_q * sqrtf(qn);
-    const bool all_kept = list.worst == KEY_MAX;   // fewer than Kc candidates in all: no segment dropped one
+    // Fewer than Kc candidates in all, of a list that has no more or under a predicate: no segment dropped one.  (A longer list has
+    // to leave Kc of a query without a predicate: one that does not has lost some, and its query is answered by the definition.)
+    bool all_kept = list.worst == KEY_MAX;
+    if (all_kept && it.n > Kc) all_kept = p.others_off != nullptr && p.others_off[it.qrow + 1] > p.others_off[it.qrow];
     // The kept candidates are re-scored in the order of their approximations, first k and a few to spare, then eight
     // at a time, until everything not re-scored is provably worse than the k-th result: those candidates have
     // approximations >= T, the approximation of the first one not re-scored (the last one kept, once all are),

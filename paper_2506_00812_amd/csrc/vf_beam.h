@@ -812,7 +812,8 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) { qn += __shfl_xor(qn, o); en += __shfl_xor(en, o); }
         if (!(qn <= p.q_max)) return __builtin_inff();
-        return p.err_bound * (qn + p.xn_max) + p.err_q * sqrtf(qn) + (p.scale > 0.f ? 2.001f * sqrtf(en * p.xn_max) : 0.f);
+        // (roots before the product: squared norms of 1e-24 to 1e30 are admitted, and en is smaller still by 2^24)
+        return p.err_bound * (qn + p.xn_max) + p.err_q * sqrtf(qn) + (p.scale > 0.f ? 2.001f * (sqrtf(en) * sqrtf(p.xn_max)) : 0.f);
     };
     // The seeds that may belong to the list, for queries without a predicate: with tau at or above the itopk-th smallest
     // approximation, itopk seeds have ordered distances of at most tau + B, and a seed of an approximation above tau + 2 B has

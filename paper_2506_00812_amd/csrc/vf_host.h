@@ -226,7 +226,8 @@ struct SeedCopy {
     bool has_f16 = false;        // blk16 is valid (float32 data only)
     float f16_delta = 0.f;       // upper bound of the rounding errors |x - x^| of the seeds of the copy
     uint64_t last_use = 0;
-    DevBuf blk, blk16, norm, goff;
+    DevBuf blk, blk16, norm;
+    DevBuf goff;                 // first group of each graph list, and behind them the tables that the copy was made from
     DevBuf map;                  // [group * 32 + v] global id of the seed (AND predicate inside the seed kernel)
     std::vector<DevBuf *> bufs() { return {&blk, &blk16, &norm, &goff, &map}; }
 };

@@ -301,6 +301,8 @@ void launch_seed_pass_count(const int32_t *gq_query, const int32_t *gq_label, co
 // seed_map[g * 32 + v] = global id of seed j = grp_j0[g] + v of graph list grp_slot[g] (local id floor(j n / ns)),
 // 0 for v beyond the list's seeds
 void launch_seed_pack_f16(const uint4 *blk32, int64_t n_groups, int32_t nch16, float scale, uint4 *blk16, uint32_t *err2_max, hipStream_t s);
+void launch_seed_rows_f16(const void *X, int32_t dim, const int32_t *map, const int32_t *grp_cnt, int64_t n_groups, int32_t nch16, float scale,
+                          uint4 *blk16, float *norm, uint32_t *err2_max, hipStream_t s);
 void launch_seed_pack_bf16(const uint4 *blk32, int64_t n_groups, int32_t nch16, uint4 *blk16, float *err2, hipStream_t s);
 void launch_seed_map(const int32_t *M_HS, const int64_t *slot_base, const int32_t *slot_n, int32_t n_seeds,
                      const int32_t *grp_slot, const int32_t *grp_j0, int64_t n_groups, int32_t *seed_map, hipStream_t s);

@@ -108,7 +108,8 @@ int drop_seed_copies(vf_index *ix)
 // The interleaved copy of the seeds of every graph list for n_seeds (see SeedCopy): the resident one, or a new
 // one built on the caller's stream (the call returns after it is complete, so later calls on any stream may
 // read it).  The index keeps kSeedCopies of them; the least recently used one makes room, after the device
-// has drained, since calls on other streams may still be reading it.  (*out)->ok is false when a copy would need
+// has drained, since calls on other streams may still be reading it (dimensions without a kernel instantiation of their own keep
+// the first ones).  (*out)->ok is false when a copy would need
 // more than half of the free device memory: the seed kernel then gathers rows from the vector table.
 bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_seeds)
 {
@@ -131,6 +132,8 @@ int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, Seed
     for (SeedCopy &x : ix->seed_copies)
         if (x.n_seeds < 0) { c = &x; break; }
     if (c == nullptr) {
+        // (dimensions without a kernel instantiation of their own score any further seed count without a copy, and wait for nothing)
+        if (!seed_mfma_own(ix->dtype, ix->dim)) return VF_OK;
         c = &ix->seed_copies[0];
         for (SeedCopy &x : ix->seed_copies)
             if (x.last_use < c->last_use) c = &x;
@@ -143,7 +146,7 @@ int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, Seed
 }
 
 // Fills *c for n_seeds on stream s (complete when the call returns).  want_f16: float32 data also get the
-// binary16 form (and lose the float32 one when it is larger than 128 MiB, unless it is to be kept).
+// binary16 form (and have the float32 one only up to 128 MiB, unless it is to be kept).
 int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16, bool keep_f32, SeedCopy *c)
 {
     c->n_seeds = n_seeds;
@@ -151,20 +154,8 @@ int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16,
     c->f16_delta = 0.f;
     if (!ix->tune.seed_cache) return VF_OK;
     const size_t n_gl = ix->graph_labels.size();
-    std::vector<int64_t> goff(n_gl), slot_base(n_gl);
-    std::vector<int32_t> slot_n(n_gl), grp_slot, grp_j0, grp_cnt;
-    std::vector<int64_t> grp_src;
     int64_t n_groups = 0;
-    for (size_t t = 0; t < n_gl; ++t) {
-        const int32_t l = ix->graph_labels[t];
-        const int32_t n = ix->S[(size_t)l], ns = std::min(n_seeds, n);
-        goff[t] = n_groups; slot_base[t] = ix->O_HS[(size_t)l]; slot_n[t] = n;
-        for (int32_t j0 = 0; j0 < ns; j0 += 32) {
-            grp_slot.push_back((int32_t)t); grp_j0.push_back(j0);
-            grp_src.push_back(n_groups * 32); grp_cnt.push_back(std::min(32, ns - j0));
-            ++n_groups;
-        }
-    }
+    for (const int32_t l : ix->graph_labels) n_groups += ((int64_t)std::min(n_seeds, ix->S[(size_t)l]) + 31) / 32;
     if (n_groups == 0) return VF_OK;
     {
         const size_t need = (size_t)n_groups * (ix->group_bytes() * 3 / 2 + 32 * 4 + 32 * 4 + 32 * 4 + 32 * 4 + 32);
@@ -172,46 +163,51 @@ int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16,
         VF_HIP(hipMemGetInfo(&free_b, &total_b));
         if (need + need / 4 > free_b / 2) return VF_OK;
     }
+    // What the copy is made from, in one buffer that stays with it.  (Nothing is given back here: that waits for the whole device,
+    // and beside a serving session until the session ends.)
+    const size_t ng = (size_t)n_groups;
+    std::vector<int64_t> tables(2 * n_gl + ng + (n_gl + 3 * ng + 2) / 2, 0);
+    int64_t *goff = tables.data(), *slot_base = goff + n_gl, *grp_src = slot_base + n_gl;
+    int32_t *slot_n = (int32_t *)(grp_src + ng), *grp_slot = slot_n + n_gl, *grp_j0 = grp_slot + ng, *grp_cnt = grp_j0 + ng, *err2 = grp_cnt + ng;
+    size_t g = 0;
+    for (size_t t = 0; t < n_gl; ++t) {
+        const int32_t l = ix->graph_labels[t];
+        const int32_t n = ix->S[(size_t)l], ns = std::min(n_seeds, n);
+        goff[t] = (int64_t)g; slot_base[t] = ix->O_HS[(size_t)l]; slot_n[t] = n;
+        for (int32_t j0 = 0; j0 < ns; j0 += 32, ++g) {
+            grp_slot[g] = (int32_t)t; grp_j0[g] = j0;
+            grp_src[g] = (int64_t)g * 32; grp_cnt[g] = std::min(32, ns - j0);
+        }
+    }
     int rc;
-    DevBuf d_base(&ix->alloc), d_n(&ix->alloc), d_slot(&ix->alloc), d_j0(&ix->alloc), d_src(&ix->alloc), d_cnt(&ix->alloc),
-        d_err2(&ix->alloc);
-    DevBufGuard rel{&d_base, &d_n, &d_slot, &d_j0, &d_src, &d_cnt, &d_err2};
-    DevBuf &d_map = c->map;
-    if ((rc = c->blk.reserve((size_t)n_groups * ix->group_bytes())) != VF_OK) return rc;
-    if ((rc = c->norm.reserve((size_t)n_groups * 32 * 4)) != VF_OK) return rc;
-    if ((rc = d_map.reserve((size_t)n_groups * 32 * 4)) != VF_OK) return rc;
-    if ((rc = upload(c->goff, goff, s)) != VF_OK) return rc;
-    if ((rc = upload(d_base, slot_base, s)) != VF_OK) return rc;
-    if ((rc = upload(d_n, slot_n, s)) != VF_OK) return rc;
-    if ((rc = upload(d_slot, grp_slot, s)) != VF_OK) return rc;
-    if ((rc = upload(d_j0, grp_j0, s)) != VF_OK) return rc;
-    if ((rc = upload(d_src, grp_src, s)) != VF_OK) return rc;
-    if ((rc = upload(d_cnt, grp_cnt, s)) != VF_OK) return rc;
-    launch_seed_map(ix->d_M_HS.as<int32_t>(), d_base.as<int64_t>(), d_n.as<int32_t>(), n_seeds, d_slot.as<int32_t>(),
-                    d_j0.as<int32_t>(), n_groups, d_map.as<int32_t>(), s);
-    launch_interleave(ix->dtype, ix->X, ix->dim, d_map.as<int32_t>(), d_src.as<int64_t>(), d_cnt.as<int32_t>(),
-                      n_groups * 32, n_groups, ix->ncp, c->blk.as<uint4>(), c->norm.p, s);
-    VF_HIP(hipGetLastError());
-    VF_HIP(hipStreamSynchronize(s));   // the tables above are pageable host memory and temporaries
-    c->has_f32 = true;
+    // small batches are served from the float32 copy, so one of up to 128 MiB stays (dimensions that have a kernel for it)
+    const bool want_own = !want_f16 || keep_f32 || (seed_mfma_own(ix->dtype, ix->dim) && ng * ix->group_bytes() <= ((size_t)128 << 20));
+    if (want_own && (rc = c->blk.reserve(ng * ix->group_bytes())) != VF_OK) return rc;
+    if (want_f16 && (rc = c->blk16.reserve(ng * ix->group_bytes() / 2)) != VF_OK) return rc;
+    if ((rc = c->norm.reserve(ng * 32 * 4)) != VF_OK) return rc;
+    if ((rc = c->map.reserve(ng * 32 * 4)) != VF_OK) return rc;
+    if ((rc = upload(c->goff, tables, s)) != VF_OK) return rc;
+    auto on_device = [&](const void *host) { return (void *)(c->goff.as<char>() + ((const char *)host - (const char *)tables.data())); };
+    const int32_t *d_cnt = (const int32_t *)on_device(grp_cnt);
+    launch_seed_map(ix->d_M_HS.as<int32_t>(), (const int64_t *)on_device(slot_base), (const int32_t *)on_device(slot_n), n_seeds,
+                    (const int32_t *)on_device(grp_slot), (const int32_t *)on_device(grp_j0), n_groups, c->map.as<int32_t>(), s);
+    if (want_own)
+        launch_interleave(ix->dtype, ix->X, ix->dim, c->map.as<int32_t>(), (const int64_t *)on_device(grp_src), d_cnt, n_groups * 32, n_groups,
+                          ix->ncp, c->blk.as<uint4>(), c->norm.p, s);
+    float mx = 0.f;
     if (want_f16) {
-        // float32 data: a second copy in binary16; the largest rounding error of a seed goes into the
-        // beam kernel's proof (zero for integer-valued data of up to 11 bits, SIFT's kind)
-        if ((rc = c->blk16.reserve((size_t)n_groups * ix->group_bytes() / 2)) != VF_OK) return rc;
-        if ((rc = d_err2.reserve(4)) != VF_OK) return rc;
-        VF_HIP(hipMemsetAsync(d_err2.p, 0, 4, s));
-        launch_seed_pack_f16(c->blk.as<uint4>(), n_groups, ix->ncp, ix->seed_scale(), c->blk16.as<uint4>(), d_err2.as<uint32_t>(), s);
-        float mx = 0.f;
-        VF_HIP(hipMemcpyAsync(&mx, d_err2.p, 4, hipMemcpyDeviceToHost, s));
-        VF_HIP(hipStreamSynchronize(s));
-        const bool finite = mx >= 0.f && mx <= 3.0e38f;
-        if (!finite) c->blk16.release();
-        if (finite) {
-            // small batches are served from the float32 copy, so one of up to 128 MiB stays (dimensions that have a kernel for it)
-            if (!keep_f32 && ((size_t)n_groups * ix->group_bytes() > ((size_t)128 << 20) || !seed_mfma_own(ix->dtype, ix->dim))) {
-                c->blk.release();
-                c->has_f32 = false;
-            }
+        // float32 data: the copy in binary16; the largest rounding error of a seed goes into the beam kernel's proof (zero for
+        // integer-valued data of up to 11 bits, SIFT's kind)
+        uint32_t *d_err2 = (uint32_t *)on_device(err2);
+        if (want_own) launch_seed_pack_f16(c->blk.as<uint4>(), n_groups, ix->ncp, ix->seed_scale(), c->blk16.as<uint4>(), d_err2, s);
+        else launch_seed_rows_f16(ix->X, ix->dim, c->map.as<int32_t>(), d_cnt, n_groups, ix->ncp, ix->seed_scale(), c->blk16.as<uint4>(), c->norm.as<float>(), d_err2, s);
+        VF_HIP(hipMemcpyAsync(&mx, d_err2, 4, hipMemcpyDeviceToHost, s));
+    }
+    VF_HIP(hipGetLastError());
+    VF_HIP(hipStreamSynchronize(s));   // (the tables are pageable host memory)
+    c->has_f32 = want_own;
+    if (want_f16) {
+        if (mx >= 0.f && mx <= 3.0e38f) {
             c->has_f16 = true;
             c->f16_delta = (float)(std::sqrt((double)mx) * 1.001);
             if (!ix->h_fb) {
@@ -224,7 +220,7 @@ int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16,
             }
         }
     }
-    c->ok = true;
+    c->ok = c->has_f32 || c->has_f16;
     return VF_OK;
 }
 
@@ -1004,13 +1000,15 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
             ix->fb_last = now;
             ix->fb_pending = false;
             if ((int64_t)failed * 64 > ix->fb_sent_q) {
-                ix->seed_bf16_off = true;   // the copies are rebuilt in float32
-                if ((rc = drop_seed_copies(ix)) != VF_OK) return rc;
+                ix->seed_bf16_off = true;
+                // the copies are rebuilt in float32 (other dimensions have no use for those: theirs stay until the index is freed, and
+                // this call waits for nothing)
+                if (seed_mfma_own(ix->dtype, ix->dim) && (rc = drop_seed_copies(ix)) != VF_OK) return rc;
             }
         } else if (ix->fb_pending) {
             (void)hipGetLastError();      // "not ready" is no error
         }
-        if ((rc = seed_copy_for(ix, n_seeds, s, true, &sc)) != VF_OK) return rc;
+        if (wants_seed_copy(ix, exact, itopk, n_seeds) && (rc = seed_copy_for(ix, n_seeds, s, true, &sc)) != VF_OK) return rc;
     }
     CallPlan P(tune);
     struct Lend {

@@ -808,6 +808,50 @@ void launch_seed_pack_f16(const uint4 *blk32, int64_t n_groups, int32_t nch16, f
                        n_groups * 32, nch16, scale, blk16, err2_max);
 }
 
+// The same from the vector table where no float32 copy is kept, with the norms of the unrounded vectors (0 for a seed that does not
+// exist): map[g * 32 + v] is the seed's row, grp_cnt[g] the seeds of group g.  One thread per seed; a lane's next 32 bytes are in the
+// line it has just read.
+__global__ void seed_rows_f16_kernel(const float *X, int32_t dim, const int32_t *map, const int32_t *grp_cnt, int64_t n_vec, int32_t nch16,
+                                     float scale, uint4 *blk16, float *norm, uint32_t *err2_max)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n_vec) return;
+    const int64_t g = t >> 5;
+    const int v = (int)(t & 31);
+    const bool valid = v < grp_cnt[g];
+    const float *row = X + (int64_t)(valid ? map[t] : 0) * dim;
+    const float unscale = 1.0f / scale;
+    float e2 = 0.f, acc = 0.f;
+    for (int c = 0; c < nch16; ++c) {
+        uint4 a = make_uint4(0, 0, 0, 0), b = a;
+        if (valid && 8 * c < dim) a = *(const uint4 *)(row + 8 * c);
+        if (valid && 8 * c + 4 < dim) b = *(const uint4 *)(row + 8 * c + 4);
+        const uint4 r = scaled_half8(a, b, scale);
+        const v8h_seed x = __builtin_bit_cast(v8h_seed, r);
+        const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float f = __uint_as_float(w[i]), d = f - (float)x[i] * unscale;
+            acc += f * f;
+            e2 += d * d;
+        }
+        blk16[(g * nch16 + c) * 32 + v] = r;
+    }
+    norm[t] = acc;
+    uint32_t most = __float_as_uint(e2);
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) { const uint32_t other = (uint32_t)__shfl_xor((int)most, o, 32); most = other > most ? other : most; }
+    if (v == 0) atomicMax(err2_max, most);
+}
+
+void launch_seed_rows_f16(const void *X, int32_t dim, const int32_t *map, const int32_t *grp_cnt, int64_t n_groups, int32_t nch16, float scale,
+                          uint4 *blk16, float *norm, uint32_t *err2_max, hipStream_t s)
+{
+    if (n_groups <= 0) return;
+    hipLaunchKernelGGL(seed_rows_f16_kernel, dim3((unsigned)((n_groups * 32 + 255) / 256)), dim3(256), 0, s, (const float *)X, dim, map, grp_cnt,
+                       n_groups * 32, nch16, scale, blk16, norm, err2_max);
+}
+
 // The interleaved float32 copy of the seeds (groups of 32, 2 * nch16 chunks of 4 components) rounded to
 // bfloat16 (nch16 chunks of 8 components); err2[group * 32 + v] = |x - bf16(x)|^2.  One thread per seed.
 __global__ void seed_pack_bf16_kernel(const uint4 *blk32, int64_t n_vec, int32_t nch16, uint4 *blk16, float *err2)

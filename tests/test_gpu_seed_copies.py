@@ -1,0 +1,53 @@
+"""The copies of the seeds that calls make and keep: searches with new seed counts beside a serving session, and more seed counts than
+an index keeps copies of."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _table(dtype, dim, n=12_000, nq=300, seed=0):
+    rng = np.random.default_rng(dim + seed)
+    x = rng.normal(size=(20, dim))[rng.integers(0, 20, n)] * 2 + rng.normal(size=(n, dim))
+    q = x[rng.integers(0, n, nq)] + 0.4 * rng.normal(size=(nq, dim))
+    x, q = ((np.rint(a * 25 + 128).clip(0, 255).astype(np.uint8) if dtype == "uint8" else a.astype(np.float32)) for a in (x, q))
+    carry = rng.random((n, 3)) < [0.9, 0.5, 0.1]
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    return x, off, np.nonzero(carry)[1].astype(np.int32), q, np.arange(nq + 1), rng.integers(0, 3, nq).astype(np.int32)
+
+
+@pytest.mark.parametrize("dtype,dim", [("float32", 100), ("float32", 200), ("float32", 36), ("uint8", 112), ("uint8", 400)])
+def test_new_seed_counts_beside_a_session(dtype, dim):
+    """Dimensions without a kernel instantiation of their own: a call with a new seed count waits for no session, whether it makes a
+    copy of the seeds or there are as many as are kept.  (A wait for the device is one for the session's idle bound, and the session
+    is over.)"""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_exact, to_np
+    x, off, ids, q, qoff, qids = _table(dtype, dim)
+    ix = vf.build_index(torch.from_numpy(x).cuda(), off, ids, 3, 300, 16)
+    Q = torch.from_numpy(q).cuda()
+    params = dict(itopk=32, width=1, iters=5)
+    outs = [(torch.empty((len(q), 10), dtype=torch.int64, device="cuda"), torch.empty((len(q), 10), device="cuda")) for _ in range(6)]
+    ix.profile_enable(True)
+    vf.search(ix, Q, qoff, qids, 10, n_seeds=3000, out_ids=outs[0][0], out_dists=outs[0][1], **params)      # the workspace is at its size
+    ix.profile_read()
+    torch.cuda.synchronize()
+    counts = (2500, 1200, 800, 500, 300, 200)     # the last three: beyond the copies that are kept
+    srv = vf.Server(ix, 10, n_workers=32, ring_slots=64, idle_polls=200_000, n_seeds=1000, **params)
+    try:
+        first = srv.run(q, qoff, qids, in_flight=32)
+        on = []
+        for n_seeds, (oi, od) in zip(counts, outs):
+            vf.search(ix, Q, qoff, qids, 10, n_seeds=n_seeds, out_ids=oi, out_dists=od, **params)
+            on.append(ix.profile_read()["seeds_on_matrix_cores"])
+        again = srv.run(q, qoff, qids, in_flight=32)
+    finally:
+        done, why = srv.end()
+    assert (done, why) == (2 * len(q), 1)
+    assert on == [2 if dtype == "float32" else 1] * 3 + [0] * 3
+    assert_exact(first[0], first[1], again[0], again[1], "session")
+    ix.tune("seed_exact", 1)
+    for n_seeds, (oi, od) in zip(counts, outs):
+        want = vf.search(ix, Q, qoff, qids, 10, n_seeds=n_seeds, **params)
+        assert_exact(to_np(oi), to_np(od), to_np(want[0]), to_np(want[1]), f"{n_seeds} seeds")

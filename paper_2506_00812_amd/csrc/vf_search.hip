@@ -145,6 +145,20 @@ int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, Seed
     return build_seed_copy(ix, n_seeds, s, ix->dtype == VF_F32 && ix->tune.seed_bf16 && !ix->seed_bf16_off, false, c);
 }
 
+// The watch on failed proofs of the binary16 form: its counter, and where the host reads it.
+static int reserve_failed_proofs(vf_index *ix, hipStream_t s)
+{
+    if (ix->h_fb) return VF_OK;
+    int rc = ix->d_fb_count.reserve(4);
+    if (rc != VF_OK) return rc;
+    VF_HIP(hipMemsetAsync(ix->d_fb_count.p, 0, 4, s));
+    VF_HIP(hipStreamSynchronize(s));
+    if (!ix->ev_fb) VF_HIP(hipEventCreateWithFlags(&ix->ev_fb, hipEventDisableTiming));
+    VF_HIP(hipHostMalloc((void **)&ix->h_fb, 4, hipHostMallocDefault));
+    *ix->h_fb = 0;
+    return VF_OK;
+}
+
 // Fills *c for n_seeds on stream s (complete when the call returns).  want_f16: float32 data also get the
 // binary16 form (and have the float32 one only up to 128 MiB, unless it is to be kept).
 int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16, bool keep_f32, SeedCopy *c)
@@ -182,11 +196,24 @@ int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16,
     int rc;
     // small batches are served from the float32 copy, so one of up to 128 MiB stays (dimensions that have a kernel for it)
     const bool want_own = !want_f16 || keep_f32 || (seed_mfma_own(ix->dtype, ix->dim) && ng * ix->group_bytes() <= ((size_t)128 << 20));
-    if (want_own && (rc = c->blk.reserve(ng * ix->group_bytes())) != VF_OK) return rc;
-    if (want_f16 && (rc = c->blk16.reserve(ng * ix->group_bytes() / 2)) != VF_OK) return rc;
-    if ((rc = c->norm.reserve(ng * 32 * 4)) != VF_OK) return rc;
-    if ((rc = c->map.reserve(ng * 32 * 4)) != VF_OK) return rc;
-    if ((rc = upload(c->goff, tables, s)) != VF_OK) return rc;
+    // No memory for it: no copy, as where the device is known to be short of it.  No memory for the binary16 form beside one that is
+    // made anyway: that one alone.  (The largest first: nothing to give back where that fails.)
+    auto without = [&](int why) {
+        if (why != VF_ENOMEM) return why;
+        (void)hipGetLastError();
+        for (DevBuf *b : c->bufs()) b->release();
+        return (int)VF_OK;
+    };
+    if (want_own && (rc = c->blk.reserve(ng * ix->group_bytes())) != VF_OK) return without(rc);
+    if (want_f16 && ((rc = c->blk16.reserve(ng * ix->group_bytes() / 2)) != VF_OK || (rc = reserve_failed_proofs(ix, s)) != VF_OK)) {
+        if (rc != VF_ENOMEM || !want_own) return without(rc);
+        (void)hipGetLastError();
+        c->blk16.release();
+        want_f16 = false;
+    }
+    if ((rc = c->norm.reserve(ng * 32 * 4)) != VF_OK) return without(rc);
+    if ((rc = c->map.reserve(ng * 32 * 4)) != VF_OK) return without(rc);
+    if ((rc = upload(c->goff, tables, s)) != VF_OK) return without(rc);
     auto on_device = [&](const void *host) { return (void *)(c->goff.as<char>() + ((const char *)host - (const char *)tables.data())); };
     const int32_t *d_cnt = (const int32_t *)on_device(grp_cnt);
     launch_seed_map(ix->d_M_HS.as<int32_t>(), (const int64_t *)on_device(slot_base), (const int32_t *)on_device(slot_n), n_seeds,
@@ -210,14 +237,6 @@ int build_seed_copy(vf_index *ix, int32_t n_seeds, hipStream_t s, bool want_f16,
         if (mx >= 0.f && mx <= 3.0e38f) {
             c->has_f16 = true;
             c->f16_delta = (float)(std::sqrt((double)mx) * 1.001);
-            if (!ix->h_fb) {
-                if ((rc = ix->d_fb_count.reserve(4)) != VF_OK) return rc;
-                VF_HIP(hipMemsetAsync(ix->d_fb_count.p, 0, 4, s));
-                VF_HIP(hipStreamSynchronize(s));
-                VF_HIP(hipHostMalloc((void **)&ix->h_fb, 4, hipHostMallocDefault));
-                *ix->h_fb = 0;
-                VF_HIP(hipEventCreateWithFlags(&ix->ev_fb, hipEventDisableTiming));
-            }
         }
     }
     c->ok = c->has_f32 || c->has_f16;

@@ -582,8 +582,13 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     if (sv->seeds.ok && sv->seeds.has_f32) {
         p.bp.sblk = sv->seeds.blk.as<uint4>(); p.bp.sgoff = sv->seeds.goff.as<int64_t>(); p.bp.sblk_chunks = 2 * ix->ncp;
     }
-    if (p.bp.sblk != nullptr && sv->seeds.has_f16) {
-        if ((rc = sv->d_rows.reserve((size_t)n_workers * row_words * 4)) != VF_OK) return rc;
+    bool filter = p.bp.sblk != nullptr && sv->seeds.has_f16;
+    if (filter && (rc = sv->d_rows.reserve((size_t)n_workers * row_words * 4)) != VF_OK) {   // (no memory for them: the float32 copy serves)
+        if (rc != VF_ENOMEM) return rc;
+        (void)hipGetLastError();
+        filter = false;
+    }
+    if (filter) {
         p.sblk16 = sv->seeds.blk16.as<uint4>(); p.snorm = sv->seeds.norm.as<float>(); p.s16_chunks = ix->ncp;
         p.rows = sv->d_rows.as<uint32_t>(); p.ns_stride = ns_stride; p.row_words = row_words;
         half_bound(ix, sv->seeds.f16_delta, p.bp);

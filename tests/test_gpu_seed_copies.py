@@ -51,3 +51,70 @@ def test_new_seed_counts_beside_a_session(dtype, dim):
     for n_seeds, (oi, od) in zip(counts, outs):
         want = vf.search(ix, Q, qoff, qids, 10, n_seeds=n_seeds, **params)
         assert_exact(to_np(oi), to_np(od), to_np(want[0]), to_np(want[1]), f"{n_seeds} seeds")
+
+
+def _stingy(vf, device):
+    """An allocator that refuses the sizes in al.refuse (bytes, or "large": above 100,000), and counts what it has refused."""
+    al = vf.TorchAllocator(device)
+    inner, al.refuse, al.refused = al._alloc_cb, set(), 0
+
+    def alloc(nbytes, ctx):
+        if nbytes > 100_000 if al.refuse == "large" else nbytes in al.refuse:
+            al.refused += 1
+            return None
+        return inner(nbytes, ctx)
+    al.cb = vf.ALLOC_FN(alloc)
+    al.struct = vf.VfAllocator(al.cb, al._free_cb, None)
+    return al
+
+
+def _build_with(vf, al, X, *args):
+    real = vf.TorchAllocator
+    vf.TorchAllocator = lambda device: al
+    try:
+        return vf.build_index(X, *args)
+    finally:
+        vf.TorchAllocator = real
+
+
+@pytest.mark.parametrize("dtype,dim", [("float32", 100), ("float32", 128), ("uint8", 112), ("uint8", 192)])
+def test_no_memory_for_a_copy(dtype, dim):
+    """An allocator that gives nothing large any more, or not the binary16 copy: the search and the session do without, with the same results."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_exact, to_np
+    x, off, ids, q, qoff, qids = _table(dtype, dim, nq=600)
+    X, Q = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda()
+    n_seeds, workers = 1500, 16
+    params = dict(itopk=32, width=1, iters=5, n_seeds=n_seeds)
+    sizes = [int(s) for s in np.bincount(ids, minlength=3)]
+    groups = sum((min(n_seeds, s) + 31) // 32 for s in sizes)
+    up = lambda b: (b + 255) & ~255
+    group_bytes = 2 * ((dim * (1 if dtype == "uint8" else 4) + 31) // 32) * 512
+    stride = (max(min(n_seeds, s) for s in sizes) + 31) & ~31
+    rows = workers * (stride + ((stride // 32 + 63) & ~63)) * 4
+    al = _stingy(vf, X.device)
+    ix = _build_with(vf, al, X, off, ids, 3, 300, 16)
+    ix.tune("seed_exact", 1)
+    want = [to_np(t) for t in vf.search(ix, Q, qoff, qids, 10, **params)]      # (and the workspace is at its size)
+    ix.tune("seed_exact", 0)
+    al.refuse = "large"
+    for _ in range(2):
+        got = vf.search(ix, Q, qoff, qids, 10, **params)
+        assert_exact(to_np(got[0]), to_np(got[1]), *want, "batch without a copy")
+    assert al.refused > 0
+    for refuse in ({up(groups * group_bytes // 2)}, {up(rows)}, {up(groups * group_bytes)}):
+        al.refuse, al.refused = refuse, 0
+        srv = vf.Server(ix, 10, n_workers=workers, ring_slots=64, **params)
+        try:
+            ids_s, d_s, _ = srv.run(q, qoff, qids, in_flight=32)
+        finally:
+            assert srv.end() == (len(q), 1)
+        assert al.refused == (1 if dtype == "float32" or refuse == {up(groups * group_bytes)} else 0)
+        assert_exact(ids_s, d_s, *want, f"session without a block of {refuse} bytes")
+    al.refuse = set()
+    ix2 = _build_with(vf, al, X, off, ids, 3, 300, 16)
+    al.refuse, al.refused = {up(groups * group_bytes // 2)}, 0                 # (float32: the binary16 form alone)
+    got = vf.search(ix2, Q, qoff, qids, 10, **params)
+    assert al.refused == (1 if dtype == "float32" else 0)
+    assert_exact(to_np(got[0]), to_np(got[1]), *want, "batch without the binary16 copy")

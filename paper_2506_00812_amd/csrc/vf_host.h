@@ -449,9 +449,16 @@ struct SeedBudget {
         return need <= words;
     }
 };
+// Who may make a copy of the seeds (see seed_copy_for), and on which stream.
+struct SeedCopyMaker {
+    vf_index *ix;
+    hipStream_t stream;
+};
+// sc: the resident copy of the seeds for n_seeds, if there is one; where there is none and the call would score from it, it is made
+// (make == nullptr: nothing is).
 int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, const int32_t *qids, bool exact,
               bool first_is_searched, int32_t k, int32_t itopk, int32_t width, int32_t iters, int32_t n_seeds,
-              int32_t and_scan_limit, SeedBudget budget, const SeedCopy *sc, CallPlan &P);
+              int32_t and_scan_limit, SeedBudget budget, const SeedCopyMaker *make, SeedCopy *&sc, CallPlan &P);
 // May this call's seeds be scored on the matrix cores (so that an interleaved seed copy is worth having)?
 bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_seeds);
 // The resident copy for n_seeds, or (build = true) a new one; *out stays null when there is none.

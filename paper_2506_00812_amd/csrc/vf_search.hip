@@ -291,7 +291,7 @@ static JoinTiles join_tiles(int kind, int32_t dim, const std::vector<std::pair<i
 // beam kernel gathers the seeds itself).
 int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, const int32_t *qids, bool exact,
                      bool first_is_searched, int32_t k, int32_t itopk, int32_t width, int32_t iters, int32_t n_seeds,
-                     int32_t and_scan_limit, SeedBudget budget, const SeedCopy *sc, CallPlan &P)
+                     int32_t and_scan_limit, SeedBudget budget, const SeedCopyMaker *make, SeedCopy *&sc, CallPlan &P)
 {
     int rc;
     P.nq = nq; P.k = k; P.itopk = itopk; P.width = width; P.iters = iters; P.n_seeds = n_seeds; P.exact = exact;
@@ -467,13 +467,27 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     P.n_gq = r.gq_query.size();
     const int32_t ns_blocks = (int32_t)(((int64_t)n_seeds + 31) / 32);
     P.ns_stride = (int32_t)((int64_t)ns_blocks * 32 <= INT32_MAX ? ns_blocks * 32 : INT32_MAX & ~31);
+    auto and_queries = [&] {   // graph queries with a predicate
+        int64_t n = 0;
+        if (r.any_and)
+            for (size_t i = 0; i < P.n_gq; ++i) n += r.others_off[(size_t)r.gq_query[i] + 1] > r.others_off[(size_t)r.gq_query[i]] ? 1 : 0;
+        return n;
+    };
+    // every distance goes through the seed distance matrix, which must fit
+    const uint64_t matrix = (uint64_t)P.n_gq * (uint64_t)P.ns_stride;
     // Seeds on the matrix cores.  uint8: they give the exact integer distances, nothing else changes.
     // float32: approximations, re-ranked by the beam kernel (its proof under a predicate needs a list of at most 48 entries).
-    // Dimensions without an instantiation of their own are scored from the seeds' copy only.
-    const bool own_dim = seed_mfma_own(ix->dtype, ix->dim);
     // (a tile's rows are addressed by 32-bit offsets)
-    const bool mfma_ok = wants_seed_copy(ix, exact, itopk, n_seeds) && P.n_gq > 0 && P.ns_stride <= 1 << 23 && (ix->dtype == VF_U8 || itopk <= 48 || !r.any_and) &&
-                         (own_dim || (!P.tight && sc != nullptr && sc->ok && (ix->dtype == VF_U8 || sc->has_f16)));
+    const bool own_dim = seed_mfma_own(ix->dtype, ix->dim);
+    bool mfma_ok = wants_seed_copy(ix, exact, itopk, n_seeds) && P.n_gq > 0 && P.ns_stride <= 1 << 23 && (ix->dtype == VF_U8 || itopk <= 48 || !r.any_and);
+    auto dist_pays = [&] { return seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq, seed_dist_own(ix->dtype, ix->dim) ? 0 : and_queries()); };
+    // A copy of the seeds is made by the first call that scores from it.  Dimensions without an instantiation of their own are
+    // scored from the copy only.
+    if (mfma_ok && make != nullptr && sc == nullptr &&
+        (own_dim || (budget.fits(matrix) && (seed_mfma_pays(ix->dtype, ix->dim, itopk, n_seeds, (int64_t)P.n_gq) || dist_pays()))) &&
+        (rc = seed_copy_for(make->ix, n_seeds, make->stream, true, &sc)) != VF_OK)
+        return rc;
+    if (!own_dim && (P.tight || sc == nullptr || !sc->ok || (ix->dtype == VF_F32 && !sc->has_f16))) mfma_ok = false;
     // With an interleaved seed copy the seed kernel also selects (itopk <= 64: the beam kernel's one-register
     // list): it leaves sel_K keys per (query, seed segment) instead of every distance.  float32 data: from the
     // binary16 copy; calls with few graph queries keep the float32 copy and the unfused kernel (their proofs
@@ -510,21 +524,11 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
             P.dseed_words = (size_t)need;
         }
     }
-    auto and_queries = [&] {   // graph queries with a predicate
-        int64_t n = 0;
-        if (r.any_and)
-            for (size_t i = 0; i < P.n_gq; ++i) n += r.others_off[(size_t)r.gq_query[i] + 1] > r.others_off[(size_t)r.gq_query[i]] ? 1 : 0;
-        return n;
-    };
     if (!P.seed_select) {
-        // every distance goes through the seed distance matrix, which must fit
-        const uint64_t need = (uint64_t)P.n_gq * (uint64_t)P.ns_stride;
-        const int64_t n_and = seed_dist_own(ix->dtype, ix->dim) ? 0 : and_queries();
-        P.dense_seeds = !exact && P.n_gq > 0 && budget.fits(need) &&
-                        (seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq, n_and) ||
-                         (mfma_ok && seed_mfma_pays(ix->dtype, ix->dim, itopk, n_seeds, (int64_t)P.n_gq)));
+        P.dense_seeds = !exact && P.n_gq > 0 && budget.fits(matrix) &&
+                        (dist_pays() || (mfma_ok && seed_mfma_pays(ix->dtype, ix->dim, itopk, n_seeds, (int64_t)P.n_gq)));
         P.seeds_mfma = P.dense_seeds && mfma_ok;
-        if (P.dense_seeds) P.dseed_words = (size_t)need;
+        if (P.dense_seeds) P.dseed_words = (size_t)matrix;
     }
     if (P.dense_seeds) {
         // (without the watch on failed proofs, which needs a pinned counter, the binary16 form is used only where it is the only one)
@@ -1010,8 +1014,8 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     budget.words = W->dseed.cap / 4;
     budget.grows = true;
     budget.cap = W->dseed.cap;
-    // the interleaved copy of the seeds for this seed count (built on first use), after a look at the watch
-    // on failed float32 proofs
+    // the interleaved copy of the seeds for this seed count (made by the plan of the first call that uses it), after a look
+    // at the watch on failed float32 proofs
     SeedCopy *sc = nullptr;
     if (wants_seed_copy(ix, exact, itopk, n_seeds)) {
         if (ix->fb_pending && hipEventQuery(ix->ev_fb) == hipSuccess) {
@@ -1027,7 +1031,7 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
         } else if (ix->fb_pending) {
             (void)hipGetLastError();      // "not ready" is no error
         }
-        if (wants_seed_copy(ix, exact, itopk, n_seeds) && (rc = seed_copy_for(ix, n_seeds, s, true, &sc)) != VF_OK) return rc;
+        if ((rc = seed_copy_for(ix, n_seeds, s, false, &sc)) != VF_OK) return rc;
     }
     CallPlan P(tune);
     struct Lend {
@@ -1038,8 +1042,9 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
     } lend(P, W->plan);
     Routed &r = W->routed;
     VF_REQUIRE(and_scan_limit >= 0, "and_scan_limit must be >= 0");
+    const SeedCopyMaker make{ix, s};
     auto plan = [&] {
-        return plan_call(ix, r, nq, qoff, qids, exact, first_is_searched, k, itopk, width, iters, n_seeds, and_scan_limit, budget, sc, P);
+        return plan_call(ix, r, nq, qoff, qids, exact, first_is_searched, k, itopk, width, iters, n_seeds, and_scan_limit, budget, &make, sc, P);
     };
     if ((rc = plan()) != VF_OK) return rc;
     auto words_up = [](size_t v) { return (v + 63) & ~(size_t)63; };

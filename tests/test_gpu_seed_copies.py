@@ -118,3 +118,28 @@ def test_no_memory_for_a_copy(dtype, dim):
     got = vf.search(ix2, Q, qoff, qids, 10, **params)
     assert al.refused == (1 if dtype == "float32" else 0)
     assert_exact(to_np(got[0]), to_np(got[1]), *want, "batch without the binary16 copy")
+
+
+@pytest.mark.parametrize("dtype,dim,itopk,n_seeds,labels", [
+    ("float32", 100, 64, 300, [[0], [1]]), ("uint8", 400, 64, 300, [[0], [1]]),      # lists of 64 entries, few seeds: gathered
+    ("float32", 100, 64, 1000, [[0, 1]]), ("float32", 128, 64, 1000, [[0, 1]]),      # ... with predicates: by the ordered distance
+    ("float32", 100, 32, 1000, [[2]]), ("uint8", 112, 32, 1000, [[2]])])             # lists that are scanned
+def test_no_copy_for_calls_that_do_not_use_it(dtype, dim, itopk, n_seeds, labels):
+    """A call that scores no seeds from a copy makes none: as many blocks of memory as with copies switched off."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_exact, to_np
+    x, off, ids, q, _, _ = _table(dtype, dim)
+    asked = [labels[j % len(labels)] for j in range(len(q))]
+    qoff = np.concatenate([[0], np.cumsum([len(a) for a in asked])]).astype(np.int64)
+    qids = np.array([l for a in asked for l in a], dtype=np.int32)
+    X, Q = torch.from_numpy(x).cuda(), torch.from_numpy(q).cuda()
+    found = []
+    for cache in (1, 0):
+        ix = vf.build_index(X, off, ids, 3, 2000, 16)        # (the third list is scanned)
+        ix.tune("seed_cache", cache)
+        before = ix.allocator.n_alloc
+        out = vf.search(ix, Q, qoff, qids, 10, itopk=itopk, width=1, iters=5, n_seeds=n_seeds)
+        found.append(([to_np(t) for t in out], ix.allocator.n_alloc - before))
+    assert found[0][1] == found[1][1]
+    assert_exact(*found[0][0], *found[1][0], "without copies")

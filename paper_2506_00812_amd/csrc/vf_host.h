@@ -386,6 +386,7 @@ struct CallPlan {
     bool exact = false;
     bool tight = false;                   // temporaries live in a fixed array: nothing is spent on more segments or minima
     int32_t beam_LP = 128, beam_hb = 9;   // beam kernel geometry: list slots and visited-table size
+    int32_t ns_top = 0;                   // seeds a list may have
     int32_t ns_stride = 0;                // row length of the seed distance matrix
     int32_t nb_stride = 0;                // > 0: the seed kernel leaves the minima of its 32-seed blocks too, rows of this length
     ItemBuilder ib;

@@ -465,7 +465,15 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     }
     P.n_xq = r.xq_query.size();
     P.n_gq = r.gq_query.size();
-    const int32_t ns_blocks = (int32_t)(((int64_t)n_seeds + 31) / 32);
+    // (a list has no more seeds than entries: with seed counts beyond any list's length, "every entry", the rows of the matrix and the
+    // grids of its kernels are as long as the longest list)
+    P.ns_top = n_seeds;
+    if (n_seeds > 1 << 23) {
+        int32_t longest = 1;
+        for (const int32_t l : ix->graph_labels) longest = std::max(longest, ix->S[(size_t)l]);
+        P.ns_top = std::min(n_seeds, longest);
+    }
+    const int32_t ns_blocks = (int32_t)(((int64_t)P.ns_top + 31) / 32);
     P.ns_stride = (int32_t)((int64_t)ns_blocks * 32 <= INT32_MAX ? ns_blocks * 32 : INT32_MAX & ~31);
     auto and_queries = [&] {   // graph queries with a predicate
         int64_t n = 0;
@@ -480,11 +488,11 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     // (a tile's rows are addressed by 32-bit offsets)
     const bool own_dim = seed_mfma_own(ix->dtype, ix->dim);
     bool mfma_ok = wants_seed_copy(ix, exact, itopk, n_seeds) && P.n_gq > 0 && P.ns_stride <= 1 << 23 && (ix->dtype == VF_U8 || itopk <= 48 || !r.any_and);
-    auto dist_pays = [&] { return seed_dist_pays(ix->dtype, ix->dim, n_seeds, (int64_t)P.n_gq, seed_dist_own(ix->dtype, ix->dim) ? 0 : and_queries()); };
+    auto dist_pays = [&] { return seed_dist_pays(ix->dtype, ix->dim, P.ns_top, (int64_t)P.n_gq, seed_dist_own(ix->dtype, ix->dim) ? 0 : and_queries()); };
     // A copy of the seeds is made by the first call that scores from it.  Dimensions without an instantiation of their own are
     // scored from the copy only.
     if (mfma_ok && make != nullptr && sc == nullptr &&
-        (own_dim || (budget.fits(matrix) && (seed_mfma_pays(ix->dtype, ix->dim, itopk, n_seeds, (int64_t)P.n_gq) || dist_pays()))) &&
+        (own_dim || (budget.fits(matrix) && (seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq) || dist_pays()))) &&
         (rc = seed_copy_for(make->ix, n_seeds, make->stream, true, &sc)) != VF_OK)
         return rc;
     if (!own_dim && (P.tight || sc == nullptr || !sc->ok || (ix->dtype == VF_F32 && !sc->has_f16))) mfma_ok = false;
@@ -526,7 +534,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     }
     if (!P.seed_select) {
         P.dense_seeds = !exact && P.n_gq > 0 && budget.fits(matrix) &&
-                        (dist_pays() || (mfma_ok && seed_mfma_pays(ix->dtype, ix->dim, itopk, n_seeds, (int64_t)P.n_gq)));
+                        (dist_pays() || (mfma_ok && seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq)));
         P.seeds_mfma = P.dense_seeds && mfma_ok;
         if (P.dense_seeds) P.dseed_words = (size_t)matrix;
     }
@@ -536,7 +544,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
                       (!sc->has_f32 || !own_dim || (!P.tight && (int64_t)P.n_gq >= tune.seed_bf16_min_batch));
         size_t tile_q = P.seed_select ? 32 : P.seeds_mfma ? (size_t)seed_mfma_tile_of(ix->dtype, ix->dim, P.seeds_f16) : 64;
         // (launches that would leave SIMDs without a wave even at 128 seeds a wave: smaller tiles)
-        if (P.seeds_mfma && (int64_t)(P.n_gq / 64) * ((n_seeds + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 1024) tile_q = 32;
+        if (P.seeds_mfma && (int64_t)(P.n_gq / 64) * ((P.ns_top + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 1024) tile_q = 32;
         for (size_t i = 0; i < P.n_gq;) {
             size_t e = i;
             while (e < P.n_gq && r.gq_label[e] == r.gq_label[i]) ++e;
@@ -724,7 +732,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
             sd.scale = ix->seed_scale(); sd.minus_two_unscaled = -2.0f / (sd.scale * sd.scale);
             if (P.seeds_mfma) {
                 sd.chunk_seeds = kSeedMfmaChunk;
-                sd.max_chunks = (P.n_seeds + kSeedMfmaChunk - 1) / kSeedMfmaChunk;
+                sd.max_chunks = (P.ns_top + kSeedMfmaChunk - 1) / kSeedMfmaChunk;
                 sd.xnorm_all = ix->d_xnorm_all.as<uint32_t>();
                 float seed_delta = 0.f;
                 if (sc != nullptr && sc->ok) {
@@ -739,12 +747,12 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                     // seeds per wave: few long waves share the chip better with the scan (512 seeds:
                     // step 0.374 -> 0.340 ms on 10,000-query batches), small batches need many short ones
                     sd.chunk_seeds = 4 * kSeedMfmaChunk;
-                    if ((int64_t)P.tiles.size() * ((P.n_seeds + sd.chunk_seeds - 1) / sd.chunk_seeds) < 512)
+                    if ((int64_t)P.tiles.size() * ((P.ns_top + sd.chunk_seeds - 1) / sd.chunk_seeds) < 512)
                         sd.chunk_seeds = kSeedMfmaChunk;
                     // a launch that leaves most SIMDs without a wave even so (a handful of queries): a wave per group of
                     // 32 seeds, its four groups' serial chain of MFMAs cut to one
-                    if ((int64_t)P.tiles.size() * ((P.n_seeds + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 256) sd.chunk_seeds = 32;
-                    sd.max_chunks = (P.n_seeds + sd.chunk_seeds - 1) / sd.chunk_seeds;
+                    if ((int64_t)P.tiles.size() * ((P.ns_top + kSeedMfmaChunk - 1) / kSeedMfmaChunk) < 256) sd.chunk_seeds = 32;
+                    sd.max_chunks = (P.ns_top + sd.chunk_seeds - 1) / sd.chunk_seeds;
                     if (P.nb_stride > 0) {
                         sd.dmin = M.dseed + (P.dseed_words - n_gq * (size_t)P.nb_stride);   // (behind the matrix)
                         sd.nb_stride = P.nb_stride;
@@ -764,7 +772,7 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                     }
                 }
             } else {
-                sd.max_chunks = (P.n_seeds + kSeedChunk - 1) / kSeedChunk;
+                sd.max_chunks = (int32_t)(((int64_t)P.ns_top + kSeedChunk - 1) / kSeedChunk);
                 launch_seed_dist(ix->dtype, sd, (int)P.tiles.size(), s);
             }
             bp.dseed = sd.dseed;

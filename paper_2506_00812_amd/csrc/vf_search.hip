@@ -772,7 +772,9 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                     }
                 }
             } else {
-                sd.max_chunks = (int32_t)(((int64_t)P.ns_top + kSeedChunk - 1) / kSeedChunk);
+                // (an even number of them: with 63 chunks a tile instead of 64 the tiles of a label meet another XCD's L2 at each chunk;
+                // 1,200 queries x 1,000 seeds x 128 float32 27.8 instead of 26.1 us, AND pairs 27.8 instead of 25.0)
+                sd.max_chunks = P.ns_stride / kSeedChunk;
                 launch_seed_dist(ix->dtype, sd, (int)P.tiles.size(), s);
             }
             bp.dseed = sd.dseed;

@@ -492,7 +492,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     // A copy of the seeds is made by the first call that scores from it.  Dimensions without an instantiation of their own are
     // scored from the copy only.
     if (mfma_ok && make != nullptr && sc == nullptr &&
-        (own_dim || (budget.fits(matrix) && (seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq) || dist_pays()))) &&
+        (own_dim || ((seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq) || dist_pays()) && budget.fits(matrix))) &&
         (rc = seed_copy_for(make->ix, n_seeds, make->stream, true, &sc)) != VF_OK)
         return rc;
     if (!own_dim && (P.tight || sc == nullptr || !sc->ok || (ix->dtype == VF_F32 && !sc->has_f16))) mfma_ok = false;
@@ -533,8 +533,9 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
         }
     }
     if (!P.seed_select) {
-        P.dense_seeds = !exact && P.n_gq > 0 && budget.fits(matrix) &&
-                        (dist_pays() || (mfma_ok && seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq)));
+        // (the driver is asked last: 12 us of a call that gathers its seeds)
+        P.dense_seeds = !exact && P.n_gq > 0 && ((mfma_ok && seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq)) || dist_pays()) &&
+                        budget.fits(matrix);
         P.seeds_mfma = P.dense_seeds && mfma_ok;
         if (P.dense_seeds) P.dseed_words = (size_t)matrix;
     }

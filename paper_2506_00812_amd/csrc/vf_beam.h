@@ -358,7 +358,8 @@ struct BeamQuery {
 // LAT: for launches of so few waves that each has a SIMD to itself (small batches, serving workers): the vectors of up
 // to 64 candidates are requested before the first distance is computed (128 registers of loads in flight), so a
 // batch of children costs one memory latency instead of one per 16 candidates.
-template <int DT, int E, bool STREAM_SEEDS = false, bool AND = true, bool LAT = false>
+// WIDE: vectors of more than 32 chunks (see team_dist_bits_f32).
+template <int DT, int E, bool STREAM_SEEDS = false, bool AND = true, bool LAT = false, bool WIDE = false>
 __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const BeamQuery &bq, uint4 *smem)
 {
     const int lane = wave_lane<STREAM_SEEDS, STREAM_SEEDS && DT == 1>(), team = lane >> 3, tl = lane & 7;
@@ -517,7 +518,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
             const int my = r0 + team;
             const int g = cand_g[my < cnt ? my : 0];
             const char *xrow = (const char *)p.X + (int64_t)g * row_bytes;
-            const uint32_t bits = team_dist_bits_f32(qv, xrow, nchunks, tl);
+            const uint32_t bits = team_dist_bits_f32<(E > 1 || AND || LAT || WIDE)>(qv, xrow, nchunks, tl);
             if (tl == 0 && my < cnt) cand_d[my] = bits;
         }
         wave_sync<STREAM_SEEDS>();
@@ -1086,7 +1087,12 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 // the row as local ids (list bookkeeping) and as global ids (where the vector is): two
                 // independent coalesced loads instead of a lookup in M that depends on the first
                 const int pa = parents[j0 == 0 ? jq0 : jq1];
-                if (small_list) {
+                if constexpr (DT == 1 && AND && !LAT) {   // (scalar registers are short: 3,000 pairs x 200 272 -> 266 us, x 100 189 -> 186)
+                    const int64_t at = (base + pa) * R + (j0 == 0 ? jr0 : jr1);
+                    c = p.G[at];
+                    g = p.Gg[at];
+                    valid = c >= 0 && !(small_list ? is_seed_small((uint32_t)c, (uint32_t)n, (uint32_t)ns, ns_over_n) : is_seed((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_n));
+                } else if (small_list) {
                     const uint32_t at = __umul24((uint32_t)pa, (uint32_t)R) + (uint32_t)(j0 == 0 ? jr0 : jr1);
                     c = rows_local[at];
                     g = rows_global[at];

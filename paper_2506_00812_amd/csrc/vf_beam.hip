@@ -10,7 +10,7 @@ namespace vf {
 // spilled: measured faster on 100,000 two-label queries than 5 waves without spills); uint8 with predicate 7.
 // LAT: the instantiation for launches of at most BeamParams::lat_waves queries (every wave on a SIMD of its own): two waves per
 // SIMD's worth of registers, the candidates' vectors requested 64 at a time.
-template <int DT, int E, bool AND, bool LAT = false>
+template <int DT, int E, bool AND, bool LAT = false, bool WIDE = false>
 __global__ __launch_bounds__(64, LAT ? 2 : (DT == 1 && E == 1) ? (AND ? 6 : 7) : (E == 1 && AND) ? 7 : 8) void beam_kernel(BeamParams p)
 {
     extern __shared__ uint4 smem[];
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(64, LAT ? 2 : (DT == 1 && E == 1) ? (AND ? 6 : 7) :
     bq.dmin_row = p.dmin != nullptr ? p.dmin + (int64_t)gq * p.nb_stride : nullptr;
     bq.runs = p.seed_runs != nullptr ? p.seed_runs + (int64_t)gq * p.run_segs * p.run_K : nullptr;
     bq.seed_pass = p.seed_pass != nullptr ? p.seed_pass[gq] : -1;
-    beam_search_wave<DT, E, false, AND, LAT>(p, bq, smem);
+    beam_search_wave<DT, E, false, AND, LAT, WIDE>(p, bq, smem);
 }
 
 size_t beam_lds_bytes(const BeamParams &p, int dtype)
@@ -53,6 +53,7 @@ static void launch_beam_dt(const BeamParams &p, int n_gq, size_t lds, hipStream_
     // 40 % with a predicate: 349 us, and 391 so).
     const int lat_waves = DT == 1 && !AND && p.lat_waves <= (1 << 29) ? 2 * p.lat_waves : p.lat_waves;
     if (p.itopk <= 64 && n_gq <= lat_waves) hipExtLaunchKernelGGL((beam_kernel<DT, 1, AND, true>), grid, block, (uint32_t)lds, s, start, stop, 0, p);
+    else if (DT == 1 && !AND && p.itopk <= 64 && p.dim > 128) hipExtLaunchKernelGGL((beam_kernel<DT, 1, AND, false, DT == 1 && !AND>), grid, block, (uint32_t)lds, s, start, stop, 0, p);
     else if (p.itopk <= 64) hipExtLaunchKernelGGL((beam_kernel<DT, 1, AND>), grid, block, (uint32_t)lds, s, start, stop, 0, p);
     else if (p.itopk <= 128) hipExtLaunchKernelGGL((beam_kernel<DT, 2, AND>), grid, block, (uint32_t)lds, s, start, stop, 0, p);
     else hipExtLaunchKernelGGL((beam_kernel<DT, 4, AND>), grid, block, (uint32_t)lds, s, start, stop, 0, p);

@@ -338,6 +338,13 @@ struct vf_index {
         return std::ldexp(1.f, 6 - e);
     }
     float seed_scale() const { return xn_max > 0.f ? half_scale(xn_max) : 1.f; }
+    // Whether the proofs of approximate seeds can be expected to hold: their bound is relative to the norms, and on a table far from
+    // the origin it lets most seeds through, while ordered distances take the same time wherever the table is.  Clusters of 100
+    // components shifted by 3 / 5 / 8 / 12 / 20 times their width (norms, squared, over those from the mean: 2.8, 6, 14, 30, 81): 64
+    // queries x 4,096 seeds 49 / 49 / 50 / 52 / 66 us, ordered 81, AND pairs 78 / 76 / 76 / 77 / 259 and 99, 1,200 x 1,000 61 / 62 / 63 / 63 /
+    // 118 and 104; lists of 64 58 / 60 / 72 / 251 / 245 and 86, 4,000 x 2,500 125 / 124 / 384 / - / - and 276.  Clusters that are
+    // up to 100 times further apart than they are wide, or of 200 copies each, take as long as near ones.
+    bool seeds_provable(int32_t itopk) const { return dtype == VF_U8 || xn_max <= (itopk > 48 ? 5.0f : 20.0f) * xc_max; }
     // squared norms the join kernel takes for its lists
     const uint32_t *join_norms() const { return dtype == VF_U8 ? d_xnorm_all.as<uint32_t>() : d_xnorm_c.as<uint32_t>(); }
     // the operands of a self-join, and of a join of queries

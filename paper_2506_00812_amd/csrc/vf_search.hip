@@ -113,8 +113,13 @@ int drop_seed_copies(vf_index *ix)
 // more than half of the free device memory: the seed kernel then gathers rows from the vector table.
 bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_seeds)
 {
-    return !exact && !ix->graph_labels.empty() && ix->seed_mfma_ok && !ix->tune.seed_exact && (ix->dtype == VF_U8 || itopk <= 64) &&
-           (seed_mfma_own(ix->dtype, ix->dim) ? n_seeds > 64 : n_seeds >= kSeedMfmaLeast && (ix->dtype == VF_U8 || (ix->tune.seed_bf16 && !ix->seed_bf16_off)));
+    if (exact || ix->graph_labels.empty() || !ix->seed_mfma_ok || ix->tune.seed_exact) return false;
+    const bool own = seed_mfma_own(ix->dtype, ix->dim);
+    if (n_seeds < (own ? 65 : kSeedMfmaLeast)) return false;
+    if (ix->dtype == VF_U8) return true;
+    if (itopk > 64) return false;
+    // (the ordered kernel would score the others' seeds, whatever the vectors are)
+    return (own && itopk <= 48) || ((own || (ix->tune.seed_bf16 && !ix->seed_bf16_off)) && ix->seeds_provable(itopk));
 }
 
 int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, SeedCopy **out)

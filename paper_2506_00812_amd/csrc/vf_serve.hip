@@ -566,7 +566,7 @@ static int serve_begin_impl(vf_index *ix, const vf_serve_params *prm, vf_server 
     int32_t longest = 0;
     for (int32_t l : ix->graph_labels) longest = std::max(longest, std::min(n_seeds, ix->S[(size_t)l]));
     const int32_t ns_stride = (longest + 31) & ~31, row_words = ns_stride + (((ns_stride / 32) + 63) & ~63);
-    const bool want_f16 = ix->dtype == VF_F32 && ix->dim <= 256 && wants_seed_copy(ix, false, itopk, n_seeds) && n_seeds >= kSeedMfmaLeast && ix->tune.seed_bf16 && !ix->seed_bf16_off &&
+    const bool want_f16 = ix->dtype == VF_F32 && ix->dim <= 256 && wants_seed_copy(ix, false, itopk, n_seeds) && ix->seeds_provable(itopk) && n_seeds >= kSeedMfmaLeast && ix->tune.seed_bf16 && !ix->seed_bf16_off &&
                           longest >= kSeedMfmaLeast && (int64_t)n_workers * row_words <= ((int64_t)64 << 20);
     if (!ix->graph_labels.empty() && (rc = build_seed_copy(ix, n_seeds, sv->stream, want_f16, true, &sv->seeds)) != VF_OK) return rc;
 

@@ -285,14 +285,16 @@ struct vf_index {
     vf::SeedCopy seed_copies[kSeedCopies];
     uint64_t seed_tick = 0;
     // Watch on the 16-bit form of the seed copies: queries whose proof failed are counted on the device; the
-    // count is fetched every tune.seed_fb_window graph queries and read at a later call, and a window with more
-    // than 1/64 failures switches this index back to float32 copies (a failed proof costs its query a gather of
-    // every seed).
+    // count is fetched every tune.seed_fb_window graph queries, the first time after kFirstLook, and read at a later call.
+    // More than 1/64 failures (a failed proof costs its query a gather of every seed): calls that have ordered distances to go
+    // back to -- dimensions without a kernel instantiation of their own, lists of more than 48 entries -- do so, and after a
+    // whole window the others' copies are rebuilt in float32.
+    bool seed_proofs_off = false;
     bool seed_bf16_off = false;
     vf::DevBuf d_fb_count;
     uint32_t *h_fb = nullptr;    // pinned
     hipEvent_t ev_fb = nullptr;
-    bool fb_pending = false;
+    bool fb_pending = false, fb_looked = false, fb_first = false;   // a count is on its way; one was; it is the first
     uint32_t fb_last = 0;
     int64_t fb_window_q = 0, fb_sent_q = 0;
     // profiling

@@ -93,6 +93,8 @@ int check_search_args(const vf_index *ix, const void *queries, int64_t nq, int32
     return VF_OK;
 }
 
+constexpr int kFirstLook = 4096;   // graph queries before the first look at the failed proofs
+
 // Drops every interleaved seed copy.  Other streams may still be reading them: the device drains first.
 int drop_seed_copies(vf_index *ix)
 {
@@ -119,7 +121,7 @@ bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_se
     if (ix->dtype == VF_U8) return true;
     if (itopk > 64) return false;
     // (the ordered kernel would score the others' seeds, whatever the vectors are)
-    return (own && itopk <= 48) || ((own || (ix->tune.seed_bf16 && !ix->seed_bf16_off)) && ix->seeds_provable(itopk));
+    return (own && itopk <= 48) || ((own || ix->tune.seed_bf16) && !ix->seed_proofs_off && ix->seeds_provable(itopk));
 }
 
 int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, SeedCopy **out)
@@ -924,7 +926,11 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
     }
     if (bp.fallback_count != nullptr) {
         ix->fb_window_q += (int64_t)n_gq;
-        if (!ix->fb_pending && ix->fb_window_q >= tune.seed_fb_window) {
+        // (a first look after 4,096 queries, for the calls that have another way: a failed proof is 1 to 10 times such a query's time)
+        const bool first = !ix->fb_looked && tune.seed_fb_window > kFirstLook;
+        if (!ix->fb_pending && ix->fb_window_q >= (first ? kFirstLook : tune.seed_fb_window)) {
+            ix->fb_looked = true;
+            ix->fb_first = first;
             VF_HIP(hipMemcpyAsync(ix->h_fb, bp.fallback_count, 4, hipMemcpyDeviceToHost, s));
             VF_HIP(hipEventRecord(ix->ev_fb, s));
             ix->fb_pending = true;
@@ -1039,10 +1045,11 @@ int search_impl(vf_index *ix, const void *queries, int64_t nq, const int64_t *qo
             ix->fb_last = now;
             ix->fb_pending = false;
             if ((int64_t)failed * 64 > ix->fb_sent_q) {
-                ix->seed_bf16_off = true;
-                // the copies are rebuilt in float32 (other dimensions have no use for those: theirs stay until the index is freed, and
-                // this call waits for nothing)
-                if (seed_mfma_own(ix->dtype, ix->dim) && (rc = drop_seed_copies(ix)) != VF_OK) return rc;
+                ix->seed_proofs_off = true;
+                if (!ix->fb_first && seed_mfma_own(ix->dtype, ix->dim)) {
+                    ix->seed_bf16_off = true;   // the copies are rebuilt in float32
+                    if ((rc = drop_seed_copies(ix)) != VF_OK) return rc;
+                }
             }
         } else if (ix->fb_pending) {
             (void)hipGetLastError();      // "not ready" is no error

@@ -49,3 +49,28 @@ def test_tables_far_from_the_origin(dim, itopk, near):
         want, _ = _search(vf, ix, Q, qoff, qids, **params)
         assert_exact(*got, *want, f"shift {shift}")
         assert_exact(ids_s, d_s, *want, f"shift {shift}, session")
+
+
+@pytest.mark.parametrize("dim,itopk", [(100, 32), (128, 64)])
+def test_failing_proofs_are_noticed_early(dim, itopk):
+    """Proofs that fail: calls that have ordered distances to go back to do so after the first few thousand queries, and wait for
+    nothing; others of the same index go on."""
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_exact
+    ix, Q, qoff, qids = _index(vf, dim, 0.0)
+    params = dict(itopk=itopk, n_seeds=700)
+    want, pf = _search(vf, ix, Q, qoff, qids, **params)
+    assert pf["seeds_on_matrix_cores"] == 2 and pf["seed_fallbacks"] == 0
+    live = ix.allocator.live_bytes()
+    ix.tune("seed_slack", 1e30)      # no bound holds
+    seen = []
+    for _ in range(4):
+        got, pf = _search(vf, ix, Q, qoff, qids, **params)
+        assert_exact(*got, *want, "failed proofs")
+        seen.append((pf["seeds_on_matrix_cores"], pf["seed_fallbacks"]))
+    assert seen == [(2, len(Q))] + [(0, 0)] * 3
+    assert ix.allocator.live_bytes() >= live          # the copies stay: nothing has waited for the device
+    if dim == 128:
+        ix.tune("seed_slack", 1.0)
+        _, pf = _search(vf, ix, Q, qoff, qids, itopk=32, n_seeds=700)
+        assert pf["seeds_on_matrix_cores"] == 2

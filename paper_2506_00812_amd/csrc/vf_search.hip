@@ -496,10 +496,29 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     const bool own_dim = seed_mfma_own(ix->dtype, ix->dim);
     bool mfma_ok = wants_seed_copy(ix, exact, itopk, n_seeds) && P.n_gq > 0 && P.ns_stride <= 1 << 23 && (ix->dtype == VF_U8 || itopk <= 48 || !r.any_and);
     auto dist_pays = [&] { return seed_dist_pays(ix->dtype, ix->dim, P.ns_top, (int64_t)P.n_gq, seed_dist_own(ix->dtype, ix->dim) ? 0 : and_queries()); };
+    // float32 vectors of more than 32 chunks in batches of mostly predicates: a wave that gathers tests the predicate first and scores
+    // what passes, so the launch pays from about 80 passing seeds a query on, taking the labels as independent.  One query, gathering
+    // -> on the matrix cores, at 20 / 60 / 90 / 150 passing seeds: 160 components 25 / 37 / 38 / 64 -> 36 / 39 / 39 / 48 us, 232
+    // 27 / 40 / 39 / 68 -> 38 / 41 / 40 / 49.
+    auto few_pass = [&] {
+        if (ix->dtype != VF_F32 || ix->dim <= 128 || 2 * and_queries() <= (int64_t)P.n_gq) return false;
+        double passing = 0.0;
+        int64_t n_and = 0;
+        for (size_t i = 0; i < P.n_gq; ++i) {
+            const int32_t b = r.others_off[(size_t)r.gq_query[i]], e = r.others_off[(size_t)r.gq_query[i] + 1];
+            if (e == b) continue;
+            double pass = std::min(n_seeds, ix->S[(size_t)r.gq_label[i]]);
+            for (int32_t o = b; o < e; ++o) pass *= (double)ix->S[(size_t)r.others[(size_t)o]] / (double)ix->n;
+            passing += pass;
+            ++n_and;
+        }
+        return passing < 80.0 * (double)n_and;
+    };
+    auto mfma_pays = [&] { return seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq) && !few_pass(); };
     // A copy of the seeds is made by the first call that scores from it.  Dimensions without an instantiation of their own are
     // scored from the copy only.
     if (mfma_ok && make != nullptr && sc == nullptr &&
-        (own_dim || ((seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq) || dist_pays()) && budget.fits(matrix))) &&
+        (own_dim || ((mfma_pays() || dist_pays()) && budget.fits(matrix))) &&
         (rc = seed_copy_for(make->ix, n_seeds, make->stream, true, &sc)) != VF_OK)
         return rc;
     if (!own_dim && (P.tight || sc == nullptr || !sc->ok || (ix->dtype == VF_F32 && !sc->has_f16))) mfma_ok = false;
@@ -541,7 +560,7 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     }
     if (!P.seed_select) {
         // (the driver is asked last: 12 us of a call that gathers its seeds)
-        P.dense_seeds = !exact && P.n_gq > 0 && ((mfma_ok && seed_mfma_pays(ix->dtype, ix->dim, itopk, P.ns_top, (int64_t)P.n_gq)) || dist_pays()) &&
+        P.dense_seeds = !exact && P.n_gq > 0 && ((mfma_ok && mfma_pays()) || dist_pays()) &&
                         budget.fits(matrix);
         P.seeds_mfma = P.dense_seeds && mfma_ok;
         if (P.dense_seeds) P.dseed_words = (size_t)matrix;

@@ -74,3 +74,29 @@ def test_failing_proofs_are_noticed_early(dim, itopk):
         ix.tune("seed_slack", 1.0)
         _, pf = _search(vf, ix, Q, qoff, qids, itopk=32, n_seeds=700)
         assert pf["seeds_on_matrix_cores"] == 2
+
+
+@pytest.mark.parametrize("dim,nq", [(160, 1), (160, 300), (232, 40)])
+def test_predicates_that_few_seeds_pass(dim, nq):
+    """Wide vectors: seeds are scored on the matrix cores where enough of them pass, and gathered where few do."""
+    import torch
+    from paper_2506_00812_amd import binding as vf
+    from tests.gpu_util import assert_exact
+    rng = np.random.default_rng(dim)
+    n = 10_000
+    x = rng.normal(size=(20, dim))[rng.integers(0, 20, n)] * 2 + rng.normal(size=(n, dim))
+    Q = torch.from_numpy((x[rng.integers(0, n, nq)] + 0.4 * rng.normal(size=(nq, dim))).astype(np.float32)).cuda()
+    carry = np.zeros((n, 3), dtype=bool)
+    for l, size in enumerate((600, 6000, 1000)):     # of the first list's seeds 360 carry the second label, 60 the third
+        carry[rng.permutation(n)[:size], l] = True
+    off = np.concatenate([[0], np.cumsum(carry.sum(1))]).astype(np.int64)
+    ix = vf.build_index(torch.from_numpy(x.astype(np.float32)).cuda(), off, np.nonzero(carry)[1].astype(np.int32), 3, 300, 16)
+    qoff = np.arange(nq + 1) * 2
+    for other, on in ((1, 2), (2, 0)):
+        qids = np.tile([0, other], nq).astype(np.int32)
+        got, pf = _search(vf, ix, Q, qoff, qids, itopk=32, n_seeds=2000)
+        assert pf["seeds_on_matrix_cores"] == on
+        ix.tune("seed_exact", 1)
+        want, _ = _search(vf, ix, Q, qoff, qids, itopk=32, n_seeds=2000)
+        ix.tune("seed_exact", 0)
+        assert_exact(*got, *want, f"partner {other}")

@@ -147,9 +147,11 @@ __device__ __forceinline__ int larger(int a, int b) { return a > b ? a : b; }
 
 constexpr int kJoinQueue = 16;   // pending keys per row
 constexpr int kJoinMerge = 10;   // a row with as many of them is merged when its wave delivers
-constexpr int kJoinFlat = 128;   // candidates on their way to the rows' queues (two rows of a group add up to 64)
+// candidates on their way to the rows' queues (two rows of a group add up to 64); one wave by itself has the LDS for twice as many: before
+// thresholds tighten, rows that keep 60 entries and more have over 128 in a group
+__host__ __device__ constexpr int join_flat(int w) { return w == 1 ? 256 : 128; }
 constexpr int kJoinFull = 64;    // as many of them make the waves of a workgroup deliver together
-constexpr int kJoinWaveLds = 32 * kJoinQueue * 8 + kJoinFlat * 8 + 32 * 4 + 32 * 4 + kJoinFlat;   // bytes of a wave
+__host__ __device__ constexpr int join_wave_lds(int w) { return 32 * kJoinQueue * 8 + join_flat(w) * 8 + 32 * 4 + 32 * 4 + join_flat(w); }   // bytes of a wave
 // Groups that are looked at first, for a row's first threshold; a quarter of them where the rows and what is kept of each
 // are so few (kJoinFew keys in all) that reading 64 groups twice costs more than the candidates it saves (a lone query over a
 // list of 300,000 x 128, segments of 147 groups, split operands: 371 -> 341 us).
@@ -187,7 +189,7 @@ __host__ __device__ constexpr int join_buffers(int nc) { return nc <= 32 ? 2 : 1
 template <int DT, int NK, int W> constexpr size_t join_lds_bytes()
 {
     constexpr int NC = join_chunks<DT>(NK);
-    return (size_t)(W > 1 ? join_buffers(NC) * NC * 512 + 16 : 0) + (size_t)W * (kJoinWaveLds + join_lds_steps(NK) * 1024);
+    return (size_t)(W > 1 ? join_buffers(NC) * NC * 512 + 16 : 0) + (size_t)W * (join_wave_lds(W) + join_lds_steps(NK) * 1024);
 }
 
 // NK: contraction steps (16 components of float32, 32 of uint8), the vectors zero padded to them.  W: waves of a workgroup,
@@ -207,6 +209,7 @@ __global__ __launch_bounds__(64 * W, join_waves(DT, NK, W)) void join_kernel(Joi
     const int wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
     const int K = p.K, row_base = wave * 32;
     const int rows = it.q_count - row_base < 32 ? it.q_count - row_base : 32;   // rows of this wave (<= 0: none)
+    constexpr int kJoinFlat = join_flat(W), kJoinWaveLds = join_wave_lds(W);
     static_assert(kJoinWaveLds % 16 == 0, "alignment");
     uint64_t *pend = (uint64_t *)((char *)(smem + NBUF * STAGE) + wave * kJoinWaveLds);   // [32 rows][kJoinQueue]
     uint64_t *flat = pend + 32 * kJoinQueue;                   // (v << 32 | entry) of a candidate

@@ -86,12 +86,14 @@ __device__ __forceinline__ bool is_seed_small(uint32_t c, uint32_t n, uint32_t n
     return r < ns || r + n < ns;
 }
 
-// floor(j * n / ns) for j < ns <= n: a 32-bit division where the products fit (uint8 AND pairs, 64 queries x 16,384 seeds of lists of
-// 54,000: 87 us, and 129.5 without this branch, which one list takes as a whole); else the quotient estimated in double
-// precision (inv_ns = 1 / ns; below 2^31, so off by at most one), corrected with the exact remainder.
+// floor(j * n / ns) for j < ns <= n: quotient estimated in double precision (inv_ns = 1 / ns; below 2^31, so off by at most one),
+// corrected with the exact remainder.  SHORT: a 32-bit division where the products fit, which a list does as a whole: uint8 with
+// predicates (64 AND pairs x 16,384 seeds of lists of 54,000: 87.5 us, 129 without) and lists of more than one register; the
+// branch costs the other kernels 2 to 3 % (18,400 queries x 96, 32 seeds, 25 x 2 rows: 200 us, 206 with it).
+template <bool SHORT = false>
 __device__ __forceinline__ int seed_local_id(uint32_t j, uint32_t n, uint32_t ns, double inv_ns)
 {
-    if ((((uint64_t)n * ns) >> 32) == 0) return (int)(j * n / ns);
+    if (SHORT && (((uint64_t)n * ns) >> 32) == 0) return (int)(j * n / ns);
     const uint64_t prod = (uint64_t)j * n;
     uint32_t q = (uint32_t)((double)j * (double)n * inv_ns);
     int64_t r = (int64_t)prod - (int64_t)((uint64_t)q * ns);
@@ -362,6 +364,7 @@ struct BeamQuery {
 template <int DT, int E, bool STREAM_SEEDS = false, bool AND = true, bool LAT = false, bool WIDE = false>
 __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const BeamQuery &bq, uint4 *smem)
 {
+    constexpr bool SHORT_DIVISION = (DT == 0 && AND) || E > 1;   // (see seed_local_id)
     const int lane = wave_lane<STREAM_SEEDS, STREAM_SEEDS && DT == 1>(), team = lane >> 3, tl = lane & 7;
     const int label = bq.label;
     const int n = p.meta.S[label];
@@ -406,7 +409,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
     const int32_t *smap = nullptr;
     if (AND && o_cnt > 0 && p.seed_map != nullptr) smap = p.seed_map + p.seed_goff[p.meta.hs_slot[label]] * 32;
     auto seed_gid = [&](int j) -> int {
-        return smap != nullptr ? smap[j] : p.meta.M_HS[base + seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns)];
+        return smap != nullptr ? smap[j] : p.meta.M_HS[base + seed_local_id<SHORT_DIVISION>((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns)];
     };
 
     TopM<E> top;
@@ -627,7 +630,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 const int i = i0 + lane;
                 const bool valid = i < cnt;
                 int c = valid ? cand_c[i] : 0;
-                if (!as_index) c = seed_local_id((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_ns);
+                if (!as_index) c = seed_local_id<SHORT_DIVISION>((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_ns);
                 offer_seeds_to(list, valid, valid ? cand_d[i] : 0u, c);
             }
             wave_sync<STREAM_SEEDS>();
@@ -760,7 +763,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 bool valid = i < cnt;
                 int c = valid ? cand_c[i] : 0;
                 if (lazy || !as_index) {
-                    const int cl = seed_local_id((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_ns);
+                    const int cl = seed_local_id<SHORT_DIVISION>((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_ns);
                     if (lazy && valid) valid = passes(seed_gid(c));
                     if (!as_index) c = cl;
                 }
@@ -790,7 +793,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
             uint64_t key = KEY_MAX;
             if (raw != KEY_MAX) {
                 const uint32_t j = (uint32_t)raw;
-                const uint32_t c = as_index ? j : (uint32_t)seed_local_id(j, (uint32_t)n, (uint32_t)ns, inv_ns);
+                const uint32_t c = as_index ? j : (uint32_t)seed_local_id<SHORT_DIVISION>(j, (uint32_t)n, (uint32_t)ns, inv_ns);
                 key = (raw & 0xFFFFFFFF00000000ull) | ((uint64_t)c << 1) | 1ull;
             }
             merge_sorted_run(list, key, lane);
@@ -925,7 +928,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
             // (every one of them: the approximations were of no use)
             if (cnt <= 128 && (cnt < ns || ns <= 64)) {
                 for (int i = lane; i < cnt; i += 64) {
-                    const int c = seed_local_id((uint32_t)cand_c[i], (uint32_t)n, (uint32_t)ns, inv_ns);
+                    const int c = seed_local_id<SHORT_DIVISION>((uint32_t)cand_c[i], (uint32_t)n, (uint32_t)ns, inv_ns);
                     cand_c[i] = c;
                     cand_g[i] = p.meta.M_HS[base + c];
                 }
@@ -955,7 +958,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 fix_seed_count();
                 const uint64_t key = tmp.cur[0];
                 const bool valid = key != KEY_MAX;
-                const int c = valid ? seed_local_id((uint32_t)(key >> 1) & 0x7FFFFFFFu, (uint32_t)n, (uint32_t)ns, inv_ns) : 0;
+                const int c = valid ? seed_local_id<SHORT_DIVISION>((uint32_t)(key >> 1) & 0x7FFFFFFFu, (uint32_t)n, (uint32_t)ns, inv_ns) : 0;
                 // the kept seeds sit in lanes 0 .. cnt - 1 (sorted list) and have passed the predicate already
                 wave_sync<STREAM_SEEDS>();
                 const int cnt = __popcll(__ballot(valid));
@@ -1020,13 +1023,13 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 const bool full = top.worst != KEY_MAX;
                 if (full) { lazy_used = true; pass = valid && bits <= (uint32_t)(top.worst >> 32); }
                 if (pass) {
-                    c = seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns);
+                    c = seed_local_id<SHORT_DIVISION>((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns);
                     pass = passes(seed_gid(j));
                 }
                 n_scored += __popcll(__ballot(pass));
             } else {
                 n_scored += __popcll(__ballot(valid));
-                if (pass && bits <= (uint32_t)(top.worst >> 32)) c = seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns);
+                if (pass && bits <= (uint32_t)(top.worst >> 32)) c = seed_local_id<SHORT_DIVISION>((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns);
             }
             offer(pass, bits, c);
         }
@@ -1037,7 +1040,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
         for (int j0 = 0; j0 < ns; j0 += 64) {
             const int j = j0 + lane;
             const bool valid = j < ns;
-            const int c = valid ? seed_local_id((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns) : 0;
+            const int c = valid ? seed_local_id<SHORT_DIVISION>((uint32_t)j, (uint32_t)n, (uint32_t)ns, inv_ns) : 0;
             wave_sync<STREAM_SEEDS>();
             const int cnt = filter_and_compact(valid, c, 0);
             wave_sync<STREAM_SEEDS>();
@@ -1087,12 +1090,7 @@ __device__ __forceinline__ void beam_search_wave(const BeamParams &p, const Beam
                 // the row as local ids (list bookkeeping) and as global ids (where the vector is): two
                 // independent coalesced loads instead of a lookup in M that depends on the first
                 const int pa = parents[j0 == 0 ? jq0 : jq1];
-                if constexpr (DT == 1 && AND && !LAT) {   // (scalar registers are short: 3,000 pairs x 200 272 -> 266 us, x 100 189 -> 186)
-                    const int64_t at = (base + pa) * R + (j0 == 0 ? jr0 : jr1);
-                    c = p.G[at];
-                    g = p.Gg[at];
-                    valid = c >= 0 && !(small_list ? is_seed_small((uint32_t)c, (uint32_t)n, (uint32_t)ns, ns_over_n) : is_seed((uint32_t)c, (uint32_t)n, (uint32_t)ns, inv_n));
-                } else if (small_list) {
+                if (small_list) {
                     const uint32_t at = __umul24((uint32_t)pa, (uint32_t)R) + (uint32_t)(j0 == 0 ? jr0 : jr1);
                     c = rows_local[at];
                     g = rows_global[at];

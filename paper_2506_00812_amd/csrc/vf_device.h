@@ -80,9 +80,9 @@ __device__ __forceinline__ int team_sum_i(int v)
 // No lane takes a branch: those without a chunk in the last step read an existing one and leave its terms out (a load or
 // an LDS read under a lane's condition is a branch of its own, and its wait stands in front of the next: 6,400 queries of
 // 24 rows of 32 edges 141 -> 137 us).  LANES: with those branches and a register or two less, which is the better form everywhere
-// else: lists of more than one register (1,200 queries x 200, lists of 128: 320 us, 329 without), predicates (4,000 pairs x 200
-// 108 and 111), vectors of more than 32 chunks (2,500 queries x 200 that gather 150 seeds: 147 and 153.5; in the latency form,
-// whose shorter vectors go another way, 1,000 pairs x 200 607 and 635).
+// else: lists of more than one register (1,200 queries x 200, lists of 128: 319 us, 330 without), predicates (3,000 pairs x 200
+// that gather 260 and 270), the latency form where vectors have more than 32 chunks (1,000 pairs x 200 597 and 617), and such
+// vectors without predicates (2,500 queries x 200, 40 x 2 rows, 163.5 and 170).
 __device__ __forceinline__ float team_acc_f32(float acc, const uint4 &q, const uint4 &x, bool in)
 {
     float d, a = acc;
@@ -101,22 +101,22 @@ __device__ __forceinline__ uint32_t team_dist_bits_f32(const uint4 *qv, const ch
         uint4 x[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {   // all loads of the batch are issued before the first use
+            if (!LANES && u > 0 && st0 + u >= steps) break;   // (wave-uniform)
             const int ci = (st0 + u) * 8 + tl;
             if constexpr (LANES) {
                 x[u] = make_uint4(0, 0, 0, 0);
                 if (ci < nchunks) x[u] = *(const uint4 *)(xrow + ci * kChunkBytes);
             } else {
-                if (u > 0 && st0 + u >= steps) break;   // (wave-uniform)
                 x[u] = *(const uint4 *)(xrow + (ci < nchunks ? ci : 0) * kChunkBytes);
             }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
+            if (!LANES && u > 0 && st0 + u >= steps) break;
             const int ci = (st0 + u) * 8 + tl;
             if constexpr (LANES) {
                 if (ci < nchunks) acc = team_acc_f32(acc, qv[ci], x[u], true);
             } else {
-                if (u > 0 && st0 + u >= steps) break;
                 acc = team_acc_f32(acc, qv[ci < nchunks ? ci : 0], x[u], ci < nchunks);
             }
         }

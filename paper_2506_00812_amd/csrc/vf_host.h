@@ -107,7 +107,10 @@ struct Tuning {
     int seed_margin_bf16 = 24;    // the same from the 16-bit (binary16) copy
     int seed_cache = 1;           // 0: no interleaved copy of the seeds, the seed kernel gathers rows
     int seed_bf16 = 1;            // 0: float32 data keep only the float32 copy of the seeds, not the 16-bit one
-    int seed_bf16_min_batch = 512;   // calls with fewer graph queries use the float32 copy when it is resident
+    // Calls with fewer graph queries use the float32 copy when it is resident.  Without predicates neither is the better one by much (a batch
+    // of 64, 6,144 seeds: binary16 1 - 4 % faster); predicates' proofs re-score 16 seeds fewer from the float32 copy, which
+    // a few queries notice (one pair 66 against 72 us), and from some 256 pairs on binary16 is ahead.
+    int seed_bf16_min_batch = 512;
     int seed_fb_window = 131072;  // graph queries between two looks at the failed-proof counter
     int seed_select = 0;          // 1: the seed kernel also selects (runs of keys instead of every distance; itopk <= 64)
     int seed_seg_seeds = 0;       // seeds per wave of the selecting seed kernel; 0: chosen per call (512 .. 16384)
@@ -218,7 +221,8 @@ struct Workspace {
 // The seeds of every graph list for one n_seeds (local ids floor(j n / ns)), interleaved like a scan list, so
 // that the matrix-core seed kernel reads its B operand with coalesced loads.  Derived from the index and
 // n_seeds alone.  An index keeps a few of them (calls on different streams may use different seed counts at
-// the same time); a copy is only rebuilt or dropped after the whole device has drained.
+// the same time); a copy is only rebuilt or dropped after the whole device has drained, which dimensions without a kernel
+// instantiation of their own never ask for: they keep the first ones and score any further seed count without a copy.
 struct SeedCopy {
     int32_t n_seeds = -1;        // -1: slot unused
     bool ok = false;             // false: the copy did not fit, the kernel gathers rows from the vector table

@@ -169,7 +169,9 @@ __device__ __forceinline__ int lanes_before(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
-// Waves per SIMD that the registers are shared out for: the most that need no scratch memory in the loop over the groups.
+// Waves per SIMD that the registers are shared out for: as many as the row operand leaves registers for, without scratch memory but for
+// uint8 of 4 steps with predicates where one wave reads the list (20 bytes a lane), of 6 steps where four do (16 bytes) and split
+// operands of 16 steps (116 bytes, at two waves).
 __host__ __device__ constexpr int join_waves(int dt, int nk, int w)
 {
     return dt == 1 || nk > 8 ? 2 : (w == 1 ? nk > (dt == 0 ? 4 : 6) : nk > (dt == 0 ? 6 : 8)) ? 3 : 4;

@@ -107,12 +107,6 @@ int drop_seed_copies(vf_index *ix)
     return VF_OK;
 }
 
-// The interleaved copy of the seeds of every graph list for n_seeds (see SeedCopy): the resident one, or a new
-// one built on the caller's stream (the call returns after it is complete, so later calls on any stream may
-// read it).  The index keeps kSeedCopies of them; the least recently used one makes room, after the device
-// has drained, since calls on other streams may still be reading it (dimensions without a kernel instantiation of their own keep
-// the first ones).  (*out)->ok is false when a copy would need
-// more than half of the free device memory: the seed kernel then gathers rows from the vector table.
 bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_seeds)
 {
     if (exact || ix->graph_labels.empty() || !ix->seed_mfma_ok || ix->tune.seed_exact) return false;
@@ -124,6 +118,12 @@ bool wants_seed_copy(const vf_index *ix, bool exact, int32_t itopk, int32_t n_se
     return (own && itopk <= 48) || ((own || ix->tune.seed_bf16) && !ix->seed_proofs_off && ix->seeds_provable(itopk));
 }
 
+// The interleaved copy of the seeds of every graph list for n_seeds (see SeedCopy): the resident one, or a new
+// one built on the caller's stream (the call returns after it is complete, so later calls on any stream may
+// read it).  The index keeps kSeedCopies of them; the least recently used one makes room, after the device
+// has drained, since calls on other streams may still be reading it (dimensions without a kernel instantiation of their own keep
+// the first ones).  (*out)->ok is false when a copy would need
+// more than half of the free device memory: the seed kernel then gathers rows from the vector table.
 int seed_copy_for(vf_index *ix, int32_t n_seeds, hipStream_t s, bool build, SeedCopy **out)
 {
     SeedCopy *c = nullptr;
@@ -524,8 +524,8 @@ int plan_call(const vf_index *ix, Routed &r, int64_t nq, const int64_t *qoff, co
     if (!own_dim && (P.tight || sc == nullptr || !sc->ok || (ix->dtype == VF_F32 && !sc->has_f16))) mfma_ok = false;
     // With an interleaved seed copy the seed kernel also selects (itopk <= 64: the beam kernel's one-register
     // list): it leaves sel_K keys per (query, seed segment) instead of every distance.  float32 data: from the
-    // binary16 copy; calls with few graph queries keep the float32 copy and the unfused kernel (their proofs
-    // need fewer re-scored seeds, which a latency-bound call notices).
+    // binary16 copy; calls with few graph queries keep the float32 copy and the unfused kernel (see
+    // seed_bf16_min_batch).
     const Tuning &tune = ix->tune;
     if (mfma_ok && sc != nullptr && sc->ok && tune.seed_select && itopk <= 64 &&
         seed_select_supported(ix->dtype, ix->dim, sc->has_f16) &&
@@ -846,8 +846,8 @@ int launch_call(vf_index *ix, const CallPlan &P, const Routed &r, const CallMem 
                 RerankParams rp{};
                 rp.items = d_merges; rp.res_idx = sp.res_idx; rp.res_bits = sp.res_bits; rp.map = sp.map;
                 rp.X = ix->X; rp.Q = queries; rp.dim = ix->dim; rp.Kc = P.scan_keep; rp.K = k;
-                // the bound of the bfloat16 seed proofs (same arithmetic: two bfloat16 products per component into a
-                // float32 accumulator, norms of the unrounded vectors), with the lists' own largest norm and rounding error
+                // two bfloat16 products per component into a float32 accumulator, norms of the unrounded vectors, the lists'
+                // own largest norm and rounding error
                 rp.err_bound = ix->seed_err_bound() * 8.0f; rp.xn_max = ix->ls_xn_max; rp.err_q = 2.0f * ix->ls_bf16_delta;
                 rp.approx_unit = 1.f; rp.q_max = 3.0e38f;
                 rp.fail_count = ix->d_scan_fb.as<uint32_t>();

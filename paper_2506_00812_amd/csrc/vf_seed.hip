@@ -852,8 +852,8 @@ void launch_seed_rows_f16(const void *X, int32_t dim, const int32_t *map, const 
                        n_groups * 32, nch16, scale, blk16, norm, err2_max);
 }
 
-// The interleaved float32 copy of the seeds (groups of 32, 2 * nch16 chunks of 4 components) rounded to
-// bfloat16 (nch16 chunks of 8 components); err2[group * 32 + v] = |x - bf16(x)|^2.  One thread per seed.
+// An interleaved float32 copy (of the scan lists; groups of 32, 2 * nch16 chunks of 4 components) rounded to
+// bfloat16 (nch16 chunks of 8 components); err2[group * 32 + v] = |x - bf16(x)|^2.  One thread per vector.
 __global__ void seed_pack_bf16_kernel(const uint4 *blk32, int64_t n_vec, int32_t nch16, uint4 *blk16, float *err2)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
